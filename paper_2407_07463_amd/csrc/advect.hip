@@ -7,7 +7,8 @@ using namespace advect;
 
 namespace {
 
-constexpr int kChunk = 32;  // cells per thread along its marching axis
+constexpr int kMaxChunk = 32;       // cells per thread along its marching axis, at most
+constexpr int64_t kWaves = 8192;  // wavefronts a sweep should have: 8 per SIMD
 constexpr int kXWaves = 8;  // wavefronts per workgroup of the x-sweep: a 512-cell row per workgroup
 
 __global__ __launch_bounds__(256) void k_scan_mixed(const double *__restrict__ c, int64_t total,
@@ -80,7 +81,8 @@ struct SweepBuffers {
   uint32_t *list[2];
   int *counts[2];
   int64_t nregions[2];  // regions filled into each list
-  int rsize;
+  int stride[2];        // entries per region of each list
+  int rsize;            // entries per region a streaming pass fills
 };
 
 static const char *stream_name(int d, int g) {
@@ -94,6 +96,36 @@ static const char *stream_name(int d, int g) {
 // most `chunk` segments (so a wavefront's cells fit its list region), else
 // kXWaves wavefronts sharing segment ends through LDS.
 static inline int x_wpb(int words, int chunk) { return words <= chunk ? 0 : kXWaves; }
+
+// Marching chunk of the streaming passes: the longest that still gives every
+// sweep kWaves wavefronts (a long chunk re-reads fewer rows at its ends; a
+// wavefront's march is a serial chain of dependent positions, so a grid of
+// few wavefronts takes the chain's time however little it has to do). Never
+// below a row's segments, so that the x-sweep keeps whole-row wavefronts where
+// it has them at the longest chunk. One step, chunk 32 everywhere against this
+// rule (the scan below included): 64^3 x 2 184.7 -> 60 us (chunk 4),
+// 134x129x141 x 7 716 -> 546 us, 200x180x210 x 4 747 -> 700 us; kWaves 4096
+// leaves the second at 667, 16384 and 32768 are within 2% of 8192 on all.
+static int pick_chunk(int nx, int ny, int nz, int ntr) {
+  const int words = (nx + 63) / 64;
+  int chunk = kMaxChunk;
+  while (chunk > 4 && words <= chunk / 2) {
+    int64_t least = INT64_MAX;
+    for (int d = 0; d < 3; ++d) {
+      const int64_t w = stream_waves(d, nx, ny, nz, chunk, d == 0 ? x_wpb(words, chunk) : 4) * num_groups(ntr);
+      least = w < least ? w : least;
+    }
+    if (least >= kWaves) break;
+    chunk /= 2;
+  }
+  return chunk;
+}
+// Tracer-cells per wavefront of the initial scan, by the same rule.
+static int scan_span(int64_t total) {
+  int span = region_size(kMaxChunk);
+  while (span > 64 * kScanBatch && total / span < kWaves) span /= 2;
+  return span;
+}
 
 // One streaming launch over ngrp consecutive groups of G tracers from t0;
 // group k fills list regions region0 + k*per onwards.
@@ -130,7 +162,7 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
   static const char *plic_names[3] = {"k_plic<0>", "k_plic<1>", "k_plic<2>"};
   const int rec = prof_begin(ctx, plic_names[D], stream);
   hipLaunchKernelGGL((k_plic<D>), dim3(ceil_div(nreg, 4)), dim3(256), 0, stream, cin, s, sb.list[cur],
-                     sb.counts[cur], nreg, sb.rsize, sb.fmix, nx, ny, nz, dv);
+                     sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
   prof_end(ctx, rec, stream);
   const int64_t per = stream_waves(D, nx, ny, nz, chunk, D == 0 ? x_wpb(words, chunk) : 4);
   static_assert(kMaxGroup == 4, "streaming passes are instantiated for groups of 4, 2 and 1");
@@ -151,6 +183,7 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
     region0 += per;
   }
   sb.nregions[nxt] = region0;
+  sb.stride[nxt] = sb.rsize;
 }
 
 static int launch_sweep(vofmt_ctx *ctx, int d, const double *cin, double *cout, const double *s, SweepBuffers &sb,
@@ -170,7 +203,7 @@ extern "C" int vofmt_advect(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, 
                    nx, ny, nz, ntracers, nsteps, (long long)step0);
   if (ntracers == 0 || nsteps == 0) return VOFMT_OK;
   if (!c || !sx || !sy || !sz) return set_err(ctx, VOFMT_E_ARG, "vofmt_advect: null pointer");
-  if (ny > 65535 || ceil_div(nz, 4) > 65535 || ceil_div(ny, kChunk) > 65535 || ceil_div(nz, kChunk) > 65535)
+  if (ny > 65535 || ceil_div(nz, 4) > 65535 || ceil_div(ny, kMaxChunk) > 65535 || ceil_div(nz, kMaxChunk) > 65535)
     return set_err(ctx, VOFMT_E_ARG, "vofmt_advect: grid too large");
   VOFMT_HIP(ctx, hipSetDevice(ctx->device));
   const int64_t n3 = (int64_t)nx * ny * nz;
@@ -183,12 +216,16 @@ extern "C" int vofmt_advect(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, 
   double *fmix = (double *)scratch(ctx, SLOT_FMIX, field_bytes);
   uint64_t *bits = (uint64_t *)scratch(ctx, SLOT_CCBITS, sizeof(uint64_t) * (size_t)ntracers * nz * ny * words);
   // list regions: enough for the largest sweep launch set and for the initial scan
-  const int rsize = region_size(kChunk);
-  const int64_t maxreg = max_regions(nx, ny, nz, ntracers, kChunk, x_wpb(words, kChunk));
+  const int chunk = pick_chunk(nx, ny, nz, ntracers);
+  const int rsize = region_size(chunk);
   const int64_t total = (int64_t)ntracers * n3;
-  const int64_t scanreg = (total + rsize - 1) / rsize;
+  const int span = scan_span(total);
+  const int64_t scanreg = (total + span - 1) / span;
+  int64_t maxreg = max_regions(nx, ny, nz, ntracers, chunk, x_wpb(words, chunk));
+  if (maxreg * rsize < scanreg * span) maxreg = (scanreg * span + rsize - 1) / rsize;
+  const int64_t maxcnt = maxreg > scanreg ? maxreg : scanreg;
   uint32_t *lists = (uint32_t *)scratch(ctx, SLOT_MIXLIST, sizeof(uint32_t) * 2 * (size_t)maxreg * rsize);
-  int *counts = (int *)scratch(ctx, SLOT_COUNTS, sizeof(int) * 2 * (size_t)maxreg);
+  int *counts = (int *)scratch(ctx, SLOT_COUNTS, sizeof(int) * 2 * (size_t)maxcnt);
   if (!tmp || !fmix || !bits || !lists || !counts) return VOFMT_E_NOMEM;
   SweepBuffers sb;
   sb.fmix = fmix;
@@ -196,15 +233,16 @@ extern "C" int vofmt_advect(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, 
   sb.list[0] = lists;
   sb.list[1] = lists + (size_t)maxreg * rsize;
   sb.counts[0] = counts;
-  sb.counts[1] = counts + maxreg;
+  sb.counts[1] = counts + maxcnt;
   sb.nregions[0] = scanreg;
   sb.nregions[1] = 0;
+  sb.stride[0] = span;
+  sb.stride[1] = rsize;
   sb.rsize = rsize;
-  const int chunk = kChunk;
   // mixed cells of the input field
   const int rec = prof_begin(ctx, "k_scan_mixed", stream);
   hipLaunchKernelGGL(k_scan_mixed, dim3(ceil_div(scanreg, 4)), dim3(256), 0, stream, c, total, sb.list[0],
-                     sb.counts[0], scanreg, rsize);
+                     sb.counts[0], scanreg, span);
   prof_end(ctx, rec, stream);
   VOFMT_HIP(ctx, hipGetLastError());
   int cur_list = 0;

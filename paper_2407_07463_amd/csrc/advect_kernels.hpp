@@ -85,7 +85,9 @@ struct Divisors {
 };
 
 // Mixed cells of the initial field: wavefront w scans tracer-cells
-// [w*rsize, (w+1)*rsize) of the whole array.
+// [w*rsize, (w+1)*rsize) of the whole array, kScanBatch loads in flight per
+// lane (the list position depends on every earlier ballot, the loads do not).
+constexpr int kScanBatch = 8;
 __device__ __forceinline__ void scan_body(const double *__restrict__ c, int64_t total, uint32_t *__restrict__ list,
                                           int *__restrict__ counts, int64_t nregions, int rsize, int64_t w) {
   const int lane = threadIdx.x & 63;
@@ -93,12 +95,21 @@ __device__ __forceinline__ void scan_body(const double *__restrict__ c, int64_t 
   uint32_t *out = list + w * rsize;
   int n = 0;
   const uint64_t below = (1ull << lane) - 1;
-  for (int64_t base = w * rsize; base < (w + 1) * rsize && base < total; base += 64) {
-    const int64_t q = base + lane;
-    const bool mixed = (q < total) && plic::is_mixed(c[q]);
-    const uint64_t mask = __ballot(mixed);
-    if (mixed) out[n + __popcll(mask & below)] = (uint32_t)q;
-    n += __popcll(mask);
+  const int64_t end = (w + 1) * rsize < total ? (w + 1) * rsize : total;
+  for (int64_t base = w * rsize; base < end; base += 64 * kScanBatch) {
+    double v[kScanBatch];
+#pragma unroll
+    for (int j = 0; j < kScanBatch; ++j) {
+      const int64_t q = base + 64 * j + lane;
+      v[j] = (q < end) ? c[q] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < kScanBatch; ++j) {
+      const bool mixed = plic::is_mixed(v[j]);  // (0 past the end: not mixed)
+      const uint64_t mask = __ballot(mixed);
+      if (mixed) out[n + __popcll(mask & below)] = (uint32_t)(base + 64 * j + lane);
+      n += __popcll(mask);
+    }
   }
   if (lane == 0) counts[w] = n;
 }
