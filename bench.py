@@ -551,9 +551,9 @@ def main():
     stream_names = [k for k in prof if k.startswith("k_stream<")]
     launches = sum(prof[k][0] for k in stream_names)
     total_ms = sum(prof[k][1] for k in stream_names)
-    # tracers per streaming launch: every full group of 4 in one launch
-    gsz = 4 if ntr >= 4 else ntr  # tracers per group (template argument)
-    tpl = 4 * (ntr // 4) if ntr >= 4 else ntr
+    # one streaming launch covers all tracers, in groups of up to 4
+    gsz = 4 if ntr >= 4 else ntr
+    tpl = ntr
     bytes_launch = sweep_model_bytes(ntr) * tpl * n3
     avg_launch_s = total_ms / launches / 1e3
     achieved = bytes_launch / avg_launch_s / 1e9
@@ -562,7 +562,7 @@ def main():
     traffic = None
     tr, sha = profiling.read_traffic(TRAFFIC_FILE)
     if tr and sha == profiling.advect_source_sha():
-        vals = [v for k, v in tr.items() if k.startswith(("k_stream<", "k_stream_rows<"))]
+        vals = [v for k, v in tr.items() if k.startswith(("k_stream<", "k_stream_rows"))]
         if vals:
             traffic = sum(vals) / len(vals)
     step_bytes = 3.0 * sweep_model_bytes(ntr) * ntr * n3  # 51.5 B per tracer-cell-step at 8 tracers
@@ -599,7 +599,7 @@ def main():
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": traffic,
-            "kernel": f"k_stream<D,{gsz}> / k_stream_rows<{gsz}> (streaming pass of {tpl} tracers in groups of {gsz}, all axes)",
+            "kernel": f"k_stream<D> / k_stream_rows (streaming pass of {tpl} tracers in groups of {gsz}, all axes)",
             "bytes_per_launch": bytes_launch,
             "bytes_model": f"{sweep_model_bytes(ntr):.3f} B per tracer-cell-sweep x {tpl} x n^3",
             "avg_launch_ms": 1e3 * avg_launch_s,

@@ -26,32 +26,33 @@ __global__ __launch_bounds__(256) void k_plic(const double *__restrict__ cin, co
                ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
 }
 
-template <int D, int G>
-__global__ __launch_bounds__(64 * kXWaves) void k_stream(const double *__restrict__ cin, double *__restrict__ cout,
-                                                        const double *__restrict__ s, const double *__restrict__ fmix,
-                                                        uint64_t *__restrict__ ccbits, int write_cc, int t0, int nx,
-                                                        int ny, int nz, int words, int chunk,
-                                                        uint32_t *__restrict__ list_next, int *__restrict__ counts_next,
-                                                        int64_t region0, int rsize, int ngrp, int64_t gstride) {
+// One streaming pass over every tracer: ngrp groups of GM or GM - 1, group k
+// filling list regions k * gstride onwards. D = 0 with rows above a list
+// region's cells: kXWaves wavefronts per workgroup share segment ends.
+template <int D, int GM>
+__global__ __launch_bounds__(D == 0 ? 64 * kXWaves : 256) void k_stream(
+    const double *__restrict__ cin, double *__restrict__ cout, const double *__restrict__ s,
+    const double *__restrict__ fmix, uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx, int ny, int nz,
+    int words, int chunk, uint32_t *__restrict__ list_next, int *__restrict__ counts_next, int rsize, int ngrp,
+    int64_t gstride) {
   const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
                                  gridDim.y, gridDim.z / ngrp, ngrp, D == 1);
-  stream_body<D, G, kXWaves>(cin, cout, s, fmix, ccbits, write_cc, t0 + g.grp * G, nx, ny, nz, words, chunk,
-                             list_next, counts_next, region0 + g.grp * gstride, rsize, g.bx, g.by, g.bz, gridDim.x,
-                             gridDim.y);
+  stream_group<D, GM, kXWaves>(cin, cout, s, fmix, ccbits, write_cc, ntr, nx, ny, nz, words, chunk, list_next,
+                           counts_next, g.grp * gstride, rsize, g, gridDim.x, gridDim.y);
 }
 
 // The x-sweep marching along whole rows (4 wavefronts per workgroup).
-template <int G>
+template <int GM>
 __global__ __launch_bounds__(256) void k_stream_rows(const double *__restrict__ cin, double *__restrict__ cout,
                                                      const double *__restrict__ s, const double *__restrict__ fmix,
-                                                     uint64_t *__restrict__ ccbits, int write_cc, int t0, int nx,
+                                                     uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx,
                                                      int ny, int nz, int words, int chunk,
                                                      uint32_t *__restrict__ list_next, int *__restrict__ counts_next,
-                                                     int64_t region0, int rsize, int ngrp, int64_t gstride) {
+                                                     int rsize, int ngrp, int64_t gstride) {
   const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
                                  gridDim.y, gridDim.z / ngrp, ngrp, false);
-  stream_body<0, G, 0>(cin, cout, s, fmix, ccbits, write_cc, t0 + g.grp * G, nx, ny, nz, words, chunk, list_next,
-                       counts_next, region0 + g.grp * gstride, rsize, g.bx, g.by, g.bz, gridDim.x, gridDim.y);
+  stream_group<0, GM, 0>(cin, cout, s, fmix, ccbits, write_cc, ntr, nx, ny, nz, words, chunk, list_next, counts_next,
+                     g.grp * gstride, rsize, g, gridDim.x, gridDim.y);
 }
 
 // Per-block maximum of |s| over the three arrays and a non-finite flag.
@@ -84,13 +85,6 @@ struct SweepBuffers {
   int stride[2];        // entries per region of each list
   int rsize;            // entries per region a streaming pass fills
 };
-
-static const char *stream_name(int d, int g) {
-  static const char *names[3][3] = {{"k_stream<0,1>", "k_stream<0,2>", "k_stream<0,4>"},
-                                    {"k_stream<1,1>", "k_stream<1,2>", "k_stream<1,4>"},
-                                    {"k_stream<2,1>", "k_stream<2,2>", "k_stream<2,4>"}};
-  return names[d][g == 4 ? 2 : (g == 2 ? 1 : 0)];
-}
 
 // Workgroup layout of the x-sweep: whole-row wavefronts (0) when a row has at
 // most `chunk` segments (so a wavefront's cells fit its list region), else
@@ -127,26 +121,18 @@ static int scan_span(int64_t total) {
   return span;
 }
 
-// One streaming launch over ngrp consecutive groups of G tracers from t0;
-// group k fills list regions region0 + k*per onwards.
-template <int D, int G>
-static void launch_stream(vofmt_ctx *ctx, const double *cin, double *cout, const double *s, SweepBuffers &sb, int wcc,
-                          int t0, int ngrp, int nx, int ny, int nz, int words, int chunk, int nxt, int64_t region0,
-                          int64_t per, hipStream_t stream) {
-  const int wpb = (D == 0) ? x_wpb(words, chunk) : 4;
-  const Tiles tg = stream_tiles(D, nx, ny, nz, chunk, wpb);
-  dim3 grid(tg.gx, tg.gy, tg.gz * ngrp);
-  const int rec = prof_begin(ctx, stream_name(D, G), stream);
-  if (D == 0 && wpb == 0)
-    hipLaunchKernelGGL((k_stream_rows<G>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, wcc,
-                       t0, nx, ny, nz, words, chunk,
-                       sb.list[nxt], sb.counts[nxt], region0, sb.rsize, ngrp, per);
+template <int D, int GM>
+static void launch_stream(dim3 grid, hipStream_t stream, const double *cin, double *cout, const double *s,
+                          SweepBuffers &sb, int wcc, int nx, int ny, int nz, int ntr, int words, int chunk, int nxt,
+                          int64_t per) {
+  const int ngrp = num_groups(ntr);
+  if (D == 0 && x_wpb(words, chunk) == 0)
+    hipLaunchKernelGGL((k_stream_rows<GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, wcc, ntr, nx,
+                       ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per);
   else
-    hipLaunchKernelGGL((k_stream<D, G>), grid, dim3(D == 0 ? 64 * kXWaves : 256), 0, stream, cin, cout, s,
-                       sb.fmix, sb.bits, wcc, t0, nx, ny,
-                       nz,
-                       words, chunk, sb.list[nxt], sb.counts[nxt], region0, sb.rsize, ngrp, per);
-  prof_end(ctx, rec, stream);
+    hipLaunchKernelGGL((k_stream<D, GM>), grid, dim3(D == 0 ? 64 * kXWaves : 256), 0, stream, cin, cout, s, sb.fmix,
+                       sb.bits, wcc, ntr, nx, ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp,
+                       per);
 }
 
 template <int D>
@@ -160,29 +146,25 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
   dv.nx = make_fastdiv((uint32_t)nx);
   dv.ny = make_fastdiv((uint32_t)ny);
   static const char *plic_names[3] = {"k_plic<0>", "k_plic<1>", "k_plic<2>"};
-  const int rec = prof_begin(ctx, plic_names[D], stream);
+  static const char *stream_names[3] = {"k_stream<0>", "k_stream<1>", "k_stream<2>"};
+  int rec = prof_begin(ctx, plic_names[D], stream);
   hipLaunchKernelGGL((k_plic<D>), dim3(ceil_div(nreg, 4)), dim3(256), 0, stream, cin, s, sb.list[cur],
                      sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
   prof_end(ctx, rec, stream);
-  const int64_t per = stream_waves(D, nx, ny, nz, chunk, D == 0 ? x_wpb(words, chunk) : 4);
-  static_assert(kMaxGroup == 4, "streaming passes are instantiated for groups of 4, 2 and 1");
-  // every full group of 4 in one launch, then the groups of 2 and 1 left
-  const int nfull = ntr / kMaxGroup;
-  int64_t region0 = 0;
-  int t = 0;
-  if (nfull > 0) {
-    launch_stream<D, 4>(ctx, cin, cout, s, sb, wcc, 0, nfull, nx, ny, nz, words, chunk, nxt, 0, per, stream);
-    t = nfull * kMaxGroup;
-    region0 = nfull * per;
+  const int wpb = (D == 0) ? x_wpb(words, chunk) : 4;
+  const int64_t per = stream_waves(D, nx, ny, nz, chunk, wpb);
+  const Tiles tg = stream_tiles(D, nx, ny, nz, chunk, wpb);
+  const dim3 grid(tg.gx, tg.gy, tg.gz * num_groups(ntr));
+  static_assert(kMaxGroup == 4, "streaming passes are instantiated for groups of at most 4");
+  rec = prof_begin(ctx, stream_names[D], stream);
+  switch (largest_group(ntr)) {
+    case 4: launch_stream<D, 4>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 3: launch_stream<D, 3>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 2: launch_stream<D, 2>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    default: launch_stream<D, 1>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
   }
-  while (t < ntr) {
-    const int g = group_size(ntr - t);
-    if (g == 2) launch_stream<D, 2>(ctx, cin, cout, s, sb, wcc, t, 1, nx, ny, nz, words, chunk, nxt, region0, per, stream);
-    else launch_stream<D, 1>(ctx, cin, cout, s, sb, wcc, t, 1, nx, ny, nz, words, chunk, nxt, region0, per, stream);
-    t += g;
-    region0 += per;
-  }
-  sb.nregions[nxt] = region0;
+  prof_end(ctx, rec, stream);
+  sb.nregions[nxt] = num_groups(ntr) * per;
   sb.stride[nxt] = sb.rsize;
 }
 

@@ -596,6 +596,38 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   if (lane == 0) counts_next[wave] = nlist;
 }
 
+// Tracer groups of a pass: the fewest of at most kMaxGroup tracers, of even
+// sizes (5 tracers: 3 + 2; 7: 4 + 3; 9: 3 + 3 + 3), the larger ones first. One
+// launch covers them all: launched as groups of 4, 2 and 1, a grid of 7
+// tracers ran three streaming passes a sweep, each with its own nearly empty
+// end, and a wavefront of one tracer keeps too few bytes in flight (one step
+// of 134x129x141 x 7: 546 -> 497 us; 333x300x310 x 5: 3626 -> 3539 us, and
+// 3862 us with 4 + 1 in one launch).
+__host__ __device__ inline int num_groups(int ntr) { return (ntr + kMaxGroup - 1) / kMaxGroup; }
+__host__ __device__ inline int largest_group(int ntr) {
+  const int n = num_groups(ntr);
+  return n > 0 ? (ntr + n - 1) / n : 0;
+}
+
+// Group g.grp of ntr tracers, whose largest group is GM: a group of GM, or one
+// of GM - 1 (uniform over the workgroup).
+template <int D, int GM, int WPB = 4>
+__device__ __forceinline__ void stream_group(const double *__restrict__ cin, double *__restrict__ cout,
+                                             const double *__restrict__ s, const double *__restrict__ fmix,
+                                             uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx, int ny,
+                                             int nz, int words, int chunk, uint32_t *__restrict__ list_next,
+                                             int *__restrict__ counts_next, int64_t region0, int rsize,
+                                             const GroupTile &g, int gx, int gy) {
+  const int small = num_groups(ntr) * GM - ntr;  // groups of GM - 1, the last ones
+  const int large = num_groups(ntr) - small;
+  if (GM == 1 || g.grp < large)
+    stream_body<D, GM, WPB>(cin, cout, s, fmix, ccbits, write_cc, g.grp * GM, nx, ny, nz, words, chunk, list_next,
+                            counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy);
+  else if constexpr (GM > 1)
+    stream_body<D, GM - 1, WPB>(cin, cout, s, fmix, ccbits, write_cc, large * GM + (g.grp - large) * (GM - 1), nx, ny,
+                                nz, words, chunk, list_next, counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy);
+}
+
 // ---------------------------------------------------------------- host side
 
 // Wavefronts of one streaming pass along axis d (each owns one list region).
@@ -604,19 +636,6 @@ static inline int64_t stream_waves(int d, int nx, int ny, int nz, int chunk, int
   return ((d == 0 && wpb > 0) ? wpb : 4) * (int64_t)g.gx * g.gy * g.gz;
 }
 
-// Tracer groups of one sweep: kMaxGroup tracers at a time, then groups of
-// 2 and 1 for the rest. Launches and the sizing of the list regions both use
-// these functions.
-static inline int group_size(int left) {
-  if (left >= kMaxGroup) return kMaxGroup;
-  if (left >= 2) return 2;
-  return 1;
-}
-static inline int num_groups(int ntr) {
-  int n = 0;
-  for (int t = 0; t < ntr; t += group_size(ntr - t)) ++n;
-  return n;
-}
 // List entries per region: every cell a wavefront of a streaming pass writes.
 static inline int region_size(int chunk) { return 64 * chunk * kMaxGroup; }
 // Regions of one list: the largest streaming sweep, or the initial scan.

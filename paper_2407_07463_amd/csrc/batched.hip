@@ -10,6 +10,7 @@
 // persistent grid size in workgroups per compute unit; the autotuner times a
 // set of candidates on copies of the fields and returns the fastest.
 #include <cstring>
+#include <type_traits>
 
 #include "advect_kernels.hpp"
 
@@ -29,15 +30,14 @@ struct BoxDev {
   int *counts[2];
 };
 
-// A run of work items that belong to one box (and, in a streaming pass, to
-// ngrp consecutive tracer groups of one size).
+// A run of work items that belong to one box (in a streaming pass: its tiles
+// times its tracer groups).
 struct Seg {
   int64_t item0;    // first global work item of the run
   int64_t nitems;   // its length
-  int box, t0;      // box, first tracer of the first group
-  int64_t region0;  // first list region of the first group
+  int box;
   int gx, gy, gz;   // tile grid of the streaming pass (x blocks, row blocks, chunks)
-  int ngrp;         // groups (group k: tracers from t0 + k * G, regions from region0 + k * gstride)
+  int ngrp;         // tracer groups (group k fills list regions from k * gstride)
   int64_t gstride;
 };
 
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes
 }
 
 // work items: 4-wavefront tiles of a streaming pass
-template <int D, int G>
+template <int D>
 __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
                                                   int nseg, int64_t nitems, int chunk, int rsize, int par, int nxt,
                                                   int write_cc) {
@@ -85,14 +85,21 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
     const BoxDev &b = boxes[sg.box];
     // (the grid is a multiple of 8 workgroups, so items 8 apart share an XCD)
     const GroupTile g = group_tile(item - sg.item0, sg.gx, sg.gy, sg.gz, sg.ngrp, D == 1);
-    const int t0 = sg.t0 + g.grp * G;
-    const int64_t region0 = sg.region0 + g.grp * sg.gstride;
-    if (D == 0 && b.xwpb == 0)  // uniform over the workgroup
-      stream_body<D, G, 0>(b.f[par], b.f[par ^ 1], b.s[D], b.fmix, b.bits, write_cc, t0, b.nx, b.ny, b.nz, b.words,
-                           chunk, b.list[nxt], b.counts[nxt], region0, rsize, g.bx, g.by, g.bz, sg.gx, sg.gy);
-    else
-      stream_body<D, G>(b.f[par], b.f[par ^ 1], b.s[D], b.fmix, b.bits, write_cc, t0, b.nx, b.ny, b.nz, b.words,
-                        chunk, b.list[nxt], b.counts[nxt], region0, rsize, g.bx, g.by, g.bz, sg.gx, sg.gy);
+    const int64_t region0 = g.grp * sg.gstride;
+    const int gm = largest_group(b.ntr);  // uniform over the workgroup
+    auto pass = [&](auto GM) {
+      constexpr int G = decltype(GM)::value;
+      if (D == 0 && b.xwpb == 0)
+        stream_group<D, G, 0>(b.f[par], b.f[par ^ 1], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz,
+                              b.words, chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy);
+      else
+        stream_group<D, G>(b.f[par], b.f[par ^ 1], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz, b.words,
+                           chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy);
+    };
+    if (gm == 4) pass(std::integral_constant<int, 4>{});
+    else if (gm == 3) pass(std::integral_constant<int, 3>{});
+    else if (gm == 2) pass(std::integral_constant<int, 2>{});
+    else pass(std::integral_constant<int, 1>{});
   }
 }
 
@@ -119,12 +126,10 @@ struct Plan {
   size_t off_plic[3];  // list regions after a sweep along d
   int n_plic[3];
   int64_t items_plic[3];
-  size_t off_stream[3][3];  // [d][group kind: 4, 2, 1]
-  int n_stream[3][3];
-  int64_t items_stream[3][3];
+  size_t off_stream[3];  // streaming passes along d
+  int n_stream[3];
+  int64_t items_stream[3];
 };
-
-int kind_of(int g) { return g == 4 ? 0 : (g == 2 ? 1 : 2); }
 
 // x-sweep layout of a box: whole-row wavefronts when a row has at most `chunk`
 // segments (its cells then fit a wavefront's list region), else 4 wavefronts
@@ -234,43 +239,26 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
       ++pl.n_plic[d];
     }
   }
-  for (int d = 0; d < 3; ++d)
-    for (int kind = 0; kind < 3; ++kind) {
-      begin_table(pl.off_stream[d][kind], pl.n_stream[d][kind], pl.items_stream[d][kind]);
-      for (int i = 0; i < nboxes; ++i) {
-        const vofmt_box &b = boxes[i];
-        const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-        const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw);
-        const int gx = tg.gx, gy = tg.gy, gz = tg.gz;
-        const int64_t per = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw);
-        // all full groups of the box in one run of items, then one run per
-        // group of 2 or 1 (list regions in group order, as in the plain path)
-        const int nfull = b.ntracers / kMaxGroup;
-        int64_t region0 = 0;
-        for (int t = 0; t < b.ntracers;) {
-          const int g = group_size(b.ntracers - t);
-          const int ng = (g == kMaxGroup) ? nfull : 1;
-          if (kind_of(g) == kind) {
-            Seg s{};
-            s.item0 = pl.items_stream[d][kind];
-            s.nitems = (int64_t)gx * gy * gz * ng;
-            s.box = i;
-            s.t0 = t;
-            s.region0 = region0;
-            s.gx = gx;
-            s.gy = gy;
-            s.gz = gz;
-            s.ngrp = ng;
-            s.gstride = per;
-            seg_all.push_back(s);
-            pl.items_stream[d][kind] += s.nitems;
-            ++pl.n_stream[d][kind];
-          }
-          t += g * ng;
-          region0 += per * ng;
-        }
-      }
+  for (int d = 0; d < 3; ++d) {
+    begin_table(pl.off_stream[d], pl.n_stream[d], pl.items_stream[d]);
+    for (int i = 0; i < nboxes; ++i) {
+      const vofmt_box &b = boxes[i];
+      const int xw = box_xwpb((b.nx + 63) / 64, chunk);
+      const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw);
+      Seg s{};
+      s.item0 = pl.items_stream[d];
+      s.gx = tg.gx;
+      s.gy = tg.gy;
+      s.gz = tg.gz;
+      s.ngrp = num_groups(b.ntracers);
+      s.nitems = (int64_t)tg.gx * tg.gy * tg.gz * s.ngrp;
+      s.box = i;
+      s.gstride = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw);
+      seg_all.push_back(s);
+      pl.items_stream[d] += s.nitems;
+      ++pl.n_stream[d];
     }
+  }
   // tables after the per-box buffers: boxes, then segments
   pl.off_boxes = off;
   off = align256(off + sizeof(BoxDev) * (size_t)(nboxes > 0 ? nboxes : 1));
@@ -281,7 +269,7 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
   pl.off_scan = to_bytes(pl.off_scan);
   for (int d = 0; d < 3; ++d) {
     pl.off_plic[d] = to_bytes(pl.off_plic[d]);
-    for (int k = 0; k < 3; ++k) pl.off_stream[d][k] = to_bytes(pl.off_stream[d][k]);
+    pl.off_stream[d] = to_bytes(pl.off_stream[d]);
   }
   return off;
 }
@@ -302,21 +290,9 @@ static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, i
     pitems = pl.items_plic[prev_d];
   }
   hipLaunchKernelGGL((k_plic_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize, par, cur);
-  for (int kind = 0; kind < 3; ++kind) {
-    if (pl.n_stream[D][kind] == 0) continue;
-    const Seg *ss = (const Seg *)(slab + pl.off_stream[D][kind]);
-    const int n = pl.n_stream[D][kind];
-    const int64_t it = pl.items_stream[D][kind];
-    if (kind == 0)
-      hipLaunchKernelGGL((k_stream_b<D, 4>), dim3(pl.grid), dim3(256), 0, st, dboxes, ss, n, it, pl.chunk, pl.rsize,
-                         par, cur ^ 1, wcc);
-    else if (kind == 1)
-      hipLaunchKernelGGL((k_stream_b<D, 2>), dim3(pl.grid), dim3(256), 0, st, dboxes, ss, n, it, pl.chunk, pl.rsize,
-                         par, cur ^ 1, wcc);
-    else
-      hipLaunchKernelGGL((k_stream_b<D, 1>), dim3(pl.grid), dim3(256), 0, st, dboxes, ss, n, it, pl.chunk, pl.rsize,
-                         par, cur ^ 1, wcc);
-  }
+  hipLaunchKernelGGL((k_stream_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes,
+                     (const Seg *)(slab + pl.off_stream[D]), pl.n_stream[D], pl.items_stream[D], pl.chunk, pl.rsize,
+                     par, cur ^ 1, wcc);
 }
 
 extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, int64_t step0,

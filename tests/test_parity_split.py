@@ -37,6 +37,8 @@ def _random(shape, ntr, seed):
     ((1, 1, 7), 1, 0, 1), ((4, 3, 1), 2, 2, 2),     # single rows and columns
     ((37, 40, 257), 3, 2, 2),                       # 5 segments a row: chunk 8
     ((8, 31, 515), 2, 0, 2),                        # 9 segments: chunk 16
+    # tracer groups of even sizes: 3 + 2, 4 + 3, 4 + 3 + 3 + 3
+    ((9, 10, 70), 5, 0, 1), ((13, 8, 66), 7, 1, 2), ((6, 9, 65), 13, 2, 1),
     ((300, 150, 128), 2, 0, 1),                     # chunk 8 from the number of wavefronts
     ((300, 300, 128), 1, 1, 1),                     # chunk 16
     ((129, 258, 320), 4, 2, 1),                     # chunk 16 to 32, a scan span that does not divide the field
