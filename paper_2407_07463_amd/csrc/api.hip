@@ -47,6 +47,23 @@ void *scratch(vofmt_ctx *ctx, int slot, size_t bytes) {
   return p;
 }
 
+void *scratch_if_free(vofmt_ctx *ctx, int slot, size_t bytes, hipStream_t stream) {
+  if (ctx->cap[slot] >= bytes && ctx->buf[slot]) return ctx->buf[slot];
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (st != hipStreamCaptureStatusNone) return nullptr;
+  const std::string err = ctx->err;
+  void *p = scratch(ctx, slot, bytes);
+  if (!p) {
+    (void)hipGetLastError();
+    ctx->err = err;
+  }
+  return p;
+}
+
 void *host_scratch(vofmt_ctx *ctx, size_t bytes) {
   if (bytes == 0) bytes = 64;
   if (ctx->host_cap >= bytes) return ctx->host;

@@ -22,7 +22,7 @@ struct BoxDev {
   int nx, ny, nz, ntr, words;
   int xwpb;  // x-sweep: 0 whole-row wavefronts (a row's cells fit one list region), else 4 per workgroup
   Divisors dv;
-  double *f[2];  // the caller's field and its ping-pong copy
+  double *f[3];  // the caller's field, its ping-pong copy and the third one of an odd number of sweeps
   const double *s[3];
   double *fmix;
   uint64_t *bits;
@@ -65,12 +65,12 @@ __global__ __launch_bounds__(256) void k_scan_b(const BoxDev *__restrict__ boxes
 
 template <int D>
 __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
-                                                int nseg, int64_t nitems, int rsize, int par, int cur) {
+                                                int nseg, int64_t nitems, int rsize, int src, int cur) {
   for (int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; gw < nitems;
        gw += (int64_t)gridDim.x * 4) {
     const Seg sg = segs[find_seg(segs, nseg, gw)];
     const BoxDev &b = boxes[sg.box];
-    plic_body<D>(b.f[par], b.s[D], b.list[cur], b.counts[cur], sg.nitems, rsize, b.fmix, b.nx, b.ny, b.nz, b.dv,
+    plic_body<D>(b.f[src], b.s[D], b.list[cur], b.counts[cur], sg.nitems, rsize, b.fmix, b.nx, b.ny, b.nz, b.dv,
                  gw - sg.item0);
   }
 }
@@ -78,8 +78,8 @@ __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes
 // work items: 4-wavefront tiles of a streaming pass
 template <int D>
 __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
-                                                  int nseg, int64_t nitems, int chunk, int rsize, int par, int nxt,
-                                                  int write_cc) {
+                                                  int nseg, int64_t nitems, int chunk, int rsize, int src, int dst,
+                                                  int nxt, int write_cc) {
   for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
     const Seg sg = segs[find_seg(segs, nseg, item)];
     const BoxDev &b = boxes[sg.box];
@@ -90,10 +90,10 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
     auto pass = [&](auto GM) {
       constexpr int G = decltype(GM)::value;
       if (D == 0 && b.xwpb == 0)
-        stream_group<D, G, 0>(b.f[par], b.f[par ^ 1], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz,
+        stream_group<D, G, 0>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz,
                               b.words, chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy);
       else
-        stream_group<D, G>(b.f[par], b.f[par ^ 1], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz, b.words,
+        stream_group<D, G>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz, b.words,
                            chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy);
     };
     if (gm == 4) pass(std::integral_constant<int, 4>{});
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
   }
 }
 
-// result back into the caller's fields (after an odd number of sweeps)
+// result back into the caller's fields (an odd number of sweeps without the third copies)
 __global__ __launch_bounds__(256) void k_copy_b(const BoxDev *__restrict__ boxes, int nboxes) {
   for (int bi = 0; bi < nboxes; ++bi) {
     const BoxDev &b = boxes[bi];
@@ -114,6 +114,9 @@ __global__ __launch_bounds__(256) void k_copy_b(const BoxDev *__restrict__ boxes
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+inline size_t field_bytes(const vofmt_box &b) {
+  return align256(sizeof(double) * (size_t)b.ntracers * b.nx * b.ny * b.nz);
+}
 
 struct Plan {
   int nboxes;
@@ -275,8 +278,8 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
 }
 
 template <int D>
-static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, int prev_d, int par, int cur,
-                          int wcc, hipStream_t st) {
+static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, int prev_d, int src, int dst,
+                          int cur, int wcc, hipStream_t st) {
   const Seg *psegs;
   int pn;
   int64_t pitems;
@@ -289,10 +292,10 @@ static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, i
     pn = pl.n_plic[prev_d];
     pitems = pl.items_plic[prev_d];
   }
-  hipLaunchKernelGGL((k_plic_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize, par, cur);
+  hipLaunchKernelGGL((k_plic_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize, src, cur);
   hipLaunchKernelGGL((k_stream_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes,
                      (const Seg *)(slab + pl.off_stream[D]), pl.n_stream[D], pl.items_stream[D], pl.chunk, pl.rsize,
-                     par, cur ^ 1, wcc);
+                     src, dst, cur ^ 1, wcc);
 }
 
 extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, int64_t step0,
@@ -317,8 +320,18 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus < 1)
     cus = 256;
   pl.grid = cus * wg;
+  // third copies of the fields for an odd number of sweeps (else the result is copied back)
+  uint8_t *third = nullptr;
+  if (nsteps % 2 == 1) {
+    size_t all = 0;
+    for (int i = 0; i < nboxes; ++i) all += field_bytes(boxes[i]);
+    third = (uint8_t *)scratch_if_free(ctx, SLOT_THIRD, all, stream);
+  }
+  size_t third_off = 0;
   for (int i = 0; i < nboxes; ++i) {
     BoxDev &d = bd[i];
+    d.f[2] = third ? (double *)(third + third_off) : nullptr;
+    third_off += field_bytes(boxes[i]);
     d.f[0] = boxes[i].c;
     d.f[1] = (double *)(slab + boff[6 * i + 0]);
     d.fmix = (double *)(slab + boff[6 * i + 1]);
@@ -332,7 +345,7 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   // the key of this configuration: boxes, tuning, sweep order, slab
   std::string key;
   key.append((const char *)boxes, sizeof(vofmt_box) * (size_t)nboxes);
-  const int64_t hdr[5] = {step0 % 3, nsteps, chunk, wg, (int64_t)(uintptr_t)slab};
+  const int64_t hdr[6] = {step0 % 3, nsteps, chunk, wg, (int64_t)(uintptr_t)slab, (int64_t)(uintptr_t)third};
   key.append((const char *)hdr, sizeof(hdr));
   if (ctx->graph && ctx->graph_key == key) {
     VOFMT_HIP(ctx, hipGraphLaunch(ctx->graph, stream));
@@ -358,21 +371,23 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   VOFMT_HIP(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
   hipLaunchKernelGGL(k_scan_b, dim3(pl.grid), dim3(256), 0, cs, dboxes, (const Seg *)(slab + pl.off_scan), pl.n_scan,
                      pl.items_scan, pl.rsize);
-  int par = 0, cur = 0, prev_d = -1;
+  int src = 0, dst = 1, cur = 0, prev_d = -1;
   for (int32_t st = 0; st < nsteps; ++st) {
     const int64_t g = step0 + st;
     for (int r = 0; r < 3; ++r) {
       const int d = (int)((g + r) % 3);
       const int wcc = (r == 0);
-      if (d == 0) enqueue_sweep<0>(slab, pl, dboxes, prev_d, par, cur, wcc, cs);
-      else if (d == 1) enqueue_sweep<1>(slab, pl, dboxes, prev_d, par, cur, wcc, cs);
-      else enqueue_sweep<2>(slab, pl, dboxes, prev_d, par, cur, wcc, cs);
+      if (d == 0) enqueue_sweep<0>(slab, pl, dboxes, prev_d, src, dst, cur, wcc, cs);
+      else if (d == 1) enqueue_sweep<1>(slab, pl, dboxes, prev_d, src, dst, cur, wcc, cs);
+      else enqueue_sweep<2>(slab, pl, dboxes, prev_d, src, dst, cur, wcc, cs);
       prev_d = d;
-      par ^= 1;
+      const int was = src;
+      src = dst;
+      dst = (third && st == 0) ? (r == 0 ? 2 : (r == 1 ? 0 : 1)) : was;
       cur ^= 1;
     }
   }
-  if (par == 1) hipLaunchKernelGGL(k_copy_b, dim3(pl.grid), dim3(256), 0, cs, dboxes, nboxes);
+  if (src != 0) hipLaunchKernelGGL(k_copy_b, dim3(pl.grid), dim3(256), 0, cs, dboxes, nboxes);
   hipGraph_t graph = nullptr;
   const hipError_t launch_err = hipGetLastError();
   const hipError_t end_err = hipStreamEndCapture(cs, &graph);

@@ -11,7 +11,7 @@
 
 #include "vofmt.h"
 
-enum { kNumSlotsDecl = 27 };
+enum { kNumSlotsDecl = 28 };
 
 // One timed launch: HIP events recorded before and after it on its stream.
 struct ProfRec {
@@ -70,7 +70,8 @@ enum ScratchSlot {
   SLOT_OCC = 24,           // recolouring, stencil mode: occupancy bits per 64-cell row segment
   SLOT_OCC_OTHERS = 25,    // and those of the other tracers
   SLOT_LIST_BITS = 26,     // interface-cell lists: one bit per cell from the counting pass
-  kNumSlots = 27,
+  SLOT_THIRD = 27,         // third copy of the fields: an odd number of sweeps ends in the caller's
+  kNumSlots = 28,
 };
 static_assert(kNumSlots == kNumSlotsDecl, "scratch slot count");
 
@@ -81,6 +82,10 @@ hipError_t noalloc_setup(int device);
 int hip_check(vofmt_ctx *ctx, hipError_t e, const char *what);
 // Device scratch of at least `bytes` in slot `slot`; nullptr on failure (error set).
 void *scratch(vofmt_ctx *ctx, int slot, size_t bytes);
+// The same for a buffer that the call can do without: nullptr and no error when
+// the memory is not there, or when it would have to be allocated while `stream`
+// is being captured.
+void *scratch_if_free(vofmt_ctx *ctx, int slot, size_t bytes, hipStream_t stream);
 void *host_scratch(vofmt_ctx *ctx, size_t bytes);
 // Timing of one launch when profiling is on: prof_begin before the launch
 // (returns a record index, or -1), prof_end after it.
