@@ -68,7 +68,7 @@ enum ScratchSlot {
   SLOT_CURV_HF = 22,     // cells handed to the height-function fallback; recolouring: list predicate bits
   SLOT_RECOLOR_LIST = 23,  // recolouring: drop-boundary and shared cells
   SLOT_OCC = 24,           // recolouring, stencil mode: occupancy bits per 64-cell row segment
-  SLOT_OCC_OTHERS = 25,    // and those of the other tracers
+  SLOT_OCC_LIST = 25,      // and the segments that may hold a pair
   SLOT_LIST_BITS = 26,     // interface-cell lists: one bit per cell from the counting pass
   SLOT_THIRD = 27,         // third copy of the fields: an odd number of sweeps ends in the caller's
   kNumSlots = 28,

@@ -11,26 +11,28 @@
 // GPU scheme:
 //   1. own[p]: global id of the only drop occupying cell p, -1 if none,
 //      -2 if several (drops of different tracers overlapping);
-//   2. every occupied cell scans the offsets of the ball and sets the bit of
-//      each neighbouring drop in a D x D adjacency bitmap (atomicOr; the
-//      bitmap is symmetric and its content independent of thread order);
+//   2. the boundary cells of the drops scan the offsets of the ball and set
+//      the bits of each pair of neighbouring drops in a D x D adjacency bitmap
+//      (atomicOr in both directions; its content is independent of thread
+//      order): tile by tile in LDS where the ball reaches 4 cells or less,
+//      from an ordered list of those cells beyond that;
 //   3. the bitmap is turned into sorted neighbour lists (CSR);
-//   4. one wavefront runs the greedy pass: tracers of all drops in LDS,
-//      neighbour lists streamed through LDS in chunks, one ballot per drop
-//      for the conflict test and an OR-reduction for the tracers in use;
+//   4. the greedy pass: in rounds by one workgroup, or by one wavefront when a
+//      drop needs a new tracer;
 //   5. the host reads back the tracer count (capacity check), then every
 //      cell clears its moved-out values and adds them to the new fields.
 //
 // Stencil mode (vofmt_recolor_tracers_stencil): the neighbour relation of
 // step 2 is the paper's criterion read literally. Within a tracer, two drops
 // are neighbours when an empty cell (label 0) has one of them and the other
-// at opposite offsets +o, -o of the 5x5x5 stencil (Steps 1-3): one wavefront
-// per 64-cell row segment tests the 62 opposite pairs on occupancy bits of
-// the 25 neighbouring rows and loads labels only for candidate pairs. Across
-// tracers, drops are neighbours ("in contact", Step 4) when cells of the two
-// lie within 4 cells along every axis (the stencil's reach), found by the
-// scan of step 2 over the half 9x9x9 cube, pairs within one tracer skipped.
-#include <cstdlib>
+// at opposite offsets +o, -o of the 5x5x5 stencil (Steps 1-3): one thread per
+// 64-cell row segment tests the 62 opposite pairs on occupancy bits of the 25
+// neighbouring rows, and one wavefront takes each segment that has a pair and
+// compares the labels. Across tracers, drops are neighbours ("in contact",
+// Step 4) when cells of the two lie within 4 cells along every axis (the
+// stencil's reach), found by the scan of step 2 over the half 9x9x9 cube,
+// pairs within one tracer skipped.
+#include <algorithm>
 #include <cstring>
 
 #include "common.hpp"
@@ -47,22 +49,27 @@ struct TracerOffsets {
   int32_t off[kMaxTracers + 1];  // first global drop id of each tracer
 };
 
+// Owners are 16-bit: at most kMaxDrops ids, -1 and -2.
+typedef int16_t owner_t;
+static_assert(kMaxDrops - 1 <= INT16_MAX, "drop ids fit 16 bits");
+
+__device__ __forceinline__ void add_owner(int32_t &o, int32_t l, int t, const TracerOffsets &to) {
+  if (l > 0 && to.off[t] + l <= to.off[t + 1]) o = (o == -1) ? to.off[t] + l - 1 : -2;
+}
+
 __global__ __launch_bounds__(kBlock) void k_owner(const int32_t *__restrict__ lab, int64_t n3, int ntr,
-                                                  TracerOffsets to, int32_t *__restrict__ own) {
+                                                  TracerOffsets to, owner_t *__restrict__ own) {
   const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (p >= n3) return;
   int32_t o = -1;
-  for (int t = 0; t < ntr; ++t) {
-    const int32_t l = lab[(int64_t)t * n3 + p];
-    if (l > 0 && to.off[t] + l <= to.off[t + 1]) o = (o == -1) ? to.off[t] + l - 1 : -2;
-  }
-  own[p] = o;
+  for (int t = 0; t < ntr; ++t) add_owner(o, lab[(int64_t)t * n3 + p], t, to);
+  own[p] = (owner_t)o;
 }
 
 // The same for 4 consecutive cells per thread with 16-byte label loads
 // (labels 16-byte aligned and n3 a multiple of 4).
 __global__ __launch_bounds__(kBlock) void k_owner4(const int4 *__restrict__ lab, int64_t n4, int ntr,
-                                                   TracerOffsets to, int4 *__restrict__ own) {
+                                                   TracerOffsets to, short4 *__restrict__ own) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= n4) return;
   int32_t o[4] = {-1, -1, -1, -1};
@@ -70,19 +77,21 @@ __global__ __launch_bounds__(kBlock) void k_owner4(const int4 *__restrict__ lab,
     const int4 l4 = lab[(int64_t)t * n4 + i];
     const int32_t l[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (l[k] > 0 && to.off[t] + l[k] <= to.off[t + 1]) o[k] = (o[k] == -1) ? to.off[t] + l[k] - 1 : -2;
+    for (int k = 0; k < 4; ++k) add_owner(o[k], l[k], t, to);
   }
-  own[i] = make_int4(o[0], o[1], o[2], o[3]);
+  own[i] = make_short4((short)o[0], (short)o[1], (short)o[2], (short)o[3]);
 }
 
 // v in (-n, 2n): one conditional add or subtract instead of a modulo
 __device__ __forceinline__ int wrap_near(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
+// The pair (a, b) in both directions.
 __device__ __forceinline__ void set_edge(uint32_t *adj, int64_t words, int32_t a, int32_t b) {
   uint32_t *w = adj + (int64_t)a * words + (b >> 5);
   const uint32_t bit = 1u << (b & 31);
-  if (!(*w & bit)) atomicOr(w, bit);
+  if (*w & bit) return;  // (whoever sets it sets the other direction too)
+  atomicOr(w, bit);
+  atomicOr(adj + (int64_t)b * words + (a >> 5), 1u << (a & 31));
 }
 
 // Calls f(id) for every drop occupying cell p (for cells shared by several drops).
@@ -95,7 +104,7 @@ __device__ __forceinline__ void for_drops_at(const int32_t *__restrict__ lab, in
   }
 }
 
-__device__ __forceinline__ void edges_of(const int32_t *__restrict__ own, const int32_t *__restrict__ lab, int nx,
+__device__ __forceinline__ void edges_of(const owner_t *__restrict__ own, const int32_t *__restrict__ lab, int nx,
                                          int ny, int nz, int ntr, const TracerOffsets &to,
                                          const int4 *__restrict__ offs, int noffs, int small_offsets,
                                          uint32_t *__restrict__ adj, int64_t words, int64_t n3, const FastDiv &fnx,
@@ -178,7 +187,7 @@ __device__ __forceinline__ void edges_of(const int32_t *__restrict__ own, const 
 // consecutive cells), its x neighbours come from the lanes beside it, and
 // only a row's end cells and the wavefront's edge lanes load theirs. The y
 // and z neighbours are loaded for cells of one drop only.
-__global__ __launch_bounds__(kBlock) void k_pair_source_counts(const int32_t *__restrict__ own, int nx, int ny,
+__global__ __launch_bounds__(kBlock) void k_pair_source_counts(const owner_t *__restrict__ own, int nx, int ny,
                                                                int nz, FastDiv fnx, FastDiv fny, int64_t n,
                                                                int32_t *__restrict__ bc, uint64_t *__restrict__ bits) {
   const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -220,7 +229,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_source_counts(const int32_t *__
 }
 
 // Near-contact pairs seen from the listed cells (persistent grid).
-__global__ __launch_bounds__(kBlock) void k_edges(const int32_t *__restrict__ own, const int32_t *__restrict__ lab,
+__global__ __launch_bounds__(kBlock) void k_edges(const owner_t *__restrict__ own, const int32_t *__restrict__ lab,
                                                   int nx, int ny, int nz, int ntr, TracerOffsets to,
                                                   const int4 *__restrict__ offs, int noffs, int small_offsets,
                                                   const int32_t *__restrict__ list, const int32_t *__restrict__ count,
@@ -234,20 +243,34 @@ __global__ __launch_bounds__(kBlock) void k_edges(const int32_t *__restrict__ ow
   }
 }
 
-// Occupancy of every 64-cell row segment of every tracer: bit l of word
-// occ[t][z][y][w] is (label > 0) of cell x = 64 w + l (0 beyond the row).
-__global__ __launch_bounds__(kBlock) void k_occ_words(const int32_t *__restrict__ lab, int nx, int64_t rows,
-                                                      int words, uint64_t *__restrict__ occ) {
+// Owners and occupancy of one 64-cell row segment per wavefront, for every
+// tracer from one read of its labels: bit l of word occ[t][z][y][w] is
+// (label > 0) of cell x = 64 w + l (0 beyond the row). nseg1: words per tracer.
+constexpr int kOccBatch = 4;  // tracers whose labels are in flight together
+__global__ __launch_bounds__(kBlock) void k_owner_occ(const int32_t *__restrict__ lab, int nx, int64_t nseg1,
+                                                      int64_t n3, int words, FastDiv fw, int ntr, TracerOffsets to,
+                                                      owner_t *__restrict__ own, uint64_t *__restrict__ occ) {
   const int64_t seg = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
-  const int64_t nseg = rows * words;
-  if (seg >= nseg) return;  // whole wavefront
-  const int64_t row = seg / words;
-  const int w = (int)(seg - row * words);
-  const int x = 64 * w + lane;
-  const bool occ_ = x < nx && lab[row * nx + x] > 0;
-  const uint64_t b = __ballot(occ_);
-  if (lane == 0) occ[seg] = b;
+  if (seg >= nseg1) return;  // whole wavefront
+  const uint32_t row = fast_div((uint32_t)seg, fw);
+  const int x = 64 * (int)((uint32_t)seg - row * (uint32_t)words) + lane;
+  const int64_t p = (int64_t)row * nx + x;
+  const bool in = x < nx;
+  int32_t o = -1;
+  for (int t0 = 0; t0 < ntr; t0 += kOccBatch) {
+    int32_t l[kOccBatch];
+#pragma unroll
+    for (int k = 0; k < kOccBatch; ++k) l[k] = (in && t0 + k < ntr) ? lab[(int64_t)(t0 + k) * n3 + p] : 0;
+#pragma unroll
+    for (int k = 0; k < kOccBatch; ++k) {
+      if (t0 + k >= ntr) break;
+      add_owner(o, l[k], t0 + k, to);
+      const uint64_t b = __ballot(l[k] > 0);
+      if (lane == 0) occ[(int64_t)(t0 + k) * nseg1 + seg] = b;
+    }
+  }
+  if (in) own[p] = (owner_t)o;
 }
 
 // Bit m of v (m < 16) to bit 4m.
@@ -260,22 +283,41 @@ __device__ __forceinline__ uint64_t spread4(uint64_t v) {
   return v;
 }
 
-// The same words when rows hold a multiple of 256 cells: one wavefront per
-// four segments of a row, each lane loading four labels at once (cells
+// The same when rows hold a multiple of 256 cells: one wavefront per four
+// segments of a row, each lane loading four labels of a tracer at once (cells
 // 4l .. 4l+3 of the 256); ballot k holds component k of every lane, and the
-// word of segment j interleaves 16 bits of each ballot.
-__global__ __launch_bounds__(kBlock) void k_occ_words4(const int4 *__restrict__ lab4, int64_t ngroups,
+// word of segment j interleaves 16 bits of each ballot. One read of the labels
+// for owners and words: 104 + 108 us as two passes at 256^3 x 8, 112 us so.
+__global__ __launch_bounds__(kBlock) void k_owner_occ4(const int4 *__restrict__ lab4, int64_t ngroups, int ntr,
+                                                       TracerOffsets to, short4 *__restrict__ own,
                                                        uint64_t *__restrict__ occ) {
   const int64_t g = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (g >= ngroups) return;  // whole wavefront
-  const int4 v = lab4[g * 64 + lane];  // segments 4g .. 4g+3 are cells 256g .. 256g+255 of the fields
-  const uint64_t b0 = __ballot(v.x > 0), b1 = __ballot(v.y > 0), b2 = __ballot(v.z > 0), b3 = __ballot(v.w > 0);
-  if (lane < 4) {
-    const int sh = 16 * lane;
-    occ[4 * g + lane] = spread4(b0 >> sh) | (spread4(b1 >> sh) << 1) | (spread4(b2 >> sh) << 2) |
-                        (spread4(b3 >> sh) << 3);
+  int32_t o[4] = {-1, -1, -1, -1};
+  for (int t0 = 0; t0 < ntr; t0 += kOccBatch) {
+    int4 v[kOccBatch];
+#pragma unroll
+    for (int k = 0; k < kOccBatch; ++k)  // segments 4g .. 4g+3 are cells 256g .. 256g+255 of a field
+      v[k] = lab4[((int64_t)(t0 + k < ntr ? t0 + k : t0) * ngroups + g) * 64 + lane];
+#pragma unroll
+    for (int k = 0; k < kOccBatch; ++k) {
+      const int t = t0 + k;
+      if (t >= ntr) break;
+      add_owner(o[0], v[k].x, t, to);
+      add_owner(o[1], v[k].y, t, to);
+      add_owner(o[2], v[k].z, t, to);
+      add_owner(o[3], v[k].w, t, to);
+      const uint64_t b0 = __ballot(v[k].x > 0), b1 = __ballot(v[k].y > 0), b2 = __ballot(v[k].z > 0),
+                     b3 = __ballot(v[k].w > 0);
+      if (lane < 4) {
+        const int sh = 16 * lane;
+        occ[4 * ((int64_t)t * ngroups + g) + lane] =
+            spread4(b0 >> sh) | (spread4(b1 >> sh) << 1) | (spread4(b2 >> sh) << 2) | (spread4(b3 >> sh) << 3);
+      }
+    }
   }
+  own[g * 64 + lane] = make_short4((short)o[0], (short)o[1], (short)o[2], (short)o[3]);
 }
 
 // Bits of cells xs, xs+1, ..., xs+63 (periodic in x, xs any integer) of one
@@ -325,39 +367,141 @@ static StencilPairs make_stencil_pairs() {
   return sp;
 }
 
-// Steps 1-3 within tracer t for the 64 cells of one row segment. Lane k < 62
-// takes the opposite pair k of the stencil, offsets +o and -o, and forms over
-// the segment's cells at once, from three 64-bit windows of occupancy bits,
-// the cells whose centre is empty (label 0) and whose cells at +o and -o are
-// both occupied; for each such cell it loads the two labels and records the
-// two drops as neighbours when they differ (Step 3). Every pair is tested for
-// every cell, as in the definition; a lane's bit operations replace 64
-// per-cell tests.
-constexpr int kStencilSegs = 16;  // segments per wavefront of k_stencil_edges (1: 5.32 ms, 4: 4.92, 8: 4.76, 16: 4.64 at 512^3 x 8)
+// (t, row of the tracer, y, z, word) of segment seg of all tracers: segment
+// counts stay below 2^31, so the divisions are 32-bit multiply-shifts.
+struct SegAt {
+  int t, w, y, z;
+  int64_t r;
+};
+__device__ __forceinline__ SegAt seg_at(uint32_t seg, int words, int64_t rows, int ny, const FastDiv &fw,
+                                        const FastDiv &frows, const FastDiv &fny) {
+  SegAt s;
+  const uint32_t tr = fast_div(seg, fw);
+  s.w = (int)(seg - tr * (uint32_t)words);
+  const uint32_t t32 = fast_div(tr, frows);
+  s.t = (int)t32;
+  s.r = (int64_t)(tr - t32 * (uint32_t)rows);
+  const uint32_t z32 = fast_div((uint32_t)s.r, fny);
+  s.z = (int)z32;
+  s.y = (int)((uint32_t)s.r - z32 * (uint32_t)ny);
+  return s;
+}
+
+// offsets reach 2 cells: one conditional wrap when the axis has 3 cells or more
+__device__ __forceinline__ int wrap2(int v, int n) {
+  return n >= 3 ? (v < 0 ? v + n : (v >= n ? v - n : v)) : wrap_any(v, n);
+}
+
+// Steps 1-3 find a pair around an empty cell p (label 0) when p + o and p - o
+// are occupied for one of the 62 opposite offset pairs. One thread per row
+// segment tests all pairs for its 64 cells on occupancy bits: for each of the
+// 12 opposite row pairs (and the cell's own row) the row's 64 cells shifted by
+// -2 .. 2, and the AND of opposite shifts with the empty cells. A drop of
+// convex shape has no such cell (the midpoint of a point in p + o and one in
+// p - o lies in p), so few segments are left; their indices are appended to
+// `list` in any order. One wavefront per segment instead, a lane per pair,
+// spent a wavefront's whole pass on every segment: 642 us at 256^3 x 8, 4.64
+// ms at 512^3 x 8, against 95 us and 0.70 ms for this pass and the
+// listed segments together.
+//
+// A row's window needs the two cells before and after its 64. FAST: rows of 3
+// cells or more whose last segment holds at least 2 (nx % 64 != 1): they are the
+// top and bottom bits of the words beside it (at a row's ends, of its other
+// end), and every shifted half is one funnel shift.
+template <bool FAST>
+__global__ __launch_bounds__(kBlock) void k_stencil_segments(const uint64_t *__restrict__ occ, int nx, int ny, int nz,
+                                                             int words, int64_t nseg, FastDiv fw, FastDiv frows,
+                                                             FastDiv fny, int32_t *__restrict__ list,
+                                                             uint32_t *__restrict__ count) {
+  const int64_t seg = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t rows = (int64_t)nz * ny;
+  uint64_t any = 0;
+  if (seg < nseg) {
+    const SegAt s = seg_at((uint32_t)seg, words, rows, ny, fw, frows, fny);
+    const uint64_t *occ_t = occ + (int64_t)s.t * rows * words;
+    const int x0 = 64 * s.w;
+    const bool end = s.w == words - 1;
+    const int nlast = nx - 64 * (words - 1), nvalid = end ? nlast : 64;
+    const uint64_t valid = nvalid == 64 ? ~0ull : ((1ull << nvalid) - 1ull);
+    const int ip = s.w > 0 ? s.w - 1 : words - 1;  // the words before and after, around the row
+    const int in = end ? 0 : s.w + 1;
+    const int shp = s.w > 0 ? 0 : 64 - nlast;      // brings the cell before x0 to bit 63
+    const int shn = 64 - nvalid;                   // and the cell after the 64 to bit 0
+    // the 64 cells from x0 + d, d = -2 .. 2, of a row, as halves
+    struct Shifts {
+      uint32_t lo[5], hi[5];
+    };
+    auto shifts = [&](int dy, int dz) -> Shifts {
+      const uint64_t *rw = occ_t + (uint32_t)((wrap2(s.z + dz, nz) * ny + wrap2(s.y + dy, ny)) * words);
+      Shifts o;
+      if constexpr (FAST) {
+        const uint64_t nw = rw[in], w0 = rw[s.w];
+        const uint32_t before = (uint32_t)((rw[ip] << shp) >> 32), after = (uint32_t)(nw >> shn);
+        const uint64_t w = shn > 0 ? w0 | (nw << nvalid) : w0;
+        const uint32_t l = (uint32_t)w, h = (uint32_t)(w >> 32);
+        o.lo[0] = __builtin_amdgcn_alignbit(l, before, 30);
+        o.hi[0] = __builtin_amdgcn_alignbit(h, l, 30);
+        o.lo[1] = __builtin_amdgcn_alignbit(l, before, 31);
+        o.hi[1] = __builtin_amdgcn_alignbit(h, l, 31);
+        o.lo[2] = l;
+        o.hi[2] = h;
+        o.lo[3] = __builtin_amdgcn_alignbit(h, l, 1);
+        o.hi[3] = __builtin_amdgcn_alignbit(after, h, 1);
+        o.lo[4] = __builtin_amdgcn_alignbit(h, l, 2);
+        o.hi[4] = __builtin_amdgcn_alignbit(after, h, 2);
+      } else {
+        for (int d = 0; d < 5; ++d) {
+          const uint64_t v = row_window(rw, nx, x0 + d - 2);
+          o.lo[d] = (uint32_t)v;
+          o.hi[d] = (uint32_t)(v >> 32);
+        }
+      }
+      return o;
+    };
+    const Shifts c = shifts(0, 0);
+    uint32_t lo = (c.lo[0] & c.lo[4]) | (c.lo[1] & c.lo[3]), hi = (c.hi[0] & c.hi[4]) | (c.hi[1] & c.hi[3]);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const int dz = k < 2 ? 0 : (k < 7 ? 1 : 2), dy = k < 2 ? k + 1 : (k < 7 ? k - 4 : k - 9);
+      const Shifts a = shifts(dy, dz), b = shifts(-dy, -dz);
+#pragma unroll
+      for (int d = 0; d < 5; ++d) {
+        lo |= a.lo[d] & b.lo[4 - d];
+        hi |= a.hi[d] & b.hi[4 - d];
+      }
+    }
+    any = (((uint64_t)hi << 32) | lo) & ~(((uint64_t)c.hi[2] << 32) | c.lo[2]) & valid;
+  }
+  const uint64_t mask = __ballot(any != 0ull);
+  if (mask == 0ull) return;  // whole wavefront
+  const int lane = threadIdx.x & 63;
+  uint32_t base = 0;
+  if (lane == 0) base = atomicAdd(count, (uint32_t)__popcll(mask));
+  base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+  if (any != 0ull) list[base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = (int32_t)seg;
+}
+
+// The pairs of the listed segments (persistent grid, one wavefront per
+// segment). Lane k < 62 takes the opposite pair k of the stencil, offsets +o
+// and -o, and forms from three 64-bit windows of occupancy bits the cells whose
+// centre is empty and whose cells at +o and -o are both occupied; for each such
+// cell it loads the two labels and records the two drops as neighbours when
+// they differ (Step 3).
 __global__ __launch_bounds__(kBlock) void k_stencil_edges(const int32_t *__restrict__ lab,
                                                           const uint64_t *__restrict__ occ, int nx, int ny, int nz,
-                                                          int ntr, int words, TracerOffsets to, StencilPairs sp,
+                                                          int words, TracerOffsets to, StencilPairs sp,
                                                           uint32_t *__restrict__ adj, int64_t awords, FastDiv fw,
-                                                          FastDiv frows, FastDiv fny) {
+                                                          FastDiv frows, FastDiv fny, const int32_t *__restrict__ list,
+                                                          const uint32_t *__restrict__ count) {
   const int lane = threadIdx.x & 63;
   const int64_t rows = (int64_t)nz * ny;
-  const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-  for (int ks = 0; ks < kStencilSegs; ++ks) {  // consecutive segments of one wavefront
-  const int64_t seg = wave * kStencilSegs + ks;
-  if (seg >= (int64_t)ntr * rows * words) return;  // whole wavefront
-  // (t, z, y) row of all tracers and word w: segment counts stay below 2^31,
-  // so the divisions are 32-bit multiply-shifts
-  const uint32_t tr = fast_div((uint32_t)seg, fw);
-  const int w = (int)((uint32_t)seg - tr * (uint32_t)words);
-  const uint32_t t32 = fast_div(tr, frows);
-  const int t = (int)t32;
-  const int64_t r = (int64_t)(tr - t32 * (uint32_t)rows);
-  const uint32_t z32 = fast_div((uint32_t)r, fny);
-  const int z = (int)z32, y = (int)((uint32_t)r - z32 * (uint32_t)ny);
+  const uint32_t nlist = *count;
+  for (uint32_t q = (blockIdx.x * kBlock + threadIdx.x) >> 6; q < nlist; q += gridDim.x * (kBlock / 64)) {
+  const SegAt sg = seg_at((uint32_t)list[q], words, rows, ny, fw, frows, fny);
+  const int t = sg.t, w = sg.w, y = sg.y, z = sg.z;
+  const int64_t r = sg.r;
   const uint64_t *occ_t = occ + (int64_t)t * rows * words;
   const int x0 = 64 * w;
-  // offsets reach 2 cells: one conditional wrap when the axis has 3 cells or more
-  auto wrap2 = [](int v, int n) { return n >= 3 ? (v < 0 ? v + n : (v >= n ? v - n : v)) : wrap_any(v, n); };
   const int nvalid = nx - x0 < 64 ? nx - x0 : 64;
   const uint64_t valid = nvalid == 64 ? ~0ull : ((1ull << nvalid) - 1ull);
   const uint64_t empty = ~occ_t[r * words + w] & valid;  // bit i: cell x0 + i has no drop of tracer t
@@ -372,7 +516,6 @@ __global__ __launch_bounds__(kBlock) void k_stencil_edges(const int32_t *__restr
     // bit i: cell x0 + i + ox of the row at +o, cell x0 + i - ox of the row at -o
     cand = row_window(rp, nx, x0 + ox) & row_window(rm, nx, x0 - ox) & empty;
   }
-  if (__ballot(cand != 0ull) == 0ull) continue;  // no pair around any empty cell of the segment
   const int64_t rowp = ((int64_t)t * nz + wrap2(z + oz, nz)) * ny + wrap2(y + oy, ny);
   const int64_t rowm = ((int64_t)t * nz + wrap2(z - oz, nz)) * ny + wrap2(y - oy, ny);
   const int64_t qc = (((int64_t)t * nz + z) * ny + y) * nx + x0;  // a cell of the segment (x0 < nx)
@@ -402,7 +545,6 @@ __global__ __launch_bounds__(kBlock) void k_stencil_edges(const int32_t *__restr
           !(a == last_a && b == last_b)) {
         const int32_t ga = to.off[t] + a - 1, gb = to.off[t] + b - 1;
         set_edge(adj, awords, ga, gb);
-        set_edge(adj, awords, gb, ga);
         last_a = a;
         last_b = b;
       }
@@ -411,89 +553,211 @@ __global__ __launch_bounds__(kBlock) void k_stencil_edges(const int32_t *__restr
   }
 }
 
-// Occupancy of the other tracers: word (row, w) of others[t] is the OR of
-// that word of occ[u] over every tracer u != t (prefix ORs going up, suffix
-// ORs coming down). nseg1: words per tracer.
-__global__ __launch_bounds__(kBlock) void k_other_tracers(const uint64_t *__restrict__ occ, int64_t nseg1, int ntr,
-                                                          uint64_t *__restrict__ others) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= nseg1) return;
-  uint64_t acc = 0;
-  for (int t = 0; t < ntr; ++t) {
-    others[(int64_t)t * nseg1 + i] = acc;
-    acc |= occ[(int64_t)t * nseg1 + i];
-  }
-  acc = 0;
-  for (int t = ntr - 1; t >= 0; --t) {
-    others[(int64_t)t * nseg1 + i] |= acc;
-    acc |= occ[(int64_t)t * nseg1 + i];
-  }
-}
+// Near-contact pairs, tile by tile: a workgroup takes 64 x 8 x 8 cells and
+// holds their owners in LDS with the halo that a half ball of reach R needs (R
+// cells along x and y on both sides, R above and one below along z). The
+// tile's boundary cells (a shared cell, or a cell of one drop with a
+// six-neighbour not owned by it: an interior cell finds no pair that a boundary
+// cell of its drop does not, since a lattice path from it towards any other
+// drop's cell, one axis step at a time, only gets closer and leaves the drop
+// through a boundary cell) are compacted into an LDS list, so that full
+// wavefronts scan the offsets, and every owner they look at is an LDS read.
+// From a list of those cells in memory (counted, scanned, written, then
+// scattered 4-byte loads, one cache line per lane) the same pairs took 1.60 ms
+// at 512^3 x 8 drops with the 40 offsets of the distance 1.5 and 0.39 ms so;
+// the 364 offsets of the stencil mode 4.9 ms, and 1.06 ms so.
+// cross_T0 != null: only drops of different tracers (initial tracer per drop)
+// are related.
+constexpr int kTileX = 64, kTileY = 8, kTileZ = 8;
+constexpr int kMaxTileReach = 4;
+constexpr int kHaloX = 4;  // cells of x-halo held, whatever the reach: the tile's rows stay 8-byte aligned
+constexpr int kPairCache = 256;
+// The half ball as rows of cells along x: row k covers x + lo .. x + hi at the
+// LDS offset `base` of its (dy, dz).
+struct TileRows {
+  int n;
+  int16_t base[(kMaxTileReach + 1) * (2 * kMaxTileReach + 1)];
+  int8_t lo[(kMaxTileReach + 1) * (2 * kMaxTileReach + 1)], hi[(kMaxTileReach + 1) * (2 * kMaxTileReach + 1)];
+};
+template <int R>
+struct TileDims {
+  static constexpr int LX = kTileX + 2 * kHaloX, LY = kTileY + 2 * R, LZ = kTileZ + R + 1;
+};
+typedef uint16_t owner2 __attribute__((ext_vector_type(2)));
 
-// Stencil mode, contacts across tracers (persistent grid over the listed
-// cells): the pairs k_edges finds with the half cube max|o_a| <= 4, where
-// only drops of different tracers are related. A listed cell p of a single
-// drop a, of tracer t, takes the cube row by row: a 9-bit window of others[t]
-// (cells x-4 .. x+4 of the row; x+1 .. x+4 in its own row) marks the cells
-// that hold a drop of another tracer, and only their owners are loaded. A
-// cell with no other tracer can pair a with no drop of another tracer, so the
-// edges are those of the full scan. Shared cells take the full scan.
-__global__ __launch_bounds__(kBlock) void k_edges_cross(const int32_t *__restrict__ own,
-                                                        const int32_t *__restrict__ lab, const uint64_t *__restrict__ others,
-                                                        int nx, int ny, int nz, int ntr, int xw, TracerOffsets to,
-                                                        const int4 *__restrict__ offs, int noffs, int small_offsets,
-                                                        const int32_t *__restrict__ list,
-                                                        const int32_t *__restrict__ count, uint32_t *__restrict__ adj,
-                                                        int64_t words, FastDiv fnx, FastDiv fny,
-                                                        const int32_t *__restrict__ T0) {
-  const int64_t n3 = (int64_t)nx * ny * nz;
-  const int64_t nseg1 = (int64_t)nz * ny * xw;
-  const int nlist = *count;
-  for (int qi = blockIdx.x * kBlock + threadIdx.x; qi < nlist; qi += gridDim.x * kBlock) {
-    const int64_t p = list[qi];
-    const int32_t a = own[p];
-    if (a < 0) {  // a shared cell
-      edges_of(own, lab, nx, ny, nz, ntr, to, offs, noffs, small_offsets, adj, words, n3, fnx, fny, T0, p);
-      continue;
+template <int R>
+__global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict__ own,
+                                                       const int32_t *__restrict__ lab, int nx, int ny, int nz,
+                                                       int ntr, TracerOffsets to, TileRows rows, int reach, int max_o2,
+                                                       int tx, int ty, uint32_t *__restrict__ adj, int64_t words,
+                                                       const int32_t *__restrict__ cross_T0) {
+  constexpr int LX = TileDims<R>::LX, LY = TileDims<R>::LY, LZ = TileDims<R>::LZ;
+  constexpr int kWaves = kBlock / 64, kRows = LY * LZ;
+  constexpr int ND = R + 1;  // pairs of cells that cover 2 R + 1 cells from either parity
+  // (8 entries behind the last row: a window's superset may end there)
+  __shared__ __attribute__((aligned(16))) owner_t tile[LX * kRows + 8];
+  // cells of one drop from the front, shared cells from the back
+  constexpr int kCellsOfTile = kTileX * kTileY * kTileZ;
+  __shared__ uint16_t list[kCellsOfTile];
+  __shared__ uint32_t known[kPairCache];  // pairs already in the bitmap
+  __shared__ int nlist, nshared;
+  // each XCD takes a contiguous run of tiles, so that a tile's halo is in its L2
+  const unsigned nwg = gridDim.x, per = nwg / 8, rem = nwg % 8, k8 = blockIdx.x % 8;
+  const unsigned L = k8 * per + (k8 < rem ? k8 : rem) + blockIdx.x / 8;
+  const int x0 = (int)(L % tx) * kTileX, y0 = (int)((L / tx) % ty) * kTileY, z0 = (int)(L / ((unsigned)tx * ty)) * kTileZ;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Cells before the tile's row (y0 - R + ly, z0 - 1 + lz): at_y[ly] + at_z[lz],
+  // -1 for a row R or more past the grid's end, nobody's neighbour here.
+  __shared__ int32_t at_y[LY], at_z[LZ];
+  if (threadIdx.x == 0) nlist = nshared = 0;
+  if (threadIdx.x < kPairCache) known[threadIdx.x] = ~0u;
+  if (threadIdx.x < 8) tile[LX * kRows + threadIdx.x] = (owner_t)-1;
+  if (threadIdx.x < LY) {
+    const int y = y0 - R + (int)threadIdx.x;
+    at_y[threadIdx.x] = y < ny + R ? wrap_near(y, ny) * nx : -1;
+  } else if (threadIdx.x >= 64 && threadIdx.x < 64 + LZ) {
+    const int z = z0 - 1 + (int)threadIdx.x - 64;
+    at_z[threadIdx.x - 64] = z < nz + R ? wrap_near(z, nz) * (ny * nx) : -1;
+  }
+  __syncthreads();
+  if (nx % 4 == 0) {
+    // groups of 4 cells, 8 bytes, that never straddle a row's end: a thread
+    // keeps its group of the row and takes every kStep-th row
+    constexpr int kGroups = LX / 4, kStep = kBlock / kGroups, kInFlight = 5;
+    const int r1 = threadIdx.x / kGroups, g = threadIdx.x % kGroups;
+    const int xg = x0 - kHaloX + 4 * g;
+    const bool mine = r1 < kStep && xg < nx + kHaloX;
+    const owner_t *src = own + wrap_near(xg, nx);
+    for (int r0 = r1; r0 < kRows; r0 += kStep * kInFlight) {
+      uint2 v[kInFlight];
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k) {
+        const int r = r0 + k * kStep;
+        v[k] = make_uint2(~0u, ~0u);
+        if (r < kRows && mine) {
+          const int oy = at_y[r % LY], oz = at_z[r / LY];
+          if (oy >= 0 && oz >= 0) v[k] = *(const uint2 *)(src + (uint32_t)(oy + oz));
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k)
+        if (r0 + k * kStep < kRows && r1 < kStep) *(uint2 *)(tile + (r0 + k * kStep) * LX + 4 * g) = v[k];
     }
-    const uint32_t r = fast_div((uint32_t)p, fnx), zz = fast_div(r, fny);  // cells < 2^31
-    const int x = (int)((uint32_t)p - r * (uint32_t)nx), y = (int)(r - zz * (uint32_t)ny), z = (int)zz;
-    const int ta = T0[a];
-    const uint64_t *ot = others + (int64_t)ta * nseg1;
-    int32_t last_b = -1;
-    auto visit = [&](int64_t q) {
-      const int32_t b = own[q];
-      if (b == -1 || b == last_b) return;
-      if (b >= 0) {
-        if (T0[b] != ta) {
-          set_edge(adj, words, a, b);
-          last_b = b;
-        }
-      } else {
-        for_drops_at(lab, n3, ntr, to, q, [&](int32_t v) {
-          if (T0[v] != ta) set_edge(adj, words, a, v);
-        });
-      }
+  } else {
+    auto owner_at = [&](int r, int i) -> owner_t {
+      const int x = x0 - kHaloX + i, oy = at_y[r % LY], oz = at_z[r / LY];
+      return (x < nx + kHaloX && oy >= 0 && oz >= 0) ? own[(uint32_t)(oy + oz + wrap_near(x, nx))] : (owner_t)-1;
     };
-    // the 40 rows of the half cube: (dz, dy) = (0, 1..4) and (1..4, -4..4)
-    for (int dz = 0; dz <= 4; ++dz)
-      for (int dy = (dz == 0 ? 1 : -4); dy <= 4; ++dy) {
-        const int64_t row = (int64_t)wrap_any(z + dz, nz) * ny + wrap_any(y + dy, ny);
-        uint64_t m = row_window(ot + row * xw, nx, x - 4) & 0x1FFull;
-        while (m) {
-          const int i = __ffsll((unsigned long long)m) - 1;
-          m &= m - 1;
-          visit(row * nx + wrap_any(x - 4 + i, nx));
-        }
+    // 64 cells of a row per wavefront, then the last 8 of the rows
+    constexpr int kInFlight = 13;
+    for (int r0 = wv; r0 < kRows; r0 += kWaves * kInFlight) {
+      owner_t v[kInFlight];
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k) v[k] = r0 + k * kWaves < kRows ? owner_at(r0 + k * kWaves, lane) : (owner_t)-1;
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k)
+        if (r0 + k * kWaves < kRows) tile[(r0 + k * kWaves) * LX + lane] = v[k];
+    }
+    for (int e = threadIdx.x; e < kRows * 8; e += kBlock) tile[(e >> 3) * LX + 64 + (e & 7)] = owner_at(e >> 3, 64 + (e & 7));
+  }
+  __syncthreads();
+  // boundary cells: 4 consecutive cells per lane, 4 rows per wavefront
+  for (int r0 = 4 * wv; r0 < kTileY * kTileZ; r0 += 4 * kWaves) {
+    const int r = r0 + (lane >> 4), dy = r % kTileY, dz = r / kTileY;
+    const int xl = 4 * (lane & 15), i = ((dz + 1) * LY + dy + R) * LX + kHaloX + xl;
+    auto four = [&](int at) { return *(const uint64_t *)(tile + at); };
+    const uint64_t c = four(i);
+    // fields that differ from a neighbour's along x, y or z
+    const uint64_t d = (c ^ ((c << 16) | (uint16_t)tile[i - 1])) | (c ^ ((c >> 16) | ((uint64_t)(uint16_t)tile[i + 4] << 48))) |
+                       (c ^ four(i - LX)) | (c ^ four(i + LX)) | (c ^ four(i - LX * LY)) | (c ^ four(i + LX * LY));
+    const bool in = y0 + dy < ny && z0 + dz < nz;
+    uint64_t mask[4];
+    int total = 0, at = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int32_t a = (int16_t)(c >> (16 * k));
+      const bool cell = in && x0 + xl + k < nx;
+      if (cell && a == -2) list[kCellsOfTile - 1 - atomicAdd(&nshared, 1)] = (uint16_t)(i + k);
+      mask[k] = __ballot(cell && a >= 0 && ((d >> (16 * k)) & 0xFFFFull) != 0ull);
+      total += (int)__popcll(mask[k]);
+    }
+    if (total == 0) continue;  // whole wavefront
+    if (lane == 0) at = atomicAdd(&nlist, total);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int e = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[k], 0u));
+      if ((mask[k] >> lane) & 1ull) list[e] = (uint16_t)(i + k);
+      at += (int)__popcll(mask[k]);
+    }
+  }
+  __syncthreads();
+  const int n = nlist;
+  const int64_t n3 = (int64_t)nx * ny * nz;
+  auto edge = [&](int32_t u, int32_t v) {
+    if (u == v) return;
+    const uint32_t key = (uint32_t)u * kMaxDrops + (uint32_t)v;
+    uint32_t *slot = &known[((uint32_t)u * 31u + (uint32_t)v) % kPairCache];
+    if (*slot == key) return;
+    *slot = key;
+    if (cross_T0 != nullptr && cross_T0[u] == cross_T0[v]) return;
+    set_edge(adj, words, u, v);
+  };
+  // A row is looked at cell by cell only where some cell of it (or of the one
+  // beside it that the pairs of cells include) holds one drop, not this cell's
+  // and not the one just paired (a boundary cell sees a neighbouring drop
+  // through many offsets). Shared cells are left to the loop below.
+  for (int q = threadIdx.x; q < n; q += kBlock) {
+    const int i = list[q];
+    const int32_t a = tile[i];
+    int32_t last = a;
+    const owner2 none = (uint16_t)0xFFFF, several = (uint16_t)0xFFFE, mine = (uint16_t)a;
+    for (int k = 0; k < rows.n; ++k) {
+      const int at = i + rows.base[k];
+      const int s0 = (at + rows.lo[k]) & ~1;
+      const owner2 before = (uint16_t)last;
+      owner2 m = 0;
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        const owner2 w = *(const owner2 *)(tile + s0 + 2 * j);
+        // 0 for -1 and -2 (the two largest), for a and for last
+        m |= __builtin_elementwise_min(__builtin_elementwise_min((owner2)(w ^ mine), (owner2)(w ^ before)),
+                                       __builtin_elementwise_min((owner2)(w ^ none), (owner2)(w ^ several)));
       }
-    // the cell's own row: x+1 .. x+4
-    {
-      const int64_t row = (int64_t)z * ny + y;
-      uint64_t m = row_window(ot + row * xw, nx, x + 1) & 0xFull;
-      while (m) {
-        const int i = __ffsll((unsigned long long)m) - 1;
-        m &= m - 1;
-        visit(row * nx + wrap_any(x + 1 + i, nx));
+      if (__builtin_bit_cast(uint32_t, m) == 0u) continue;
+      for (int dx = rows.lo[k]; dx <= rows.hi[k]; ++dx) {
+        const int32_t b = tile[at + dx];
+        if (b < 0 || b == a || b == last) continue;
+        edge(a, b);
+        last = b;
+      }
+    }
+  }
+  // Shared cells scan the whole ball (the cells of one drop above do not look
+  // at them), a wavefront each, a lane per offset: drops sharing the cell are
+  // neighbours (offset 0 across tracers), and each of them of every drop in
+  // the ball.
+  for (int q = wv; q < nshared; q += kWaves) {
+    const int i = list[kCellsOfTile - 1 - q], r = i / LX;
+    const int x = x0 - kHaloX + i % LX, y = y0 - R + r % LY, z = z0 - 1 + r / LY;
+    const int64_t p = ((int64_t)z * ny + y) * nx + x;
+    int32_t here = -1;  // lane t: the drop of tracer t here (at most 64 tracers)
+    if (lane < ntr) {
+      const int32_t l = lab[(int64_t)lane * n3 + p];
+      if (l > 0 && to.off[lane] + l <= to.off[lane + 1]) here = to.off[lane] + l - 1;
+    }
+    const uint64_t drops = __ballot(here >= 0);
+    const int side = 2 * reach + 1, all = side * side * side;
+    for (int e = lane; e < ((all + 63) & ~63); e += 64) {
+      const int ox = e % side - reach, oy = (e / side) % side - reach, oz = e / (side * side) - reach;
+      const bool in = e < all && ox * ox + oy * oy + oz * oz <= max_o2;
+      const int64_t at = ((int64_t)wrap_near(z + (in ? oz : 0), nz) * ny + wrap_near(y + (in ? oy : 0), ny)) * nx +
+                         wrap_near(x + (in ? ox : 0), nx);
+      const int32_t b = in ? own[at] : -1;
+      for (uint64_t left = drops; left; left &= left - 1) {
+        const int32_t u = __builtin_amdgcn_readlane(here, (int)__builtin_ctzll(left));
+        if (b >= 0) edge(u, b);
+        else if (b == -2) for_drops_at(lab, n3, ntr, to, at, [&](int32_t v) { edge(u, v); });
       }
     }
   }
@@ -509,25 +773,18 @@ __global__ void k_fill_f64(double *p, int64_t n, double v) {
     p[i] = v;
 }
 
-// Degree of every drop (symmetrise first: a bit set in either direction).
-__global__ __launch_bounds__(kBlock) void k_degree(uint32_t *__restrict__ adj, int32_t D, int64_t words,
+// Degree of every drop: one wavefront per drop, its row of the bitmap read in
+// order (a thread per drop, rows apart, took 33 us at 5508 drops, 5 so).
+__global__ __launch_bounds__(kBlock) void k_degree(const uint32_t *__restrict__ adj, int32_t D, int64_t words,
                                                    int32_t *__restrict__ deg) {
-  const int32_t g = blockIdx.x * kBlock + threadIdx.x;
-  if (g >= D) return;
+  const int32_t g = (int32_t)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63;
+  if (g >= D) return;  // whole wavefront
   int s = 0;
-  for (int64_t w = 0; w < words; ++w) s += __popc(adj[(int64_t)g * words + w]);
-  deg[g] = s;
-}
-
-__global__ __launch_bounds__(kBlock) void k_symmetrise(uint32_t *adj, int32_t D, int64_t words) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= (int64_t)D * D) return;
-  const int32_t a = (int32_t)(i / D), b = (int32_t)(i % D);
-  if (a >= b) return;
-  const bool ab = (adj[(int64_t)a * words + (b >> 5)] >> (b & 31)) & 1u;
-  const bool ba = (adj[(int64_t)b * words + (a >> 5)] >> (a & 31)) & 1u;
-  if (ab && !ba) atomicOr(&adj[(int64_t)b * words + (a >> 5)], 1u << (a & 31));
-  if (ba && !ab) atomicOr(&adj[(int64_t)a * words + (b >> 5)], 1u << (b & 31));
+  for (int64_t w = lane; w < words; w += 64) s += __popc(adj[(int64_t)g * words + w]);
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1) s += __shfl_xor(s, k, 64);
+  if (lane == 0) deg[g] = s;
 }
 
 // Exclusive scan of D degrees (single workgroup) into rowptr[0..D].
@@ -555,18 +812,31 @@ __global__ __launch_bounds__(1024) void k_scan_deg(const int32_t *__restrict__ d
   if (t == 1023) rowptr[D] = (int32_t)part[1023];
 }
 
+// The neighbours of every drop in ascending order, one wavefront per drop: 64
+// words a round, each lane's offset from the words before it.
 __global__ __launch_bounds__(kBlock) void k_csr_fill(const uint32_t *__restrict__ adj, int32_t D, int64_t words,
                                                      const int32_t *__restrict__ rowptr, int32_t *__restrict__ nbr) {
-  const int32_t g = blockIdx.x * kBlock + threadIdx.x;
-  if (g >= D) return;
-  int32_t e = rowptr[g];
-  for (int64_t w = 0; w < words; ++w) {
-    uint32_t bits = adj[(int64_t)g * words + w];
+  const int32_t g = (int32_t)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63;
+  if (g >= D) return;  // whole wavefront
+  int32_t e0 = rowptr[g];
+  for (int64_t w0 = 0; w0 < words; w0 += 64) {
+    const int64_t w = w0 + lane;
+    uint32_t bits = w < words ? adj[(int64_t)g * words + w] : 0u;
+    const int mine = __popc(bits);
+    int upto = mine;  // of the lanes up to this one
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+      const int below = __shfl_up(upto, k, 64);
+      if (lane >= k) upto += below;
+    }
+    int32_t e = e0 + upto - mine;
     while (bits) {
       const int b = __ffs(bits) - 1;
       bits &= bits - 1;
       nbr[e++] = (int32_t)(w * 32 + b);
     }
+    e0 += __shfl(upto, 63, 64);
   }
 }
 
@@ -733,7 +1003,7 @@ __global__ void k_initial_tracers(int32_t *T0, int32_t D, int ntr, TracerOffsets
 // one drop (own >= 0, tracer T0[own]) needs only the owner array; cells
 // shared by several drops read every tracer's labels.
 __global__ __launch_bounds__(kBlock) void k_move(double *__restrict__ c, const int32_t *__restrict__ lab, int64_t n3,
-                                                 int ntr, TracerOffsets to, const int32_t *__restrict__ own,
+                                                 int ntr, TracerOffsets to, const owner_t *__restrict__ own,
                                                  const int32_t *__restrict__ T0, const int32_t *__restrict__ newt) {
   const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (p >= n3) return;
@@ -845,7 +1115,7 @@ static int recolor_impl(vofmt_ctx *ctx, const char *fn, int stencil, int32_t nx,
   VOFMT_HIP(ctx, hipSetDevice(ctx->device));
   // Offsets scanned from the listed cells, one of each opposite pair (o > 0
   // in (z, y, x) order): a pair of drops is found from one side only, and
-  // k_symmetrise completes the adjacency.
+  // set_edge records it in both directions.
   // - distance mode: the half ball |o|^2 < (1+gap)^2. Every pair is still
   //   found: the two cells of the pair at the smallest offset are both listed
   //   (a cell whose six neighbours all held its drop would have a neighbour
@@ -857,112 +1127,124 @@ static int recolor_impl(vofmt_ctx *ctx, const char *fn, int stencil, int32_t nx,
   //   lowers the sum and does not raise the maximum.
   const int R = stencil ? 4 : (int)floor(1.0 + gap_cells);
   const double lim = stencil ? 1e300 : (1.0 + gap_cells) * (1.0 + gap_cells);
-  int4 *hoffs = nullptr;
-  int noffs = 0;
-  {
-    const int side = 2 * R + 1;
-    hoffs = (int4 *)malloc(sizeof(int4) * (size_t)side * side * side);
-    for (int oz = -R; oz <= R; ++oz)
-      for (int oy = -R; oy <= R; ++oy)
-        for (int ox = -R; ox <= R; ++ox) {
-          const double o2 = (double)(ox * ox + oy * oy + oz * oz);
-          if (o2 == 0.0 || !(o2 < lim)) continue;
-          if (!(oz > 0 || (oz == 0 && (oy > 0 || (oy == 0 && ox > 0))))) continue;
-          hoffs[noffs++] = make_int4(ox, oy, oz, 0);
-        }
-  }
+  std::vector<int4> hoffs;
+  for (int oz = -R; oz <= R; ++oz)
+    for (int oy = -R; oy <= R; ++oy)
+      for (int ox = -R; ox <= R; ++ox) {
+        const double o2 = (double)(ox * ox + oy * oy + oz * oz);
+        if (o2 == 0.0 || !(o2 < lim)) continue;
+        if (!(oz > 0 || (oz == 0 && (oy > 0 || (oy == 0 && ox > 0))))) continue;
+        hoffs.push_back(make_int4(ox, oy, oz, 0));
+      }
+  const int noffs = (int)hoffs.size();
+  // Tiles in LDS up to the reach that fits them (kMaxTileReach), where every
+  // axis is longer than the tile's halo (an owner then wraps at most once);
+  // the ordered list of boundary cells for the rest.
+  const int Rt = R <= 2 ? 2 : kMaxTileReach;
+  const bool tiled = R <= kMaxTileReach && kHaloX < nx && Rt < ny && Rt < nz;
   const int64_t words = (D + 31) / 32;
-  int32_t *own = (int32_t *)scratch(ctx, SLOT_LABEL_B, sizeof(int32_t) * (size_t)n3);
-  uint32_t *adj = (uint32_t *)scratch(ctx, SLOT_LABEL_A, sizeof(uint32_t) * (size_t)(D * words));
+  owner_t *own = (owner_t *)scratch(ctx, SLOT_LABEL_B, sizeof(owner_t) * (size_t)n3);
+  // the bitmap, then the number of listed row segments (stencil mode)
+  uint32_t *adj = (uint32_t *)scratch(ctx, SLOT_LABEL_A, sizeof(uint32_t) * (size_t)(D * words + 1));
+  uint32_t *nsegs = adj + D * words;
   int32_t *small = (int32_t *)scratch(ctx, SLOT_LABEL_C, sizeof(int32_t) * (size_t)(4 * D + 16));
-  int4 *doffs = (int4 *)scratch(ctx, SLOT_MISC2, sizeof(int4) * (size_t)(noffs > 0 ? noffs : 1));
-  // pinned staging: results in the first 256 bytes, offsets after them
   int32_t *hres = (int32_t *)host_scratch(ctx, 256 + sizeof(int4) * (size_t)noffs);
-  if (!own || !adj || !small || !doffs || !hres) {
-    free(hoffs);
-    return VOFMT_E_NOMEM;
-  }
-  memcpy(hres + 64, hoffs, sizeof(int4) * noffs);
-  free(hoffs);
-  if (noffs > 0)
-    VOFMT_HIP(ctx, hipMemcpyAsync(doffs, hres + 64, sizeof(int4) * noffs, hipMemcpyHostToDevice, stream));
-  const int small_offsets = (R < nx && R < ny && R < nz) ? 1 : 0;
+  if (!own || !adj || !small || !hres) return VOFMT_E_NOMEM;
   int32_t *deg = small, *rowptr = small + D, *T0 = small + 2 * D + 1, *res = small + 3 * D + 2;
   int32_t *nbr = nullptr;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus < 1)
+    cus = 256;
   const unsigned nbc = ceil_div(n3, kBlock);
-  if (n3 % 4 == 0 && ((uintptr_t)labels & 15) == 0)
-    hipLaunchKernelGGL(k_owner4, dim3(ceil_div(n3 / 4, kBlock)), dim3(kBlock), 0, stream, (const int4 *)labels,
-                       n3 / 4, ntr, to, (int4 *)own);
-  else
-    hipLaunchKernelGGL(k_owner, dim3(nbc), dim3(kBlock), 0, stream, labels, n3, ntr, to, own);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, stream, adj, D * words, 0u);
+  hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, stream, adj, D * words + 1, 0u);
   // initial tracer of every drop (the stencil mode's cross-tracer filter reads it)
   hipLaunchKernelGGL(k_initial_tracers, dim3(ceil_div(D, 256)), dim3(256), 0, stream, T0, (int32_t)D, ntr, to);
-  uint64_t *others = nullptr;
-  int xw_stencil = 0;
   if (stencil) {
-    // Steps 1-3 within every tracer, on occupancy bits per row segment
+    // owners and occupancy bits per row segment, then Steps 1-3 within every tracer on the bits
     const int xw = (int)ceil_div(nx, 64);
     const int64_t rows = (int64_t)nz * ny;
-    const int64_t nseg = (int64_t)ntr * rows * xw;
+    const int64_t nseg1 = rows * xw, nseg = ntr * nseg1;
+    if ((nseg * 64 + kBlock - 1) / kBlock > INT32_MAX || nseg >= INT32_MAX)
+      return set_err(ctx, VOFMT_E_ARG, "%s: grid too large", fn);
     uint64_t *occ = (uint64_t *)scratch(ctx, SLOT_OCC, sizeof(uint64_t) * (size_t)nseg);
-    if (!occ) return VOFMT_E_NOMEM;
-    const int64_t nblk = (nseg * 64 + kBlock - 1) / kBlock;
-    const int64_t nblk_se = (ceil_div(nseg, kStencilSegs) * 64 + kBlock - 1) / kBlock;  // k_stencil_edges
-    if (nblk > INT32_MAX || nseg >= INT32_MAX) return set_err(ctx, VOFMT_E_ARG, "%s: grid too large", fn);
-    if (nx % 256 == 0 && ((uintptr_t)labels & 15) == 0) {
-      const int64_t ngroups = nseg / 4;  // rows of whole 256-cell groups: segment 4g + j is cells 64(4g + j) ..
-      hipLaunchKernelGGL(k_occ_words4, dim3((unsigned)((ngroups * 64 + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                         stream, (const int4 *)labels, ngroups, occ);
-    } else {
-      hipLaunchKernelGGL(k_occ_words, dim3((unsigned)nblk), dim3(kBlock), 0, stream, labels, nx,
-                         (int64_t)ntr * rows, xw, occ);
-    }
-    hipLaunchKernelGGL(k_stencil_edges, dim3((unsigned)nblk_se), dim3(kBlock), 0, stream, labels, occ, nx, ny, nz, ntr,
-                       xw, to, make_stencil_pairs(), adj, words, make_fastdiv((uint32_t)xw),
-                       make_fastdiv((uint32_t)rows), make_fastdiv((uint32_t)ny));
-    // the other tracers' occupancy, for the contacts across tracers
-    const int64_t nseg1 = rows * xw;
-    others = (uint64_t *)scratch(ctx, SLOT_OCC_OTHERS, sizeof(uint64_t) * (size_t)nseg);
-    if (!others) return VOFMT_E_NOMEM;
-    hipLaunchKernelGGL(k_other_tracers, dim3(ceil_div(nseg1, kBlock)), dim3(kBlock), 0, stream, occ, nseg1, ntr,
-                       others);
-    xw_stencil = xw;
+    int32_t *seglist = (int32_t *)scratch(ctx, SLOT_OCC_LIST, sizeof(int32_t) * (size_t)nseg);
+    if (!occ || !seglist) return VOFMT_E_NOMEM;
+    const FastDiv fw = make_fastdiv((uint32_t)xw), frows = make_fastdiv((uint32_t)rows),
+                  fny = make_fastdiv((uint32_t)ny);
+    const unsigned nblk = ceil_div(nseg1, kBlock / 64);
+    if (nx % 256 == 0 && ((uintptr_t)labels & 15) == 0)
+      hipLaunchKernelGGL(k_owner_occ4, dim3(ceil_div(nseg1 / 4, kBlock / 64)), dim3(kBlock), 0, stream,
+                         (const int4 *)labels, nseg1 / 4, ntr, to, (short4 *)own, occ);
+    else
+      hipLaunchKernelGGL(k_owner_occ, dim3(nblk), dim3(kBlock), 0, stream, labels, nx, nseg1, n3, xw, fw, ntr, to,
+                         own, occ);
+    const unsigned nblk_s = ceil_div(nseg, kBlock);
+    if (nx >= 3 && nx % 64 != 1)
+      hipLaunchKernelGGL((k_stencil_segments<true>), dim3(nblk_s), dim3(kBlock), 0, stream, occ, nx, ny, nz, xw, nseg,
+                         fw, frows, fny, seglist, nsegs);
+    else
+      hipLaunchKernelGGL((k_stencil_segments<false>), dim3(nblk_s), dim3(kBlock), 0, stream, occ, nx, ny, nz, xw,
+                         nseg, fw, frows, fny, seglist, nsegs);
+    hipLaunchKernelGGL(k_stencil_edges, dim3(8 * cus), dim3(kBlock), 0, stream, labels, occ, nx, ny, nz, xw, to,
+                       make_stencil_pairs(), adj, words, fw, frows, fny, seglist, nsegs);
+  } else if (n3 % 4 == 0 && ((uintptr_t)labels & 15) == 0) {
+    hipLaunchKernelGGL(k_owner4, dim3(ceil_div(n3 / 4, kBlock)), dim3(kBlock), 0, stream, (const int4 *)labels,
+                       n3 / 4, ntr, to, (short4 *)own);
+  } else {
+    hipLaunchKernelGGL(k_owner, dim3(nbc), dim3(kBlock), 0, stream, labels, n3, ntr, to, own);
   }
-  {
+  if (tiled) {
+    const int LX = TileDims<2>::LX, LY = kTileY + 2 * Rt;
+    TileRows lo{};  // hoffs is in (z, y, x) order: a row's offsets are consecutive
+    for (const int4 &o : hoffs) {
+      const int16_t base = (int16_t)((o.z * LY + o.y) * LX);
+      if (lo.n == 0 || lo.base[lo.n - 1] != base) {
+        lo.base[lo.n] = base;
+        lo.lo[lo.n++] = (int8_t)o.x;
+      }
+      lo.hi[lo.n - 1] = (int8_t)o.x;
+    }
+    const int tx = (int)ceil_div(nx, kTileX), ty = (int)ceil_div(ny, kTileY);
+    const int64_t tiles = (int64_t)tx * ty * ceil_div(nz, kTileZ);
+    const int32_t *cross = stencil ? (const int32_t *)T0 : nullptr;
+    int max_o2 = 0;  // the ball's offsets are those of |o|^2 <= max_o2 in the cube of reach R
+    for (const int4 &o : hoffs) max_o2 = std::max(max_o2, o.x * o.x + o.y * o.y + o.z * o.z);
+    if (Rt == 2)
+      hipLaunchKernelGGL((k_tile_edges<2>), dim3((unsigned)tiles), dim3(kBlock), 0, stream, own, labels, nx, ny, nz,
+                         ntr, to, lo, R, max_o2, tx, ty, adj, words, cross);
+    else
+      hipLaunchKernelGGL((k_tile_edges<kMaxTileReach>), dim3((unsigned)tiles), dim3(kBlock), 0, stream, own, labels,
+                         nx, ny, nz, ntr, to, lo, R, max_o2, tx, ty, adj, words, cross);
+  } else {
     // the cells that can see a pair, in order, then the pairs they see
     const int64_t lt = compact::list_tiles_if(n3);
+    int4 *doffs = (int4 *)scratch(ctx, SLOT_MISC2, sizeof(int4) * (size_t)(noffs > 0 ? noffs : 1));
     int32_t *srcs = (int32_t *)scratch(ctx, SLOT_RECOLOR_LIST, sizeof(int32_t) * (size_t)n3);
     int32_t *bc = (int32_t *)scratch(ctx, SLOT_MISC, sizeof(int32_t) * (size_t)nbc);
     int32_t *tot = (int32_t *)scratch(ctx, SLOT_CURV_COUNT, sizeof(int32_t) * (size_t)(lt + 2));
     uint64_t *pbits = (uint64_t *)scratch(ctx, SLOT_CURV_HF, sizeof(uint64_t) * (size_t)((n3 + 63) / 64));
-    if (!srcs || !bc || !tot || !pbits) return VOFMT_E_NOMEM;
-    {
-      // the ordered list of those cells: counts and bits, the tiled scan, the list from the bits
-      const int64_t nb = (n3 + kBlock - 1) / kBlock, nt = (nb + compact::kTile - 1) / compact::kTile;
-      static_assert(kBlock == compact::kBlock, "block counts and the tiled scan share the block size");
-      hipLaunchKernelGGL(k_pair_source_counts, dim3((unsigned)nb), dim3(kBlock), 0, stream, own, nx, ny, nz,
-                         make_fastdiv((uint32_t)nx), make_fastdiv((uint32_t)ny), n3, bc, pbits);
-      hipLaunchKernelGGL(compact::k_scan_tile, dim3((unsigned)nt), dim3(compact::kTile), 0, stream, bc, nb, tot,
-                         (int64_t)0, (int64_t)0);
-      hipLaunchKernelGGL(compact::k_scan_totals, dim3(1), dim3(compact::kTile), 0, stream, tot, nt, (int64_t)0);
-      hipLaunchKernelGGL(compact::k_write_ordered_bits, dim3((unsigned)((nb + kBlock / 64 - 1) / (kBlock / 64))),
-                         dim3(kBlock), 0, stream, n3, pbits, bc, tot, srcs);
+    if (!doffs || !srcs || !bc || !tot || !pbits) return VOFMT_E_NOMEM;
+    // pinned staging: results in the first 256 bytes, offsets after them
+    if (noffs > 0) {
+      memcpy(hres + 64, hoffs.data(), sizeof(int4) * noffs);
+      VOFMT_HIP(ctx, hipMemcpyAsync(doffs, hres + 64, sizeof(int4) * noffs, hipMemcpyHostToDevice, stream));
     }
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus < 1)
-      cus = 256;
-    if (stencil)
-      hipLaunchKernelGGL(k_edges_cross, dim3(8 * cus), dim3(kBlock), 0, stream, own, labels, others, nx, ny, nz, ntr,
-                         xw_stencil, to, doffs, noffs, small_offsets, srcs, tot + lt, adj, words,
-                         make_fastdiv((uint32_t)nx), make_fastdiv((uint32_t)ny), (const int32_t *)T0);
-    else
-      hipLaunchKernelGGL(k_edges, dim3(8 * cus), dim3(kBlock), 0, stream, own, labels, nx, ny, nz, ntr, to, doffs,
-                         noffs, small_offsets, srcs, tot + lt, adj, words, make_fastdiv((uint32_t)nx),
-                         make_fastdiv((uint32_t)ny), nullptr);
+    const int small_offsets = (R < nx && R < ny && R < nz) ? 1 : 0;
+    // the ordered list of those cells: counts and bits, the tiled scan, the list from the bits
+    const int64_t nb = (n3 + kBlock - 1) / kBlock, nt = (nb + compact::kTile - 1) / compact::kTile;
+    static_assert(kBlock == compact::kBlock, "block counts and the tiled scan share the block size");
+    hipLaunchKernelGGL(k_pair_source_counts, dim3((unsigned)nb), dim3(kBlock), 0, stream, own, nx, ny, nz,
+                       make_fastdiv((uint32_t)nx), make_fastdiv((uint32_t)ny), n3, bc, pbits);
+    hipLaunchKernelGGL(compact::k_scan_tile, dim3((unsigned)nt), dim3(compact::kTile), 0, stream, bc, nb, tot,
+                       (int64_t)0, (int64_t)0);
+    hipLaunchKernelGGL(compact::k_scan_totals, dim3(1), dim3(compact::kTile), 0, stream, tot, nt, (int64_t)0);
+    hipLaunchKernelGGL(compact::k_write_ordered_bits, dim3((unsigned)((nb + kBlock / 64 - 1) / (kBlock / 64))),
+                       dim3(kBlock), 0, stream, n3, pbits, bc, tot, srcs);
+    hipLaunchKernelGGL(k_edges, dim3(8 * cus), dim3(kBlock), 0, stream, own, labels, nx, ny, nz, ntr, to, doffs,
+                       noffs, small_offsets, srcs, tot + lt, adj, words, make_fastdiv((uint32_t)nx),
+                       make_fastdiv((uint32_t)ny), stencil ? (const int32_t *)T0 : nullptr);
   }
-  hipLaunchKernelGGL(k_symmetrise, dim3(ceil_div(D * D, kBlock)), dim3(kBlock), 0, stream, adj, (int32_t)D, words);
-  hipLaunchKernelGGL(k_degree, dim3(ceil_div(D, kBlock)), dim3(kBlock), 0, stream, adj, (int32_t)D, words, deg);
+  hipLaunchKernelGGL(k_degree, dim3(ceil_div(D, kBlock / 64)), dim3(kBlock), 0, stream, adj, (int32_t)D, words, deg);
   hipLaunchKernelGGL(k_scan_deg, dim3(1), dim3(1024), 0, stream, deg, (int32_t)D, rowptr);
   VOFMT_HIP(ctx, hipGetLastError());
   // the number of directed edges sizes the neighbour array
@@ -971,7 +1253,7 @@ static int recolor_impl(vofmt_ctx *ctx, const char *fn, int stencil, int32_t nx,
   const int64_t E = hres[8];
   nbr = (int32_t *)scratch(ctx, SLOT_MISC3, sizeof(int32_t) * (size_t)(E > 0 ? E : 1));
   if (!nbr) return VOFMT_E_NOMEM;
-  hipLaunchKernelGGL(k_csr_fill, dim3(ceil_div(D, kBlock)), dim3(kBlock), 0, stream, adj, (int32_t)D, words, rowptr,
+  hipLaunchKernelGGL(k_csr_fill, dim3(ceil_div(D, kBlock / 64)), dim3(kBlock), 0, stream, adj, (int32_t)D, words, rowptr,
                      nbr);
   hipLaunchKernelGGL(k_greedy_rounds, dim3(1), dim3(1024), 0, stream, rowptr, nbr, T0, (int32_t)D, ntr, new_tracer,
                      res);

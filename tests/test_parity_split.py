@@ -1,8 +1,16 @@
-"""GPU parity of the advection against the CPU oracle where the split of the
-work over wavefronts changes: the marching chunk falls from 32 to 16, 8 and 4
-with the number of wavefronts of a sweep, and the initial scan's span with the
-number of tracer-cells. Bar: 1e-12, the volume-fraction tolerance of the
-other advection tests (one or two steps of fields whose values are O(1))."""
+"""GPU parity against the CPU oracle where the split of the work changes with
+sizes.
+
+Advection: the marching chunk falls from 32 to 16, 8 and 4 with the number of
+wavefronts of a sweep, the initial scan's span with the number of tracer-cells,
+and the tracers form groups of even sizes. Bar: 1e-12, the volume-fraction
+tolerance of the other advection tests (one or two steps of fields whose
+values are O(1)).
+
+Reassignment: pairs found in LDS tiles of 64 x 8 x 8 cells (reach up to 2, up
+to 4) or from the list of boundary cells (above, or an axis no longer than the
+tile's halo), rows read in groups of 4 cells or one by one, row segments whose
+neighbours come by shifts or bit by bit (nx % 64 == 1, nx < 3). Bit-exact."""
 import numpy as np
 import pytest
 
@@ -52,3 +60,42 @@ def test_work_split(ctx, shape, ntr, step0, nsteps):
     ctx.advect(tc, *[torch.from_numpy(a).to("cuda:0") for a in s], step0=step0, nsteps=nsteps)
     torch.cuda.synchronize()
     assert np.abs(tc.cpu().numpy() - oracle.advect(c, *s, step0, nsteps)).max() <= TOL
+
+
+def _labelled(shape, ntr, seed, spread):
+    """Small drops, some of them touching or overlapping drops of other tracers, and their labels."""
+    nz, ny, nx = shape
+    rng = synth.Splitmix64(seed)
+    n = max(2 * ntr, nx * ny * nz // 260)
+    centres = rng.uniform(3 * n).reshape(n, 3) * np.array([nx, ny, nz])
+    radii = np.minimum(1.0 + spread * rng.uniform(n), 0.45 * min(shape) - 0.5).clip(0.4)
+    c = synth.fill_spheres(shape, ntr, centres, radii, np.arange(n) % ntr)
+    np.minimum(c, 1.0, out=c)
+    lab, nd = zip(*[oracle.label(c[t]) for t in range(ntr)])
+    return c, np.stack(lab), list(nd)
+
+
+@pytest.mark.parametrize("gap", [0.0, 0.9, 1.5, 2.2, 3.9, 4.3, None])
+@pytest.mark.parametrize("shape,ntr", [((9, 10, 68), 3), ((17, 9, 65), 2), ((8, 8, 64), 5), ((7, 25, 131), 4),
+                                       ((5, 5, 6), 2), ((4, 9, 20), 2), ((3, 6, 2), 1), ((16, 8, 256), 3)])
+def test_reassignment_tiles(ctx, shape, ntr, gap):
+    """gap None: the 5x5x5 stencil criterion."""
+    import torch
+
+    c, labels, nd = _labelled(shape, ntr, 900 + sum(shape), 1.6)
+    maxt = ntr + 24
+    note(f"reassignment tiles {shape} ntr={ntr} gap={gap}")
+    full = np.concatenate([c, np.zeros((24,) + shape)])
+    if gap is None:
+        o, ontr, onewt, omoved, rc = oracle.recolor_stencil(full, labels, nd, ntr, maxt)
+    else:
+        o, ontr, onewt, omoved, rc = oracle.recolor(full, labels, nd, ntr, maxt, gap)
+    assert rc == 0
+    tc = torch.from_numpy(full).to("cuda:0")
+    lab = torch.from_numpy(np.ascontiguousarray(labels)).to("cuda:0")
+    newt = torch.zeros(max(sum(nd), 1), dtype=torch.int32, device="cuda:0")
+    args = (tc, ntr, lab, np.array(nd, dtype=np.int32))
+    gntr, gmoved = ctx.recolor_tracers_stencil(*args, newt) if gap is None else ctx.recolor_tracers(*args, gap, newt)
+    assert (gntr, gmoved) == (ontr, omoved)
+    assert np.array_equal(newt.cpu().numpy()[:sum(nd)], onewt)
+    assert np.array_equal(tc.cpu().numpy(), o)
