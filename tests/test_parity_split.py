@@ -10,7 +10,10 @@ values are O(1)).
 Reassignment: pairs found in LDS tiles of 64 x 8 x 8 cells (reach up to 2, up
 to 4) or from the list of boundary cells (above, or an axis no longer than the
 tile's halo), rows read in groups of 4 cells or one by one, row segments whose
-neighbours come by shifts or bit by bit (nx % 64 == 1, nx < 3). Bit-exact."""
+neighbours come by shifts or bit by bit (nx % 64 == 1, nx < 3). Bit-exact.
+
+Surface-tension force: every group size, one and two groups, and 2 to 32 planes
+per workgroup with a remainder. Bit-exact."""
 import numpy as np
 import pytest
 
@@ -99,3 +102,20 @@ def test_reassignment_tiles(ctx, shape, ntr, gap):
     assert (gntr, gmoved) == (ontr, omoved)
     assert np.array_equal(newt.cpu().numpy()[:sum(nd)], onewt)
     assert np.array_equal(tc.cpu().numpy(), o)
+
+
+@pytest.mark.parametrize("shape,ntr", [((3, 17, 70), 5), ((33, 9, 65), 6), ((7, 8, 129), 7), ((5, 20, 64), 10),
+                                       ((2, 3, 5), 15), ((1, 1, 1), 3), ((561, 120, 65), 1), ((1101, 120, 65), 2)])
+def test_force_groups(ctx, shape, ntr):
+    import torch
+
+    rng = np.random.default_rng(sum(shape) + ntr)
+    c = rng.random((ntr,) + shape)
+    c[c < 0.4] = 0.0
+    kappa = rng.standard_normal((ntr,) + shape)
+    kappa[rng.random((ntr,) + shape) < 0.5] = np.nan
+    note(f"force {shape} ntr={ntr}")
+    f = [torch.empty(shape, dtype=torch.float64, device="cuda:0") for _ in range(3)]
+    ctx.csf_force(torch.from_numpy(c).to("cuda:0"), torch.from_numpy(kappa).to("cuda:0"), 0.7, *f)
+    for g, o in zip(f, oracle.csf_force(c, kappa, 0.7)):
+        assert np.array_equal(g.cpu().numpy(), o)
