@@ -16,37 +16,48 @@ constexpr int kTile = 1024;  // entries per scan tile
 constexpr double kResidue = 1e-12;
 __device__ __forceinline__ bool is_mixed(double v) { return v > kResidue && v < 1.0 - kResidue; }
 
-// The mixed-cell list takes kPer cells per thread: block b covers cells
-// [b kCells, (b + 1) kCells) as kPer coalesced sub-chunks of kBlock cells
-// (sub-chunk k at b kCells + k kBlock), whose values are all loaded before
-// the first is used. Far fewer, longer-lived workgroups than one per
-// kBlock cells.
-constexpr int kPer = 8;
-constexpr int64_t kCells = (int64_t)kBlock * kPer;
+// The mixed-cell list takes blocks of kCells cells, a wavefront kWave
+// consecutive ones of them as kListWords 64-cell words: few, long-lived
+// workgroups (blocks of 2048 cells: the counting pass 231 us over a 512^3 field,
+// 193 us so).
+constexpr int kListWords = 32;
+constexpr int kWave = 64 * kListWords;
+constexpr int64_t kCells = (int64_t)kWave * (kBlock / 64);
 
 // Mixed cells per block of kCells cells, and the mixed-cell bits: word
-// p / 64 of `bits` for the 64 cells p of a wavefront's sub-chunk (64-aligned).
+// p / 64 of `bits` for cells p .. p + 63.
 __global__ __launch_bounds__(kBlock) void k_block_counts(const double *__restrict__ c, int64_t n3,
                                                          int32_t *__restrict__ bc, uint64_t *__restrict__ bits) {
-  const int64_t p0 = (int64_t)blockIdx.x * kCells + threadIdx.x;
-  double v[kPer];
+  constexpr int kInFlight = 16;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t pw = blockIdx.x * kCells + (int64_t)w * kWave;  // the wavefront's first cell
+  uint32_t lo = 0, hi = 0;                                      // lane j: word j
+  int n = 0;                                                    // wavefront-uniform
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) v[k] = (p0 + k * kBlock < n3) ? c[p0 + k * kBlock] : 0.0;
-  int n = 0;  // wavefront-uniform
-  const int64_t pw0 = p0 - (threadIdx.x & 63);  // the wavefront's first cell of sub-chunk 0
+  for (int j0 = 0; j0 < kListWords; j0 += kInFlight) {
+    double v[kInFlight];
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const uint64_t mk = __ballot(p0 + k * kBlock < n3 && is_mixed(v[k]));
-    n += (int)__popcll(mk);
-    const int64_t pw = pw0 + k * kBlock;
-    if ((threadIdx.x & 63) == 0 && pw < n3) bits[pw >> 6] = mk;
+    for (int j = 0; j < kInFlight; ++j) {
+      const int64_t p = pw + 64 * (j0 + j) + lane;
+      v[j] = p < n3 ? c[p] : 0.0;  // (0: not mixed)
+    }
+#pragma unroll
+    for (int j = 0; j < kInFlight; ++j) {
+      const uint64_t mk = __ballot(is_mixed(v[j]));
+      n += (int)__popcll(mk);
+      if (lane == j0 + j) {
+        lo = (uint32_t)mk;
+        hi = (uint32_t)(mk >> 32);
+      }
+    }
   }
+  if (lane < kListWords && pw + 64 * lane < n3) bits[(pw >> 6) + lane] = ((uint64_t)hi << 32) | lo;
   __shared__ int wc[kBlock / 64];
-  if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = n;
+  if (lane == 0) wc[w] = n;
   __syncthreads();
   if (threadIdx.x == 0) {
     int t = 0;
-    for (int w = 0; w < kBlock / 64; ++w) t += wc[w];
+    for (int k = 0; k < kBlock / 64; ++k) t += wc[k];
     bc[blockIdx.x] = t;
   }
 }
@@ -100,43 +111,65 @@ __global__ __launch_bounds__(kTile) void k_scan_totals(int32_t *__restrict__ tot
   if (threadIdx.x == 0) tot[ntiles] = carry;
 }
 
-// Ordered list: block b writes its mixed cells from bc[b] + tot[b / kTile],
-// sub-chunk by sub-chunk, wavefront by wavefront, from the bits of the
-// counting pass (the field is not read again). With kappa/status given,
-// also writes NaN / 0 into every cell that is not mixed.
+// Ordered list: block b writes its mixed cells from the bits of the counting
+// pass (the field is not read again), after the entries of the blocks before
+// it: bc[b] plus the totals of the tiles before its own, or (SCANNED false) the
+// sum of the counts before bc[b]. The last block stores the list's length in
+// tot[ntiles]. With
+// kappa/status given, every cell first gets NaN / 0 (the listed cells are
+// written later, by the list's readers): 16 bytes a lane and not kept in the
+// caches (272 us with a store of 8 and one of 1 byte a lane over a 512^3 field,
+// 238 us so).
+template <bool SCANNED>
 __global__ __launch_bounds__(kBlock) void k_write_ordered(const uint64_t *__restrict__ bits, int64_t n3,
-                                                          const int32_t *__restrict__ bc,
-                                                          const int32_t *__restrict__ tot, int32_t *__restrict__ list,
+                                                          const int32_t *__restrict__ bc, int32_t *__restrict__ tot,
+                                                          int64_t ntiles, int32_t *__restrict__ list,
                                                           double *__restrict__ kappa, uint8_t *__restrict__ status) {
-  const int64_t p0 = (int64_t)blockIdx.x * kCells + threadIdx.x;
+  typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));
+  typedef uint32_t uint4u __attribute__((ext_vector_type(4), aligned(1)));
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t pw0 = p0 - lane;
-  uint64_t wd[kPer];
+  const int64_t pw = blockIdx.x * kCells + (int64_t)w * kWave;
+  uint64_t word = (lane < kListWords && pw + 64 * lane < n3) ? bits[(pw >> 6) + lane] : 0ull;
+  if (kappa) {
+    const double nan = __builtin_nan("");
+    if (pw + kWave <= n3) {
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) wd[k] = (pw0 + k * kBlock < n3) ? bits[(pw0 + k * kBlock) >> 6] : 0ull;
-  __shared__ int wc[kPer][kBlock / 64];
-  uint64_t mk[kPer];
+      for (int j = 0; j < kWave / 128; ++j)
+        __builtin_nontemporal_store((double2u){nan, nan}, (double2u *)(kappa + pw + 128 * j + 2 * lane));
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int64_t p = p0 + k * kBlock;
-    const bool inside = p < n3;
-    const bool mixed = inside && ((wd[k] >> lane) & 1ull);
-    if (inside && !mixed && kappa) {
-      kappa[p] = __builtin_nan("");
-      status[p] = 0;
+      for (int j = 0; j < kWave / 1024; ++j)
+        __builtin_nontemporal_store((uint4u){0u, 0u, 0u, 0u}, (uint4u *)(status + pw + 1024 * j + 16 * lane));
+    } else {
+      for (int64_t p = pw + lane; p < n3; p += 64) {
+        kappa[p] = nan;
+        status[p] = 0;
+      }
     }
-    mk[k] = __ballot(mixed);
-    if (lane == 0) wc[k][w] = (int)__popcll(mk[k]);
   }
-  __syncthreads();
-  int run = bc[blockIdx.x] + tot[blockIdx.x / kTile];  // entries of the cells before sub-chunk k
-  const uint64_t below = (1ull << lane) - 1;
+  // entries of the words before this lane's, of the wavefronts and of the tiles before
+  const int mine = (int)__popcll(word);
+  int upto = mine;
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    int idx = run;
-    for (int j = 0; j < w; ++j) idx += wc[k][j];
-    if ((mk[k] >> lane) & 1ull) list[idx + (int)__popcll(mk[k] & below)] = (int32_t)(p0 + k * kBlock);
-    for (int j = 0; j < kBlock / 64; ++j) run += wc[k][j];
+  for (int k = 1; k < 64; k <<= 1) {
+    const int below = __shfl_up(upto, k, 64);
+    if (lane >= k) upto += below;
+  }
+  __shared__ int wc[kBlock / 64], before[kBlock / 64];
+  if (lane == 63) wc[w] = upto;
+  const int32_t *v = SCANNED ? tot : bc;
+  int part = 0;
+  for (int64_t k = threadIdx.x; k < (SCANNED ? blockIdx.x / kTile : blockIdx.x); k += kBlock) part += v[k];
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1) part += __shfl_xor(part, k, 64);
+  if (lane == 0) before[w] = part;
+  __syncthreads();
+  int run = SCANNED ? bc[blockIdx.x] : 0;
+  for (int k = 0; k < kBlock / 64; ++k) run += before[k] + (k < w ? wc[k] : 0);
+  if (blockIdx.x == gridDim.x - 1 && w == kBlock / 64 - 1 && lane == 63) tot[ntiles] = run + upto;
+  run += upto - mine;
+  while (word) {
+    list[run++] = (int32_t)(pw + 64 * lane) + (int32_t)__builtin_ctzll(word);
+    word &= word - 1;
   }
 }
 
@@ -149,10 +182,17 @@ inline void launch_ordered_list(const double *c, int64_t n3, int32_t *bc, int32_
   const int64_t nb = (n3 + kCells - 1) / kCells;
   const int64_t ntiles = (nb + kTile - 1) / kTile;
   hipLaunchKernelGGL(k_block_counts, dim3((unsigned)nb), dim3(kBlock), 0, stream, c, n3, bc, bits);
+  // up to kDirect blocks (33M cells) each sums the counts before its own: the
+  // scan is one more launch of about 5 us (64^3: 41 -> 38 us for the call)
+  constexpr int64_t kDirect = 4096;
+  if (nb <= kDirect) {
+    hipLaunchKernelGGL(k_write_ordered<false>, dim3((unsigned)nb), dim3(kBlock), 0, stream, bits, n3, bc, tot, ntiles,
+                       list, kappa, status);
+    return;
+  }
   hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)ntiles), dim3(kTile), 0, stream, bc, nb, tot, (int64_t)0, (int64_t)0);
-  hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kTile), 0, stream, tot, ntiles, (int64_t)0);
-  hipLaunchKernelGGL(k_write_ordered, dim3((unsigned)nb), dim3(kBlock), 0, stream, bits, n3, bc, tot, list, kappa,
-                     status);
+  hipLaunchKernelGGL(k_write_ordered<true>, dim3((unsigned)nb), dim3(kBlock), 0, stream, bits, n3, bc, tot, ntiles,
+                     list, kappa, status);
 }
 
 // Scan tiles of the mixed-cell list of n3 cells (its length is at tot[list_tiles(n3)]).

@@ -12,6 +12,10 @@ to 4) or from the list of boundary cells (above, or an axis no longer than the
 tile's halo), rows read in groups of 4 cells or one by one, row segments whose
 neighbours come by shifts or bit by bit (nx % 64 == 1, nx < 3). Bit-exact.
 
+Interface-cell list: fields of 1 to a few blocks of 8192 cells around the edges
+of words, wavefronts and blocks, at addresses that are multiples of 8 bytes (1
+for the status) only, and above 4096 blocks, where the counts are scanned. Exact.
+
 Surface-tension force: every group size, one and two groups, and 2 to 32 planes
 per workgroup with a remainder. Bit-exact."""
 import numpy as np
@@ -119,3 +123,33 @@ def test_force_groups(ctx, shape, ntr):
     ctx.csf_force(torch.from_numpy(c).to("cuda:0"), torch.from_numpy(kappa).to("cuda:0"), 0.7, *f)
     for g, o in zip(f, oracle.csf_force(c, kappa, 0.7)):
         assert np.array_equal(g.cpu().numpy(), o)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 1, 63), (1, 5, 13), (1, 1, 2047), (3, 683, 1), (1, 1, 2049), (8191, 1, 1),
+                                   (1, 8193, 1), (25, 33, 31), (1, 127, 129), (323, 322, 324)])
+def test_interface_list(ctx, shape):
+    import torch
+
+    n = int(np.prod(shape))
+    rng = np.random.default_rng(n)
+    c = np.zeros((2, n + 1))  # the second field is only 8-byte aligned for odd n + 1
+    hit = rng.random(n) < 0.03
+    c[1, :n][hit] = rng.random(int(hit.sum()))
+    c[1, :n][~hit & (rng.random(n) < 0.5)] = 1.0
+    field = c[1, :n].reshape(shape)
+    want = np.flatnonzero((field.ravel() > 1e-12) & (field.ravel() < 1 - 1e-12))
+    note(f"interface list {shape}")
+    dev = "cuda:0"
+    f = torch.from_numpy(c).to(dev)[1, :n].reshape(shape)
+    m = len(want)
+    xs = torch.zeros((m + 1, 27), dtype=torch.float32, device=dev)
+    cell, sign = torch.zeros(m + 1, dtype=torch.int32, device=dev), torch.zeros(m + 1, dtype=torch.int8, device=dev)
+    assert ctx.mlp_stencils(f, xs, cell, sign) == m
+    assert np.array_equal(cell.cpu().numpy()[:m], want)
+    kappa = torch.zeros(2 * n + 1, dtype=torch.float64, device=dev)[n + 1:].reshape(shape)
+    status = torch.full((2 * n + 1,), 77, dtype=torch.uint8, device=dev)
+    ctx.curvature_hf(f, kappa, status[n:2 * n].reshape(shape))
+    st = status.cpu().numpy()
+    assert np.array_equal(np.flatnonzero(st[n:2 * n]), want)
+    assert np.all(st[:n] == 77) and st[2 * n] == 77  # nothing written beside the field
+    assert np.isnan(kappa.cpu().numpy().ravel()[st[n:2 * n] == 0]).all()
