@@ -768,40 +768,32 @@ static inline int run_shift(int nx) {
 // drop, the first cell and the min/max of both frames on each axis, and a
 // per-drop step turns them into the box.
 
-// Wavefront-wide minimum / maximum (every lane passes a value; lanes outside
-// the set pass the neutral value).
-__device__ __forceinline__ int wave_min(int v) {
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ int wave_max(int v) {
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
-// Per-drop reductions go through a small hash table in LDS per workgroup: a
-// workgroup sweeps kChunk consecutive cells, the lanes of a wavefront holding
-// the same drop are combined first, each such group updates the drop's LDS
-// record with LDS atomics, and at the end the workgroup applies one set of
-// global atomics per drop it met. Global atomics on one address from many
-// workgroups are serialised; this makes them about kChunk / (cells of a
-// drop's row run) times fewer. A drop that finds the table full goes to the
-// global atomics directly. Integer min/max are order-independent, so the
-// result does not depend on scheduling.
-// 32768 cells (64 rows of 512) and 16 loads in flight per thread measured
-// best on 512^3 fields: fewer workgroups flush fewer records (8192 cells
-// and 8 loads: moments 3.40 against 2.93 ms for 8 tracers).
-constexpr int kChunk = 32768;  // cells per workgroup (128 per thread)
+// Per-drop reductions go through a small hash table in LDS per workgroup. A
+// workgroup takes a tile of up to 128 x 16 x 16 cells (compact, so that few
+// tiles meet a drop: each applies one set of global atomics per drop it met,
+// and global atomics on one address from many workgroups are serialised). A
+// wavefront takes 64 cells of a row at a time, kBatch of them in flight, and
+// notes every run of equal labels in an LDS list: a lane at a run's start finds
+// its end from the ballot of the ends. Full wavefronts of noted runs are merged
+// into the table at once, a run a lane. A drop that finds the table full goes
+// to the global atomics directly. Integer min/max are order-independent, so
+// the result does not depend on scheduling.
+// Before, one lane per run built and merged its record while the others waited,
+// and the tiles were 64 rows of one plane: 1483 us at 512^3 x 8 (5000 drops),
+// 770 us so, where the labels' read takes 720 at the card's copy rate.
+constexpr int kScanX = 2, kScanY = 16, kScanZ = 16;  // tile of the scan: 64-cell segments, rows, planes
 constexpr int kTable = 64;     // LDS records per workgroup (power of two)
-constexpr int kBatch = 16;     // positions per thread whose loads are issued together
+constexpr int kBatch = 16;     // segments of a wavefront whose loads are issued together
+constexpr int kRuns = 128;     // runs a wavefront notes before it merges 64 of them
 constexpr int kFrames = 12;    // per drop: axis a -> min A, max A, min B, max B at 4a
-static_assert(kTable == 64 && kChunk % kBlock == 0, "table_slot hashes to 6 bits");
-static_assert((kChunk / kBlock) % kBatch == 0, "whole batches per thread");
+static_assert(kTable == 64, "table_slot hashes to 6 bits");
+static_assert((kScanX * kScanY * kScanZ / (kBlock / 64)) % kBatch == 0, "whole batches per wavefront");
 
 __device__ __forceinline__ int table_slot(int32_t *key, int32_t l) {
   const uint32_t h = ((uint32_t)l * 2654435761u) >> 26;  // 6 bits: kTable = 64
   for (int k = 0; k < kTable; ++k) {
     const int s = (int)((h + k) & (kTable - 1));
+    if (key[s] == l) return s;
     const int32_t prev = atomicCAS(&key[s], 0, l);
     if (prev == 0 || prev == l) return s;
   }
@@ -814,27 +806,37 @@ __global__ void k_scan_init(int32_t *first, int32_t *frames, int64_t K) {
   if (i < kFrames * K) frames[i] = (i & 1) ? INT32_MIN : INT32_MAX;
 }
 
-// One drop's record (first cell, frame extents) merged into the workgroup's
-// LDS table, or into the global arrays when the table is full.
-__device__ __forceinline__ void merge_record(int32_t *key, int32_t *rfirst, int32_t (*rec)[kFrames],
-                                             int32_t *first, int32_t *frames, int32_t l, int32_t f,
-                                             const int32_t *e) {
+// A run of cells p .. p + len - 1 of one row and drop, merged into the
+// workgroup's LDS table, or into the global arrays when the table is full.
+// Frame A of an axis is the coordinate a, frame B (a + n/2) mod n.
+__device__ __forceinline__ void merge_run(int32_t *key, int32_t *rfirst, int32_t (*rec)[kFrames], int32_t *first,
+                                          int32_t *frames, int32_t l, int32_t p, int len, int nx, int ny, int nz,
+                                          const FastDiv &fnx, const FastDiv &fny) {
+  const uint32_t row = fast_div((uint32_t)p, fnx), zz = fast_div(row, fny);
+  const int x = (int)((uint32_t)p - row * (uint32_t)nx), y = (int)(row - zz * (uint32_t)ny), z = (int)zz;
+  auto other = [](int a, int n) { return a + n / 2 >= n ? a + n / 2 - n : a + n / 2; };
+  // the run passes the cut of frame B between x = nx - nx/2 - 1 and nx - nx/2
+  const int cut = nx - nx / 2, xe = x + len - 1;
+  const bool over = x < cut && xe >= cut;
+  const int yb = other(y, ny), zb = other(z, nz);
+  const int e[kFrames] = {x, xe, over ? 0 : other(x, nx), over ? nx - 1 : other(xe, nx), y, y, yb, yb, z, z, zb, zb};
   const int s = table_slot(key, l);
-  int32_t *pf = (s >= 0) ? &rfirst[s] : &first[l - 1];
-  int32_t *g = (s >= 0) ? &rec[s][0] : &frames[kFrames * (int64_t)(l - 1)];
-  atomicMin(pf, f);
+  atomicMin(s >= 0 ? &rfirst[s] : &first[l - 1], p);
+  int32_t *g = s >= 0 ? &rec[s][0] : &frames[kFrames * (int64_t)(l - 1)];
+#pragma unroll
   for (int k = 0; k < kFrames; k += 2) {
     atomicMin(&g[k], e[k]);
     atomicMax(&g[k + 1], e[k + 1]);
   }
 }
 
-// First cell and the frame extents of every drop.
+// First cell and the frame extents of every drop. Tile blockIdx.x (x, then y,
+// then z; tx tiles along x, ty along y) of field blockIdx.y, whose drops are
+// records toff[t] .. toff[t+1]-1.
 __global__ __launch_bounds__(kBlock) void k_drop_scan(const int32_t *__restrict__ lab, int64_t n3, int nx, int ny,
-                                                      int nz, FastDiv fnx, FastDiv fny,
+                                                      int nz, int tx, int ty, FastDiv fnx, FastDiv fny,
                                                       const int32_t *__restrict__ toff,
                                                       int32_t *__restrict__ first, int32_t *__restrict__ frames) {
-  // field blockIdx.y: its drops are records toff[t] .. toff[t+1]-1
   const int t = blockIdx.y;
   const int32_t o = toff[t], K = toff[t + 1] - o;
   if (K == 0) return;  // (uniform over the workgroup)
@@ -844,6 +846,8 @@ __global__ __launch_bounds__(kBlock) void k_drop_scan(const int32_t *__restrict_
   __shared__ int32_t key[kTable];
   __shared__ int32_t rfirst[kTable];
   __shared__ int32_t rec[kTable][kFrames];
+  __shared__ int32_t run_label[kBlock / 64][kRuns], run_cell[kBlock / 64][kRuns];
+  __shared__ uint8_t run_len[kBlock / 64][kRuns];
   for (int i = threadIdx.x; i < kTable; i += kBlock) {
     key[i] = 0;
     rfirst[i] = INT32_MAX;
@@ -851,76 +855,51 @@ __global__ __launch_bounds__(kBlock) void k_drop_scan(const int32_t *__restrict_
   }
   __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int n[3] = {nx, ny, nz};
-  const int h[3] = {nx / 2, ny / 2, nz / 2};
-  const int64_t c0 = (int64_t)blockIdx.x * kChunk;
-  for (int it0 = 0; it0 < kChunk / kBlock; it0 += kBatch) {
-    int32_t lb[kBatch];  // the labels of kBatch positions are loaded together
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bx = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % tx)),
+            by = __builtin_amdgcn_readfirstlane((int)((blockIdx.x / tx) % ty)),
+            bz = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / ((unsigned)tx * ty)));
+  int32_t *const rl = run_label[wv], *const rc = run_cell[wv];
+  uint8_t *const rn = run_len[wv];
+  int n = 0;  // runs noted, wavefront-uniform
+  auto merge = [&](int q) { merge_run(key, rfirst, rec, first, frames, rl[q], rc[q], rn[q], nx, ny, nz, fnx, fny); };
+  constexpr int kPer = kScanX * kScanY * kScanZ / (kBlock / 64);  // segments per wavefront
+  for (int i0 = wv * kPer; i0 < (wv + 1) * kPer; i0 += kBatch) {
+    int32_t lb[kBatch];  // the labels of kBatch segments are loaded together
+    int32_t cell[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int64_t p = c0 + (int64_t)(it0 + u) * kBlock + threadIdx.x;
-      lb[u] = (p < n3) ? lab[p] : 0;
+      const int i = i0 + u;  // segment of the tile: x, then y, then z
+      const int x = 64 * (bx * kScanX + i % kScanX), y = by * kScanY + (i / kScanX) % kScanY,
+                z = bz * kScanZ + i / (kScanX * kScanY);
+      const bool in = y < ny && z < nz;
+      cell[u] = in ? (z * ny + y) * nx + x : 0;
+      lb[u] = (in && x + lane < nx) ? lab[(int64_t)cell[u] + lane] : 0;
     }
-#pragma unroll 1
+#pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int64_t pw = c0 + (int64_t)(it0 + u) * kBlock + (threadIdx.x & ~63);  // the wavefront's first cell
-      const int64_t p = pw + lane;
-      const int32_t l = lb[u];
-      const bool valid = l > 0 && l <= K;
-      uint64_t todo = __ballot(valid);
-      if (!todo) continue;  // wave-uniform
-      // row of the wavefront's first and last cells (wave-uniform, scalar)
-      const uint32_t pw32 = __builtin_amdgcn_readfirstlane((uint32_t)pw);
-      const uint32_t rw = fast_div(pw32, fnx);
-      const uint32_t rl = fast_div((uint32_t)(pw32 + 63 < n3 ? pw32 + 63 : n3 - 1), fnx);
-      const bool one_row = (rw == rl);  // cell x = x of the first cell + lane
-      const int xw = (int)(pw32 - rw * (uint32_t)nx);
-      // coordinates of this lane's cell (needed only when the cells span two rows)
-      int c[3] = {0, 0, 0};
-      if (!one_row) {
-        const uint32_t pc = valid ? (uint32_t)p : pw32;
-        const uint32_t r = fast_div(pc, fnx), zz = fast_div(r, fny);
-        c[0] = (int)(pc - r * (uint32_t)nx);
-        c[1] = (int)(r - zz * (uint32_t)ny);
-        c[2] = (int)zz;
+      const int32_t l = lb[u] <= K ? lb[u] : 0;  // (0 and below: no drop)
+      if (__ballot(l > 0) == 0ull) continue;     // wave-uniform
+      const int32_t before = __shfl_up(l, 1, 64), after = __shfl_down(l, 1, 64);
+      const uint64_t starts = __ballot(l > 0 && (lane == 0 || before != l));
+      const uint64_t ends = __ballot(l > 0 && (lane == 63 || after != l));
+      if ((starts >> lane) & 1ull) {
+        const int q = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(starts >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)starts, 0u));
+        rl[q] = l;
+        rc[q] = cell[u] + lane;
+        rn[q] = (uint8_t)(__builtin_ctzll(ends >> lane) + 1);
       }
-      while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int32_t lv = __shfl(l, leader, 64);
-        const uint64_t same = __ballot(valid && l == lv);
-        int e[kFrames];
-        if (one_row) {
-          // x: the group's lanes in increasing x; frame B cuts at x = nx - nx/2
-          const int lo = leader, hi = 63 - __clzll(same);
-          e[0] = xw + lo;
-          e[1] = xw + hi;
-          const int cut = nx - h[0] - xw;  // first lane with x >= nx - nx/2 (may be outside 0..63)
-          const uint64_t above = (cut <= 0) ? ~0ull : ((cut >= 64) ? 0ull : (~0ull << cut));
-          const uint64_t mhi = same & above, mlo = same & ~above;
-          e[2] = mhi ? xw + (__ffsll((unsigned long long)mhi) - 1) - (nx - h[0]) : xw + lo + h[0];
-          e[3] = mlo ? xw + (63 - __clzll(mlo)) + h[0] : xw + hi - (nx - h[0]);
-          // y and z are those of the row
-          const int zr = (int)fast_div(rw, fny), yr = (int)(rw - (uint32_t)zr * (uint32_t)ny);
-          e[4] = e[5] = yr;
-          e[6] = e[7] = (yr + h[1] >= ny) ? yr + h[1] - ny : yr + h[1];
-          e[8] = e[9] = zr;
-          e[10] = e[11] = (zr + h[2] >= nz) ? zr + h[2] - nz : zr + h[2];
-        } else {
-          const bool mine = valid && l == lv;
-          for (int a = 0; a < 3; ++a) {
-            const int vb = (c[a] + h[a] >= n[a]) ? c[a] + h[a] - n[a] : c[a] + h[a];
-            e[4 * a] = wave_min(mine ? c[a] : INT32_MAX);
-            e[4 * a + 1] = wave_max(mine ? c[a] : INT32_MIN);
-            e[4 * a + 2] = wave_min(mine ? vb : INT32_MAX);
-            e[4 * a + 3] = wave_max(mine ? vb : INT32_MIN);
-          }
-        }
-        if (lane == leader)  // the lowest lane holds the group's first cell
-          merge_record(key, rfirst, rec, first, frames, lv, (int32_t)p, e);
-        todo &= ~same;
+      n += (int)__popcll(starts);
+      if (n > kRuns - 64) {  // room for the next segment's: a full wavefront of runs is merged
+        __builtin_amdgcn_wave_barrier();
+        n -= 64;
+        merge(n + lane);
       }
     }
   }
+  __builtin_amdgcn_wave_barrier();
+  if (lane < n) merge(lane);
   __syncthreads();
   for (int i = threadIdx.x; i < kTable; i += kBlock) {
     const int32_t lv = key[i];
@@ -1003,6 +982,27 @@ __device__ __forceinline__ int field_of(const int32_t *__restrict__ toff, int32_
   while (toff[t + 1] <= g) ++t;
   return t;
 }
+// Sums of N values over the workgroup, value k to out[k]: the fixed tree that adds
+// thread t + w to thread t for w = 128, 64, 32, .. 1. The first two levels are
+// taken from LDS by the wavefront that owns the value, the others inside it:
+// one barrier. The shapes of 125 drops take 15.5 us so, 17 with a barrier per
+// level; those of 5000 drops 744 us both ways: there the cache lines that the
+// drops' rows touch in six fields (4.2 GB by the counters, 5.6 TB/s) bind.
+template <int N>
+__device__ __forceinline__ void block_sums(const double *acc, double (*red)[kBlock], double *out) {
+  static_assert(kBlock == 256, "two levels across four wavefronts");
+#pragma unroll
+  for (int k = 0; k < N; ++k) red[k][threadIdx.x] = acc[k];
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int k = wv; k < N; k += kBlock / 64) {
+    double v = (red[k][lane] + red[k][lane + 128]) + (red[k][lane + 64] + red[k][lane + 192]);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w, 64);  // (lanes below w hold the tree's values)
+    if (lane == 0) out[k] = v;
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void k_drop_sums(const double *__restrict__ c, const int32_t *__restrict__ lab,
                                                       int nx, int ny, int nz, const int32_t *__restrict__ toff,
                                                       const int32_t *__restrict__ rootpos,
@@ -1027,7 +1027,7 @@ __global__ __launch_bounds__(kBlock) void k_drop_sums(const double *__restrict__
   // a drop spans less than half the box along each axis: its box has < 2^31 cells
   const int nbox = ex * ey * ez;
   const int q0 = (int)((int64_t)nbox * sl / kSumSplit), q1 = (int)((int64_t)nbox * (sl + 1) / kSumSplit);
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
   const int qs = q0 + (int)threadIdx.x;
   BoxWalk bw(qs, ex, ey);
   for (int q = qs; q < q1; q += kSumBatch * kBlock) {
@@ -1061,24 +1061,14 @@ __global__ __launch_bounds__(kBlock) void k_drop_sums(const double *__restrict__
     for (int u = 0; u < kSumBatch; ++u) {
       if (!in[u] || lv[u] != l) continue;
       const double v = cv[u];
-      s0 += v;
-      s1 += v * (double)d[u][0];
-      s2 += v * (double)d[u][1];
-      s3 += v * (double)d[u][2];
+      acc[0] += v;
+      acc[1] += v * (double)d[u][0];
+      acc[2] += v * (double)d[u][1];
+      acc[3] += v * (double)d[u][2];
     }
   }
   __shared__ double red[4][kBlock];
-  red[0][threadIdx.x] = s0;
-  red[1][threadIdx.x] = s1;
-  red[2][threadIdx.x] = s2;
-  red[3][threadIdx.x] = s3;
-  __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int k = 0; k < 4; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x < 4) part[((int64_t)g * kSumSplit + sl) * 4 + threadIdx.x] = red[threadIdx.x][0];
+  block_sums<4>(acc, red, part + ((int64_t)g * kSumSplit + sl) * 4);
 }
 
 // Volume and periodic centroid of every drop from its kSumSplit parts.
@@ -1178,16 +1168,7 @@ __global__ __launch_bounds__(kBlock) void k_shape_sums(const double *__restrict_
     }
   }
   __shared__ double red[kShapeSums][kBlock];
-#pragma unroll
-  for (int k = 0; k < kShapeSums; ++k) red[k][threadIdx.x] = acc[k];
-  __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int k = 0; k < kShapeSums; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x < kShapeSums)
-    part[((int64_t)g * kSumSplit + sl) * kShapeSums + threadIdx.x] = red[threadIdx.x][0];
+  block_sums<kShapeSums>(acc, red, part + ((int64_t)g * kSumSplit + sl) * kShapeSums);
 }
 
 // Inertia tensor about the centroid, aspect ratio and mean velocity of every
@@ -1443,10 +1424,11 @@ extern "C" int vofmt_drop_moments(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_
   VOFMT_HIP(ctx, upload_offsets(ndrops_host, ntracers, fh + 2, toff, stream));
   VOFMT_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(int32_t) * 2, stream));
   const FastDiv fnx = make_fastdiv((uint32_t)nx), fny = make_fastdiv((uint32_t)ny);
-  const unsigned nbc = ceil_div(n3, kChunk);  // workgroups of the per-drop reductions, per field
+  const int tx = (int)ceil_div(nx, 64 * kScanX), ty = (int)ceil_div(ny, kScanY);
+  const int64_t ntile = (int64_t)tx * ty * ceil_div(nz, kScanZ);
   hipLaunchKernelGGL(k_scan_init, dim3(ceil_div(kFrames * D, 256)), dim3(256), 0, stream, rootpos, frames, D);
-  hipLaunchKernelGGL(k_drop_scan, dim3(nbc, ntracers), dim3(kBlock), 0, stream, labels, n3, nx, ny, nz, fnx, fny, toff,
-                     rootpos, frames);
+  hipLaunchKernelGGL(k_drop_scan, dim3((unsigned)ntile, ntracers), dim3(kBlock), 0, stream, labels, n3, nx, ny, nz, tx, ty,
+                     fnx, fny, toff, rootpos, frames);
   hipLaunchKernelGGL(k_drop_box, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, rootpos, frames,
                      box);
   hipLaunchKernelGGL(k_drop_sums, dim3((unsigned)(D * kSumSplit)), dim3(kBlock), 0, stream, c, labels, nx, ny, nz, toff,
@@ -1497,10 +1479,11 @@ static int drop_shapes_impl(vofmt_ctx *ctx, const char *fn, bool moments, int32_
   VOFMT_HIP(ctx, upload_offsets(ndrops_host, ntracers, fh + 2, toff, stream));
   VOFMT_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(int32_t) * 2, stream));
   const FastDiv fnx = make_fastdiv((uint32_t)nx), fny = make_fastdiv((uint32_t)ny);
-  const unsigned nbc = ceil_div(n3, kChunk);
+  const int tx = (int)ceil_div(nx, 64 * kScanX), ty = (int)ceil_div(ny, kScanY);
+  const int64_t ntile = (int64_t)tx * ty * ceil_div(nz, kScanZ);
   hipLaunchKernelGGL(k_scan_init, dim3(ceil_div(kFrames * D, 256)), dim3(256), 0, stream, rootpos, frames, D);
-  hipLaunchKernelGGL(k_drop_scan, dim3(nbc, ntracers), dim3(kBlock), 0, stream, labels, n3, nx, ny, nz, fnx, fny, toff,
-                     rootpos, frames);
+  hipLaunchKernelGGL(k_drop_scan, dim3((unsigned)ntile, ntracers), dim3(kBlock), 0, stream, labels, n3, nx, ny, nz, tx, ty,
+                     fnx, fny, toff, rootpos, frames);
   hipLaunchKernelGGL(k_drop_box, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, rootpos, frames,
                      box);
   hipLaunchKernelGGL(k_shape_sums, dim3((unsigned)(D * kSumSplit)), dim3(kBlock), 0, stream, c, labels, sx, sy, sz, nx,

@@ -16,6 +16,11 @@ Interface-cell list: fields of 1 to a few blocks of 8192 cells around the edges
 of words, wavefronts and blocks, at addresses that are multiples of 8 bytes (1
 for the status) only, and above 4096 blocks, where the counts are scanned. Exact.
 
+Drop scan: tiles of 128 x 16 x 16 cells, rows of one cell to several segments,
+runs that end at a segment's end, more runs than a wavefront notes at once, more
+drops in a tile than its table holds. Volumes and centroids within the bounds of
+the other moment tests (1e-12 relative; 1e-12 of the box).
+
 Surface-tension force: every group size, one and two groups, and 2 to 32 planes
 per workgroup with a remainder. Bit-exact."""
 import numpy as np
@@ -153,3 +158,45 @@ def test_interface_list(ctx, shape):
     assert np.array_equal(np.flatnonzero(st[n:2 * n]), want)
     assert np.all(st[:n] == 77) and st[2 * n] == 77  # nothing written beside the field
     assert np.isnan(kappa.cpu().numpy().ravel()[st[n:2 * n] == 0]).all()
+
+
+def _separate(kind, shape, rng):
+    """One field of drops that nowhere touch and span less than half of every axis."""
+    nz, ny, nx = shape
+    k, j, i = np.meshgrid(*[np.arange(n) for n in shape], indexing="ij")
+    inside = (k < nz - nz % 2) & (j < ny - ny % 2) & (i < nx - 1)  # (no contact across the boundary)
+    if kind == "cells":  # single cells in a checkered pattern
+        hit = ((k + j + i) % 2 == 0) & (i < nx - nx % 2) & (rng.random(shape) < 0.5)
+    elif kind == "bars":  # runs of cells of 1 to 3 n/8 along x, in every other row and plane
+        cut = rng.random((nz, ny, 1)) * nx
+        length = max(1, 3 * nx // 8)
+        hit = (k % 2 == 0) & (j % 2 == 0) & ((i + cut.astype(int)) % (length + 1) != 0) & (rng.random((nz, ny, 1)) < 0.8)
+    else:  # blocks of up to 5 x 4 x 6 cells
+        hit = (k % 6 < 5) & (j % 5 < 4) & (i % 7 < 6) & (rng.random(shape) < 0.97) & (k < nz - nz % 6) & (j < ny - ny % 5) \
+            & (i < nx - nx % 7)
+    return np.where(hit & inside, 0.1 + 0.9 * rng.random(shape), 0.0)
+
+
+@pytest.mark.parametrize("kind,shape", [("blocks", (17, 16, 128)), ("blocks", (16, 17, 129)), ("blocks", (36, 35, 300)),
+                                        ("bars", (33, 5, 65)), ("bars", (4, 40, 63)), ("bars", (18, 20, 300)),
+                                        ("bars", (2, 3, 1000)), ("cells", (16, 16, 128)), ("cells", (5, 6, 200)),
+                                        ("cells", (40, 3, 3))])
+def test_drop_scan_tiles(ctx, kind, shape):
+    import torch
+
+    nz, ny, nx = shape
+    rng = np.random.default_rng(sum(shape))
+    c = np.stack([_separate(kind, shape, rng) for _ in range(2)])
+    lab, nd = zip(*[oracle.label(f) for f in c])
+    D = sum(nd)
+    note(f"drop scan {kind} {shape} drops={D}")
+    dev = "cuda:0"
+    vol, xyz = torch.zeros(D, dtype=torch.float64, device=dev), torch.zeros((D, 3), dtype=torch.float64, device=dev)
+    ref = [oracle.drop_moments(c[t], lab[t], nd[t]) for t in range(2)]
+    assert all(r[2] == 0 for r in ref)
+    ctx.drop_moments(torch.from_numpy(c).to(dev), torch.from_numpy(np.stack(lab)).to(dev), np.array(nd, dtype=np.int32), vol, xyz)
+    rv, rx = np.concatenate([r[0] for r in ref]), np.concatenate([r[1] for r in ref])
+    assert np.all(np.abs(vol.cpu().numpy() - rv) <= 1e-12 * rv)
+    box = np.array([nx, ny, nz], dtype=np.float64)
+    d = np.abs(xyz.cpu().numpy() - rx)
+    assert np.all(np.minimum(d, box - d) <= 1e-12 * box)
