@@ -16,6 +16,11 @@ Interface-cell list: fields of 1 to a few blocks of 8192 cells around the edges
 of words, wavefronts and blocks, at addresses that are multiples of 8 bytes (1
 for the status) only, and above 4096 blocks, where the counts are scanned. Exact.
 
+Training forward: a workgroup per 64 samples up to 1024 tiles, whole tiles per
+wavefront above. The activation records equal the forward pass's bit for bit
+(the same operations in the same order), the loss the mean of its terms to the
+rounding of an FP32 sum over m (m 2^-23 relative: all terms are positive).
+
 Drop scan: tiles of 128 x 16 x 16 cells, rows of one cell to several segments,
 runs that end at a segment's end, more runs than a wavefront notes at once, more
 drops in a tile than its table holds. Volumes and centroids within the bounds of
@@ -200,3 +205,25 @@ def test_drop_scan_tiles(ctx, kind, shape):
     box = np.array([nx, ny, nz], dtype=np.float64)
     d = np.abs(xyz.cpu().numpy() - rx)
     assert np.all(np.minimum(d, box - d) <= 1e-12 * box)
+
+
+@pytest.mark.parametrize("m", [1, 15, 17, 64, 65, 1000, 65536, 65537])
+def test_training_forward_tiles(ctx, m):
+    import torch
+
+    from paper_2407_07463_amd import training
+
+    rng = np.random.default_rng(m)
+    x = torch.from_numpy(rng.random((m, 27), dtype=np.float32)).to("cuda:0")
+    t = torch.from_numpy(rng.standard_normal(m).astype(np.float32)).to("cuda:0")
+    params = torch.from_numpy(training.init_params(3)).to("cuda:0")
+    y = torch.empty(m, dtype=torch.float32, device="cuda:0")
+    acts = torch.zeros((m, 384), dtype=torch.int16, device="cuda:0")
+    trace = torch.zeros((m, 640), dtype=torch.int16, device="cuda:0")
+    note(f"training forward m={m}")
+    ctx.mlp_forward(params, x, y, acts)
+    loss = ctx.mlp_train_step(params, torch.zeros_like(params), torch.zeros_like(params), 1, 1e-3, x, t, trace=trace)
+    assert torch.equal(trace[:, :384], acts)
+    yd, td = y.double(), t.double()
+    want = float(((yd - td) ** 2 / td.abs().clamp(min=0.05) ** 2).mean())
+    assert abs(loss - want) <= (m + 8) * 2.0**-23 * want
