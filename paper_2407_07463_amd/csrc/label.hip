@@ -25,9 +25,8 @@
 //               tiles of whole rows are made in LDS, each tile by one
 //               workgroup (2a), then those across tile boundaries on the run
 //               table (2b);
-//   3. flatten: every run points at its root; roots counted per workgroup;
-//   4. rank:    the counts are scanned and each root's entry becomes
-//               -(1 + number of roots before it);
+//   3. count:   roots counted per workgroup;
+//   4. rank:    each root's entry becomes -(1 + number of roots before it);
 //   5. resolve: every other run's entry becomes its root's;
 //   6. labels:  each cell reads its run's entry and writes the label, 0 for
 //               empty cells.
@@ -51,15 +50,6 @@ struct RunTable {
     return P + (int64_t)(id & ((1 << shift) - 1)) * nseg + (id >> shift);
   }
 };
-
-__device__ __forceinline__ int find_root(const RunTable &T, int32_t a) {
-  int32_t b = *T.at(a);
-  while (b != a) {
-    a = b;
-    b = *T.at(a);
-  }
-  return a;
-}
 
 // Root search with path halving: every node passed gets its grandparent as
 // parent. Only nodes that are no longer roots are written, and always with
@@ -102,7 +92,6 @@ __device__ __forceinline__ void unite(const RunTable &T, int32_t a, int32_t b) {
 // of the cells is the order of (segment, lane)), so a workgroup covers
 // 4 * kSegs segments.
 constexpr int kSegs = 16;   // occupancy pass (1.58 ms at 512^3 x 8; 4: 1.78, 8: 1.65, 32: 1.68)
-constexpr int kSegsW = 16;  // label-writing pass
 
 // Row segment `sgi` (all segments of the field in linear order):
 // row = z * ny + y, x = 64 * seg + lane. Segment counts stay below 2^31 (at
@@ -548,62 +537,52 @@ __device__ __forceinline__ int count_roots(const RunTable &T, uint64_t m, int64_
 // workgroup covers the 64 consecutive segments 64 (kSegT w + k) .. + 63 of
 // the workgroup's kBlock * kSegT, one per lane, so the segments of a
 // workgroup are in (wavefront, round, lane) order, their linear order.
-constexpr int kSegT = 4;  // (flatten + rank + resolve at 512^3 x 8: 1: 0.196 ms, 2: 0.178, 4: 0.166, 8: 0.186)
+constexpr int kSegT = 4;  // (the three at 512^3 x 8: 1: 0.196 ms, 2: 0.178, 4: 0.166, 8: 0.186)
 __device__ __forceinline__ int64_t pass_segment(int k) {
   return ((int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63)) * kSegT + 64 * k + (threadIdx.x & 63);
 }
 
-// Pass 3: every run points at its root; roots counted per workgroup.
-__global__ __launch_bounds__(kBlock) void k_label_flatten(const uint64_t *__restrict__ occ, RunTable T, int64_t nseg,
-                                                          uint32_t *__restrict__ blockcount, int64_t nrun) {
+// Pass 3: roots counted per workgroup. (Pointing every run at its root here, so
+// that pass 5 makes one step, reads and writes the entries once more: 62 + 51 +
+// 47 us for passes 3 to 5 at 512^3 x 8, 35 + 51 + 58 so.)
+__global__ __launch_bounds__(kBlock) void k_label_count(const uint64_t *__restrict__ occ, RunTable T, int64_t nseg,
+                                                        int32_t *__restrict__ blockcount, int64_t nrun) {
   occ += blockIdx.y * nseg;
   T.P += blockIdx.y * nrun;
   blockcount += blockIdx.y * gridDim.x;
   uint64_t m[kSegT];
 #pragma unroll
   for (int k = 0; k < kSegT; ++k) m[k] = (pass_segment(k) < nseg) ? occ[pass_segment(k)] : 0ull;
-  uint32_t nroot = 0;
+  int nroot = 0;
 #pragma unroll
-  for (int k = 0; k < kSegT; ++k) {
-    const int nr = __popcll(m[k] & ~(m[k] << 1));
-    for (int r = 0; r < nr; ++r) {
-      const int32_t id = (int32_t)((pass_segment(k) << T.shift) + r);
-      const int32_t root = find_root(T, id);
-      if (root == id) ++nroot;
-      else *T.at(id) = root;
-    }
-  }
+  for (int k = 0; k < kSegT; ++k) nroot += m[k] ? count_roots(T, m[k], pass_segment(k)) : 0;
   for (int o = 32; o > 0; o >>= 1) nroot += __shfl_xor(nroot, o, 64);
-  __shared__ uint32_t wcount[kBlock / 64];
+  __shared__ int wcount[kBlock / 64];
   if ((threadIdx.x & 63) == 0) wcount[threadIdx.x >> 6] = nroot;
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t sum = 0;
+    int sum = 0;
     for (int w = 0; w < kBlock / 64; ++w) sum += wcount[w];
     blockcount[blockIdx.x] = sum;
   }
 }
 
-// The totals of the tiled scans (one per field, tstride apart) into total[].
-__global__ void k_copy_total(const int32_t *__restrict__ tot, int64_t ntiles, int64_t tstride, int nfields,
-                             int32_t *__restrict__ total) {
-  const int t = threadIdx.x;
-  if (t < nfields) total[t] = tot[t * tstride + ntiles];
-}
-
 // Pass 4: each root's entry becomes -(1 + number of roots before it), in
-// linear order: the workgroup's offset from the scanned block counts, then
+// linear order: the roots of the workgroups before (the sum of their counts, or
+// with SCANNED the scanned count and the sums of the scan tiles before), then
 // within the workgroup the roots of earlier wavefronts, earlier rounds and
-// lower lanes.
+// lower lanes. The last workgroup stores the field's number of roots in total
+// (host memory).
+template <bool SCANNED>
 __global__ __launch_bounds__(kBlock) void k_label_rank(const uint64_t *__restrict__ occ, RunTable T, int64_t nseg,
                                                        const int32_t *__restrict__ blockoff,
-                                                       const int32_t *__restrict__ tileoff, int64_t nrun,
-                                                       int64_t tstride) {
+                                                       const int32_t *__restrict__ tilesum, int64_t nrun,
+                                                       int64_t tstride, int32_t *__restrict__ total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   occ += blockIdx.y * nseg;
   T.P += blockIdx.y * nrun;
   blockoff += blockIdx.y * gridDim.x;
-  tileoff += blockIdx.y * tstride;
+  tilesum += blockIdx.y * tstride;
   uint64_t m[kSegT];
 #pragma unroll
   for (int k = 0; k < kSegT; ++k) m[k] = (pass_segment(k) < nseg) ? occ[pass_segment(k)] : 0ull;
@@ -620,11 +599,18 @@ __global__ __launch_bounds__(kBlock) void k_label_rank(const uint64_t *__restric
     excl[k] = wtotal + incl - mine;
     wtotal += __shfl(incl, 63, 64);
   }
-  __shared__ int wtot[kBlock / 64];
+  __shared__ int wtot[kBlock / 64], wbefore[kBlock / 64];
   if (lane == 0) wtot[w] = wtotal;
+  const int32_t *v = SCANNED ? tilesum : blockoff;
+  int part = 0;
+  for (unsigned k = threadIdx.x; k < (SCANNED ? blockIdx.x / compact::kTile : blockIdx.x); k += kBlock) part += v[k];
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1) part += __shfl_xor(part, k, 64);
+  if (lane == 0) wbefore[w] = part;
   __syncthreads();
-  int base = blockoff[blockIdx.x] + tileoff[blockIdx.x / compact::kTile];
-  for (int k = 0; k < w; ++k) base += wtot[k];
+  int base = SCANNED ? blockoff[blockIdx.x] : 0;
+  for (int k = 0; k < kBlock / 64; ++k) base += wbefore[k] + (k < w ? wtot[k] : 0);
+  if (blockIdx.x == gridDim.x - 1 && w == kBlock / 64 - 1 && lane == 0) total[blockIdx.y] = base + wtotal;
 #pragma unroll
   for (int k = 0; k < kSegT; ++k) {
     if (!m[k]) continue;
@@ -637,8 +623,9 @@ __global__ __launch_bounds__(kBlock) void k_label_rank(const uint64_t *__restric
   }
 }
 
-// Pass 5: every run that is not a root takes its root's entry (the negative
-// label); roots are only read.
+// Pass 5: every run that is not a root walks up to its root's entry (the
+// negative label) and takes it; an entry on the way that another thread has
+// already replaced holds the same label.
 __global__ __launch_bounds__(kBlock) void k_label_resolve(const uint64_t *__restrict__ occ, RunTable T, int64_t nseg,
                                                           int64_t nrun) {
   occ += blockIdx.y * nseg;
@@ -651,85 +638,62 @@ __global__ __launch_bounds__(kBlock) void k_label_resolve(const uint64_t *__rest
     const int nr = __popcll(m[k] & ~(m[k] << 1));
     for (int r = 0; r < nr; ++r) {
       int32_t *e = T.at((int32_t)((pass_segment(k) << T.shift) + r));
-      const int32_t v = *e;
-      if (v >= 0) *e = *T.at(v);
+      int32_t v = *e;
+      if (v < 0) continue;
+      while (v >= 0) v = *T.at(v);
+      *e = v;
     }
   }
 }
 
-// Pass 6: label of every cell of the field (0 for empty cells). The
-// occupancy words, then the run entries of the wavefront's kSegsW segments
-// are each loaded together: every lane loads (from a valid slot when it has
-// no cell) and selects afterwards, since a load under a lane condition is
-// compiled as a branch that waits for it.
+// Pass 6: label of every cell of the field (0 for empty cells). A lane writes V
+// consecutive cells of the field with one store, a wavefront kCellsW
+// consecutive cells; V = 4 (2) where rows hold a multiple of 4 (2) cells, so
+// that a lane's cells lie in one row segment, and the labels are aligned to it.
+// The occupancy words and then the run entries of all the wavefront's cells are
+// loaded before the first store: every lane loads (from a valid slot when its
+// cell is empty) and selects afterwards, since a load under a lane condition
+// is compiled as a branch that waits for it.
+// LINEAR: rows of whole segments (nx % 64 == 0), where cell p lies in segment p / 64.
+constexpr int kCellsW = 1024;
+template <int V, bool LINEAR>
 __global__ __launch_bounds__(kBlock) void k_label_write(const uint64_t *__restrict__ occ, RunTable T,
-                                                        int32_t *__restrict__ lab, int nx, int ny, int nz, int words,
-                                                        SegDiv dv, int64_t nrun) {
+                                                        int32_t *__restrict__ lab, int64_t n3, int nx, int words,
+                                                        FastDiv fnx, int64_t nrun) {
+  typedef int32_t vec __attribute__((ext_vector_type(V)));
+  constexpr int kGroups = kCellsW / (64 * V);
   const int lane = threadIdx.x & 63;
-  const int64_t nseg = (int64_t)ny * nz * words, s0 = first_segment<kSegsW>();
+  const int64_t nseg = T.nseg;
+  const int64_t c0 = (((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6) * kCellsW + V * lane;
   occ += blockIdx.y * nseg;
   T.P += blockIdx.y * nrun;
-  lab += blockIdx.y * ((int64_t)nx * ny * nz);
-  uint64_t m[kSegsW];
-  int32_t e[kSegsW];
+  lab += blockIdx.y * n3;
+  uint64_t m[kGroups];
+  int32_t sg[kGroups];
+  int b0[kGroups];
 #pragma unroll
-  for (int k = 0; k < kSegsW; ++k) m[k] = (s0 + k < nseg) ? occ[s0 + k] : 0ull;
-  bool on[kSegsW];
-#pragma unroll
-  for (int k = 0; k < kSegsW; ++k) {
-    on[k] = (m[k] >> lane) & 1ull;
-    const int64_t sg = (s0 + k < nseg) ? s0 + k : nseg - 1;
-    e[k] = T.P[(int64_t)(on[k] ? run_index(m[k], lane) : 0) * nseg + sg];
-  }
-#pragma unroll
-  for (int k = 0; k < kSegsW; ++k) e[k] = on[k] ? -e[k] : 0;
-#pragma unroll
-  for (int k = 0; k < kSegsW; ++k) {
-    const int64_t sgi = s0 + k;
-    if (sgi >= nseg) break;  // wave-uniform
-    const Segment sg = segment_of(sgi, dv);
-    const int x = sg.seg * 64 + lane;
-    if (x < nx) __builtin_nontemporal_store(e[k], &lab[sg.row * nx + x]);  // streamed out
-  }
-}
-
-// Pass 6 when rows hold a multiple of 256 cells: lane l of a wavefront
-// writes cells 4l .. 4l+3 of each of its kGroupsW 256-cell groups (segment
-// 4g + l/16, bits 4(l%16) .. +3) with one 16-byte store. The occupancy
-// words and then the run entries of all the wavefront's groups are loaded
-// before the first store, as in k_label_write.
-constexpr int kGroupsW = 4;
-typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
-__global__ __launch_bounds__(kBlock) void k_label_write4(const uint64_t *__restrict__ occ, RunTable T,
-                                                         int32_t *__restrict__ lab, int64_t n3, int64_t nrun) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nseg = T.nseg, ngroups = nseg / 4;
-  const int64_t g0 = (((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6) * kGroupsW;
-  occ += blockIdx.y * nseg;
-  T.P += blockIdx.y * nrun;
-  v4i32 *lab4 = reinterpret_cast<v4i32 *>(lab + blockIdx.y * n3);
-  const int j = lane >> 4, b0 = 4 * (lane & 15);
-  uint64_t m[kGroupsW];
-  int64_t sg[kGroupsW];
-#pragma unroll
-  for (int k = 0; k < kGroupsW; ++k) {
-    sg[k] = (g0 + k < ngroups) ? 4 * (g0 + k) + j : nseg - 1;
+  for (int k = 0; k < kGroups; ++k) {
+    const int64_t p = c0 + 64 * V * k;
+    const uint32_t pc = (uint32_t)(p < n3 ? p : 0);
+    const uint32_t row = LINEAR ? 0u : fast_div(pc, fnx);
+    const uint32_t x = LINEAR ? pc : pc - row * (uint32_t)nx;
+    sg[k] = (int32_t)(row * (uint32_t)words + (x >> 6));
+    b0[k] = (int)(x & 63u);
     m[k] = occ[sg[k]];
   }
-  int32_t e[kGroupsW][4];
+  vec e[kGroups];
 #pragma unroll
-  for (int k = 0; k < kGroupsW; ++k)
+  for (int k = 0; k < kGroups; ++k)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool on = (m[k] >> (b0 + i)) & 1ull;
-      const int32_t v = T.P[(int64_t)(on ? run_index(m[k], b0 + i) : 0) * nseg + sg[k]];
+    for (int i = 0; i < V; ++i) {
+      const bool on = (m[k] >> (b0[k] + i)) & 1ull;
+      const int32_t v = T.P[(int64_t)(on ? run_index(m[k], b0[k] + i) : 0) * nseg + sg[k]];
       e[k][i] = on ? -v : 0;
     }
 #pragma unroll
-  for (int k = 0; k < kGroupsW; ++k) {
-    if (g0 + k >= ngroups) break;  // wave-uniform
-    const v4i32 v = {e[k][0], e[k][1], e[k][2], e[k][3]};
-    __builtin_nontemporal_store(v, &lab4[(g0 + k) * 64 + lane]);  // streamed out
+  for (int k = 0; k < kGroups; ++k) {
+    const int64_t p = c0 + 64 * V * k;
+    if (p < n3) __builtin_nontemporal_store(e[k], (vec *)(lab + p));  // streamed out
   }
 }
 
@@ -1264,6 +1228,10 @@ __global__ void k_shape_finish(int32_t K, int nx, int ny, int nz, const int32_t 
 // 256: 0.44 ms for passes 2a + 2b, 1024: 0.28, 2048: 0.27, 4096: 0.59 with
 // one workgroup per CU).
 constexpr int kTileSegs = 2048;
+// Grids with few such tiles take tiles of 512 (198x187x206 x 3, 226 tiles: 27 -> 13
+// us; 330x280x310 x 4, 1020 tiles: 60 -> 32 us; at 512^3 x 8, 8192 tiles, 0.44 ms
+// against 0.27 for passes 2a + 2b).
+constexpr int kSmallTileSegs = 512, kFewTiles = 4096;
 // Row tiles of the local union pass: as many whole rows as fit ts segments,
 // tz the largest power of two up to their square root (at most nz), the rest
 // along y. Rows longer than ts segments take the global unions only (ty = 0).
@@ -1301,23 +1269,26 @@ static void launch_local(vofmt_ctx *ctx, int ntile, unsigned nt, hipStream_t str
 // All passes over the T fields at once (blockIdx.y = field), each field with
 // its own work arrays.
 static int label_all(vofmt_ctx *ctx, int nx, int ny, int nz, int T, const double *c, double c_eps, int32_t *lab,
-                     uint64_t *occ, int32_t *runs, uint32_t *blockcount, int32_t *tileoff, int64_t tstride,
-                     int32_t *k_dev, hipStream_t stream) {
+                     uint64_t *occ, int32_t *runs, int32_t *blockcount, int32_t *tilesum, int64_t tstride,
+                     int32_t *total, hipStream_t stream) {
   const int words = (int)ceil_div(nx, 64);
   const int64_t nseg = (int64_t)ny * nz * words;
   const RunTable R{runs, nseg, run_shift(nx)};
   const int64_t nrun = nseg << R.shift;
   const unsigned nbc = (unsigned)label_blocks(nx, ny, nz, kSegs);    // occupancy pass
-  const unsigned nbw = (unsigned)label_blocks(nx, ny, nz, kSegsW);   // label-writing pass
   const unsigned nbs = (unsigned)segment_blocks(nx, ny, nz);  // per-segment passes
   const SegDiv dv{make_fastdiv((uint32_t)words), make_fastdiv((uint32_t)ny)};
   const unsigned nt = (unsigned)T;
   hipLaunchKernelGGL(k_label_occ, dim3(nbc, nt), dim3(kBlock), 0, stream, c, c_eps, occ, R, nx, ny, nz, words, dv,
                      nrun);
-  const RowTiles rt = row_tiles(ny, nz, words, kTileSegs);
+  // smaller row tiles while the larger ones would leave compute units without one
+  RowTiles rt = row_tiles(ny, nz, words, kTileSegs);
+  const bool few = rt.ty > 0 && (int64_t)rt.nty * ceil_div(nz, rt.tz) * T < kFewTiles && words <= kSmallTileSegs;
+  if (few) rt = row_tiles(ny, nz, words, kSmallTileSegs);
   if (rt.ty > 0) {
     const int ntile = (int)(rt.nty * ceil_div(nz, rt.tz));
-    launch_local<kTileSegs>(ctx, ntile, nt, stream, occ, R, nx, ny, nz, words, rt, nrun);
+    if (few) launch_local<kSmallTileSegs>(ctx, ntile, nt, stream, occ, R, nx, ny, nz, words, rt, nrun);
+    else launch_local<kTileSegs>(ctx, ntile, nt, stream, occ, R, nx, ny, nz, words, rt, nrun);
     const EdgeRows e = edge_rows(rt, ny, nz);
     const int64_t nedge = ((int64_t)e.nzb * ny + (int64_t)e.nyb * (nz - e.nzb)) * words;
     if (nedge > 0)
@@ -1327,26 +1298,33 @@ static int label_all(vofmt_ctx *ctx, int nx, int ny, int nz, int T, const double
     hipLaunchKernelGGL(k_label_union, dim3(nbs, nt), dim3(kBlock), 0, stream, occ, R, nx, ny, nz, words, dv, nrun);
   }
   const unsigned nbg = (unsigned)ceil_div(nseg, (int64_t)kBlock * kSegT);  // passes 3-5 (<= nbs)
-  hipLaunchKernelGGL(k_label_flatten, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, blockcount, nrun);
-  static_assert(kBlock == compact::kBlock, "block counts and the tiled scan share the block size");
-  const int64_t ntiles = (nbg + compact::kTile - 1) / compact::kTile;
-  int32_t *bc = (int32_t *)blockcount;
-  hipLaunchKernelGGL(compact::k_scan_tile, dim3((unsigned)ntiles, nt), dim3(compact::kTile), 0, stream, bc,
-                     (int64_t)nbg, tileoff, (int64_t)nbg, tstride);
-  hipLaunchKernelGGL(compact::k_scan_totals, dim3(1, nt), dim3(compact::kTile), 0, stream, tileoff, ntiles, tstride);
-  hipLaunchKernelGGL(k_copy_total, dim3(1), dim3(64 * ((T + 63) / 64)), 0, stream, tileoff, ntiles, tstride, T,
-                     k_dev);
-  hipLaunchKernelGGL(k_label_rank, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, bc, tileoff, nrun, tstride);
-  hipLaunchKernelGGL(k_label_resolve, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, nrun);
-  if (nx % 256 == 0 && ((uintptr_t)lab & 15) == 0) {
-    const int64_t ngroups = nseg / 4;  // whole 256-cell groups: segment s is cells 64 s .. 64 s + 63
-    const int64_t per = (int64_t)(kBlock / 64) * kGroupsW;
-    hipLaunchKernelGGL(k_label_write4, dim3((unsigned)((ngroups + per - 1) / per), nt), dim3(kBlock), 0, stream, occ,
-                       R, lab, (int64_t)nx * ny * nz, nrun);
+  hipLaunchKernelGGL(k_label_count, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, blockcount, nrun);
+  // up to kDirect workgroups each sums the counts before its own: two launches
+  // of about 5 us less than a scan, and a copy with the totals stored by pass 4
+  constexpr unsigned kDirect = 4096;
+  if (nbg <= kDirect) {
+    hipLaunchKernelGGL(k_label_rank<false>, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, blockcount, tilesum,
+                       nrun, tstride, total);
   } else {
-    hipLaunchKernelGGL(k_label_write, dim3(nbw, nt), dim3(kBlock), 0, stream, occ, R, lab, nx, ny, nz, words, dv,
-                       nrun);
+    static_assert(kBlock == compact::kBlock, "block counts and the tiled scan share the block size");
+    const int64_t ntiles = (nbg + compact::kTile - 1) / compact::kTile;
+    hipLaunchKernelGGL(compact::k_scan_tile, dim3((unsigned)ntiles, nt), dim3(compact::kTile), 0, stream, blockcount,
+                       (int64_t)nbg, tilesum, (int64_t)nbg, tstride);
+    hipLaunchKernelGGL(k_label_rank<true>, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, blockcount, tilesum,
+                       nrun, tstride, total);
   }
+  hipLaunchKernelGGL(k_label_resolve, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, nrun);
+  const int64_t n3 = (int64_t)nx * ny * nz;
+  const dim3 nbw((unsigned)ceil_div(n3, (int64_t)(kBlock / 64) * kCellsW), nt);
+  const FastDiv fnx = make_fastdiv((uint32_t)nx);
+  auto aligned = [&](int v) { return nx % v == 0 && ((uintptr_t)lab & (4 * v - 1)) == 0; };
+  auto write = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, nbw, dim3(kBlock), 0, stream, occ, R, lab, n3, nx, words, fnx, nrun);
+  };
+  if (aligned(4) && nx % 64 == 0) write(k_label_write<4, true>);
+  else if (aligned(4)) write(k_label_write<4, false>);
+  else if (aligned(2)) write(k_label_write<2, false>);
+  else write(k_label_write<1, false>);
   return hip_check(ctx, hipGetLastError(), "label kernels");
 }
 
@@ -1369,18 +1347,16 @@ extern "C" int vofmt_label_drops(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t
   // touched at the runs that exist)
   const int64_t tstride = nbs / compact::kTile + 2;
   const size_t T = (size_t)ntracers;
-  uint32_t *blockcount = (uint32_t *)scratch(ctx, SLOT_LABEL_A, sizeof(uint32_t) * (size_t)nbs * T);
+  int32_t *blockcount = (int32_t *)scratch(ctx, SLOT_LABEL_A, sizeof(int32_t) * (size_t)nbs * T);
   int32_t *runs = (int32_t *)scratch(ctx, SLOT_LABEL_B, sizeof(int32_t) * (size_t)nrun * T);
   uint64_t *occ = (uint64_t *)scratch(ctx, SLOT_LABEL_C, sizeof(uint64_t) * (size_t)nseg * T);
-  int32_t *kdev = (int32_t *)scratch(ctx, SLOT_MISC, sizeof(int32_t) * T);
-  int32_t *tileoff = (int32_t *)scratch(ctx, SLOT_MISC3, sizeof(int32_t) * (size_t)tstride * T);
+  int32_t *tilesum = (int32_t *)scratch(ctx, SLOT_MISC3, sizeof(int32_t) * (size_t)tstride * T);
   int32_t *kh = (int32_t *)host_scratch(ctx, sizeof(int32_t) * T);
-  if (!blockcount || !runs || !occ || !kdev || !tileoff || !kh) return VOFMT_E_NOMEM;
-  int rc = label_all(ctx, nx, ny, nz, ntracers, c, c_eps, labels, occ, runs, blockcount, tileoff, tstride, kdev,
+  if (!blockcount || !runs || !occ || !tilesum || !kh) return VOFMT_E_NOMEM;
+  int rc = label_all(ctx, nx, ny, nz, ntracers, c, c_eps, labels, occ, runs, blockcount, tilesum, tstride, kh,
                      stream);
   if (rc) return rc;
-  VOFMT_HIP(ctx, hipMemcpyAsync(kh, kdev, sizeof(int32_t) * ntracers, hipMemcpyDeviceToHost, stream));
-  VOFMT_HIP(ctx, hipStreamSynchronize(stream));
+  VOFMT_HIP(ctx, hipStreamSynchronize(stream));  // (the totals are in kh, pinned, from the kernels)
   for (int t = 0; t < ntracers; ++t) ndrops_host[t] = kh[t];
   return VOFMT_OK;
 }

@@ -21,6 +21,10 @@ wavefront above. The activation records equal the forward pass's bit for bit
 (the same operations in the same order), the loss the mean of its terms to the
 rounding of an FP32 sum over m (m 2^-23 relative: all terms are positive).
 
+Labelling: labels written 4, 2 or 1 cells a lane, as rows and the array's
+alignment go, union tiles of 512 or 2048 segments, the roots before a workgroup
+summed or (above 4096 workgroups) scanned. Exact.
+
 Drop scan: tiles of 128 x 16 x 16 cells, rows of one cell to several segments,
 runs that end at a segment's end, more runs than a wavefront notes at once, more
 drops in a tile than its table holds. Volumes and centroids within the bounds of
@@ -227,3 +231,23 @@ def test_training_forward_tiles(ctx, m):
     yd, td = y.double(), t.double()
     want = float(((yd - td) ** 2 / td.abs().clamp(min=0.05) ** 2).mean())
     assert abs(loss - want) <= (m + 8) * 2.0**-23 * want
+
+
+@pytest.mark.parametrize("shape,offset", [((7, 9, 64), 0), ((7, 9, 64), 1), ((7, 9, 64), 2), ((6, 5, 66), 0), ((6, 5, 66), 1),
+                                          ((5, 7, 67), 0), ((9, 33, 260), 0), ((3, 1025, 3), 0), ((2100, 2001, 1), 0),
+                                          ((300, 290, 65), 0)])
+def test_label_forms(ctx, shape, offset):
+    """offset: of the label array from a 16-byte boundary, in labels."""
+    import torch
+
+    rng = np.random.default_rng(sum(shape) + offset)
+    c = np.where(rng.random((2,) + shape) < 0.3, rng.random((2,) + shape), 0.0)
+    note(f"labels {shape} offset={offset}")
+    buf = torch.full((c.size + offset + 1,), -7, dtype=torch.int32, device="cuda:0")
+    lab = buf[offset:offset + c.size].reshape(c.shape)
+    nd = ctx.label_drops(torch.from_numpy(c).to("cuda:0"), lab)
+    for t in range(2):
+        want, k = oracle.label(c[t])
+        assert nd[t] == k
+        assert np.array_equal(lab[t].cpu().numpy(), want)
+    assert int(buf[-1]) == -7 and (offset == 0 or bool((buf[:offset] == -7).all()))
