@@ -250,7 +250,7 @@ int vofmt_compact_tracers(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, in
  * nn_index  : [n] int32 output (smallest nearest j). nn_ties: [n] int32 output (N_i).
  * hist_fixed: [nr*ntheta + 1] uint64 output. M: [3], R: [9] FP64 outputs.
  * A         : [9] FP64 output, or NULL.
- * Synchronises the stream (host staging of the edges). Scratch: 16 bytes per
+ * Synchronises the stream. Scratch: 16 bytes per
  * drop and candidate slice (at most 64 slices) plus 104 bytes per drop.
  */
 int vofmt_nearest_pair_stats(vofmt_ctx *ctx, int32_t n, const double *xyz, const double *box, int32_t vertical_axis,
@@ -295,7 +295,7 @@ int vofmt_nearest_pair_stats_noalloc(vofmt_ctx *ctx, int32_t n, const double *xy
  *              overflow slot, if present, is not read).
  * events     : E, the number of drops summed over the histograms (>= 1).
  * P          : [nr][ntheta] FP64 device output. Pr: [nr] FP64 device output.
- * Synchronises the stream (host staging of the edges).
+ * Synchronises the stream.
  */
 int vofmt_pair_pdfs(vofmt_ctx *ctx, int32_t nr, int32_t ntheta, const double *r_edges, const double *theta_edges,
                     const uint64_t *hist_fixed, int64_t events, double *P, double *Pr, hipStream_t stream);

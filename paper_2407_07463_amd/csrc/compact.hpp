@@ -115,15 +115,16 @@ __global__ __launch_bounds__(kTile) void k_scan_totals(int32_t *__restrict__ tot
 // pass (the field is not read again), after the entries of the blocks before
 // it: bc[b] plus the totals of the tiles before its own, or (SCANNED false) the
 // sum of the counts before bc[b]. The last block stores the list's length in
-// tot[ntiles]. With
+// *length. With
 // kappa/status given, every cell first gets NaN / 0 (the listed cells are
 // written later, by the list's readers): 16 bytes a lane and not kept in the
 // caches (272 us with a store of 8 and one of 1 byte a lane over a 512^3 field,
 // 238 us so).
 template <bool SCANNED>
 __global__ __launch_bounds__(kBlock) void k_write_ordered(const uint64_t *__restrict__ bits, int64_t n3,
-                                                          const int32_t *__restrict__ bc, int32_t *__restrict__ tot,
-                                                          int64_t ntiles, int32_t *__restrict__ list,
+                                                          const int32_t *__restrict__ bc,
+                                                          const int32_t *__restrict__ tot,
+                                                          int32_t *__restrict__ length, int32_t *__restrict__ list,
                                                           double *__restrict__ kappa, uint8_t *__restrict__ status) {
   typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));
   typedef uint32_t uint4u __attribute__((ext_vector_type(4), aligned(1)));
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(kBlock) void k_write_ordered(const uint64_t *__rest
   __syncthreads();
   int run = SCANNED ? bc[blockIdx.x] : 0;
   for (int k = 0; k < kBlock / 64; ++k) run += before[k] + (k < w ? wc[k] : 0);
-  if (blockIdx.x == gridDim.x - 1 && w == kBlock / 64 - 1 && lane == 63) tot[ntiles] = run + upto;
+  if (blockIdx.x == gridDim.x - 1 && w == kBlock / 64 - 1 && lane == 63) *length = run + upto;
   run += upto - mine;
   while (word) {
     list[run++] = (int32_t)(pw + 64 * lane) + (int32_t)__builtin_ctzll(word);
@@ -174,11 +175,10 @@ __global__ __launch_bounds__(kBlock) void k_write_ordered(const uint64_t *__rest
 }
 
 // The ordered list of the mixed cells of c into `list` (capacity n3), its
-// length into tot[ntiles] on the device. bc: ceil(n3 / kBlock) ints of
-// scratch; tot: ntiles + 1 ints, ntiles = ceil(bc length / kTile); bits:
-// ceil(n3 / 64) words of scratch.
+// length into *length (device or pinned host memory). bc: ceil(n3 / kBlock) ints of
+// scratch; tot: list_tiles(n3) ints; bits: ceil(n3 / 64) words of scratch.
 inline void launch_ordered_list(const double *c, int64_t n3, int32_t *bc, int32_t *tot, int32_t *list, double *kappa,
-                                uint8_t *status, uint64_t *bits, hipStream_t stream) {
+                                uint8_t *status, uint64_t *bits, int32_t *length, hipStream_t stream) {
   const int64_t nb = (n3 + kCells - 1) / kCells;
   const int64_t ntiles = (nb + kTile - 1) / kTile;
   hipLaunchKernelGGL(k_block_counts, dim3((unsigned)nb), dim3(kBlock), 0, stream, c, n3, bc, bits);
@@ -186,16 +186,16 @@ inline void launch_ordered_list(const double *c, int64_t n3, int32_t *bc, int32_
   // scan is one more launch of about 5 us (64^3: 41 -> 38 us for the call)
   constexpr int64_t kDirect = 4096;
   if (nb <= kDirect) {
-    hipLaunchKernelGGL(k_write_ordered<false>, dim3((unsigned)nb), dim3(kBlock), 0, stream, bits, n3, bc, tot, ntiles,
+    hipLaunchKernelGGL(k_write_ordered<false>, dim3((unsigned)nb), dim3(kBlock), 0, stream, bits, n3, bc, tot, length,
                        list, kappa, status);
     return;
   }
   hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)ntiles), dim3(kTile), 0, stream, bc, nb, tot, (int64_t)0, (int64_t)0);
-  hipLaunchKernelGGL(k_write_ordered<true>, dim3((unsigned)nb), dim3(kBlock), 0, stream, bits, n3, bc, tot, ntiles,
+  hipLaunchKernelGGL(k_write_ordered<true>, dim3((unsigned)nb), dim3(kBlock), 0, stream, bits, n3, bc, tot, length,
                      list, kappa, status);
 }
 
-// Scan tiles of the mixed-cell list of n3 cells (its length is at tot[list_tiles(n3)]).
+// Scan tiles of the mixed-cell list of n3 cells.
 inline int64_t list_tiles(int64_t n3) { return ((n3 + kCells - 1) / kCells + kTile - 1) / kTile; }
 // Scan tiles of a predicate list of n cells (one block count per kBlock cells).
 inline int64_t list_tiles_if(int64_t n) { return ((n + kBlock - 1) / kBlock + kTile - 1) / kTile; }

@@ -61,7 +61,7 @@ extern "C" int vofmt_curvature_hf(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_
   uint64_t *bits = (uint64_t *)scratch(ctx, SLOT_LIST_BITS, sizeof(uint64_t) * (size_t)ceil_div(n3, 64));
   if (!list || !bc || !tot || !bits) return VOFMT_E_NOMEM;
   int rec = prof_begin(ctx, "mixed_list", stream);
-  compact::launch_ordered_list(c, n3, bc, tot, list, kappa, status, bits, stream);
+  compact::launch_ordered_list(c, n3, bc, tot, list, kappa, status, bits, tot + ntiles, stream);
   prof_end(ctx, rec, stream);
   const int32_t *count = tot + ntiles;
   rec = prof_begin(ctx, "k_curv_hf_list", stream);

@@ -764,10 +764,19 @@ __device__ __forceinline__ int table_slot(int32_t *key, int32_t l) {
   return -1;
 }
 
-__global__ void k_scan_init(int32_t *first, int32_t *frames, int64_t K) {
+// Drop records' offsets of up to kArgFields fields, as a kernel argument.
+constexpr int kArgFields = 64;
+struct FieldOffsets {
+  int32_t off[kArgFields + 1];
+};
+
+// The first launch of a call: every record empty, and the offsets of the fields
+// stored (noff of them, 0 where they were copied).
+__global__ void k_scan_init(int32_t *first, int32_t *frames, int64_t K, FieldOffsets fo, int noff, int32_t *toff) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < K) first[i] = INT32_MAX;
   if (i < kFrames * K) frames[i] = (i & 1) ? INT32_MIN : INT32_MAX;
+  if (i < noff) toff[i] = fo.off[i];
 }
 
 // A run of cells p .. p + len - 1 of one row and drop, merged into the
@@ -971,7 +980,7 @@ __global__ __launch_bounds__(kBlock) void k_drop_sums(const double *__restrict__
                                                       int nx, int ny, int nz, const int32_t *__restrict__ toff,
                                                       const int32_t *__restrict__ rootpos,
                                                       const int32_t *__restrict__ box, double *__restrict__ part,
-                                                      int32_t *__restrict__ extent_err) {
+                                                      int32_t *__restrict__ flags) {
   const int32_t g = blockIdx.x / kSumSplit;  // record (drop of every field)
   const int sl = blockIdx.x % kSumSplit;
   const int t = field_of(toff, g);
@@ -982,7 +991,7 @@ __global__ __launch_bounds__(kBlock) void k_drop_sums(const double *__restrict__
   const int32_t p0 = rootpos[g];
   const int32_t *b = box + 6 * (int64_t)g;
   if (p0 == INT32_MAX || b[0] > b[1]) {  // label without cells: inconsistent input
-    if (threadIdx.x == 0) atomicOr(extent_err, 2);
+    if (threadIdx.x == 0) flags[1] = 1;
     return;
   }
   const int x0 = p0 % nx, y0 = (p0 / nx) % ny, z0 = p0 / (nx * ny);
@@ -1038,7 +1047,7 @@ __global__ __launch_bounds__(kBlock) void k_drop_sums(const double *__restrict__
 // Volume and periodic centroid of every drop from its kSumSplit parts.
 __global__ void k_drop_finish(int32_t K, int nx, int ny, int nz, const int32_t *__restrict__ rootpos,
                               const int32_t *__restrict__ box, const double *__restrict__ part,
-                              double *__restrict__ vol, double *__restrict__ xyz, int32_t *__restrict__ extent_err) {
+                              double *__restrict__ vol, double *__restrict__ xyz, int32_t *__restrict__ flags) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= K) return;
   const int32_t p0 = rootpos[i];
@@ -1056,7 +1065,7 @@ __global__ void k_drop_finish(int32_t K, int nx, int ny, int nz, const int32_t *
     if (x >= (double)n[a]) x -= (double)n[a];
     if (x < 0.0) x += (double)n[a];
     xyz[3 * i + a] = x;
-    if (2 * (b[2 * a + 1] - b[2 * a]) >= n[a]) atomicOr(extent_err, 1);
+    if (2 * (b[2 * a + 1] - b[2 * a]) >= n[a]) flags[0] = 1;
   }
 }
 
@@ -1072,7 +1081,7 @@ __global__ __launch_bounds__(kBlock) void k_shape_sums(const double *__restrict_
                                                        const int32_t *__restrict__ toff,
                                                        const int32_t *__restrict__ rootpos,
                                                        const int32_t *__restrict__ box, double *__restrict__ part,
-                                                       int32_t *__restrict__ extent_err) {
+                                                       int32_t *__restrict__ flags) {
   const int32_t g = blockIdx.x / kSumSplit;  // record (drop of every field)
   const int sl = blockIdx.x % kSumSplit;
   const int t = field_of(toff, g);
@@ -1083,7 +1092,7 @@ __global__ __launch_bounds__(kBlock) void k_shape_sums(const double *__restrict_
   const int32_t p0 = rootpos[g];
   const int32_t *b = box + 6 * (int64_t)g;
   if (p0 == INT32_MAX || b[0] > b[1]) {  // label without cells: inconsistent input
-    if (threadIdx.x == 0) atomicOr(extent_err, 2);
+    if (threadIdx.x == 0) flags[1] = 1;
     return;
   }
   const int x0 = p0 % nx, y0 = (p0 / nx) % ny, z0 = p0 / (nx * ny);
@@ -1150,7 +1159,7 @@ __global__ __launch_bounds__(kBlock) void k_shape_sums(const double *__restrict_
 __global__ void k_shape_finish(int32_t K, int nx, int ny, int nz, const int32_t *__restrict__ rootpos,
                                const int32_t *__restrict__ box, const double *__restrict__ part,
                                double *__restrict__ inertia, double *__restrict__ chi, double *__restrict__ vel,
-                               double *__restrict__ vol, double *__restrict__ xyz, int32_t *__restrict__ extent_err) {
+                               double *__restrict__ vol, double *__restrict__ xyz, int32_t *__restrict__ flags) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= K) return;
   const int32_t p0 = rootpos[i];
@@ -1219,7 +1228,7 @@ __global__ void k_shape_finish(int32_t K, int nx, int ny, int nz, const int32_t 
     }
   }
   for (int e = 0; e < 3; ++e)
-    if (2 * (b[2 * e + 1] - b[2 * e]) >= n[e]) atomicOr(extent_err, 1);
+    if (2 * (b[2 * e + 1] - b[2 * e]) >= n[e]) flags[0] = 1;
 }
 
 }  // namespace
@@ -1361,14 +1370,50 @@ extern "C" int vofmt_label_drops(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t
   return VOFMT_OK;
 }
 
-// Offsets of every field's drop records (prefix sums of the drop counts)
-// into device memory, staged in pinned host memory `stage` (ntr + 1 ints,
-// not touched again before the call synchronises).
-static hipError_t upload_offsets(const int32_t *ndrops_host, int ntr, int32_t *stage, int32_t *dev,
-                                 hipStream_t stream) {
-  stage[0] = 0;
-  for (int t = 0; t < ntr; ++t) stage[t + 1] = stage[t] + ndrops_host[t];
-  return hipMemcpyAsync(dev, stage, sizeof(int32_t) * (size_t)(ntr + 1), hipMemcpyHostToDevice, stream);
+// Work arrays of the drop sums, and the scan that fills the drops' boxes.
+// The flags of the sums (0: a drop spans half the box, 1: a label without
+// cells) are in pinned memory: the kernels store to it, nothing is copied.
+struct DropScan {
+  int32_t *first, *box, *toff;
+  int32_t *flags;
+};
+static int scan_drops(vofmt_ctx *ctx, int nx, int ny, int nz, int ntracers, const int32_t *labels,
+                      const int32_t *ndrops_host, int64_t D, DropScan &ds, hipStream_t stream) {
+  // records of every field's drops, field after field (toff: their offsets)
+  ds.first = (int32_t *)scratch(ctx, SLOT_LABEL_C, sizeof(int32_t) * (size_t)(D + 1));
+  ds.box = (int32_t *)scratch(ctx, SLOT_MISC2, sizeof(int32_t) * (6 + kFrames) * (size_t)(D + 1));
+  ds.toff = (int32_t *)scratch(ctx, SLOT_MISC, sizeof(int32_t) * (size_t)(ntracers + 1));
+  ds.flags = (int32_t *)host_scratch(ctx, sizeof(int32_t) * (size_t)(2 + ntracers + 1));
+  if (!ds.first || !ds.box || !ds.toff || !ds.flags) return VOFMT_E_NOMEM;
+  int32_t *frames = ds.box + 6 * (D + 1);
+  ds.flags[0] = ds.flags[1] = 0;
+  FieldOffsets fo{};
+  const bool args = ntracers <= kArgFields;
+  int32_t *off = args ? fo.off : ds.flags + 2;
+  off[0] = 0;
+  for (int t = 0; t < ntracers; ++t) off[t + 1] = off[t] + ndrops_host[t];
+  if (!args)
+    VOFMT_HIP(ctx, hipMemcpyAsync(ds.toff, off, sizeof(int32_t) * (size_t)(ntracers + 1), hipMemcpyHostToDevice, stream));
+  const int noff = args ? ntracers + 1 : 0;
+  const FastDiv fnx = make_fastdiv((uint32_t)nx), fny = make_fastdiv((uint32_t)ny);
+  const int tx = (int)ceil_div(nx, 64 * kScanX), ty = (int)ceil_div(ny, kScanY);
+  const int64_t ntile = (int64_t)tx * ty * ceil_div(nz, kScanZ);
+  hipLaunchKernelGGL(k_scan_init, dim3(ceil_div(kFrames * D > noff ? kFrames * D : noff, 256)), dim3(256), 0, stream,
+                     ds.first, frames, D, fo, noff, ds.toff);
+  hipLaunchKernelGGL(k_drop_scan, dim3((unsigned)ntile, ntracers), dim3(kBlock), 0, stream, labels,
+                     (int64_t)nx * ny * nz, nx, ny, nz, tx, ty, fnx, fny, ds.toff, ds.first, frames);
+  hipLaunchKernelGGL(k_drop_box, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, ds.first, frames,
+                     ds.box);
+  return VOFMT_OK;
+}
+
+// The end of a call: the sums have run, their flags tell.
+static int check_drops(vofmt_ctx *ctx, const char *fn, const DropScan &ds, hipStream_t stream) {
+  VOFMT_HIP(ctx, hipGetLastError());
+  VOFMT_HIP(ctx, hipStreamSynchronize(stream));
+  if (ds.flags[1]) return set_err(ctx, VOFMT_E_ARG, "%s: labels do not match ndrops_host", fn);
+  if (ds.flags[0]) return set_err(ctx, VOFMT_E_EXTENT, "%s: a drop spans half the box or more", fn);
+  return VOFMT_OK;
 }
 
 extern "C" int vofmt_drop_moments(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, int32_t ntracers,
@@ -1388,35 +1433,16 @@ extern "C" int vofmt_drop_moments(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_
   const int64_t n3 = (int64_t)nx * ny * nz;
   if (n3 >= INT32_MAX) return set_err(ctx, VOFMT_E_ARG, "vofmt_drop_moments: more than 2^31-1 cells per field");
   VOFMT_HIP(ctx, hipSetDevice(ctx->device));
-  // records of every field's drops, field after field (toff: their offsets)
-  int32_t *rootpos = (int32_t *)scratch(ctx, SLOT_LABEL_C, sizeof(int32_t) * (size_t)(D + 1));
-  int32_t *box = (int32_t *)scratch(ctx, SLOT_MISC2, sizeof(int32_t) * (6 + kFrames) * (size_t)(D + 1));
-  int32_t *frames = box ? box + 6 * (D + 1) : nullptr;
-  int32_t *flags = (int32_t *)scratch(ctx, SLOT_MISC, sizeof(int32_t) * (size_t)(2 + ntracers + 1));
-  int32_t *toff = flags ? flags + 2 : nullptr;
   double *part = (double *)scratch(ctx, SLOT_LABEL_A, sizeof(double) * 4 * kSumSplit * (size_t)(D + 1));
-  int32_t *fh = (int32_t *)host_scratch(ctx, sizeof(int32_t) * (size_t)(2 + ntracers + 1));
-  if (!rootpos || !box || !flags || !part || !fh) return VOFMT_E_NOMEM;
-  VOFMT_HIP(ctx, upload_offsets(ndrops_host, ntracers, fh + 2, toff, stream));
-  VOFMT_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(int32_t) * 2, stream));
-  const FastDiv fnx = make_fastdiv((uint32_t)nx), fny = make_fastdiv((uint32_t)ny);
-  const int tx = (int)ceil_div(nx, 64 * kScanX), ty = (int)ceil_div(ny, kScanY);
-  const int64_t ntile = (int64_t)tx * ty * ceil_div(nz, kScanZ);
-  hipLaunchKernelGGL(k_scan_init, dim3(ceil_div(kFrames * D, 256)), dim3(256), 0, stream, rootpos, frames, D);
-  hipLaunchKernelGGL(k_drop_scan, dim3((unsigned)ntile, ntracers), dim3(kBlock), 0, stream, labels, n3, nx, ny, nz, tx, ty,
-                     fnx, fny, toff, rootpos, frames);
-  hipLaunchKernelGGL(k_drop_box, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, rootpos, frames,
-                     box);
-  hipLaunchKernelGGL(k_drop_sums, dim3((unsigned)(D * kSumSplit)), dim3(kBlock), 0, stream, c, labels, nx, ny, nz, toff,
-                     rootpos, box, part, flags);
-  hipLaunchKernelGGL(k_drop_finish, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, rootpos, box,
-                     part, vol, xyz, flags);
-  VOFMT_HIP(ctx, hipGetLastError());
-  VOFMT_HIP(ctx, hipMemcpyAsync(fh, flags, sizeof(int32_t) * 2, hipMemcpyDeviceToHost, stream));
-  VOFMT_HIP(ctx, hipStreamSynchronize(stream));
-  if (fh[0] & 2) return set_err(ctx, VOFMT_E_ARG, "vofmt_drop_moments: labels do not match ndrops_host");
-  if (fh[0]) return set_err(ctx, VOFMT_E_EXTENT, "vofmt_drop_moments: a drop spans half the box or more");
-  return VOFMT_OK;
+  if (!part) return VOFMT_E_NOMEM;
+  DropScan ds;
+  const int rc = scan_drops(ctx, nx, ny, nz, ntracers, labels, ndrops_host, D, ds, stream);
+  if (rc) return rc;
+  hipLaunchKernelGGL(k_drop_sums, dim3((unsigned)(D * kSumSplit)), dim3(kBlock), 0, stream, c, labels, nx, ny, nz,
+                     ds.toff, ds.first, ds.box, part, ds.flags);
+  hipLaunchKernelGGL(k_drop_finish, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, ds.first,
+                     ds.box, part, vol, xyz, ds.flags);
+  return check_drops(ctx, "vofmt_drop_moments", ds, stream);
 }
 
 // Shapes (and, with vol and xyz, the moments) of the drops: one scan of the
@@ -1443,35 +1469,16 @@ static int drop_shapes_impl(vofmt_ctx *ctx, const char *fn, bool moments, int32_
   const int64_t n3 = (int64_t)nx * ny * nz;
   if (n3 >= INT32_MAX) return set_err(ctx, VOFMT_E_ARG, "%s: more than 2^31-1 cells per field", fn);
   VOFMT_HIP(ctx, hipSetDevice(ctx->device));
-  // records of every field's drops, field after field (toff: their offsets)
-  int32_t *rootpos = (int32_t *)scratch(ctx, SLOT_LABEL_C, sizeof(int32_t) * (size_t)(D + 1));
-  int32_t *box = (int32_t *)scratch(ctx, SLOT_MISC2, sizeof(int32_t) * (6 + kFrames) * (size_t)(D + 1));
-  int32_t *frames = box ? box + 6 * (D + 1) : nullptr;
-  int32_t *flags = (int32_t *)scratch(ctx, SLOT_MISC, sizeof(int32_t) * (size_t)(2 + ntracers + 1));
-  int32_t *toff = flags ? flags + 2 : nullptr;
   double *part = (double *)scratch(ctx, SLOT_LABEL_A, sizeof(double) * kShapeSums * kSumSplit * (size_t)(D + 1));
-  int32_t *fh = (int32_t *)host_scratch(ctx, sizeof(int32_t) * (size_t)(2 + ntracers + 1));
-  if (!rootpos || !box || !flags || !part || !fh) return VOFMT_E_NOMEM;
-  VOFMT_HIP(ctx, upload_offsets(ndrops_host, ntracers, fh + 2, toff, stream));
-  VOFMT_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(int32_t) * 2, stream));
-  const FastDiv fnx = make_fastdiv((uint32_t)nx), fny = make_fastdiv((uint32_t)ny);
-  const int tx = (int)ceil_div(nx, 64 * kScanX), ty = (int)ceil_div(ny, kScanY);
-  const int64_t ntile = (int64_t)tx * ty * ceil_div(nz, kScanZ);
-  hipLaunchKernelGGL(k_scan_init, dim3(ceil_div(kFrames * D, 256)), dim3(256), 0, stream, rootpos, frames, D);
-  hipLaunchKernelGGL(k_drop_scan, dim3((unsigned)ntile, ntracers), dim3(kBlock), 0, stream, labels, n3, nx, ny, nz, tx, ty,
-                     fnx, fny, toff, rootpos, frames);
-  hipLaunchKernelGGL(k_drop_box, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, rootpos, frames,
-                     box);
+  if (!part) return VOFMT_E_NOMEM;
+  DropScan ds;
+  const int rc = scan_drops(ctx, nx, ny, nz, ntracers, labels, ndrops_host, D, ds, stream);
+  if (rc) return rc;
   hipLaunchKernelGGL(k_shape_sums, dim3((unsigned)(D * kSumSplit)), dim3(kBlock), 0, stream, c, labels, sx, sy, sz, nx,
-                     ny, nz, toff, rootpos, box, part, flags);
-  hipLaunchKernelGGL(k_shape_finish, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, rootpos,
-                     box, part, inertia, chi, withu ? vel : nullptr, vol, xyz, flags);
-  VOFMT_HIP(ctx, hipGetLastError());
-  VOFMT_HIP(ctx, hipMemcpyAsync(fh, flags, sizeof(int32_t) * 2, hipMemcpyDeviceToHost, stream));
-  VOFMT_HIP(ctx, hipStreamSynchronize(stream));
-  if (fh[0] & 2) return set_err(ctx, VOFMT_E_ARG, "%s: labels do not match ndrops_host", fn);
-  if (fh[0]) return set_err(ctx, VOFMT_E_EXTENT, "%s: a drop spans half the box or more", fn);
-  return VOFMT_OK;
+                     ny, nz, ds.toff, ds.first, ds.box, part, ds.flags);
+  hipLaunchKernelGGL(k_shape_finish, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, ds.first,
+                     ds.box, part, inertia, chi, withu ? vel : nullptr, vol, xyz, ds.flags);
+  return check_drops(ctx, fn, ds, stream);
 }
 
 extern "C" int vofmt_drop_shapes(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, int32_t ntracers,

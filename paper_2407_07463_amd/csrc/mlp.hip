@@ -964,12 +964,11 @@ extern "C" int vofmt_mlp_train_step(vofmt_ctx *ctx, float *params, float *adam_m
   const int per_group = (ntiles + groups - 1) / groups;
   groups = (ntiles + per_group - 1) / per_group;
   uint8_t *acts = (uint8_t *)scratch(ctx, SLOT_MLP_ACTS, (size_t)ACT_BYTES * (size_t)m);
-  float *gbuf = (float *)scratch(ctx, SLOT_MLP_G, sizeof(float) * ((size_t)m + (size_t)ntiles + 4));
+  float *gbuf = (float *)scratch(ctx, SLOT_MLP_G, sizeof(float) * ((size_t)m + (size_t)ntiles));
   float *partial = (float *)scratch(ctx, SLOT_MLP_PART, sizeof(float) * (size_t)groups * NPARAMS);
   float *hl = (float *)host_scratch(ctx, sizeof(float) * 4);
   if (!acts || !gbuf || !partial || !hl) return VOFMT_E_NOMEM;
   float *loss_part = gbuf + m;
-  float *loss_out = gbuf + m + ntiles;
   int rec = prof_begin(ctx, "k_mlp_fwd(train)", stream);
   if (ntiles <= kSmallTiles)
     hipLaunchKernelGGL(k_mlp_fwd_small, dim3(ntiles), dim3(64 * WMT), 0, stream, params, (const uint4 *)w[0],
@@ -984,10 +983,9 @@ extern "C" int vofmt_mlp_train_step(vofmt_ctx *ctx, float *params, float *adam_m
   prof_end(ctx, rec, stream);
   rec = prof_begin(ctx, "k_mlp_adam", stream);
   hipLaunchKernelGGL(k_mlp_adam, dim3(ceil_div(NPARAMS, 256)), dim3(256), 0, stream, params, adam_m, adam_v, partial,
-                     groups, ntiles, step, lr, grads, loss_part, loss_out, m);
+                     groups, ntiles, step, lr, grads, loss_part, hl, m);  // (the loss goes to pinned memory)
   prof_end(ctx, rec, stream);
   VOFMT_HIP(ctx, hipGetLastError());
-  VOFMT_HIP(ctx, hipMemcpyAsync(hl, loss_out, sizeof(float), hipMemcpyDeviceToHost, stream));
   VOFMT_HIP(ctx, hipStreamSynchronize(stream));
   *loss_host = hl[0];
   return VOFMT_OK;
@@ -1015,9 +1013,8 @@ extern "C" int vofmt_mlp_stencils(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_
   int32_t *hc = (int32_t *)host_scratch(ctx, sizeof(int32_t) * 2);
   uint64_t *bits = (uint64_t *)scratch(ctx, SLOT_LIST_BITS, sizeof(uint64_t) * (size_t)ceil_div(n3, 64));
   if (!bc || !tot || !list || !hc || !bits) return VOFMT_E_NOMEM;
-  compact::launch_ordered_list(c, n3, bc, tot, list, (double *)nullptr, (uint8_t *)nullptr, bits, stream);
+  compact::launch_ordered_list(c, n3, bc, tot, list, (double *)nullptr, (uint8_t *)nullptr, bits, hc, stream);
   VOFMT_HIP(ctx, hipGetLastError());
-  VOFMT_HIP(ctx, hipMemcpyAsync(hc, tot + ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
   VOFMT_HIP(ctx, hipStreamSynchronize(stream));
   const int total = hc[0];
   *count_host = total;
@@ -1050,10 +1047,9 @@ extern "C" int vofmt_curvature_mlp(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32
   if (!list || !bc || !tot || !hc || !bits) return VOFMT_E_NOMEM;
   int32_t *hf_counts = tot + lt + 1;  // fallback cells per workgroup of the fused kernel
   int rec = prof_begin(ctx, "mixed_list", stream);
-  compact::launch_ordered_list(c, n3, bc, tot, list, kappa, status, bits, stream);
+  compact::launch_ordered_list(c, n3, bc, tot, list, kappa, status, bits, hc, stream);
   prof_end(ctx, rec, stream);
   VOFMT_HIP(ctx, hipGetLastError());
-  VOFMT_HIP(ctx, hipMemcpyAsync(hc, tot + lt, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
   VOFMT_HIP(ctx, hipStreamSynchronize(stream));
   const int nm = hc[0];
   if (nmixed_host) *nmixed_host = nm;

@@ -815,7 +815,9 @@ __global__ __launch_bounds__(1024) void k_scan_deg(const int32_t *__restrict__ d
 // The neighbours of every drop in ascending order, one wavefront per drop: 64
 // words a round, each lane's offset from the words before it.
 __global__ __launch_bounds__(kBlock) void k_csr_fill(const uint32_t *__restrict__ adj, int32_t D, int64_t words,
-                                                     const int32_t *__restrict__ rowptr, int32_t *__restrict__ nbr) {
+                                                     const int32_t *__restrict__ rowptr, int32_t cap,
+                                                     int32_t *__restrict__ nbr) {
+  if (rowptr[D] > cap) return;  // (k_greedy_rounds tells)
   const int32_t g = (int32_t)(((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63;
   if (g >= D) return;  // whole wavefront
@@ -920,11 +922,20 @@ __global__ __launch_bounds__(64) void k_greedy(const int32_t *__restrict__ rowpt
 // earlier neighbours are, and the result is the sequential pass's: each round
 // decides every such drop (the smallest undecided drop always is one, so the
 // rounds end), then applies the decisions. If some drop needs a new tracer,
-// res[3] = 1 and the caller runs the sequential pass instead.
+// res[3] = 1 and the caller runs the sequential pass instead; if the neighbour
+// list was too short, res[3] = 2 and res[4] its length.
 __global__ __launch_bounds__(1024) void k_greedy_rounds(const int32_t *__restrict__ rowptr,
                                                         const int32_t *__restrict__ nbr,
                                                         const int32_t *__restrict__ T0, int32_t D, int ntr,
-                                                        int32_t *__restrict__ new_tracer, int32_t *__restrict__ res) {
+                                                        int32_t cap, int32_t *__restrict__ new_tracer,
+                                                        int32_t *__restrict__ res) {
+  if (rowptr[D] > cap) {  // (uniform) more neighbours than the list holds: nothing decided
+    if (threadIdx.x == 0) {
+      res[3] = 2;
+      res[4] = rowptr[D];
+    }
+    return;
+  }
   __shared__ int8_t T[kMaxDrops];
   __shared__ int8_t dec[kMaxDrops];  // this round's decisions, -1 for none
   __shared__ uint32_t done[kMaxDrops / 32];
@@ -1150,7 +1161,7 @@ static int recolor_impl(vofmt_ctx *ctx, const char *fn, int stencil, int32_t nx,
   int32_t *small = (int32_t *)scratch(ctx, SLOT_LABEL_C, sizeof(int32_t) * (size_t)(4 * D + 16));
   int32_t *hres = (int32_t *)host_scratch(ctx, 256 + sizeof(int4) * (size_t)noffs);
   if (!own || !adj || !small || !hres) return VOFMT_E_NOMEM;
-  int32_t *deg = small, *rowptr = small + D, *T0 = small + 2 * D + 1, *res = small + 3 * D + 2;
+  int32_t *deg = small, *rowptr = small + D, *T0 = small + 2 * D + 1;
   int32_t *nbr = nullptr;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus < 1)
@@ -1246,25 +1257,26 @@ static int recolor_impl(vofmt_ctx *ctx, const char *fn, int stencil, int32_t nx,
   }
   hipLaunchKernelGGL(k_degree, dim3(ceil_div(D, kBlock / 64)), dim3(kBlock), 0, stream, adj, (int32_t)D, words, deg);
   hipLaunchKernelGGL(k_scan_deg, dim3(1), dim3(1024), 0, stream, deg, (int32_t)D, rowptr);
-  VOFMT_HIP(ctx, hipGetLastError());
-  // the number of directed edges sizes the neighbour array
-  VOFMT_HIP(ctx, hipMemcpyAsync(hres + 8, rowptr + D, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-  VOFMT_HIP(ctx, hipStreamSynchronize(stream));
-  const int64_t E = hres[8];
-  nbr = (int32_t *)scratch(ctx, SLOT_MISC3, sizeof(int32_t) * (size_t)(E > 0 ? E : 1));
-  if (!nbr) return VOFMT_E_NOMEM;
-  hipLaunchKernelGGL(k_csr_fill, dim3(ceil_div(D, kBlock / 64)), dim3(kBlock), 0, stream, adj, (int32_t)D, words, rowptr,
-                     nbr);
-  hipLaunchKernelGGL(k_greedy_rounds, dim3(1), dim3(1024), 0, stream, rowptr, nbr, T0, (int32_t)D, ntr, new_tracer,
-                     res);
-  VOFMT_HIP(ctx, hipGetLastError());
-  VOFMT_HIP(ctx, hipMemcpyAsync(hres, res, sizeof(int32_t) * 4, hipMemcpyDeviceToHost, stream));
-  VOFMT_HIP(ctx, hipStreamSynchronize(stream));
+  // The neighbour list has room for 32 per drop, or what an earlier call needed;
+  // the kernels check, and a longer list is filled again. Results go to pinned
+  // memory.
+  int32_t cap = (int32_t)std::min<int64_t>(INT32_MAX, std::max<int64_t>(32 * D, (int64_t)(ctx->cap[SLOT_MISC3] / sizeof(int32_t))));
+  while (true) {
+    nbr = (int32_t *)scratch(ctx, SLOT_MISC3, sizeof(int32_t) * (size_t)cap);
+    if (!nbr) return VOFMT_E_NOMEM;
+    hipLaunchKernelGGL(k_csr_fill, dim3(ceil_div(D, kBlock / 64)), dim3(kBlock), 0, stream, adj, (int32_t)D, words,
+                       rowptr, cap, nbr);
+    hipLaunchKernelGGL(k_greedy_rounds, dim3(1), dim3(1024), 0, stream, rowptr, nbr, T0, (int32_t)D, ntr, cap,
+                       new_tracer, hres);
+    VOFMT_HIP(ctx, hipGetLastError());
+    VOFMT_HIP(ctx, hipStreamSynchronize(stream));
+    if (hres[3] != 2) break;
+    cap = hres[4];
+  }
   if (hres[3]) {  // a drop needs a new tracer: the sequential pass
     hipLaunchKernelGGL(k_greedy, dim3(1), dim3(64), 0, stream, rowptr, nbr, T0, (int32_t)D, ntr, max_tracers,
-                       new_tracer, res);
+                       new_tracer, hres);
     VOFMT_HIP(ctx, hipGetLastError());
-    VOFMT_HIP(ctx, hipMemcpyAsync(hres, res, sizeof(int32_t) * 3, hipMemcpyDeviceToHost, stream));
     VOFMT_HIP(ctx, hipStreamSynchronize(stream));
   }
   const int Nnew = hres[0], moved = hres[1], overflow = hres[2];

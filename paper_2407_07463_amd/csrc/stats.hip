@@ -251,9 +251,20 @@ __global__ __launch_bounds__(kBlock) void k_pair_pdfs(int32_t nr, int32_t nth, c
   Pr[k] = (double)row / (E * (4.0 * pi * (rc * rc) * dr));
 }
 
-__global__ void k_zero_u64(uint64_t *p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+// Bin edges as a kernel argument: no staging buffer and no copy.
+constexpr int32_t kMaxEdgeArgs = 384;
+struct EdgeTable {
+  double e[kMaxEdgeArgs];
+};
+static_assert(sizeof(EdgeTable) <= 3072, "kernel argument size");
+
+// The first launch of a call: the histogram cleared (n entries) and the edges
+// (ne of them, 0 where they were copied) stored.
+__global__ __launch_bounds__(kBlock) void k_begin(EdgeTable t, int32_t ne, double *__restrict__ edges,
+                                                  uint64_t *__restrict__ hist, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) hist[i] = 0;
+  if (i < ne) edges[i] = t.e[i];
 }
 
 }  // namespace
@@ -291,10 +302,31 @@ static SliceShape slice_shape(int32_t n) {
   return sh;
 }
 
-// The kernels of one call, on device buffers: dedge (edges, already on the
-// device), best [n], part [12 n], sl (ns * n * 16 bytes).
-static void launch_stats(int32_t n, const double *xyz, const double *box, int32_t vertical_axis, int32_t nr,
-                         int32_t ntheta, const double *dedge, double *best, double *part, char *sl,
+// Edges first [0 .. n0] and second [0 .. n1] on the device: as a kernel argument
+// where they fit (ne > 0; k_begin stores them), else copied through the pinned
+// staging buffer `stage` (which must stay as it is until the stream has run).
+struct Edges {
+  EdgeTable t;
+  int32_t ne;
+};
+static hipError_t put_edges(Edges &ed, const double *first, int32_t n0, const double *second, int32_t n1,
+                            double *stage, double *dedge, hipStream_t stream) {
+  const int64_t all = (int64_t)n0 + n1 + 2;
+  ed.ne = all <= kMaxEdgeArgs ? (int32_t)all : 0;
+  double *to = ed.ne > 0 ? ed.t.e : stage;
+  for (int e = 0; e <= n0; ++e) to[e] = first[e];
+  for (int e = 0; e <= n1; ++e) to[n0 + 1 + e] = second[e];
+  if (ed.ne > 0) {
+    for (int e = ed.ne; e < kMaxEdgeArgs; ++e) ed.t.e[e] = 0.0;
+    return hipSuccess;
+  }
+  return hipMemcpyAsync(dedge, stage, sizeof(double) * (size_t)all, hipMemcpyHostToDevice, stream);
+}
+
+// The kernels of one call, on device buffers: dedge (where the edges are or go),
+// best [n], part [12 n], sl (ns * n * 16 bytes).
+static void launch_stats(const Edges &ed, int32_t n, const double *xyz, const double *box, int32_t vertical_axis, int32_t nr,
+                         int32_t ntheta, double *dedge, double *best, double *part, char *sl,
                          int32_t *nn_index, int32_t *nn_ties, uint64_t *hist_fixed, double *M, double *R, double *A,
                          hipStream_t stream) {
   const SliceShape sh = slice_shape(n);
@@ -304,7 +336,8 @@ static void launch_stats(int32_t n, const double *xyz, const double *box, int32_
   Box b;
   for (int a = 0; a < 3; ++a) b.L[a] = box[a];
   const int64_t nh = (int64_t)nr * ntheta + 1;
-  hipLaunchKernelGGL(k_zero_u64, dim3(ceil_div(nh, 256)), dim3(256), 0, stream, hist_fixed, nh);
+  hipLaunchKernelGGL(k_begin, dim3(ceil_div(nh > ed.ne ? nh : ed.ne, kBlock)), dim3(kBlock), 0, stream, ed.t, ed.ne,
+                     dedge, hist_fixed, nh);
   hipLaunchKernelGGL(k_nearest_slice, dim3(sh.nblk, sh.ns), dim3(kBlock), 0, stream, xyz, n, b, sh.len, sbest, sbj,
                      sties);
   hipLaunchKernelGGL(k_nearest_combine, dim3(sh.nblk), dim3(kBlock), 0, stream, n, sh.ns, sbest, sbj, sties,
@@ -332,13 +365,11 @@ extern "C" int vofmt_nearest_pair_stats(vofmt_ctx *ctx, int32_t n, const double 
   char *sl = (char *)scratch(ctx, SLOT_LABEL_A, (sizeof(double) + 2 * sizeof(int32_t)) * (size_t)sh.ns * n);
   double *hstage = (double *)host_scratch(ctx, sizeof(double) * nedge);
   if (!dedge || !best || !part || !sl || !hstage) return VOFMT_E_NOMEM;
-  for (int e = 0; e <= nr; ++e) hstage[e] = r2_edges[e];
-  for (int e = 0; e <= ntheta; ++e) hstage[nr + 1 + e] = cos_edges[e];
-  VOFMT_HIP(ctx, hipMemcpyAsync(dedge, hstage, sizeof(double) * nedge, hipMemcpyHostToDevice, stream));
-  launch_stats(n, xyz, box, vertical_axis, nr, ntheta, dedge, best, part, sl, nn_index, nn_ties, hist_fixed, M, R, A,
-               stream);
+  Edges ed;
+  VOFMT_HIP(ctx, put_edges(ed, r2_edges, nr, cos_edges, ntheta, hstage, dedge, stream));
+  launch_stats(ed, n, xyz, box, vertical_axis, nr, ntheta, dedge, best, part, sl, nn_index, nn_ties, hist_fixed, M, R,
+               A, stream);
   VOFMT_HIP(ctx, hipGetLastError());
-  // the staging buffer must stay valid until the copy has run
   VOFMT_HIP(ctx, hipStreamSynchronize(stream));
   return VOFMT_OK;
 }
@@ -352,7 +383,7 @@ extern "C" int vofmt_nearest_pair_stats(vofmt_ctx *ctx, int32_t n, const double 
 // nr + ntheta + 2 <= kNoAllocMaxEdges. Every call on a device shares the
 // device's copy of the array: calls that overlap on one device race.
 constexpr int32_t kNoAllocMaxDrops = 8192;
-constexpr int32_t kNoAllocMaxEdges = 384;
+constexpr int32_t kNoAllocMaxEdges = kMaxEdgeArgs;
 constexpr size_t kNoAllocOffBest = 256 * ((sizeof(double) * kNoAllocMaxEdges + 255) / 256);
 constexpr size_t kNoAllocOffPart = kNoAllocOffBest + sizeof(double) * kNoAllocMaxDrops;
 constexpr size_t kNoAllocOffSlices = kNoAllocOffPart + 12 * sizeof(double) * kNoAllocMaxDrops;
@@ -382,15 +413,6 @@ hipError_t noalloc_setup(int device) {
   return hipSuccess;
 }
 
-struct EdgeTable {
-  double e[kNoAllocMaxEdges];
-};
-static_assert(sizeof(EdgeTable) <= 3072, "kernel argument size");
-
-__global__ void k_store_edges(EdgeTable t, int32_t n, double *__restrict__ out) {
-  for (int32_t i = threadIdx.x; i < n; i += blockDim.x) out[i] = t.e[i];
-}
-
 extern "C" int vofmt_nearest_pair_stats_noalloc(vofmt_ctx *ctx, int32_t n, const double *xyz, const double *box,
                                                 int32_t vertical_axis, int32_t nr, int32_t ntheta,
                                                 const double *r2_edges, const double *cos_edges, int32_t *nn_index,
@@ -418,14 +440,10 @@ extern "C" int vofmt_nearest_pair_stats_noalloc(vofmt_ctx *ctx, int32_t n, const
   double *best = (double *)(base + kNoAllocOffBest);
   double *part = (double *)(base + kNoAllocOffPart);
   char *sl = base + kNoAllocOffSlices;
-  EdgeTable t;
-  const int32_t ne = nr + 1 + ntheta + 1;
-  for (int e = 0; e <= nr; ++e) t.e[e] = r2_edges[e];
-  for (int e = 0; e <= ntheta; ++e) t.e[nr + 1 + e] = cos_edges[e];
-  for (int e = ne; e < kNoAllocMaxEdges; ++e) t.e[e] = 0.0;
-  hipLaunchKernelGGL(k_store_edges, dim3(1), dim3(256), 0, stream, t, ne, dedge);
-  launch_stats(n, xyz, box, vertical_axis, nr, ntheta, dedge, best, part, sl, nn_index, nn_ties, hist_fixed, M, R, A,
-               stream);
+  Edges ed;
+  VOFMT_HIP(ctx, put_edges(ed, r2_edges, nr, cos_edges, ntheta, nullptr, dedge, stream));
+  launch_stats(ed, n, xyz, box, vertical_axis, nr, ntheta, dedge, best, part, sl, nn_index, nn_ties, hist_fixed, M, R,
+               A, stream);
   VOFMT_HIP(ctx, hipGetLastError());
   return VOFMT_OK;
 }
@@ -451,13 +469,14 @@ extern "C" int vofmt_pair_pdfs(vofmt_ctx *ctx, int32_t nr, int32_t ntheta, const
   double *dedge = (double *)scratch(ctx, SLOT_MISC, sizeof(double) * nedge);
   double *hstage = (double *)host_scratch(ctx, sizeof(double) * nedge);
   if (!dedge || !hstage) return VOFMT_E_NOMEM;
-  for (int e = 0; e <= nr; ++e) hstage[e] = r_edges[e];
-  for (int e = 0; e <= ntheta; ++e) hstage[nr + 1 + e] = theta_edges[e];
-  VOFMT_HIP(ctx, hipMemcpyAsync(dedge, hstage, sizeof(double) * nedge, hipMemcpyHostToDevice, stream));
+  Edges ed;
+  VOFMT_HIP(ctx, put_edges(ed, r_edges, nr, theta_edges, ntheta, hstage, dedge, stream));
+  if (ed.ne > 0)
+    hipLaunchKernelGGL(k_begin, dim3(ceil_div(ed.ne, kBlock)), dim3(kBlock), 0, stream, ed.t, ed.ne, dedge,
+                       (uint64_t *)nullptr, (int64_t)0);
   hipLaunchKernelGGL(k_pair_pdfs, dim3(ceil_div((int64_t)nr * ntheta + nr, kBlock)), dim3(kBlock), 0, stream, nr, ntheta, dedge, hist_fixed,
                      events, P, Pr);
   VOFMT_HIP(ctx, hipGetLastError());
-  // the staging buffer must stay valid until the copy has run
   VOFMT_HIP(ctx, hipStreamSynchronize(stream));
   return VOFMT_OK;
 }
