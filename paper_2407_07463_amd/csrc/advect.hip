@@ -34,11 +34,25 @@ __global__ __launch_bounds__(D == 0 ? 64 * kXWaves : 256) void k_stream(
     const double *__restrict__ cin, double *__restrict__ cout, const double *__restrict__ s,
     const double *__restrict__ fmix, uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx, int ny, int nz,
     int words, int chunk, uint32_t *__restrict__ list_next, int *__restrict__ counts_next, int rsize, int ngrp,
-    int64_t gstride) {
+    int64_t gstride, FastDiv fnx) {
   const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
                                  gridDim.y, gridDim.z / ngrp, ngrp, D == 1);
   stream_group<D, GM, kXWaves>(cin, cout, s, fmix, ccbits, write_cc, ntr, nx, ny, nz, words, chunk, list_next,
-                           counts_next, g.grp * gstride, rsize, g, gridDim.x, gridDim.y);
+                           counts_next, g.grp * gstride, rsize, g, gridDim.x, gridDim.y, fnx);
+}
+
+// The y- and z-sweeps in the flat layout.
+template <int D, int GM>
+__global__ __launch_bounds__(256) void k_stream_flat(const double *__restrict__ cin, double *__restrict__ cout,
+                                                     const double *__restrict__ s, const double *__restrict__ fmix,
+                                                     uint64_t *__restrict__ ccbits, int ntr, int nx, int ny, int nz,
+                                                     int words, int chunk, uint32_t *__restrict__ list_next,
+                                                     int *__restrict__ counts_next, int rsize, int ngrp,
+                                                     int64_t gstride, FastDiv fnx) {
+  const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
+                                 gridDim.y, gridDim.z / ngrp, ngrp, D == 1);
+  stream_group<D, GM, kFlat>(cin, cout, s, fmix, ccbits, 0, ntr, nx, ny, nz, words, chunk, list_next, counts_next,
+                             g.grp * gstride, rsize, g, gridDim.x, gridDim.y, fnx);
 }
 
 // The x-sweep marching along whole rows (4 wavefronts per workgroup).
@@ -48,11 +62,11 @@ __global__ __launch_bounds__(256) void k_stream_rows(const double *__restrict__ 
                                                      uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx,
                                                      int ny, int nz, int words, int chunk,
                                                      uint32_t *__restrict__ list_next, int *__restrict__ counts_next,
-                                                     int rsize, int ngrp, int64_t gstride) {
+                                                     int rsize, int ngrp, int64_t gstride, FastDiv fnx) {
   const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
                                  gridDim.y, gridDim.z / ngrp, ngrp, false);
   stream_group<0, GM, 0>(cin, cout, s, fmix, ccbits, write_cc, ntr, nx, ny, nz, words, chunk, list_next, counts_next,
-                     g.grp * gstride, rsize, g, gridDim.x, gridDim.y);
+                     g.grp * gstride, rsize, g, gridDim.x, gridDim.y, fnx);
 }
 
 // Per-block maximum of |s| over the three arrays and a non-finite flag.
@@ -122,17 +136,24 @@ static int scan_span(int64_t total) {
 }
 
 template <int D, int GM>
-static void launch_stream(dim3 grid, hipStream_t stream, const double *cin, double *cout, const double *s,
-                          SweepBuffers &sb, int wcc, int nx, int ny, int nz, int ntr, int words, int chunk, int nxt,
-                          int64_t per) {
+static void launch_stream(dim3 grid, bool flat, const FastDiv &fnx, hipStream_t stream, const double *cin, double *cout,
+                          const double *s, SweepBuffers &sb, int wcc, int nx, int ny, int nz, int ntr, int words,
+                          int chunk, int nxt, int64_t per) {
   const int ngrp = num_groups(ntr);
+  if constexpr (D != 0) {
+    if (flat) {
+      hipLaunchKernelGGL((k_stream_flat<D, GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, ntr, nx, ny,
+                         nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
+      return;
+    }
+  }
   if (D == 0 && x_wpb(words, chunk) == 0)
     hipLaunchKernelGGL((k_stream_rows<GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, wcc, ntr, nx,
-                       ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per);
+                       ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
   else
     hipLaunchKernelGGL((k_stream<D, GM>), grid, dim3(D == 0 ? 64 * kXWaves : 256), 0, stream, cin, cout, s, sb.fmix,
                        sb.bits, wcc, ntr, nx, ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp,
-                       per);
+                       per, fnx);
 }
 
 template <int D>
@@ -152,16 +173,17 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
                      sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
   prof_end(ctx, rec, stream);
   const int wpb = (D == 0) ? x_wpb(words, chunk) : 4;
-  const int64_t per = stream_waves(D, nx, ny, nz, chunk, wpb);
-  const Tiles tg = stream_tiles(D, nx, ny, nz, chunk, wpb);
+  const bool flat = D != 0 && !wcc && flat_rows(nx, ny, nz);
+  const int64_t per = stream_waves(D, nx, ny, nz, chunk, wpb, flat);
+  const Tiles tg = stream_tiles(D, nx, ny, nz, chunk, wpb, flat);
   const dim3 grid(tg.gx, tg.gy, tg.gz * num_groups(ntr));
   static_assert(kMaxGroup == 4, "streaming passes are instantiated for groups of at most 4");
   rec = prof_begin(ctx, stream_names[D], stream);
   switch (largest_group(ntr)) {
-    case 4: launch_stream<D, 4>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    case 3: launch_stream<D, 3>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    case 2: launch_stream<D, 2>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    default: launch_stream<D, 1>(grid, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 4: launch_stream<D, 4>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 3: launch_stream<D, 3>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 2: launch_stream<D, 2>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    default: launch_stream<D, 1>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
   }
   prof_end(ctx, rec, stream);
   sb.nregions[nxt] = num_groups(ntr) * per;

@@ -55,6 +55,9 @@ constexpr int kMaxGroup = 4;  // tracers per streaming pass (register budget)
 //          gx = segments, gy = groups of 4 z-rows (no idle wavefronts on
 //          short rows); gz = chunks of y.
 //   d = 2: the same with y-rows and chunks of z.
+//   d = 1 and 2, flat: the lanes run over the cells of the plane across the
+//          axis (x, then z or y) without regard to rows: gx = 1, gy = groups of
+//          256 consecutive cells (64 per wavefront), gz = chunks.
 struct Tiles {
   int gx, gy, gz;
 };
@@ -64,8 +67,11 @@ __host__ __device__ inline int x_segments_per_row(int words, int wpb) { return w
 __host__ __device__ inline int x_row_positions(int words, int chunk) {
   return (chunk / 2) / words > 0 ? (chunk / 2) / words : 1;
 }
-__host__ __device__ inline Tiles stream_tiles(int d, int nx, int ny, int nz, int chunk, int wpb = 4) {
+__host__ __device__ inline Tiles stream_tiles(int d, int nx, int ny, int nz, int chunk, int wpb = 4,
+                                              bool flat = false) {
   const int words = (nx + 63) / 64;
+  if (flat && d != 0)
+    return Tiles{1, (int)(((int64_t)nx * (d == 1 ? nz : ny) + 255) / 256), ((d == 1 ? ny : nz) + chunk - 1) / chunk};
   if (d == 0 && wpb == 0) {
     const int P = x_row_positions(words, chunk);
     return Tiles{1, (ny + 3) / 4, (nz + P - 1) / P};
@@ -246,14 +252,19 @@ __host__ __device__ inline GroupTile group_tile(int64_t L, int gx, int gy, int g
 }
 
 // Tile (bx, by, bz) of a streaming pass laid out as a gx x gy x gz grid of
-// workgroups (stream_tiles): 4 wavefronts, or WPB for the x-sweep.
+// workgroups (stream_tiles): 4 wavefronts, or WPB for the x-sweep. WPB =
+// kFlat (d = 1 and 2): the flat layout, for sweeps that read the c_c words (a
+// ballot over the lanes is no word of a row).
+constexpr int kFlat = -1;
 template <int D, int G, int WPB = 4>
 __device__ __forceinline__ void stream_body(const double *__restrict__ cin, double *__restrict__ cout,
                                             const double *__restrict__ s, const double *__restrict__ fmix,
                                             uint64_t *__restrict__ ccbits, int write_cc, int t0, int nx, int ny,
                                             int nz, int words, int chunk, uint32_t *__restrict__ list_next,
                                             int *__restrict__ counts_next, int64_t region0, int rsize, int bx, int by,
-                                            int bz, int gx, int gy) {
+                                            int bz, int gx, int gy, const FastDiv &fnx) {
+  static_assert(D != 0 || WPB != kFlat, "the x-sweep has no flat layout");
+  constexpr bool FLAT = WPB == kFlat;
   const int lane = threadIdx.x & 63;
   // wavefront-uniform: kept in a scalar register, like everything derived from it
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -276,14 +287,18 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   const int nm = (D == 1) ? ny : nz;
   const int64_t wave = region0 + (((int64_t)bz * gy + by) * gx + bx) * W + wv;
   // whole wavefront (the LDS x-sweep keeps every wavefront for its barriers)
-  if ((D != 0 || ROWS) && (row >= nrow || (D != 0 && seg >= words))) {
+  // flat: the lane's cell of the plane, (fx, fr), a lane past the end shadowing the last one
+  const int64_t nq = FLAT ? (int64_t)nx * nrow : 0, q0 = FLAT ? ((int64_t)by * 4 + wv) * 64 : 0;
+  const uint32_t fq = FLAT ? (uint32_t)(q0 + lane < nq ? q0 + lane : nq - 1) : 0u;
+  const uint32_t fr = FLAT ? fast_div(fq, fnx) : 0u, fx = fq - fr * (uint32_t)nx;
+  if (FLAT ? q0 >= nq : ((D != 0 || ROWS) && (row >= nrow || (D != 0 && seg >= words)))) {
     if (lane == 0) counts_next[wave] = 0;
     return;
   }
   uint32_t *reg = list_next + wave * rsize;
   int nlist = 0;  // wavefront-uniform
   const uint64_t below = (1ull << lane) - 1;
-  bool live = tile_ok && x < nx;  // (an idle x-sweep wavefront has no live lane)
+  bool live = FLAT ? q0 + lane < nq : tile_ok && x < nx;  // (an idle x-sweep wavefront has no live lane)
   int xs = live ? x : nx - 1;  // dead lanes shadow a valid cell, never store
   const int64_t n3 = (int64_t)nx * ny * nz;
   const int64_t nbits = (int64_t)nz * ny * words;
@@ -295,11 +310,16 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   const double *f_g = fmix + (int64_t)t0 * n3;
   uint64_t *b_g = ccbits + (int64_t)t0 * nbits;
 
+  // (a tracer's cells and words stay below 2^32)
+  const uint32_t fcell = D == 1 ? fr * ((uint32_t)ny * nx) + fx : fq;
+  const uint32_t fword = fr * (D == 1 ? (uint32_t)ny * words : (uint32_t)words) + (fx >> 6);
   auto cell = [&](int xx, int mm) -> int64_t {
+    if (FLAT) return (int64_t)(fcell + (uint32_t)mm * (D == 1 ? (uint32_t)nx : (uint32_t)nx * ny));
     if (D == 1) return ((int64_t)row * ny + mm) * nx + xx;
     return ((int64_t)mm * ny + row) * nx + xx;
   };
   auto bitword = [&](int mm) -> int64_t {
+    if (FLAT) return (int64_t)(fword + (uint32_t)mm * (D == 1 ? (uint32_t)words : (uint32_t)ny * words));
     if (D == 1) return ((int64_t)row * ny + mm) * words + seg;
     return ((int64_t)mm * ny + row) * words + seg;
   };
@@ -316,20 +336,20 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   // sweep writes them), loaded ahead of their use so their latency overlaps
   // other work
   auto load_words = [&](int64_t wrow, uint64_t *ccw) {
-    const bool ok = tile_ok && seg < words;  // idle: no cells
+    const bool ok = FLAT || (tile_ok && seg < words);  // idle: no cells
 #pragma unroll
-    for (int t = 0; t < G; ++t) ccw[t] = (!write_cc && ok) ? b_g[t * nbits + wrow] : 0ull;
+    for (int t = 0; t < G; ++t) ccw[t] = ((FLAT || !write_cc) && ok) ? b_g[t * nbits + wrow] : 0ull;
   };
   // new value of cell pc, its c_c bit, and its entry in the next list
   auto finish = [&](int t, double cold, double f_lo, double f_hi, double s_lo, double s_hi, int64_t pc, int64_t wrow,
                     uint64_t ccw) {
     double ccv;
-    if (write_cc) {
+    if (!FLAT && write_cc) {
       const uint64_t word = __ballot(live && cold > 0.5);
       if (lane == 0 && tile_ok && seg < words) b_g[t * nbits + wrow] = word;
       ccv = (cold > 0.5) ? 1.0 : 0.0;
     } else {
-      ccv = ((ccw >> lane) & 1ull) ? 1.0 : 0.0;
+      ccv = ((ccw >> (FLAT ? (int)(fx & 63u) : lane)) & 1ull) ? 1.0 : 0.0;
     }
     const double cn = (cold - (f_hi - f_lo)) + ccv * (s_hi - s_lo);
     // streamed out (not read again by this pass): a non-temporal store
@@ -617,25 +637,37 @@ __device__ __forceinline__ void stream_group(const double *__restrict__ cin, dou
                                              uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx, int ny,
                                              int nz, int words, int chunk, uint32_t *__restrict__ list_next,
                                              int *__restrict__ counts_next, int64_t region0, int rsize,
-                                             const GroupTile &g, int gx, int gy) {
+                                             const GroupTile &g, int gx, int gy, const FastDiv &fnx) {
   const int small = num_groups(ntr) * GM - ntr;  // groups of GM - 1, the last ones
   const int large = num_groups(ntr) - small;
   if (GM == 1 || g.grp < large)
     stream_body<D, GM, WPB>(cin, cout, s, fmix, ccbits, write_cc, g.grp * GM, nx, ny, nz, words, chunk, list_next,
-                            counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy);
+                            counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy, fnx);
   else if constexpr (GM > 1)
     stream_body<D, GM - 1, WPB>(cin, cout, s, fmix, ccbits, write_cc, large * GM + (g.grp - large) * (GM - 1), nx, ny,
-                                nz, words, chunk, list_next, counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy);
+                                nz, words, chunk, list_next, counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy, fnx);
 }
 
 // ---------------------------------------------------------------- host side
 
 // Wavefronts of one streaming pass along axis d (each owns one list region).
-static inline int64_t stream_waves(int d, int nx, int ny, int nz, int chunk, int wpb = 4) {
-  const Tiles g = stream_tiles(d, nx, ny, nz, chunk, wpb);
+static inline int64_t stream_waves(int d, int nx, int ny, int nz, int chunk, int wpb = 4, bool flat = false) {
+  const Tiles g = stream_tiles(d, nx, ny, nz, chunk, wpb, flat);
   return ((d == 0 && wpb > 0) ? wpb : 4) * (int64_t)g.gx * g.gy * g.gz;
 }
 
+// Whether the y- and z-sweeps that read the c_c words (the second and third of
+// a step) take the flat layout. A row of 134 cells leaves 58 of its 192 lanes
+// idle in the layout by segments; by cells every wavefront but the last of a
+// plane is full (one step, by segments -> flat: 134x129x141 x 7 444 -> 419 us;
+// 65x300x300 x 8 1136 -> 1015; 250^3 x 8, 2% idle, 2138 -> 2112; 32 boxes of 64
+// to 192 cells, three steps, 25.4 -> 24.3 ms). Rows of whole segments fill them
+// either way and keep scalar bit words and addresses; a plane of more than
+// 65535 workgroups is no grid of the plain path.
+static inline bool flat_rows(int nx, int ny, int nz) {
+  const int64_t widest = (int64_t)nx * (ny > nz ? ny : nz);
+  return nx % 64 != 0 && widest <= 65535ll * 256;
+}
 // List entries per region: every cell a wavefront of a streaming pass writes.
 static inline int region_size(int chunk) { return 64 * chunk * kMaxGroup; }
 // Regions of one list: the largest streaming sweep, or the initial scan.
@@ -644,6 +676,8 @@ static inline int64_t max_regions(int nx, int ny, int nz, int ntr, int chunk, in
   for (int d = 0; d < 3; ++d) {
     const int64_t w = stream_waves(d, nx, ny, nz, chunk, wpb) * num_groups(ntr);
     r = w > r ? w : r;
+    const int64_t wf = stream_waves(d, nx, ny, nz, chunk, wpb, flat_rows(nx, ny, nz)) * num_groups(ntr);
+    r = wf > r ? wf : r;
   }
   const int64_t total = (int64_t)ntr * nx * ny * nz;
   const int64_t scan = (total + region_size(chunk) - 1) / region_size(chunk);

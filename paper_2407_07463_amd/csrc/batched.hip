@@ -20,6 +20,7 @@ namespace {
 
 struct BoxDev {
   int nx, ny, nz, ntr, words;
+  int flat;  // y- and z-sweeps that read the c_c words: the flat layout (flat_rows)
   int xwpb;  // x-sweep: 0 whole-row wavefronts (a row's cells fit one list region), else 4 per workgroup
   Divisors dv;
   double *f[3];  // the caller's field, its ping-pong copy and the third one of an odd number of sweeps
@@ -75,8 +76,10 @@ __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes
   }
 }
 
-// work items: 4-wavefront tiles of a streaming pass
-template <int D>
+// work items: 4-wavefront tiles of a streaming pass. FLAT: a y- or z-sweep that
+// reads the c_c words, with the tables made for it; each box has the layout
+// that flat_rows gives it.
+template <int D, bool FLAT>
 __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
                                                   int nseg, int64_t nitems, int chunk, int rsize, int src, int dst,
                                                   int nxt, int write_cc) {
@@ -89,12 +92,19 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
     const int gm = largest_group(b.ntr);  // uniform over the workgroup
     auto pass = [&](auto GM) {
       constexpr int G = decltype(GM)::value;
+      if constexpr (FLAT) {
+        if (b.flat) {
+          stream_group<D, G, kFlat>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, 0, b.ntr, b.nx, b.ny, b.nz, b.words,
+                                    chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
+          return;
+        }
+      }
       if (D == 0 && b.xwpb == 0)
         stream_group<D, G, 0>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz,
-                              b.words, chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy);
+                              b.words, chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
       else
         stream_group<D, G>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz, b.words,
-                           chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy);
+                           chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
     };
     if (gm == 4) pass(std::integral_constant<int, 4>{});
     else if (gm == 3) pass(std::integral_constant<int, 3>{});
@@ -121,17 +131,19 @@ inline size_t field_bytes(const vofmt_box &b) {
 struct Plan {
   int nboxes;
   int chunk, rsize, grid;
+  bool any_flat;  // some box has the flat layout
   // table offsets in the slab (bytes) and segment counts
   size_t off_boxes;
   size_t off_scan;
   int n_scan;
   int64_t items_scan;
-  size_t off_plic[3];  // list regions after a sweep along d
-  int n_plic[3];
-  int64_t items_plic[3];
-  size_t off_stream[3];  // streaming passes along d
-  int n_stream[3];
-  int64_t items_stream[3];
+  // entry d + 3 * reads: a sweep along d that writes (0) or reads (1) the c_c words
+  size_t off_plic[6];  // list regions after the sweep
+  int n_plic[6];
+  int64_t items_plic[6];
+  size_t off_stream[6];  // its streaming pass
+  int n_stream[6];
+  int64_t items_stream[6];
 };
 
 // x-sweep layout of a box: whole-row wavefronts when a row has at most `chunk`
@@ -172,6 +184,7 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
                           std::vector<Seg> &seg_all, std::vector<size_t> &box_off) {
   const int rsize = region_size(chunk);
   pl.nboxes = nboxes;
+  pl.any_flat = false;
   pl.chunk = chunk;
   pl.rsize = rsize;
   size_t off = 0;
@@ -201,6 +214,8 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
     d.nz = b.nz;
     d.ntr = b.ntracers;
     d.words = words;
+    d.flat = flat_rows(b.nx, b.ny, b.nz);
+    pl.any_flat = pl.any_flat || d.flat;
     d.xwpb = xw;
     d.dv.n3 = make_fastdiv((uint32_t)n3);
     d.dv.nx = make_fastdiv((uint32_t)b.nx);
@@ -228,38 +243,40 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
     pl.items_scan += s.nitems;
     ++pl.n_scan;
   }
-  for (int d = 0; d < 3; ++d) {
-    begin_table(pl.off_plic[d], pl.n_plic[d], pl.items_plic[d]);
+  for (int e = 0; e < 6; ++e) {
+    begin_table(pl.off_plic[e], pl.n_plic[e], pl.items_plic[e]);
     for (int i = 0; i < nboxes; ++i) {
       const vofmt_box &b = boxes[i];
       Seg s{};
-      s.item0 = pl.items_plic[d];
+      s.item0 = pl.items_plic[e];
       const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-      s.nitems = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw) * num_groups(b.ntracers);
+      s.nitems = stream_waves(e % 3, b.nx, b.ny, b.nz, chunk, xw, e >= 3 && bd[i].flat) * num_groups(b.ntracers);
       s.box = i;
       seg_all.push_back(s);
-      pl.items_plic[d] += s.nitems;
-      ++pl.n_plic[d];
+      pl.items_plic[e] += s.nitems;
+      ++pl.n_plic[e];
     }
   }
-  for (int d = 0; d < 3; ++d) {
-    begin_table(pl.off_stream[d], pl.n_stream[d], pl.items_stream[d]);
+  for (int e = 0; e < 6; ++e) {
+    const int d = e % 3;
+    begin_table(pl.off_stream[e], pl.n_stream[e], pl.items_stream[e]);
     for (int i = 0; i < nboxes; ++i) {
       const vofmt_box &b = boxes[i];
       const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-      const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw);
+      const bool flat = e >= 3 && bd[i].flat;
+      const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw, flat);
       Seg s{};
-      s.item0 = pl.items_stream[d];
+      s.item0 = pl.items_stream[e];
       s.gx = tg.gx;
       s.gy = tg.gy;
       s.gz = tg.gz;
       s.ngrp = num_groups(b.ntracers);
       s.nitems = (int64_t)tg.gx * tg.gy * tg.gz * s.ngrp;
       s.box = i;
-      s.gstride = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw);
+      s.gstride = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, flat);
       seg_all.push_back(s);
-      pl.items_stream[d] += s.nitems;
-      ++pl.n_stream[d];
+      pl.items_stream[e] += s.nitems;
+      ++pl.n_stream[e];
     }
   }
   // tables after the per-box buffers: boxes, then segments
@@ -270,32 +287,42 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
   // convert segment indices to byte offsets
   auto to_bytes = [&](size_t idx) { return seg_base + idx * sizeof(Seg); };
   pl.off_scan = to_bytes(pl.off_scan);
-  for (int d = 0; d < 3; ++d) {
-    pl.off_plic[d] = to_bytes(pl.off_plic[d]);
-    pl.off_stream[d] = to_bytes(pl.off_stream[d]);
+  for (int e = 0; e < 6; ++e) {
+    pl.off_plic[e] = to_bytes(pl.off_plic[e]);
+    pl.off_stream[e] = to_bytes(pl.off_stream[e]);
   }
   return off;
 }
 
+// prev: the plan's entry of the sweep before, or -1
 template <int D>
-static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, int prev_d, int src, int dst,
+static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, int prev, int src, int dst,
                           int cur, int wcc, hipStream_t st) {
   const Seg *psegs;
   int pn;
   int64_t pitems;
-  if (prev_d < 0) {
+  if (prev < 0) {
     psegs = (const Seg *)(slab + pl.off_scan);
     pn = pl.n_scan;
     pitems = pl.items_scan;
   } else {
-    psegs = (const Seg *)(slab + pl.off_plic[prev_d]);
-    pn = pl.n_plic[prev_d];
-    pitems = pl.items_plic[prev_d];
+    psegs = (const Seg *)(slab + pl.off_plic[prev]);
+    pn = pl.n_plic[prev];
+    pitems = pl.items_plic[prev];
   }
   hipLaunchKernelGGL((k_plic_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize, src, cur);
-  hipLaunchKernelGGL((k_stream_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes,
-                     (const Seg *)(slab + pl.off_stream[D]), pl.n_stream[D], pl.items_stream[D], pl.chunk, pl.rsize,
-                     src, dst, cur ^ 1, wcc);
+  const int e = D + (wcc ? 0 : 3);
+  const Seg *ssegs = (const Seg *)(slab + pl.off_stream[e]);
+  const dim3 grid(pl.grid), block(256);
+  if constexpr (D != 0) {
+    if (!wcc && pl.any_flat) {
+      hipLaunchKernelGGL((k_stream_b<D, true>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
+                         pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_stream_b<D, false>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
+                     pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
 }
 
 extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, int64_t step0,
@@ -371,16 +398,16 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   VOFMT_HIP(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
   hipLaunchKernelGGL(k_scan_b, dim3(pl.grid), dim3(256), 0, cs, dboxes, (const Seg *)(slab + pl.off_scan), pl.n_scan,
                      pl.items_scan, pl.rsize);
-  int src = 0, dst = 1, cur = 0, prev_d = -1;
+  int src = 0, dst = 1, cur = 0, prev = -1;
   for (int32_t st = 0; st < nsteps; ++st) {
     const int64_t g = step0 + st;
     for (int r = 0; r < 3; ++r) {
       const int d = (int)((g + r) % 3);
       const int wcc = (r == 0);
-      if (d == 0) enqueue_sweep<0>(slab, pl, dboxes, prev_d, src, dst, cur, wcc, cs);
-      else if (d == 1) enqueue_sweep<1>(slab, pl, dboxes, prev_d, src, dst, cur, wcc, cs);
-      else enqueue_sweep<2>(slab, pl, dboxes, prev_d, src, dst, cur, wcc, cs);
-      prev_d = d;
+      if (d == 0) enqueue_sweep<0>(slab, pl, dboxes, prev, src, dst, cur, wcc, cs);
+      else if (d == 1) enqueue_sweep<1>(slab, pl, dboxes, prev, src, dst, cur, wcc, cs);
+      else enqueue_sweep<2>(slab, pl, dboxes, prev, src, dst, cur, wcc, cs);
+      prev = d + (wcc ? 0 : 3);
       const int was = src;
       src = dst;
       dst = (third && st == 0) ? (r == 0 ? 2 : (r == 1 ? 0 : 1)) : was;

@@ -5,7 +5,10 @@ Advection: the marching chunk falls from 32 to 16, 8 and 4 with the number of
 wavefronts of a sweep, the initial scan's span with the number of tracer-cells,
 and the tracers form groups of even sizes. Bar: 1e-12, the volume-fraction
 tolerance of the other advection tests (one or two steps of fields whose
-values are O(1)).
+values are O(1)). Rows that are no multiple of 64 cells take lanes across rows in
+the y- and z-sweeps after the first of a step: planes below, at and above one
+wavefront's and one workgroup's cells, lanes of several rows, in each order of
+the sweeps, alone and in a batch with a box whose rows fill their segments.
 
 Reassignment: pairs found in LDS tiles of 64 x 8 x 8 cells (reach up to 2, up
 to 4) or from the list of boundary cells (above, or an axis no longer than the
@@ -81,6 +84,25 @@ def test_work_split(ctx, shape, ntr, step0, nsteps):
     ctx.advect(tc, *[torch.from_numpy(a).to("cuda:0") for a in s], step0=step0, nsteps=nsteps)
     torch.cuda.synchronize()
     assert np.abs(tc.cpu().numpy() - oracle.advect(c, *s, step0, nsteps)).max() <= TOL
+
+
+@pytest.mark.parametrize("step0", [0, 1, 2])
+@pytest.mark.parametrize("shape,ntr", [((1, 1, 1), 1), ((3, 5, 2), 2), ((7, 9, 7), 3), ((4, 2, 65), 5), ((16, 17, 16), 1),
+                                       ((15, 8, 127), 4), ((33, 34, 129), 2), ((2, 37, 193), 7)])
+def test_lanes_across_rows(ctx, shape, ntr, step0):
+    import torch
+
+    boxes = [_random(shape, ntr, 53 + sum(shape)), _random((3, 6, 64), 2, 59)]
+    refs = [oracle.advect(c, *s, step0, 2) for c, s in boxes]
+    note(f"advect lanes across rows {shape} ntr={ntr} step0={step0}")
+    dev = [[torch.from_numpy(a).to("cuda:0") for a in (c, *s)] for c, s in boxes]
+    alone = dev[0][0].clone()
+    ctx.advect(alone, *dev[0][1:], step0=step0, nsteps=2)
+    ctx.advect_batched([tuple(d) for d in dev], step0=step0, nsteps=2)
+    torch.cuda.synchronize()
+    assert torch.equal(alone, dev[0][0])
+    for d, ref in zip(dev, refs):
+        assert np.abs(d[0].cpu().numpy() - ref).max() <= TOL
 
 
 def _labelled(shape, ntr, seed, spread):
