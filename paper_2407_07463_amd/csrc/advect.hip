@@ -41,7 +41,7 @@ __global__ __launch_bounds__(D == 0 ? 64 * kXWaves : 256) void k_stream(
                            counts_next, g.grp * gstride, rsize, g, gridDim.x, gridDim.y, fnx);
 }
 
-// The y- and z-sweeps in the flat layout.
+// The sweeps in the flat layout.
 template <int D, int GM>
 __global__ __launch_bounds__(256) void k_stream_flat(const double *__restrict__ cin, double *__restrict__ cout,
                                                      const double *__restrict__ s, const double *__restrict__ fmix,
@@ -140,14 +140,10 @@ static void launch_stream(dim3 grid, bool flat, const FastDiv &fnx, hipStream_t 
                           const double *s, SweepBuffers &sb, int wcc, int nx, int ny, int nz, int ntr, int words,
                           int chunk, int nxt, int64_t per) {
   const int ngrp = num_groups(ntr);
-  if constexpr (D != 0) {
-    if (flat) {
-      hipLaunchKernelGGL((k_stream_flat<D, GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, ntr, nx, ny,
-                         nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
-      return;
-    }
-  }
-  if (D == 0 && x_wpb(words, chunk) == 0)
+  if (flat)
+    hipLaunchKernelGGL((k_stream_flat<D, GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, ntr, nx, ny,
+                       nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
+  else if (D == 0 && x_wpb(words, chunk) == 0)
     hipLaunchKernelGGL((k_stream_rows<GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, wcc, ntr, nx,
                        ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
   else
@@ -173,7 +169,7 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
                      sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
   prof_end(ctx, rec, stream);
   const int wpb = (D == 0) ? x_wpb(words, chunk) : 4;
-  const bool flat = D != 0 && !wcc && flat_rows(nx, ny, nz);
+  const bool flat = !wcc && flat_rows(nx, ny, nz);
   const int64_t per = stream_waves(D, nx, ny, nz, chunk, wpb, flat);
   const Tiles tg = stream_tiles(D, nx, ny, nz, chunk, wpb, flat);
   const dim3 grid(tg.gx, tg.gy, tg.gz * num_groups(ntr));

@@ -58,6 +58,8 @@ constexpr int kMaxGroup = 4;  // tracers per streaming pass (register budget)
 //   d = 1 and 2, flat: the lanes run over the cells of the plane across the
 //          axis (x, then z or y) without regard to rows: gx = 1, gy = groups of
 //          256 consecutive cells (64 per wavefront), gz = chunks.
+//   d = 0, flat: a wavefront takes chunk / 2 runs of 64 consecutive cells of
+//          the tracer; gx = groups of 4 wavefronts, gy = gz = 1.
 struct Tiles {
   int gx, gy, gz;
 };
@@ -70,7 +72,9 @@ __host__ __device__ inline int x_row_positions(int words, int chunk) {
 __host__ __device__ inline Tiles stream_tiles(int d, int nx, int ny, int nz, int chunk, int wpb = 4,
                                               bool flat = false) {
   const int words = (nx + 63) / 64;
-  if (flat && d != 0)
+  if (flat && d == 0)
+    return Tiles{(int)(((int64_t)nx * ny * nz + 128 * chunk - 1) / (128 * chunk)), 1, 1};
+  if (flat)
     return Tiles{1, (int)(((int64_t)nx * (d == 1 ? nz : ny) + 255) / 256), ((d == 1 ? ny : nz) + chunk - 1) / chunk};
   if (d == 0 && wpb == 0) {
     const int P = x_row_positions(words, chunk);
@@ -253,7 +257,7 @@ __host__ __device__ inline GroupTile group_tile(int64_t L, int gx, int gy, int g
 
 // Tile (bx, by, bz) of a streaming pass laid out as a gx x gy x gz grid of
 // workgroups (stream_tiles): 4 wavefronts, or WPB for the x-sweep. WPB =
-// kFlat (d = 1 and 2): the flat layout, for sweeps that read the c_c words (a
+// kFlat: the flat layout, for sweeps that read the c_c words (a
 // ballot over the lanes is no word of a row).
 constexpr int kFlat = -1;
 template <int D, int G, int WPB = 4>
@@ -263,19 +267,18 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
                                             int nz, int words, int chunk, uint32_t *__restrict__ list_next,
                                             int *__restrict__ counts_next, int64_t region0, int rsize, int bx, int by,
                                             int bz, int gx, int gy, const FastDiv &fnx) {
-  static_assert(D != 0 || WPB != kFlat, "the x-sweep has no flat layout");
   constexpr bool FLAT = WPB == kFlat;
   const int lane = threadIdx.x & 63;
   // wavefront-uniform: kept in a scalar register, like everything derived from it
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // x-sweep with WPB = 0: the wavefront marches along whole rows (row 4*by + wv)
   constexpr bool ROWS = (D == 0 && WPB == 0);
-  constexpr int W = (D == 0 && !ROWS) ? WPB : 4;  // wavefronts per workgroup
+  constexpr int W = (D == 0 && !ROWS && !FLAT) ? WPB : 4;  // wavefronts per workgroup
   // x-sweep (WPB > 0): wavefront wv takes segment bx*spw + sw of row by*rpb + rr;
   // whole-row x-sweep: row 4*by + wv; y- and z-sweeps: segment 4*bx + wv of
   // row by when a row has a multiple of 4 segments, else segment bx of row 4*by + wv
-  const int spw = (D == 0 && !ROWS) ? x_segments_per_row(words, W) : 1;
-  const int rpb = (D == 0 && !ROWS) ? W / spw : 1;
+  const int spw = (D == 0 && !ROWS && !FLAT) ? x_segments_per_row(words, W) : 1;
+  const int rpb = (D == 0 && !ROWS && !FLAT) ? W / spw : 1;
   const int rr = wv / spw, sw = wv % spw;
   const bool tile_ok = (D != 0 || ROWS) || (rr < rpb && by * rpb + rr < ny && bx * spw + sw < words);
   // (the whole-row march moves seg along the row)
@@ -287,10 +290,13 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   const int nm = (D == 1) ? ny : nz;
   const int64_t wave = region0 + (((int64_t)bz * gy + by) * gx + bx) * W + wv;
   // whole wavefront (the LDS x-sweep keeps every wavefront for its barriers)
-  // flat: the lane's cell of the plane, (fx, fr), a lane past the end shadowing the last one
-  const int64_t nq = FLAT ? (int64_t)nx * nrow : 0, q0 = FLAT ? ((int64_t)by * 4 + wv) * 64 : 0;
+  // flat: the lane's first cell of the plane (x-sweep: of the tracer), (fx, fr),
+  // a lane past the end shadowing the last one
+  const int64_t nq = !FLAT ? 0 : D == 0 ? (int64_t)nx * ny * nz : (int64_t)nx * nrow;
+  const int64_t q0 = !FLAT ? 0 : D == 0 ? ((int64_t)bx * 4 + wv) * (chunk / 2) * 64 : ((int64_t)by * 4 + wv) * 64;
   const uint32_t fq = FLAT ? (uint32_t)(q0 + lane < nq ? q0 + lane : nq - 1) : 0u;
-  const uint32_t fr = FLAT ? fast_div(fq, fnx) : 0u, fx = fq - fr * (uint32_t)nx;
+  const uint32_t fr = FLAT ? fast_div(fq, fnx) : 0u;
+  uint32_t fx = fq - fr * (uint32_t)nx;
   if (FLAT ? q0 >= nq : ((D != 0 || ROWS) && (row >= nrow || (D != 0 && seg >= words)))) {
     if (lane == 0) counts_next[wave] = 0;
     return;
@@ -310,16 +316,17 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   const double *f_g = fmix + (int64_t)t0 * n3;
   uint64_t *b_g = ccbits + (int64_t)t0 * nbits;
 
-  // (a tracer's cells and words stay below 2^32)
+  // (a tracer's cells and half words stay below 2^32: a row of two or more
+  // cells has no more half words than cells)
   const uint32_t fcell = D == 1 ? fr * ((uint32_t)ny * nx) + fx : fq;
-  const uint32_t fword = fr * (D == 1 ? (uint32_t)ny * words : (uint32_t)words) + (fx >> 6);
+  const uint32_t fword = fr * (D == 1 ? (uint32_t)ny * words : (uint32_t)words) * 2u + (fx >> 5);
   auto cell = [&](int xx, int mm) -> int64_t {
     if (FLAT) return (int64_t)(fcell + (uint32_t)mm * (D == 1 ? (uint32_t)nx : (uint32_t)nx * ny));
     if (D == 1) return ((int64_t)row * ny + mm) * nx + xx;
     return ((int64_t)mm * ny + row) * nx + xx;
   };
   auto bitword = [&](int mm) -> int64_t {
-    if (FLAT) return (int64_t)(fword + (uint32_t)mm * (D == 1 ? (uint32_t)words : (uint32_t)ny * words));
+    if (FLAT) return (int64_t)(fword + (uint32_t)mm * (D == 1 ? (uint32_t)words : (uint32_t)ny * words) * 2u);
     if (D == 1) return ((int64_t)row * ny + mm) * words + seg;
     return ((int64_t)mm * ny + row) * words + seg;
   };
@@ -334,22 +341,25 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   };
   // the c_c bit words of row word wrow that finish() reads (unless this
   // sweep writes them), loaded ahead of their use so their latency overlaps
-  // other work
-  auto load_words = [&](int64_t wrow, uint64_t *ccw) {
+  // other work; flat: the lane's own word, the half with its bit
+  using word_t = std::conditional_t<FLAT, uint32_t, uint64_t>;
+  const word_t *bw_g = (const word_t *)b_g;
+  constexpr int kHalves = sizeof(uint64_t) / sizeof(word_t);
+  auto load_words = [&](int64_t wrow, word_t *ccw) {
     const bool ok = FLAT || (tile_ok && seg < words);  // idle: no cells
 #pragma unroll
-    for (int t = 0; t < G; ++t) ccw[t] = ((FLAT || !write_cc) && ok) ? b_g[t * nbits + wrow] : 0ull;
+    for (int t = 0; t < G; ++t) ccw[t] = ((FLAT || !write_cc) && ok) ? bw_g[t * nbits * kHalves + wrow] : (word_t)0;
   };
   // new value of cell pc, its c_c bit, and its entry in the next list
   auto finish = [&](int t, double cold, double f_lo, double f_hi, double s_lo, double s_hi, int64_t pc, int64_t wrow,
-                    uint64_t ccw) {
+                    word_t ccw) {
     double ccv;
     if (!FLAT && write_cc) {
       const uint64_t word = __ballot(live && cold > 0.5);
       if (lane == 0 && tile_ok && seg < words) b_g[t * nbits + wrow] = word;
       ccv = (cold > 0.5) ? 1.0 : 0.0;
     } else {
-      ccv = ((ccw >> (FLAT ? (int)(fx & 63u) : lane)) & 1ull) ? 1.0 : 0.0;
+      ccv = ((ccw >> (FLAT ? (int)(fx & 31u) : lane)) & 1u) ? 1.0 : 0.0;
     }
     const double cn = (cold - (f_hi - f_lo)) + ccv * (s_hi - s_lo);
     // streamed out (not read again by this pass): a non-temporal store
@@ -382,7 +392,7 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
     // are loaded one position ahead, so their latency overlaps the previous
     // position's flux work and stores
     double s_nx = 0.0, c_nx[G];
-    uint64_t ccw[G];
+    word_t ccw[G];
     if (m0 + 1 <= m1) {
       const int64_t pu = cell(xs, (m0 + 1 == nm) ? 0 : m0 + 1);
       s_nx = s[pu];
@@ -397,7 +407,7 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
       const int64_t wrow = bitword(m - 1);
       const double s_hi = s_nx;
       double cu[G], fhi[G];
-      uint64_t ccc[G];
+      word_t ccc[G];
 #pragma unroll
       for (int t = 0; t < G; ++t) {
         cu[t] = c_nx[t];
@@ -419,6 +429,83 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
         cm[t] = cu[t];
       }
       s_lo = s_hi;
+    }
+  } else if constexpr (FLAT) {
+    // ---- x-sweep over runs of 64 consecutive cells of the tracer, rows not
+    // regarded. Lanes take their neighbours inside a run by wave shifts; lane 0
+    // takes the previous run's last cell, lane 63 the next run's first; a row's
+    // first and last cell (in any lane) load the other one, where the row
+    // closes. The next run, its rows' ends and its bit words are loaded one
+    // run ahead.
+    auto readlane_d = [](double v, int l) {
+      const long long b = __double_as_longlong(v);
+      const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+      return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+    };
+    const uint32_t last_cell = (uint32_t)(n3 - 1);
+    auto load_run = [&](int64_t q, int off, uint32_t &p, uint32_t &xk, double *cv, double &sv, double *cw, double &sw_,
+                        word_t *ccw) {
+      p = (q + off < n3) ? (uint32_t)(q + off) : last_cell;
+      const uint32_t rk = fast_div(p, fnx);
+      xk = p - rk * (uint32_t)nx;
+      sv = s[p];
+#pragma unroll
+      for (int t = 0; t < G; ++t) cv[t] = c_g[t * n3 + p];
+      load_words(rk * (uint32_t)words * 2u + (xk >> 5), ccw);
+      sw_ = 0.0;
+#pragma unroll
+      for (int t = 0; t < G; ++t) cw[t] = 0.0;
+      const bool beg = xk == 0u, end = xk == (uint32_t)nx - 1u;
+      if (beg || end) {
+        const uint32_t pw = end ? p - xk : p + (uint32_t)(nx - 1);
+        sw_ = s[pw];
+#pragma unroll
+        for (int t = 0; t < G; ++t) cw[t] = c_g[t * n3 + pw];
+      }
+    };
+    double c_cur[G], c_nxt[G], w_cur[G], w_nxt[G], c_prv[G];
+    double s_cur, s_nxt, ws_cur, ws_nxt;
+    word_t ccw[G], ccw_nxt[G];
+    uint32_t p, p_nxt, x_nxt;
+    const int64_t q1 = (q0 + (int64_t)(chunk / 2) * 64 < n3) ? q0 + (int64_t)(chunk / 2) * 64 : n3;
+    load_run(q0, lane, p, fx, c_cur, s_cur, w_cur, ws_cur, ccw);
+#pragma unroll
+    for (int t = 0; t < G; ++t) c_prv[t] = c_g[t * n3 + (q0 > 0 ? q0 - 1 : 0)];
+    for (int64_t q = q0; q < q1; q += 64) {
+      // (past the wavefront's last run only the next cell is of use)
+      load_run(q + 64, q + 64 < q1 ? lane : 0, p_nxt, x_nxt, c_nxt, s_nxt, w_nxt, ws_nxt, ccw_nxt);
+      live = q + lane < n3;
+      const bool beg = fx == 0u, end = fx == (uint32_t)nx - 1u;
+      const uint32_t pr = end ? p - fx : p + 1u;
+      const double s_up = from_lane_above(s_cur), s_e = readlane_d(s_nxt, 0);
+      const double s_hi = end ? ws_cur : (lane == 63 ? s_e : s_up);
+      double cl[G], cr[G], flo[G], fhi[G];
+#pragma unroll
+      for (int t = 0; t < G; ++t) {
+        const double up = from_lane_below(c_cur[t]);
+        const double dn = from_lane_above(c_cur[t]);
+        const double ce = readlane_d(c_nxt[t], 0);
+        cl[t] = beg ? w_cur[t] : (lane == 0 ? c_prv[t] : up);
+        cr[t] = end ? w_cur[t] : (lane == 63 ? ce : dn);
+      }
+#pragma unroll
+      for (int t = 0; t < G; ++t) {
+        flo[t] = flux(t, s_cur, cl[t], c_cur[t], p);
+        fhi[t] = flux(t, s_hi, c_cur[t], cr[t], pr);
+      }
+#pragma unroll
+      for (int t = 0; t < G; ++t) finish(t, c_cur[t], flo[t], fhi[t], s_cur, s_hi, p, 0, ccw[t]);
+#pragma unroll
+      for (int t = 0; t < G; ++t) {
+        c_prv[t] = readlane_d(c_cur[t], 63);
+        c_cur[t] = c_nxt[t];
+        w_cur[t] = w_nxt[t];
+        ccw[t] = ccw_nxt[t];
+      }
+      s_cur = s_nxt;
+      ws_cur = ws_nxt;
+      p = p_nxt;
+      fx = x_nxt;
     }
   } else if constexpr (ROWS) {
     // ---- x-sweep along whole rows: the wavefront takes its row's 64-cell
@@ -653,20 +740,22 @@ __device__ __forceinline__ void stream_group(const double *__restrict__ cin, dou
 // Wavefronts of one streaming pass along axis d (each owns one list region).
 static inline int64_t stream_waves(int d, int nx, int ny, int nz, int chunk, int wpb = 4, bool flat = false) {
   const Tiles g = stream_tiles(d, nx, ny, nz, chunk, wpb, flat);
-  return ((d == 0 && wpb > 0) ? wpb : 4) * (int64_t)g.gx * g.gy * g.gz;
+  return ((d == 0 && wpb > 0 && !flat) ? wpb : 4) * (int64_t)g.gx * g.gy * g.gz;
 }
 
-// Whether the y- and z-sweeps that read the c_c words (the second and third of
-// a step) take the flat layout. A row of 134 cells leaves 58 of its 192 lanes
-// idle in the layout by segments; by cells every wavefront but the last of a
-// plane is full (one step, by segments -> flat: 134x129x141 x 7 444 -> 419 us;
-// 65x300x300 x 8 1136 -> 1015; 250^3 x 8, 2% idle, 2138 -> 2112; 32 boxes of 64
-// to 192 cells, three steps, 25.4 -> 24.3 ms). Rows of whole segments fill them
-// either way and keep scalar bit words and addresses; a plane of more than
-// 65535 workgroups is no grid of the plain path.
+// Whether the sweeps that read the c_c words (the second and third of a step)
+// take the flat layout. A row of 134 cells leaves 58 of its 192 lanes idle in
+// the layout by segments; by cells every wavefront but the last of a plane is
+// full (one step, by segments -> y- and z-sweeps flat -> all flat:
+// 134x129x141 x 7 444 -> 420 -> 398 us; 65x300x300 x 8 1136 -> 1017 -> 954;
+// 250^3 x 8, 2% idle, 2138 -> 2115 -> 2048; 32 boxes of 64 to 192 cells, three
+// steps, 25.4 -> 24.6 -> 23.6 ms). Rows of whole segments fill them either way
+// and keep scalar bit words and addresses; a plane of more than 65535
+// workgroups is no grid of the plain path, and at nx = 1 a row's two half words
+// could number 2^32.
 static inline bool flat_rows(int nx, int ny, int nz) {
   const int64_t widest = (int64_t)nx * (ny > nz ? ny : nz);
-  return nx % 64 != 0 && widest <= 65535ll * 256;
+  return nx > 1 && nx % 64 != 0 && widest <= 65535ll * 256;
 }
 // List entries per region: every cell a wavefront of a streaming pass writes.
 static inline int region_size(int chunk) { return 64 * chunk * kMaxGroup; }

@@ -20,7 +20,7 @@ namespace {
 
 struct BoxDev {
   int nx, ny, nz, ntr, words;
-  int flat;  // y- and z-sweeps that read the c_c words: the flat layout (flat_rows)
+  int flat;  // sweeps that read the c_c words: the flat layout (flat_rows)
   int xwpb;  // x-sweep: 0 whole-row wavefronts (a row's cells fit one list region), else 4 per workgroup
   Divisors dv;
   double *f[3];  // the caller's field, its ping-pong copy and the third one of an odd number of sweeps
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes
   }
 }
 
-// work items: 4-wavefront tiles of a streaming pass. FLAT: a y- or z-sweep that
+// work items: 4-wavefront tiles of a streaming pass. FLAT: a sweep that
 // reads the c_c words, with the tables made for it; each box has the layout
 // that flat_rows gives it.
 template <int D, bool FLAT>
@@ -314,15 +314,12 @@ static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, i
   const int e = D + (wcc ? 0 : 3);
   const Seg *ssegs = (const Seg *)(slab + pl.off_stream[e]);
   const dim3 grid(pl.grid), block(256);
-  if constexpr (D != 0) {
-    if (!wcc && pl.any_flat) {
-      hipLaunchKernelGGL((k_stream_b<D, true>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
-                         pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((k_stream_b<D, false>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
-                     pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
+  if (!wcc && pl.any_flat)
+    hipLaunchKernelGGL((k_stream_b<D, true>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
+                       pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
+  else
+    hipLaunchKernelGGL((k_stream_b<D, false>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
+                       pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
 }
 
 extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, int64_t step0,
