@@ -32,12 +32,12 @@ __global__ __launch_bounds__(256) void k_plic(const double *__restrict__ cin, co
 template <int D, int GM>
 __global__ __launch_bounds__(D == 0 ? 64 * kXWaves : 256) void k_stream(
     const double *__restrict__ cin, double *__restrict__ cout, const double *__restrict__ s,
-    const double *__restrict__ fmix, uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx, int ny, int nz,
+    const double *__restrict__ fmix, uint64_t *__restrict__ ccbits, int cc, int ntr, int nx, int ny, int nz,
     int words, int chunk, uint32_t *__restrict__ list_next, int *__restrict__ counts_next, int rsize, int ngrp,
     int64_t gstride, FastDiv fnx) {
   const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
                                  gridDim.y, gridDim.z / ngrp, ngrp, D == 1);
-  stream_group<D, GM, kXWaves>(cin, cout, s, fmix, ccbits, write_cc, ntr, nx, ny, nz, words, chunk, list_next,
+  stream_group<D, GM, kXWaves>(cin, cout, s, fmix, ccbits, cc, ntr, nx, ny, nz, words, chunk, list_next,
                            counts_next, g.grp * gstride, rsize, g, gridDim.x, gridDim.y, fnx);
 }
 
@@ -45,13 +45,13 @@ __global__ __launch_bounds__(D == 0 ? 64 * kXWaves : 256) void k_stream(
 template <int D, int GM>
 __global__ __launch_bounds__(256) void k_stream_flat(const double *__restrict__ cin, double *__restrict__ cout,
                                                      const double *__restrict__ s, const double *__restrict__ fmix,
-                                                     uint64_t *__restrict__ ccbits, int ntr, int nx, int ny, int nz,
-                                                     int words, int chunk, uint32_t *__restrict__ list_next,
+                                                     uint64_t *__restrict__ ccbits, int cc, int ntr, int nx, int ny,
+                                                     int nz, int words, int chunk, uint32_t *__restrict__ list_next,
                                                      int *__restrict__ counts_next, int rsize, int ngrp,
                                                      int64_t gstride, FastDiv fnx) {
   const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
                                  gridDim.y, gridDim.z / ngrp, ngrp, D == 1);
-  stream_group<D, GM, kFlat>(cin, cout, s, fmix, ccbits, 0, ntr, nx, ny, nz, words, chunk, list_next, counts_next,
+  stream_group<D, GM, kFlat>(cin, cout, s, fmix, ccbits, cc, ntr, nx, ny, nz, words, chunk, list_next, counts_next,
                              g.grp * gstride, rsize, g, gridDim.x, gridDim.y, fnx);
 }
 
@@ -59,13 +59,13 @@ __global__ __launch_bounds__(256) void k_stream_flat(const double *__restrict__ 
 template <int GM>
 __global__ __launch_bounds__(256) void k_stream_rows(const double *__restrict__ cin, double *__restrict__ cout,
                                                      const double *__restrict__ s, const double *__restrict__ fmix,
-                                                     uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx,
+                                                     uint64_t *__restrict__ ccbits, int cc, int ntr, int nx,
                                                      int ny, int nz, int words, int chunk,
                                                      uint32_t *__restrict__ list_next, int *__restrict__ counts_next,
                                                      int rsize, int ngrp, int64_t gstride, FastDiv fnx) {
   const GroupTile g = group_tile(((int)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, gridDim.x,
                                  gridDim.y, gridDim.z / ngrp, ngrp, false);
-  stream_group<0, GM, 0>(cin, cout, s, fmix, ccbits, write_cc, ntr, nx, ny, nz, words, chunk, list_next, counts_next,
+  stream_group<0, GM, 0>(cin, cout, s, fmix, ccbits, cc, ntr, nx, ny, nz, words, chunk, list_next, counts_next,
                      g.grp * gstride, rsize, g, gridDim.x, gridDim.y, fnx);
 }
 
@@ -120,7 +120,8 @@ static int pick_chunk(int nx, int ny, int nz, int ntr) {
   while (chunk > 4 && words <= chunk / 2) {
     int64_t least = INT64_MAX;
     for (int d = 0; d < 3; ++d) {
-      const int64_t w = stream_waves(d, nx, ny, nz, chunk, d == 0 ? x_wpb(words, chunk) : 4) * num_groups(ntr);
+      const int64_t w = stream_waves(d, nx, ny, nz, chunk, d == 0 ? x_wpb(words, chunk) : 4, flat_rows(nx, ny, nz)) *
+                        num_groups(ntr);
       least = w < least ? w : least;
     }
     if (least >= kWaves) break;
@@ -137,24 +138,24 @@ static int scan_span(int64_t total) {
 
 template <int D, int GM>
 static void launch_stream(dim3 grid, bool flat, const FastDiv &fnx, hipStream_t stream, const double *cin, double *cout,
-                          const double *s, SweepBuffers &sb, int wcc, int nx, int ny, int nz, int ntr, int words,
+                          const double *s, SweepBuffers &sb, int cc, int nx, int ny, int nz, int ntr, int words,
                           int chunk, int nxt, int64_t per) {
   const int ngrp = num_groups(ntr);
   if (flat)
-    hipLaunchKernelGGL((k_stream_flat<D, GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, ntr, nx, ny,
-                       nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
+    hipLaunchKernelGGL((k_stream_flat<D, GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, cc, ntr, nx,
+                       ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
   else if (D == 0 && x_wpb(words, chunk) == 0)
-    hipLaunchKernelGGL((k_stream_rows<GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, wcc, ntr, nx,
+    hipLaunchKernelGGL((k_stream_rows<GM>), grid, dim3(256), 0, stream, cin, cout, s, sb.fmix, sb.bits, cc, ntr, nx,
                        ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp, per, fnx);
   else
     hipLaunchKernelGGL((k_stream<D, GM>), grid, dim3(D == 0 ? 64 * kXWaves : 256), 0, stream, cin, cout, s, sb.fmix,
-                       sb.bits, wcc, ntr, nx, ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp,
+                       sb.bits, cc, ntr, nx, ny, nz, words, chunk, sb.list[nxt], sb.counts[nxt], sb.rsize, ngrp,
                        per, fnx);
 }
 
 template <int D>
 static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, const double *s, SweepBuffers &sb,
-                              int wcc, int cur, int nx, int ny, int nz, int ntr, int words, int chunk,
+                              int cc, int cur, int nx, int ny, int nz, int ntr, int words, int chunk,
                               hipStream_t stream) {
   const int nxt = cur ^ 1;
   const int64_t nreg = sb.nregions[cur];
@@ -169,17 +170,17 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
                      sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
   prof_end(ctx, rec, stream);
   const int wpb = (D == 0) ? x_wpb(words, chunk) : 4;
-  const bool flat = !wcc && flat_rows(nx, ny, nz);
+  const bool flat = flat_rows(nx, ny, nz);
   const int64_t per = stream_waves(D, nx, ny, nz, chunk, wpb, flat);
   const Tiles tg = stream_tiles(D, nx, ny, nz, chunk, wpb, flat);
   const dim3 grid(tg.gx, tg.gy, tg.gz * num_groups(ntr));
   static_assert(kMaxGroup == 4, "streaming passes are instantiated for groups of at most 4");
   rec = prof_begin(ctx, stream_names[D], stream);
   switch (largest_group(ntr)) {
-    case 4: launch_stream<D, 4>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    case 3: launch_stream<D, 3>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    case 2: launch_stream<D, 2>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    default: launch_stream<D, 1>(grid, flat, dv.nx, stream, cin, cout, s, sb, wcc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 4: launch_stream<D, 4>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 3: launch_stream<D, 3>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 2: launch_stream<D, 2>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    default: launch_stream<D, 1>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
   }
   prof_end(ctx, rec, stream);
   sb.nregions[nxt] = num_groups(ntr) * per;
@@ -187,10 +188,10 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
 }
 
 static int launch_sweep(vofmt_ctx *ctx, int d, const double *cin, double *cout, const double *s, SweepBuffers &sb,
-                        int wcc, int cur, int nx, int ny, int nz, int ntr, int words, int chunk, hipStream_t stream) {
-  if (d == 0) launch_sweep_axis<0>(ctx, cin, cout, s, sb, wcc, cur, nx, ny, nz, ntr, words, chunk, stream);
-  else if (d == 1) launch_sweep_axis<1>(ctx, cin, cout, s, sb, wcc, cur, nx, ny, nz, ntr, words, chunk, stream);
-  else launch_sweep_axis<2>(ctx, cin, cout, s, sb, wcc, cur, nx, ny, nz, ntr, words, chunk, stream);
+                        int cc, int cur, int nx, int ny, int nz, int ntr, int words, int chunk, hipStream_t stream) {
+  if (d == 0) launch_sweep_axis<0>(ctx, cin, cout, s, sb, cc, cur, nx, ny, nz, ntr, words, chunk, stream);
+  else if (d == 1) launch_sweep_axis<1>(ctx, cin, cout, s, sb, cc, cur, nx, ny, nz, ntr, words, chunk, stream);
+  else launch_sweep_axis<2>(ctx, cin, cout, s, sb, cc, cur, nx, ny, nz, ntr, words, chunk, stream);
   return (int)hipGetLastError();
 }
 
@@ -257,8 +258,7 @@ extern "C" int vofmt_advect(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, 
     const int64_t g = step0 + st;
     for (int r = 0; r < 3; ++r) {
       const int d = (int)((g + r) % 3);
-      const int wcc = (r == 0);
-      int rc = launch_sweep(ctx, d, cur, nxt, s3[d], sb, wcc, cur_list, nx, ny, nz, ntracers, words, chunk, stream);
+      int rc = launch_sweep(ctx, d, cur, nxt, s3[d], sb, cc_mode(g, r), cur_list, nx, ny, nz, ntracers, words, chunk, stream);
       if (rc) return hip_check(ctx, (hipError_t)rc, "sweep launch");
       cur_list ^= 1;
       double *t = cur;

@@ -21,10 +21,11 @@
 //   the sweep axis and carry c and the lower-face flux in registers, so every
 //   field value is read from memory once; in the x-sweep each lane forms both
 //   of its faces from its own and its neighbour lanes' values. A wavefront
-//   owns 64 consecutive x-cells of one row, so every load and store of a field
-//   row is a coalesced 512-byte transaction and the c > 0.5 indicator of the
+//   owns 64 consecutive x-cells of one row (in the flat layout 64 consecutive
+//   cells of the plane its lanes lie in), so every load and store of a field
+//   is a coalesced 512-byte transaction and the c > 0.5 indicator of the
 //   64 cells is one 64-bit ballot word. The new field is written in the same
-//   row layout, and every new mixed cell is appended to the list of the next
+//   layout, and every new mixed cell is appended to the list of the next
 //   sweep.
 //
 // The list is cut into regions of rsize entries, one per wavefront of the
@@ -59,7 +60,8 @@ constexpr int kMaxGroup = 4;  // tracers per streaming pass (register budget)
 //          axis (x, then z or y) without regard to rows: gx = 1, gy = groups of
 //          256 consecutive cells (64 per wavefront), gz = chunks.
 //   d = 0, flat: a wavefront takes chunk / 2 runs of 64 consecutive cells of
-//          the tracer; gx = groups of 4 wavefronts, gy = gz = 1.
+//          a z-plane (the plane's last run may be shorter); gx = groups of 4
+//          wavefronts, gy = gz = 1.
 struct Tiles {
   int gx, gy, gz;
 };
@@ -73,7 +75,7 @@ __host__ __device__ inline Tiles stream_tiles(int d, int nx, int ny, int nz, int
                                               bool flat = false) {
   const int words = (nx + 63) / 64;
   if (flat && d == 0)
-    return Tiles{(int)(((int64_t)nx * ny * nz + 128 * chunk - 1) / (128 * chunk)), 1, 1};
+    return Tiles{(int)((((int64_t)nx * ny + 63) / 64 * nz + 2 * chunk - 1) / (2 * chunk)), 1, 1};
   if (flat)
     return Tiles{1, (int)(((int64_t)nx * (d == 1 ? nz : ny) + 255) / 256), ((d == 1 ? ny : nz) + chunk - 1) / chunk};
   if (d == 0 && wpb == 0) {
@@ -256,19 +258,28 @@ __host__ __device__ inline GroupTile group_tile(int64_t L, int gx, int gy, int g
 }
 
 // Tile (bx, by, bz) of a streaming pass laid out as a gx x gy x gz grid of
-// workgroups (stream_tiles): 4 wavefronts, or WPB for the x-sweep. WPB =
-// kFlat: the flat layout, for sweeps that read the c_c words (a
-// ballot over the lanes is no word of a row).
+// workgroups (stream_tiles): 4 wavefronts, or WPB for the x-sweep; WPB = kFlat:
+// the flat layout. cc says what the sweep does with the c_c words: kReadCc,
+// kWriteCc, or in the flat layout kReadCcY after a step's first sweep along y.
+// By segments the words are those of the rows. In the flat layout a ballot over
+// the lanes is no word of a row, and the words are those of a plane's
+// consecutive cells: of the z-planes (x, then y), or of the y-planes (x, then z)
+// where the first sweep goes along y. A sweep whose lanes lie otherwise reads
+// each lane's own.
+constexpr int kReadCc = 0, kWriteCc = 1, kReadCcY = 2;
+// cc of sweep r of step g, whose axes are (g + r) % 3
+inline int cc_mode(int64_t g, int r) { return r == 0 ? kWriteCc : (g % 3 == 1 ? kReadCcY : kReadCc); }
 constexpr int kFlat = -1;
 template <int D, int G, int WPB = 4>
 __device__ __forceinline__ void stream_body(const double *__restrict__ cin, double *__restrict__ cout,
                                             const double *__restrict__ s, const double *__restrict__ fmix,
-                                            uint64_t *__restrict__ ccbits, int write_cc, int t0, int nx, int ny,
+                                            uint64_t *__restrict__ ccbits, int cc, int t0, int nx, int ny,
                                             int nz, int words, int chunk, uint32_t *__restrict__ list_next,
                                             int *__restrict__ counts_next, int64_t region0, int rsize, int bx, int by,
                                             int bz, int gx, int gy, const FastDiv &fnx) {
   constexpr bool FLAT = WPB == kFlat;
   const int lane = threadIdx.x & 63;
+  const bool write_cc = cc == kWriteCc;
   // wavefront-uniform: kept in a scalar register, like everything derived from it
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // x-sweep with WPB = 0: the wavefront marches along whole rows (row 4*by + wv)
@@ -290,21 +301,25 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   const int nm = (D == 1) ? ny : nz;
   const int64_t wave = region0 + (((int64_t)bz * gy + by) * gx + bx) * W + wv;
   // whole wavefront (the LDS x-sweep keeps every wavefront for its barriers)
-  // flat: the lane's first cell of the plane (x-sweep: of the tracer), (fx, fr),
-  // a lane past the end shadowing the last one
-  const int64_t nq = !FLAT ? 0 : D == 0 ? (int64_t)nx * ny * nz : (int64_t)nx * nrow;
-  const int64_t q0 = !FLAT ? 0 : D == 0 ? ((int64_t)bx * 4 + wv) * (chunk / 2) * 64 : ((int64_t)by * 4 + wv) * 64;
-  const uint32_t fq = FLAT ? (uint32_t)(q0 + lane < nq ? q0 + lane : nq - 1) : 0u;
-  const uint32_t fr = FLAT ? fast_div(fq, fnx) : 0u;
-  uint32_t fx = fq - fr * (uint32_t)nx;
-  if (FLAT ? q0 >= nq : ((D != 0 || ROWS) && (row >= nrow || (D != 0 && seg >= words)))) {
+  // flat: runs of 64 cells of a z- and of a y-plane; the wavefront's first run of
+  // its plane (x-sweep: of the tracer), and for the y- and z-sweeps the lane's
+  // cell in it, (fx, fr), a lane past the end shadowing the last one
+  const uint32_t zruns = FLAT ? (uint32_t)(((int64_t)nx * ny + 63) / 64) : 0u;
+  const uint32_t yruns = FLAT ? (uint32_t)(((int64_t)nx * nz + 63) / 64) : 0u;
+  const int64_t nruns = !FLAT ? 0 : D == 0 ? (int64_t)zruns * nz : (D == 1 ? yruns : zruns);
+  const int64_t run0 = !FLAT ? 0 : D == 0 ? ((int64_t)bx * 4 + wv) * (chunk / 2) : (int64_t)by * 4 + wv;
+  const uint32_t nq = FLAT ? (uint32_t)nx * (uint32_t)nrow : 0u;
+  const int64_t ql = run0 * 64 + lane;
+  const uint32_t fq = (FLAT && D != 0) ? (uint32_t)(ql < nq ? ql : nq - 1) : 0u;
+  const uint32_t fr = FLAT ? fast_div(fq, fnx) : 0u, fx = fq - fr * (uint32_t)nx;
+  if (FLAT ? run0 >= nruns : ((D != 0 || ROWS) && (row >= nrow || (D != 0 && seg >= words)))) {
     if (lane == 0) counts_next[wave] = 0;
     return;
   }
   uint32_t *reg = list_next + wave * rsize;
   int nlist = 0;  // wavefront-uniform
   const uint64_t below = (1ull << lane) - 1;
-  bool live = FLAT ? q0 + lane < nq : tile_ok && x < nx;  // (an idle x-sweep wavefront has no live lane)
+  bool live = FLAT ? ql < nq : tile_ok && x < nx;  // (an idle x-sweep wavefront has no live lane)
   int xs = live ? x : nx - 1;  // dead lanes shadow a valid cell, never store
   const int64_t n3 = (int64_t)nx * ny * nz;
   const int64_t nbits = (int64_t)nz * ny * words;
@@ -316,19 +331,28 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
   const double *f_g = fmix + (int64_t)t0 * n3;
   uint64_t *b_g = ccbits + (int64_t)t0 * nbits;
 
-  // (a tracer's cells and half words stay below 2^32: a row of two or more
+  // (a tracer's cells and half words stay below 2^32: a plane of two or more
   // cells has no more half words than cells)
   const uint32_t fcell = D == 1 ? fr * ((uint32_t)ny * nx) + fx : fq;
-  const uint32_t fword = fr * (D == 1 ? (uint32_t)ny * words : (uint32_t)words) * 2u + (fx >> 5);
   auto cell = [&](int xx, int mm) -> int64_t {
     if (FLAT) return (int64_t)(fcell + (uint32_t)mm * (D == 1 ? (uint32_t)nx : (uint32_t)nx * ny));
     if (D == 1) return ((int64_t)row * ny + mm) * nx + xx;
     return ((int64_t)mm * ny + row) * nx + xx;
   };
+  // the c_c word of the wavefront's cells at position mm
   auto bitword = [&](int mm) -> int64_t {
-    if (FLAT) return (int64_t)(fword + (uint32_t)mm * (D == 1 ? (uint32_t)words : (uint32_t)ny * words) * 2u);
+    if (FLAT) return (int64_t)mm * (D == 1 ? yruns : zruns) + run0;
     if (D == 1) return ((int64_t)row * ny + mm) * words + seg;
     return ((int64_t)mm * ny + row) * words + seg;
+  };
+  // flat: number of the lane's cell at position mm in the plane that its word is of
+  auto bit_of = [&](int mm) -> uint32_t {
+    return (D == 1 || cc == kReadCcY) ? (uint32_t)mm * (uint32_t)nx + fx : fq;
+  };
+  // and the half word with it
+  auto half_of = [&](int mm) -> int64_t {
+    const uint32_t plane = D == 1 ? fr * zruns : (cc == kReadCcY ? fr * yruns : (uint32_t)mm * zruns);
+    return (int64_t)(plane * 2u + (bit_of(mm) >> 5));
   };
   // flux through the lower face of cell pu: donor = the lower cell (value cl)
   // if s > 0, else the upper cell (value cu); a mixed donor's flux is in fmix
@@ -339,27 +363,28 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
     if (mixed) fv = f_g[t * n3 + pu];
     return mixed ? fv : ((sv == 0.0) ? 0.0 : sv * cd);
   };
-  // the c_c bit words of row word wrow that finish() reads (unless this
-  // sweep writes them), loaded ahead of their use so their latency overlaps
-  // other work; flat: the lane's own word, the half with its bit
+  // the c_c words at w that finish() reads (unless this sweep writes them),
+  // loaded ahead of their use so their latency overlaps other work; flat: the
+  // lane's own, the half with its bit
   using word_t = std::conditional_t<FLAT, uint32_t, uint64_t>;
   const word_t *bw_g = (const word_t *)b_g;
   constexpr int kHalves = sizeof(uint64_t) / sizeof(word_t);
-  auto load_words = [&](int64_t wrow, word_t *ccw) {
+  auto load_words = [&](int64_t w, word_t *ccw) {
     const bool ok = FLAT || (tile_ok && seg < words);  // idle: no cells
 #pragma unroll
-    for (int t = 0; t < G; ++t) ccw[t] = ((FLAT || !write_cc) && ok) ? bw_g[t * nbits * kHalves + wrow] : (word_t)0;
+    for (int t = 0; t < G; ++t) ccw[t] = (!write_cc && ok) ? bw_g[t * nbits * kHalves + w] : (word_t)0;
   };
-  // new value of cell pc, its c_c bit, and its entry in the next list
-  auto finish = [&](int t, double cold, double f_lo, double f_hi, double s_lo, double s_hi, int64_t pc, int64_t wrow,
-                    word_t ccw) {
+  // new value of cell pc, its c_c bit (bit sh of ccw, or to be written to word
+  // w), and its entry in the next list
+  auto finish = [&](int t, double cold, double f_lo, double f_hi, double s_lo, double s_hi, int64_t pc, int64_t w,
+                    word_t ccw, int sh) {
     double ccv;
-    if (!FLAT && write_cc) {
+    if (write_cc) {
       const uint64_t word = __ballot(live && cold > 0.5);
-      if (lane == 0 && tile_ok && seg < words) b_g[t * nbits + wrow] = word;
+      if (lane == 0 && (FLAT || (tile_ok && seg < words))) b_g[t * nbits + w] = word;
       ccv = (cold > 0.5) ? 1.0 : 0.0;
     } else {
-      ccv = ((ccw >> (FLAT ? (int)(fx & 31u) : lane)) & 1u) ? 1.0 : 0.0;
+      ccv = ((ccw >> sh) & 1u) ? 1.0 : 0.0;
     }
     const double cn = (cold - (f_hi - f_lo)) + ccv * (s_hi - s_lo);
     // streamed out (not read again by this pass): a non-temporal store
@@ -399,12 +424,13 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
 #pragma unroll
       for (int t = 0; t < G; ++t) c_nx[t] = c_g[t * n3 + pu];
     }
-    load_words(bitword(m0), ccw);
+    load_words(FLAT ? half_of(m0) : bitword(m0), ccw);
     for (int m = m0 + 1; m <= m1; ++m) {
       const int mm = (m == nm) ? 0 : m;
       const int64_t pu = cell(xs, mm);
       const int64_t pc = cell(xs, m - 1);
       const int64_t wrow = bitword(m - 1);
+      const int sh = FLAT ? (int)(bit_of(m - 1) & 31u) : lane;
       const double s_hi = s_nx;
       double cu[G], fhi[G];
       word_t ccc[G];
@@ -418,40 +444,42 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
         s_nx = s[pn];
 #pragma unroll
         for (int t = 0; t < G; ++t) c_nx[t] = c_g[t * n3 + pn];
-        load_words(bitword(m), ccw);
+        load_words(FLAT ? half_of(m) : bitword(m), ccw);
       }
 #pragma unroll
       for (int t = 0; t < G; ++t) fhi[t] = flux(t, s_hi, cm[t], cu[t], pu);
 #pragma unroll
       for (int t = 0; t < G; ++t) {
-        finish(t, cm[t], flo[t], fhi[t], s_lo, s_hi, pc, wrow, ccc[t]);
+        finish(t, cm[t], flo[t], fhi[t], s_lo, s_hi, pc, wrow, ccc[t], sh);
         flo[t] = fhi[t];
         cm[t] = cu[t];
       }
       s_lo = s_hi;
     }
   } else if constexpr (FLAT) {
-    // ---- x-sweep over runs of 64 consecutive cells of the tracer, rows not
+    // ---- x-sweep over runs of 64 consecutive cells of a z-plane, rows not
     // regarded. Lanes take their neighbours inside a run by wave shifts; lane 0
     // takes the previous run's last cell, lane 63 the next run's first; a row's
     // first and last cell (in any lane) load the other one, where the row
-    // closes. The next run, its rows' ends and its bit words are loaded one
-    // run ahead.
+    // closes, as do the plane's. The next run, its rows' ends and its words are
+    // loaded one run ahead.
     auto readlane_d = [](double v, int l) {
       const long long b = __double_as_longlong(v);
       const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
       return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
     };
-    const uint32_t last_cell = (uint32_t)(n3 - 1);
-    auto load_run = [&](int64_t q, int off, uint32_t &p, uint32_t &xk, double *cv, double &sv, double *cw, double &sw_,
-                        word_t *ccw) {
-      p = (q + off < n3) ? (uint32_t)(q + off) : last_cell;
-      const uint32_t rk = fast_div(p, fnx);
-      xk = p - rk * (uint32_t)nx;
+    // run k of plane z, its lanes' cells p at x = xk (lane of the run: off)
+    auto load_run = [&](uint32_t z, uint32_t k, int off, uint32_t &p, uint32_t &xk, double *cv, double &sv, double *cw,
+                        double &sw_, word_t *ccw) {
+      const uint32_t q = (k * 64u + off < nq) ? k * 64u + off : nq - 1;
+      const uint32_t rk = fast_div(q, fnx);
+      xk = q - rk * (uint32_t)nx;
+      p = z * nq + q;
       sv = s[p];
 #pragma unroll
       for (int t = 0; t < G; ++t) cv[t] = c_g[t * n3 + p];
-      load_words(rk * (uint32_t)words * 2u + (xk >> 5), ccw);
+      if (cc == kReadCcY) load_words(rk * yruns * 2u + ((z * (uint32_t)nx + xk) >> 5), ccw);
+      else load_words(z * zruns * 2u + (q >> 5), ccw);
       sw_ = 0.0;
 #pragma unroll
       for (int t = 0; t < G; ++t) cw[t] = 0.0;
@@ -466,17 +494,26 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
     double c_cur[G], c_nxt[G], w_cur[G], w_nxt[G], c_prv[G];
     double s_cur, s_nxt, ws_cur, ws_nxt;
     word_t ccw[G], ccw_nxt[G];
-    uint32_t p, p_nxt, x_nxt;
-    const int64_t q1 = (q0 + (int64_t)(chunk / 2) * 64 < n3) ? q0 + (int64_t)(chunk / 2) * 64 : n3;
-    load_run(q0, lane, p, fx, c_cur, s_cur, w_cur, ws_cur, ccw);
+    uint32_t p, p_nxt, x_cur, x_nxt;
+    const int64_t run1 = (run0 + chunk / 2 < nruns) ? run0 + chunk / 2 : nruns;
+    uint32_t z = (uint32_t)run0 / zruns, k = (uint32_t)run0 - z * zruns;
+    load_run(z, k, lane, p, x_cur, c_cur, s_cur, w_cur, ws_cur, ccw);
+    const int64_t p_prv = (int64_t)z * nq + (k > 0 ? k * 64u - 1 : 0);
 #pragma unroll
-    for (int t = 0; t < G; ++t) c_prv[t] = c_g[t * n3 + (q0 > 0 ? q0 - 1 : 0)];
-    for (int64_t q = q0; q < q1; q += 64) {
+    for (int t = 0; t < G; ++t) c_prv[t] = c_g[t * n3 + p_prv];
+    for (int64_t r = run0; r < run1; ++r) {
+      uint32_t zn = z, kn = k + 1;
+      if (kn == zruns) {
+        kn = 0;
+        zn = (z + 1 < (uint32_t)nz) ? z + 1 : z;
+      }
       // (past the wavefront's last run only the next cell is of use)
-      load_run(q + 64, q + 64 < q1 ? lane : 0, p_nxt, x_nxt, c_nxt, s_nxt, w_nxt, ws_nxt, ccw_nxt);
-      live = q + lane < n3;
-      const bool beg = fx == 0u, end = fx == (uint32_t)nx - 1u;
-      const uint32_t pr = end ? p - fx : p + 1u;
+      load_run(zn, kn, r + 1 < run1 ? lane : 0, p_nxt, x_nxt, c_nxt, s_nxt, w_nxt, ws_nxt, ccw_nxt);
+      live = k * 64u + lane < nq;
+      const int64_t wrow = (int64_t)z * zruns + k;
+      const int sh = (int)((cc == kReadCcY ? z * (uint32_t)nx + x_cur : (uint32_t)lane) & 31u);
+      const bool beg = x_cur == 0u, end = x_cur == (uint32_t)nx - 1u;
+      const uint32_t pr = end ? p - x_cur : p + 1u;
       const double s_up = from_lane_above(s_cur), s_e = readlane_d(s_nxt, 0);
       const double s_hi = end ? ws_cur : (lane == 63 ? s_e : s_up);
       double cl[G], cr[G], flo[G], fhi[G];
@@ -494,7 +531,7 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
         fhi[t] = flux(t, s_hi, c_cur[t], cr[t], pr);
       }
 #pragma unroll
-      for (int t = 0; t < G; ++t) finish(t, c_cur[t], flo[t], fhi[t], s_cur, s_hi, p, 0, ccw[t]);
+      for (int t = 0; t < G; ++t) finish(t, c_cur[t], flo[t], fhi[t], s_cur, s_hi, p, wrow, ccw[t], sh);
 #pragma unroll
       for (int t = 0; t < G; ++t) {
         c_prv[t] = readlane_d(c_cur[t], 63);
@@ -505,7 +542,9 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
       s_cur = s_nxt;
       ws_cur = ws_nxt;
       p = p_nxt;
-      fx = x_nxt;
+      x_cur = x_nxt;
+      z = zn;
+      k = kn;
     }
   } else if constexpr (ROWS) {
     // ---- x-sweep along whole rows: the wavefront takes its row's 64-cell
@@ -597,7 +636,7 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
         fhi[t] = flux(t, s_hi, c_cur[t], cr[t], pr);
       }
 #pragma unroll
-      for (int t = 0; t < G; ++t) finish(t, c_cur[t], flo[t], fhi[t], s_lo, s_hi, pc, wrow, ccw[t]);
+      for (int t = 0; t < G; ++t) finish(t, c_cur[t], flo[t], fhi[t], s_lo, s_hi, pc, wrow, ccw[t], lane);
       // carry to the next step
 #pragma unroll
       for (int t = 0; t < G; ++t) {
@@ -696,7 +735,7 @@ __device__ __forceinline__ void stream_body(const double *__restrict__ cin, doub
 #pragma unroll
       for (int t = 0; t < G; ++t) {
         const uint64_t ccw = (!write_cc && tile_ok && seg < words) ? b_g[t * nbits + wrow] : 0ull;
-        finish(t, c0[t], flo[t], fhi[t], s_lo, s_hi, pc, wrow, ccw);
+        finish(t, c0[t], flo[t], fhi[t], s_lo, s_hi, pc, wrow, ccw, lane);
       }
     }
   }
@@ -721,17 +760,17 @@ __host__ __device__ inline int largest_group(int ntr) {
 template <int D, int GM, int WPB = 4>
 __device__ __forceinline__ void stream_group(const double *__restrict__ cin, double *__restrict__ cout,
                                              const double *__restrict__ s, const double *__restrict__ fmix,
-                                             uint64_t *__restrict__ ccbits, int write_cc, int ntr, int nx, int ny,
+                                             uint64_t *__restrict__ ccbits, int cc, int ntr, int nx, int ny,
                                              int nz, int words, int chunk, uint32_t *__restrict__ list_next,
                                              int *__restrict__ counts_next, int64_t region0, int rsize,
                                              const GroupTile &g, int gx, int gy, const FastDiv &fnx) {
   const int small = num_groups(ntr) * GM - ntr;  // groups of GM - 1, the last ones
   const int large = num_groups(ntr) - small;
   if (GM == 1 || g.grp < large)
-    stream_body<D, GM, WPB>(cin, cout, s, fmix, ccbits, write_cc, g.grp * GM, nx, ny, nz, words, chunk, list_next,
+    stream_body<D, GM, WPB>(cin, cout, s, fmix, ccbits, cc, g.grp * GM, nx, ny, nz, words, chunk, list_next,
                             counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy, fnx);
   else if constexpr (GM > 1)
-    stream_body<D, GM - 1, WPB>(cin, cout, s, fmix, ccbits, write_cc, large * GM + (g.grp - large) * (GM - 1), nx, ny,
+    stream_body<D, GM - 1, WPB>(cin, cout, s, fmix, ccbits, cc, large * GM + (g.grp - large) * (GM - 1), nx, ny,
                                 nz, words, chunk, list_next, counts_next, region0, rsize, g.bx, g.by, g.bz, gx, gy, fnx);
 }
 
@@ -743,16 +782,14 @@ static inline int64_t stream_waves(int d, int nx, int ny, int nz, int chunk, int
   return ((d == 0 && wpb > 0 && !flat) ? wpb : 4) * (int64_t)g.gx * g.gy * g.gz;
 }
 
-// Whether the sweeps that read the c_c words (the second and third of a step)
-// take the flat layout. A row of 134 cells leaves 58 of its 192 lanes idle in
-// the layout by segments; by cells every wavefront but the last of a plane is
-// full (one step, by segments -> y- and z-sweeps flat -> all flat:
-// 134x129x141 x 7 444 -> 420 -> 398 us; 65x300x300 x 8 1136 -> 1017 -> 954;
-// 250^3 x 8, 2% idle, 2138 -> 2115 -> 2048; 32 boxes of 64 to 192 cells, three
-// steps, 25.4 -> 24.6 -> 23.6 ms). Rows of whole segments fill them either way
-// and keep scalar bit words and addresses; a plane of more than 65535
-// workgroups is no grid of the plain path, and at nx = 1 a row's two half words
-// could number 2^32.
+// Whether the sweeps take the flat layout. A row of 134 cells leaves 58 of its
+// 192 lanes idle in the layout by segments; by cells every wavefront but the
+// last of a plane is full (one step, by segments -> flat: 134x129x141 x 7 444 ->
+// 372 us; 65x300x300 x 8 1136 -> 843; 250^3 x 8, 2% idle, 2138 -> 2050; 32 boxes
+// of 64 to 192 cells, three steps, 25.4 -> 23.2 ms). Rows of whole segments fill
+// them either way and keep scalar words and addresses; a plane of more than
+// 65535 workgroups is no grid of the plain path, and at nx = 1 a tracer's half
+// words could number 2^32.
 static inline bool flat_rows(int nx, int ny, int nz) {
   const int64_t widest = (int64_t)nx * (ny > nz ? ny : nz);
   return nx > 1 && nx % 64 != 0 && widest <= 65535ll * 256;
@@ -763,10 +800,8 @@ static inline int region_size(int chunk) { return 64 * chunk * kMaxGroup; }
 static inline int64_t max_regions(int nx, int ny, int nz, int ntr, int chunk, int wpb = 4) {
   int64_t r = 0;
   for (int d = 0; d < 3; ++d) {
-    const int64_t w = stream_waves(d, nx, ny, nz, chunk, wpb) * num_groups(ntr);
+    const int64_t w = stream_waves(d, nx, ny, nz, chunk, wpb, flat_rows(nx, ny, nz)) * num_groups(ntr);
     r = w > r ? w : r;
-    const int64_t wf = stream_waves(d, nx, ny, nz, chunk, wpb, flat_rows(nx, ny, nz)) * num_groups(ntr);
-    r = wf > r ? wf : r;
   }
   const int64_t total = (int64_t)ntr * nx * ny * nz;
   const int64_t scan = (total + region_size(chunk) - 1) / region_size(chunk);

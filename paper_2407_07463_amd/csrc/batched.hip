@@ -20,7 +20,7 @@ namespace {
 
 struct BoxDev {
   int nx, ny, nz, ntr, words;
-  int flat;  // sweeps that read the c_c words: the flat layout (flat_rows)
+  int flat;  // the flat layout (flat_rows)
   int xwpb;  // x-sweep: 0 whole-row wavefronts (a row's cells fit one list region), else 4 per workgroup
   Divisors dv;
   double *f[3];  // the caller's field, its ping-pong copy and the third one of an odd number of sweeps
@@ -76,13 +76,12 @@ __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes
   }
 }
 
-// work items: 4-wavefront tiles of a streaming pass. FLAT: a sweep that
-// reads the c_c words, with the tables made for it; each box has the layout
-// that flat_rows gives it.
+// work items: 4-wavefront tiles of a streaming pass. FLAT: some boxes have the
+// flat layout.
 template <int D, bool FLAT>
 __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
                                                   int nseg, int64_t nitems, int chunk, int rsize, int src, int dst,
-                                                  int nxt, int write_cc) {
+                                                  int nxt, int cc) {
   for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
     const Seg sg = segs[find_seg(segs, nseg, item)];
     const BoxDev &b = boxes[sg.box];
@@ -92,18 +91,14 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
     const int gm = largest_group(b.ntr);  // uniform over the workgroup
     auto pass = [&](auto GM) {
       constexpr int G = decltype(GM)::value;
-      if constexpr (FLAT) {
-        if (b.flat) {
-          stream_group<D, G, kFlat>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, 0, b.ntr, b.nx, b.ny, b.nz, b.words,
-                                    chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
-          return;
-        }
-      }
-      if (D == 0 && b.xwpb == 0)
-        stream_group<D, G, 0>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz,
+      if (FLAT && b.flat)
+        stream_group<D, G, kFlat>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, cc, b.ntr, b.nx, b.ny, b.nz, b.words,
+                                  chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
+      else if (D == 0 && b.xwpb == 0)
+        stream_group<D, G, 0>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, cc, b.ntr, b.nx, b.ny, b.nz,
                               b.words, chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
       else
-        stream_group<D, G>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, write_cc, b.ntr, b.nx, b.ny, b.nz, b.words,
+        stream_group<D, G>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, cc, b.ntr, b.nx, b.ny, b.nz, b.words,
                            chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
     };
     if (gm == 4) pass(std::integral_constant<int, 4>{});
@@ -137,13 +132,12 @@ struct Plan {
   size_t off_scan;
   int n_scan;
   int64_t items_scan;
-  // entry d + 3 * reads: a sweep along d that writes (0) or reads (1) the c_c words
-  size_t off_plic[6];  // list regions after the sweep
-  int n_plic[6];
-  int64_t items_plic[6];
-  size_t off_stream[6];  // its streaming pass
-  int n_stream[6];
-  int64_t items_stream[6];
+  size_t off_plic[3];  // list regions after a sweep along d
+  int n_plic[3];
+  int64_t items_plic[3];
+  size_t off_stream[3];  // streaming passes along d
+  int n_stream[3];
+  int64_t items_stream[3];
 };
 
 // x-sweep layout of a box: whole-row wavefronts when a row has at most `chunk`
@@ -243,40 +237,38 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
     pl.items_scan += s.nitems;
     ++pl.n_scan;
   }
-  for (int e = 0; e < 6; ++e) {
-    begin_table(pl.off_plic[e], pl.n_plic[e], pl.items_plic[e]);
+  for (int d = 0; d < 3; ++d) {
+    begin_table(pl.off_plic[d], pl.n_plic[d], pl.items_plic[d]);
     for (int i = 0; i < nboxes; ++i) {
       const vofmt_box &b = boxes[i];
       Seg s{};
-      s.item0 = pl.items_plic[e];
+      s.item0 = pl.items_plic[d];
       const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-      s.nitems = stream_waves(e % 3, b.nx, b.ny, b.nz, chunk, xw, e >= 3 && bd[i].flat) * num_groups(b.ntracers);
+      s.nitems = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, bd[i].flat) * num_groups(b.ntracers);
       s.box = i;
       seg_all.push_back(s);
-      pl.items_plic[e] += s.nitems;
-      ++pl.n_plic[e];
+      pl.items_plic[d] += s.nitems;
+      ++pl.n_plic[d];
     }
   }
-  for (int e = 0; e < 6; ++e) {
-    const int d = e % 3;
-    begin_table(pl.off_stream[e], pl.n_stream[e], pl.items_stream[e]);
+  for (int d = 0; d < 3; ++d) {
+    begin_table(pl.off_stream[d], pl.n_stream[d], pl.items_stream[d]);
     for (int i = 0; i < nboxes; ++i) {
       const vofmt_box &b = boxes[i];
       const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-      const bool flat = e >= 3 && bd[i].flat;
-      const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw, flat);
+      const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw, bd[i].flat);
       Seg s{};
-      s.item0 = pl.items_stream[e];
+      s.item0 = pl.items_stream[d];
       s.gx = tg.gx;
       s.gy = tg.gy;
       s.gz = tg.gz;
       s.ngrp = num_groups(b.ntracers);
       s.nitems = (int64_t)tg.gx * tg.gy * tg.gz * s.ngrp;
       s.box = i;
-      s.gstride = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, flat);
+      s.gstride = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, bd[i].flat);
       seg_all.push_back(s);
-      pl.items_stream[e] += s.nitems;
-      ++pl.n_stream[e];
+      pl.items_stream[d] += s.nitems;
+      ++pl.n_stream[d];
     }
   }
   // tables after the per-box buffers: boxes, then segments
@@ -287,39 +279,36 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
   // convert segment indices to byte offsets
   auto to_bytes = [&](size_t idx) { return seg_base + idx * sizeof(Seg); };
   pl.off_scan = to_bytes(pl.off_scan);
-  for (int e = 0; e < 6; ++e) {
-    pl.off_plic[e] = to_bytes(pl.off_plic[e]);
-    pl.off_stream[e] = to_bytes(pl.off_stream[e]);
+  for (int d = 0; d < 3; ++d) {
+    pl.off_plic[d] = to_bytes(pl.off_plic[d]);
+    pl.off_stream[d] = to_bytes(pl.off_stream[d]);
   }
   return off;
 }
 
-// prev: the plan's entry of the sweep before, or -1
 template <int D>
-static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, int prev, int src, int dst,
-                          int cur, int wcc, hipStream_t st) {
+static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, int prev_d, int src, int dst,
+                          int cur, int cc, hipStream_t st) {
   const Seg *psegs;
   int pn;
   int64_t pitems;
-  if (prev < 0) {
+  if (prev_d < 0) {
     psegs = (const Seg *)(slab + pl.off_scan);
     pn = pl.n_scan;
     pitems = pl.items_scan;
   } else {
-    psegs = (const Seg *)(slab + pl.off_plic[prev]);
-    pn = pl.n_plic[prev];
-    pitems = pl.items_plic[prev];
+    psegs = (const Seg *)(slab + pl.off_plic[prev_d]);
+    pn = pl.n_plic[prev_d];
+    pitems = pl.items_plic[prev_d];
   }
   hipLaunchKernelGGL((k_plic_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize, src, cur);
-  const int e = D + (wcc ? 0 : 3);
-  const Seg *ssegs = (const Seg *)(slab + pl.off_stream[e]);
-  const dim3 grid(pl.grid), block(256);
-  if (!wcc && pl.any_flat)
-    hipLaunchKernelGGL((k_stream_b<D, true>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
-                       pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
+  const Seg *ssegs = (const Seg *)(slab + pl.off_stream[D]);
+  if (pl.any_flat)
+    hipLaunchKernelGGL((k_stream_b<D, true>), dim3(pl.grid), dim3(256), 0, st, dboxes, ssegs, pl.n_stream[D],
+                       pl.items_stream[D], pl.chunk, pl.rsize, src, dst, cur ^ 1, cc);
   else
-    hipLaunchKernelGGL((k_stream_b<D, false>), grid, block, 0, st, dboxes, ssegs, pl.n_stream[e], pl.items_stream[e],
-                       pl.chunk, pl.rsize, src, dst, cur ^ 1, wcc);
+    hipLaunchKernelGGL((k_stream_b<D, false>), dim3(pl.grid), dim3(256), 0, st, dboxes, ssegs, pl.n_stream[D],
+                       pl.items_stream[D], pl.chunk, pl.rsize, src, dst, cur ^ 1, cc);
 }
 
 extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, int64_t step0,
@@ -395,16 +384,16 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   VOFMT_HIP(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
   hipLaunchKernelGGL(k_scan_b, dim3(pl.grid), dim3(256), 0, cs, dboxes, (const Seg *)(slab + pl.off_scan), pl.n_scan,
                      pl.items_scan, pl.rsize);
-  int src = 0, dst = 1, cur = 0, prev = -1;
+  int src = 0, dst = 1, cur = 0, prev_d = -1;
   for (int32_t st = 0; st < nsteps; ++st) {
     const int64_t g = step0 + st;
     for (int r = 0; r < 3; ++r) {
       const int d = (int)((g + r) % 3);
-      const int wcc = (r == 0);
-      if (d == 0) enqueue_sweep<0>(slab, pl, dboxes, prev, src, dst, cur, wcc, cs);
-      else if (d == 1) enqueue_sweep<1>(slab, pl, dboxes, prev, src, dst, cur, wcc, cs);
-      else enqueue_sweep<2>(slab, pl, dboxes, prev, src, dst, cur, wcc, cs);
-      prev = d + (wcc ? 0 : 3);
+      const int cc = cc_mode(g, r);
+      if (d == 0) enqueue_sweep<0>(slab, pl, dboxes, prev_d, src, dst, cur, cc, cs);
+      else if (d == 1) enqueue_sweep<1>(slab, pl, dboxes, prev_d, src, dst, cur, cc, cs);
+      else enqueue_sweep<2>(slab, pl, dboxes, prev_d, src, dst, cur, cc, cs);
+      prev_d = d;
       const int was = src;
       src = dst;
       dst = (third && st == 0) ? (r == 0 ? 2 : (r == 1 ? 0 : 1)) : was;
