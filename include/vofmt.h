@@ -453,7 +453,8 @@ typedef struct {
 /*
  * boxes  : HOST array of nboxes descriptors (device pointers inside). Boxes
  *          must not share fields.
- * tuning : HOST, nullable (chunk 32, 8 workgroups per CU).
+ * tuning : HOST, nullable (chunk by the number of wavefronts, no fixed grid: a
+ *          workgroup per work item). Results do not depend on it.
  * The launch sequence of all sweeps is captured into a HIP graph on the
  * context's own stream and launched on `stream`; a call with the same boxes,
  * tuning, nsteps and step0 mod 3 relaunches the cached graph. A call that

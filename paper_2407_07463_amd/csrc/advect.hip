@@ -7,8 +7,6 @@ using namespace advect;
 
 namespace {
 
-constexpr int kMaxChunk = 32;       // cells per thread along its marching axis, at most
-constexpr int64_t kWaves = 8192;  // wavefronts a sweep should have: 8 per SIMD
 constexpr int kXWaves = 8;  // wavefronts per workgroup of the x-sweep: a 512-cell row per workgroup
 
 __global__ __launch_bounds__(256) void k_scan_mixed(const double *__restrict__ c, int64_t total,
@@ -116,11 +114,12 @@ static inline int x_wpb(int words, int chunk) { return words <= chunk ? 0 : kXWa
 // leaves the second at 667, 16384 and 32768 are within 2% of 8192 on all.
 static int pick_chunk(int nx, int ny, int nz, int ntr) {
   const int words = (nx + 63) / 64;
+  const bool flat = flat_rows(nx, ny, nz);
   int chunk = kMaxChunk;
-  while (chunk > 4 && words <= chunk / 2) {
+  while (chunk > 4 && (flat || words <= chunk / 2)) {
     int64_t least = INT64_MAX;
     for (int d = 0; d < 3; ++d) {
-      const int64_t w = stream_waves(d, nx, ny, nz, chunk, d == 0 ? x_wpb(words, chunk) : 4, flat_rows(nx, ny, nz)) *
+      const int64_t w = stream_waves(d, nx, ny, nz, chunk, d == 0 ? x_wpb(words, chunk) : 4, flat) *
                         num_groups(ntr);
       least = w < least ? w : least;
     }
@@ -222,7 +221,7 @@ extern "C" int vofmt_advect(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, 
   const int64_t total = (int64_t)ntracers * n3;
   const int span = scan_span(total);
   const int64_t scanreg = (total + span - 1) / span;
-  int64_t maxreg = max_regions(nx, ny, nz, ntracers, chunk, x_wpb(words, chunk));
+  int64_t maxreg = max_regions(nx, ny, nz, ntracers, chunk, x_wpb(words, chunk), flat_rows(nx, ny, nz));
   if (maxreg * rsize < scanreg * span) maxreg = (scanreg * span + rsize - 1) / rsize;
   const int64_t maxcnt = maxreg > scanreg ? maxreg : scanreg;
   uint32_t *lists = (uint32_t *)scratch(ctx, SLOT_MIXLIST, sizeof(uint32_t) * 2 * (size_t)maxreg * rsize);

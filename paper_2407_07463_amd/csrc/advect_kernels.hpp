@@ -40,6 +40,8 @@
 namespace advect {
 
 constexpr int kMaxGroup = 4;  // tracers per streaming pass (register budget)
+constexpr int kMaxChunk = 32;     // cells per thread along its marching axis, at most (unless tuned)
+constexpr int64_t kWaves = 8192;  // wavefronts a sweep should have: 8 per SIMD
 
 // Workgroup grid of a streaming pass (4 wavefronts per workgroup, or wpb
 // for the x-sweep).
@@ -787,20 +789,20 @@ static inline int64_t stream_waves(int d, int nx, int ny, int nz, int chunk, int
 // last of a plane is full (one step, by segments -> flat: 134x129x141 x 7 444 ->
 // 372 us; 65x300x300 x 8 1136 -> 843; 250^3 x 8, 2% idle, 2138 -> 2050; 32 boxes
 // of 64 to 192 cells, three steps, 25.4 -> 23.2 ms). Rows of whole segments fill
-// them either way and keep scalar words and addresses; a plane of more than
-// 65535 workgroups is no grid of the plain path, and at nx = 1 a tracer's half
-// words could number 2^32.
-static inline bool flat_rows(int nx, int ny, int nz) {
-  const int64_t widest = (int64_t)nx * (ny > nz ? ny : nz);
-  return nx > 1 && nx % 64 != 0 && widest <= 65535ll * 256;
+// them either way and keep scalar words and addresses.
+static inline bool flat_possible(int nx, int ny, int nz) {
+  // (a plane of more than 65535 workgroups is no grid of the plain path; at
+  // nx = 1 a tracer's half words could number 2^32)
+  return nx > 1 && (int64_t)nx * (ny > nz ? ny : nz) <= 65535ll * 256;
 }
+static inline bool flat_rows(int nx, int ny, int nz) { return nx % 64 != 0 && flat_possible(nx, ny, nz); }
 // List entries per region: every cell a wavefront of a streaming pass writes.
 static inline int region_size(int chunk) { return 64 * chunk * kMaxGroup; }
 // Regions of one list: the largest streaming sweep, or the initial scan.
-static inline int64_t max_regions(int nx, int ny, int nz, int ntr, int chunk, int wpb = 4) {
+static inline int64_t max_regions(int nx, int ny, int nz, int ntr, int chunk, int wpb, bool flat) {
   int64_t r = 0;
   for (int d = 0; d < 3; ++d) {
-    const int64_t w = stream_waves(d, nx, ny, nz, chunk, wpb, flat_rows(nx, ny, nz)) * num_groups(ntr);
+    const int64_t w = stream_waves(d, nx, ny, nz, chunk, wpb, flat) * num_groups(ntr);
     r = w > r ? w : r;
   }
   const int64_t total = (int64_t)ntr * nx * ny * nz;

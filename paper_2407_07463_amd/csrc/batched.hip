@@ -1,13 +1,13 @@
 // Batched advection: many boxes of uneven sizes and tracer counts advanced
-// together. Every pass of a sweep is one persistent launch for all boxes: a
-// fixed grid walks a flattened table of work items (box, tracer group, tile)
-// and runs the same sweep bodies as the plain path, so each box's result is
+// together. Every pass of a sweep is one launch for all boxes over a flattened
+// table of work items (box, tracer group, tile), a workgroup to an item or, with
+// a tuning, a fixed grid that walks the table, and it runs the same sweep bodies as the plain path, so each box's result is
 // bit-identical to advecting it alone. The whole multi-step sequence is
 // captured once into a HIP graph and replayed with a single graph launch;
 // a later call with the same configuration reuses the graph.
 //
 // Tunables (vofmt_tuning): the marching chunk of the streaming passes and the
-// persistent grid size in workgroups per compute unit; the autotuner times a
+// fixed grid's size in workgroups per compute unit; the autotuner times a
 // set of candidates on copies of the fields and returns the fastest.
 #include <cstring>
 #include <type_traits>
@@ -20,7 +20,6 @@ namespace {
 
 struct BoxDev {
   int nx, ny, nz, ntr, words;
-  int flat;  // the flat layout (flat_rows)
   int xwpb;  // x-sweep: 0 whole-row wavefronts (a row's cells fit one list region), else 4 per workgroup
   Divisors dv;
   double *f[3];  // the caller's field, its ping-pong copy and the third one of an odd number of sweeps
@@ -52,11 +51,17 @@ __device__ __forceinline__ int find_seg(const Seg *__restrict__ segs, int nseg, 
   return lo;
 }
 
+// the wavefront's number in the grid, in scalar registers: so are then its
+// segment and box (k_plic_b: 122 -> 92 vector registers, 5 wavefronts a SIMD for
+// 4, 1.55 -> 1.32 ms for three of its launches)
+__device__ __forceinline__ int64_t first_wave() {
+  return (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
 // work items: wavefronts (one list region each)
 __global__ __launch_bounds__(256) void k_scan_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
                                                 int nseg, int64_t nitems, int rsize) {
-  for (int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; gw < nitems;
-       gw += (int64_t)gridDim.x * 4) {
+  for (int64_t gw = first_wave(); gw < nitems; gw += (int64_t)gridDim.x * 4) {
     const Seg sg = segs[find_seg(segs, nseg, gw)];
     const BoxDev &b = boxes[sg.box];
     const int64_t total = (int64_t)b.ntr * b.nx * b.ny * b.nz;
@@ -67,8 +72,7 @@ __global__ __launch_bounds__(256) void k_scan_b(const BoxDev *__restrict__ boxes
 template <int D>
 __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
                                                 int nseg, int64_t nitems, int rsize, int src, int cur) {
-  for (int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; gw < nitems;
-       gw += (int64_t)gridDim.x * 4) {
+  for (int64_t gw = first_wave(); gw < nitems; gw += (int64_t)gridDim.x * 4) {
     const Seg sg = segs[find_seg(segs, nseg, gw)];
     const BoxDev &b = boxes[sg.box];
     plic_body<D>(b.f[src], b.s[D], b.list[cur], b.counts[cur], sg.nitems, rsize, b.fmix, b.nx, b.ny, b.nz, b.dv,
@@ -76,8 +80,7 @@ __global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes
   }
 }
 
-// work items: 4-wavefront tiles of a streaming pass. FLAT: some boxes have the
-// flat layout.
+// work items: 4-wavefront tiles of a streaming pass; FLAT: of the flat layout
 template <int D, bool FLAT>
 __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
                                                   int nseg, int64_t nitems, int chunk, int rsize, int src, int dst,
@@ -91,7 +94,7 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
     const int gm = largest_group(b.ntr);  // uniform over the workgroup
     auto pass = [&](auto GM) {
       constexpr int G = decltype(GM)::value;
-      if (FLAT && b.flat)
+      if constexpr (FLAT)
         stream_group<D, G, kFlat>(b.f[src], b.f[dst], b.s[D], b.fmix, b.bits, cc, b.ntr, b.nx, b.ny, b.nz, b.words,
                                   chunk, b.list[nxt], b.counts[nxt], region0, rsize, g, sg.gx, sg.gy, b.dv.nx);
       else if (D == 0 && b.xwpb == 0)
@@ -125,8 +128,9 @@ inline size_t field_bytes(const vofmt_box &b) {
 
 struct Plan {
   int nboxes;
-  int chunk, rsize, grid;
-  bool any_flat;  // some box has the flat layout
+  int chunk, rsize;
+  int grid;  // workgroups of the persistent launches; 0: one per work item
+  bool flat;  // the boxes have the flat layout
   // table offsets in the slab (bytes) and segment counts
   size_t off_boxes;
   size_t off_scan;
@@ -145,6 +149,20 @@ struct Plan {
 // per workgroup sharing segment ends through LDS.
 int box_xwpb(int words, int chunk) { return words <= chunk ? 0 : 4; }
 
+// Whether the boxes of a batch have the flat layout: all of them, where one gains
+// by it and all can. One kernel for both layouts has the registers of the worst
+// (121 for the x-sweep, which leaves 4 wavefronts a SIMD; flat alone 94; 21.8 -> 21.4 ms for the
+// batch below).
+bool batch_flat(const vofmt_box *boxes, int nboxes) {
+  bool gain = false;
+  for (int i = 0; i < nboxes; ++i) {
+    const vofmt_box &b = boxes[i];
+    if (!flat_possible(b.nx, b.ny, b.nz)) return false;
+    gain = gain || flat_rows(b.nx, b.ny, b.nz);
+  }
+  return gain;
+}
+
 }  // namespace
 
 static int validate(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, const char *who) {
@@ -160,13 +178,46 @@ static int validate(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, cons
   return VOFMT_OK;
 }
 
-static int resolve_tuning(vofmt_ctx *ctx, const vofmt_tuning *tuning, int *chunk, int *wg_per_cu) {
-  *chunk = 32;
-  *wg_per_cu = 8;
-  if (tuning) {
-    *chunk = tuning->chunk;
-    *wg_per_cu = tuning->workgroups_per_cu;
+// Marching chunk without a tuning: as for one box, the longest that gives every
+// sweep kWaves wavefronts, over all boxes (8 boxes of 50 to 90 cells, one step:
+// 396 us at chunk 32, 342 at 16, 331 at 8), and no box's row more segments than
+// cells (its x-sweep is then by whole rows).
+static int pick_batch_chunk(const vofmt_box *boxes, int nboxes) {
+  const bool flat = batch_flat(boxes, nboxes);
+  int rows = 1;
+  for (int i = 0; i < nboxes && !flat; ++i) {
+    const int words = (int)ceil_div(boxes[i].nx, 64);
+    rows = words > rows ? words : rows;
   }
+  int chunk = kMaxChunk;
+  while (chunk > 4 && rows <= chunk / 2) {
+    int64_t waves[3] = {0, 0, 0};
+    for (int i = 0; i < nboxes; ++i) {
+      const vofmt_box &b = boxes[i];
+      const int xw = box_xwpb((int)ceil_div(b.nx, 64), chunk);
+      for (int d = 0; d < 3; ++d)
+        waves[d] += stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, flat) * num_groups(b.ntracers);
+    }
+    if (waves[0] >= kWaves && waves[1] >= kWaves && waves[2] >= kWaves) break;
+    chunk /= 2;
+  }
+  return chunk;
+}
+
+// Without a tuning the grids are one workgroup per work item (wg_per_cu 0): the
+// workgroups of a persistent grid have equal shares of the items, whatever these
+// hold, and at 5 resident on a compute unit the last of 8 run alone (32 boxes of
+// 64 to 192 cells, three steps: 23.3 ms with 8 workgroups per compute unit, 22.1
+// with 32, 21.4 so).
+static int resolve_tuning(vofmt_ctx *ctx, const vofmt_tuning *tuning, const vofmt_box *boxes, int nboxes, int *chunk,
+                          int *wg_per_cu) {
+  if (!tuning) {
+    *chunk = pick_batch_chunk(boxes, nboxes);
+    *wg_per_cu = 0;
+    return VOFMT_OK;
+  }
+  *chunk = tuning->chunk;
+  *wg_per_cu = tuning->workgroups_per_cu;
   if (!(*chunk == 8 || *chunk == 16 || *chunk == 32 || *chunk == 64) || *wg_per_cu < 1 || *wg_per_cu > 32)
     return set_err(ctx, VOFMT_E_ARG, "vofmt tuning: chunk must be 8, 16, 32 or 64 and workgroups_per_cu 1..32");
   return VOFMT_OK;
@@ -178,7 +229,7 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
                           std::vector<Seg> &seg_all, std::vector<size_t> &box_off) {
   const int rsize = region_size(chunk);
   pl.nboxes = nboxes;
-  pl.any_flat = false;
+  pl.flat = batch_flat(boxes, nboxes);
   pl.chunk = chunk;
   pl.rsize = rsize;
   size_t off = 0;
@@ -189,7 +240,7 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
     const int64_t n3 = (int64_t)b.nx * b.ny * b.nz;
     const int words = (int)ceil_div(b.nx, 64);
     const int xw = box_xwpb(words, chunk);
-    const int64_t maxreg = max_regions(b.nx, b.ny, b.nz, b.ntracers, chunk, xw);
+    const int64_t maxreg = max_regions(b.nx, b.ny, b.nz, b.ntracers, chunk, xw, pl.flat);
     const size_t field = sizeof(double) * (size_t)n3 * b.ntracers;
     box_off[6 * i + 0] = off;  // ping-pong field
     off = align256(off + field);
@@ -208,8 +259,6 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
     d.nz = b.nz;
     d.ntr = b.ntracers;
     d.words = words;
-    d.flat = flat_rows(b.nx, b.ny, b.nz);
-    pl.any_flat = pl.any_flat || d.flat;
     d.xwpb = xw;
     d.dv.n3 = make_fastdiv((uint32_t)n3);
     d.dv.nx = make_fastdiv((uint32_t)b.nx);
@@ -244,7 +293,7 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
       Seg s{};
       s.item0 = pl.items_plic[d];
       const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-      s.nitems = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, bd[i].flat) * num_groups(b.ntracers);
+      s.nitems = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, pl.flat) * num_groups(b.ntracers);
       s.box = i;
       seg_all.push_back(s);
       pl.items_plic[d] += s.nitems;
@@ -256,7 +305,7 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
     for (int i = 0; i < nboxes; ++i) {
       const vofmt_box &b = boxes[i];
       const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-      const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw, bd[i].flat);
+      const Tiles tg = stream_tiles(d, b.nx, b.ny, b.nz, chunk, xw, pl.flat);
       Seg s{};
       s.item0 = pl.items_stream[d];
       s.gx = tg.gx;
@@ -265,7 +314,7 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
       s.ngrp = num_groups(b.ntracers);
       s.nitems = (int64_t)tg.gx * tg.gy * tg.gz * s.ngrp;
       s.box = i;
-      s.gstride = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, bd[i].flat);
+      s.gstride = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, pl.flat);
       seg_all.push_back(s);
       pl.items_stream[d] += s.nitems;
       ++pl.n_stream[d];
@@ -286,6 +335,12 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
   return off;
 }
 
+// Grid of a launch over nitems work items, per of them to a workgroup.
+static dim3 grid_of(const Plan &pl, int64_t nitems, int per) {
+  const int64_t all = (nitems + per - 1) / per, most = 1 << 24;  // (a multiple of the 8 XCDs)
+  return dim3(pl.grid > 0 ? (unsigned)pl.grid : (unsigned)(all < most ? all : most));
+}
+
 template <int D>
 static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, int prev_d, int src, int dst,
                           int cur, int cc, hipStream_t st) {
@@ -301,13 +356,15 @@ static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, i
     pn = pl.n_plic[prev_d];
     pitems = pl.items_plic[prev_d];
   }
-  hipLaunchKernelGGL((k_plic_b<D>), dim3(pl.grid), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize, src, cur);
+  hipLaunchKernelGGL((k_plic_b<D>), grid_of(pl, pitems, 4), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize,
+                     src, cur);
   const Seg *ssegs = (const Seg *)(slab + pl.off_stream[D]);
-  if (pl.any_flat)
-    hipLaunchKernelGGL((k_stream_b<D, true>), dim3(pl.grid), dim3(256), 0, st, dboxes, ssegs, pl.n_stream[D],
+  const dim3 grid = grid_of(pl, pl.items_stream[D], 1);
+  if (pl.flat)
+    hipLaunchKernelGGL((k_stream_b<D, true>), grid, dim3(256), 0, st, dboxes, ssegs, pl.n_stream[D],
                        pl.items_stream[D], pl.chunk, pl.rsize, src, dst, cur ^ 1, cc);
   else
-    hipLaunchKernelGGL((k_stream_b<D, false>), dim3(pl.grid), dim3(256), 0, st, dboxes, ssegs, pl.n_stream[D],
+    hipLaunchKernelGGL((k_stream_b<D, false>), grid, dim3(256), 0, st, dboxes, ssegs, pl.n_stream[D],
                        pl.items_stream[D], pl.chunk, pl.rsize, src, dst, cur ^ 1, cc);
 }
 
@@ -318,7 +375,7 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   int rc = validate(ctx, nboxes, boxes, "vofmt_advect_batched");
   if (rc) return rc;
   int chunk, wg;
-  rc = resolve_tuning(ctx, tuning, &chunk, &wg);
+  rc = resolve_tuning(ctx, tuning, boxes, nboxes, &chunk, &wg);
   if (rc) return rc;
   if (nboxes == 0 || nsteps == 0) return VOFMT_OK;
   VOFMT_HIP(ctx, hipSetDevice(ctx->device));
@@ -382,7 +439,7 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   hipStream_t cs = ctx->capture_stream;
   const BoxDev *dboxes = (const BoxDev *)(slab + tab0);
   VOFMT_HIP(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  hipLaunchKernelGGL(k_scan_b, dim3(pl.grid), dim3(256), 0, cs, dboxes, (const Seg *)(slab + pl.off_scan), pl.n_scan,
+  hipLaunchKernelGGL(k_scan_b, grid_of(pl, pl.items_scan, 4), dim3(256), 0, cs, dboxes, (const Seg *)(slab + pl.off_scan), pl.n_scan,
                      pl.items_scan, pl.rsize);
   int src = 0, dst = 1, cur = 0, prev_d = -1;
   for (int32_t st = 0; st < nsteps; ++st) {
@@ -400,7 +457,7 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
       cur ^= 1;
     }
   }
-  if (src != 0) hipLaunchKernelGGL(k_copy_b, dim3(pl.grid), dim3(256), 0, cs, dboxes, nboxes);
+  if (src != 0) hipLaunchKernelGGL(k_copy_b, dim3(pl.grid > 0 ? pl.grid : cus * 8), dim3(256), 0, cs, dboxes, nboxes);
   hipGraph_t graph = nullptr;
   const hipError_t launch_err = hipGetLastError();
   const hipError_t end_err = hipStreamEndCapture(cs, &graph);

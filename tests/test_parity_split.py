@@ -6,7 +6,7 @@ wavefronts of a sweep, the initial scan's span with the number of tracer-cells,
 and the tracers form groups of even sizes. Bar: 1e-12, the volume-fraction
 tolerance of the other advection tests (one or two steps of fields whose
 values are O(1)). Rows that are no multiple of 64 cells take lanes across rows,
-and words of whole planes: planes below, at and above one
+and words of whole planes (a batch all its boxes): planes below, at and above one
 wavefront's and one workgroup's cells, lanes of several rows, in each order of
 the sweeps, alone and in a batch with a box whose rows fill their segments.
 
