@@ -20,8 +20,7 @@ __global__ __launch_bounds__(256) void k_plic(const double *__restrict__ cin, co
                                               const uint32_t *__restrict__ list, const int *__restrict__ counts,
                                               int64_t nregions, int rsize, double *__restrict__ fmix, int nx, int ny,
                                               int nz, Divisors dv) {
-  plic_body<D>(cin, s, list, counts, nregions, rsize, fmix, nx, ny, nz, dv,
-               ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  plic_body<D>(cin, s, list, counts, nregions, rsize, fmix, nx, ny, nz, dv, (int64_t)blockIdx.x * kPlicRegions);
 }
 
 // One streaming pass over every tracer: ngrp groups of GM or GM - 1, group k
@@ -165,7 +164,7 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
   static const char *plic_names[3] = {"k_plic<0>", "k_plic<1>", "k_plic<2>"};
   static const char *stream_names[3] = {"k_stream<0>", "k_stream<1>", "k_stream<2>"};
   int rec = prof_begin(ctx, plic_names[D], stream);
-  hipLaunchKernelGGL((k_plic<D>), dim3(ceil_div(nreg, 4)), dim3(256), 0, stream, cin, s, sb.list[cur],
+  hipLaunchKernelGGL((k_plic<D>), dim3(ceil_div(nreg, kPlicRegions)), dim3(64 * kPlicRegions), 0, stream, cin, s, sb.list[cur],
                      sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
   prof_end(ctx, rec, stream);
   const int wpb = (D == 0) ? x_wpb(words, chunk) : 4;

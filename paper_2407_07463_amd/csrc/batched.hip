@@ -35,6 +35,7 @@ struct BoxDev {
 struct Seg {
   int64_t item0;    // first global work item of the run
   int64_t nitems;   // its length
+  int64_t nregions; // list regions of the box (initial scan, PLIC passes)
   int box;
   int gx, gy, gz;   // tile grid of the streaming pass (x blocks, row blocks, chunks)
   int ngrp;         // tracer groups (group k fills list regions from k * gstride)
@@ -51,32 +52,32 @@ __device__ __forceinline__ int find_seg(const Seg *__restrict__ segs, int nseg, 
   return lo;
 }
 
-// the wavefront's number in the grid, in scalar registers: so are then its
-// segment and box (k_plic_b: 122 -> 92 vector registers, 5 wavefronts a SIMD for
-// 4, 1.55 -> 1.32 ms for three of its launches)
-__device__ __forceinline__ int64_t first_wave() {
-  return (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-}
-
-// work items: wavefronts (one list region each)
-__global__ __launch_bounds__(256) void k_scan_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
-                                                int nseg, int64_t nitems, int rsize) {
-  for (int64_t gw = first_wave(); gw < nitems; gw += (int64_t)gridDim.x * 4) {
-    const Seg sg = segs[find_seg(segs, nseg, gw)];
+// work items of the initial scan and the PLIC passes: kPlicRegions list regions
+// of a box. A workgroup's segment and box are then in scalar registers, as they
+// are not when looked up by a wavefront of its own number: k_plic_b had 122
+// vector registers, now 92, 5 wavefronts a SIMD for 4 (three of its launches on
+// 32 boxes 1.55 -> 1.32 ms, and 1.21 with the 4 regions as one list).
+__global__ __launch_bounds__(64 * kPlicRegions) void k_scan_b(const BoxDev *__restrict__ boxes,
+                                                              const Seg *__restrict__ segs, int nseg, int64_t nitems,
+                                                              int rsize) {
+  for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+    const Seg sg = segs[find_seg(segs, nseg, item)];
     const BoxDev &b = boxes[sg.box];
     const int64_t total = (int64_t)b.ntr * b.nx * b.ny * b.nz;
-    scan_body(b.f[0], total, b.list[0], b.counts[0], sg.nitems, rsize, gw - sg.item0);
+    scan_body(b.f[0], total, b.list[0], b.counts[0], sg.nregions, rsize,
+              (item - sg.item0) * kPlicRegions + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   }
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_plic_b(const BoxDev *__restrict__ boxes, const Seg *__restrict__ segs,
-                                                int nseg, int64_t nitems, int rsize, int src, int cur) {
-  for (int64_t gw = first_wave(); gw < nitems; gw += (int64_t)gridDim.x * 4) {
-    const Seg sg = segs[find_seg(segs, nseg, gw)];
+__global__ __launch_bounds__(64 * kPlicRegions) void k_plic_b(const BoxDev *__restrict__ boxes,
+                                                              const Seg *__restrict__ segs, int nseg, int64_t nitems,
+                                                              int rsize, int src, int cur) {
+  for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+    const Seg sg = segs[find_seg(segs, nseg, item)];
     const BoxDev &b = boxes[sg.box];
-    plic_body<D>(b.f[src], b.s[D], b.list[cur], b.counts[cur], sg.nitems, rsize, b.fmix, b.nx, b.ny, b.nz, b.dv,
-                 gw - sg.item0);
+    plic_body<D>(b.f[src], b.s[D], b.list[cur], b.counts[cur], sg.nregions, rsize, b.fmix, b.nx, b.ny, b.nz, b.dv,
+                 (item - sg.item0) * kPlicRegions);
   }
 }
 
@@ -274,30 +275,29 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
     n = 0;
     items = 0;
   };
+  auto add_regions = [&](int i, int64_t nregions, int &n, int64_t &items) {
+    Seg s{};
+    s.item0 = items;
+    s.nregions = nregions;
+    s.nitems = ceil_div(nregions, kPlicRegions);
+    s.box = i;
+    seg_all.push_back(s);
+    items += s.nitems;
+    ++n;
+  };
   // initial scan: regions of rsize tracer-cells
   begin_table(pl.off_scan, pl.n_scan, pl.items_scan);
   for (int i = 0; i < nboxes; ++i) {
     const int64_t total = (int64_t)boxes[i].ntracers * boxes[i].nx * boxes[i].ny * boxes[i].nz;
-    Seg s{};
-    s.item0 = pl.items_scan;
-    s.nitems = (total + rsize - 1) / rsize;
-    s.box = i;
-    seg_all.push_back(s);
-    pl.items_scan += s.nitems;
-    ++pl.n_scan;
+    add_regions(i, ceil_div(total, rsize), pl.n_scan, pl.items_scan);
   }
   for (int d = 0; d < 3; ++d) {
     begin_table(pl.off_plic[d], pl.n_plic[d], pl.items_plic[d]);
     for (int i = 0; i < nboxes; ++i) {
       const vofmt_box &b = boxes[i];
-      Seg s{};
-      s.item0 = pl.items_plic[d];
       const int xw = box_xwpb((b.nx + 63) / 64, chunk);
-      s.nitems = stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, pl.flat) * num_groups(b.ntracers);
-      s.box = i;
-      seg_all.push_back(s);
-      pl.items_plic[d] += s.nitems;
-      ++pl.n_plic[d];
+      add_regions(i, stream_waves(d, b.nx, b.ny, b.nz, chunk, xw, pl.flat) * num_groups(b.ntracers), pl.n_plic[d],
+                  pl.items_plic[d]);
     }
   }
   for (int d = 0; d < 3; ++d) {
@@ -335,10 +335,10 @@ static size_t plan_layout(const vofmt_box *boxes, int nboxes, int chunk, Plan &p
   return off;
 }
 
-// Grid of a launch over nitems work items, per of them to a workgroup.
-static dim3 grid_of(const Plan &pl, int64_t nitems, int per) {
-  const int64_t all = (nitems + per - 1) / per, most = 1 << 24;  // (a multiple of the 8 XCDs)
-  return dim3(pl.grid > 0 ? (unsigned)pl.grid : (unsigned)(all < most ? all : most));
+// Grid of a launch over nitems work items.
+static dim3 grid_of(const Plan &pl, int64_t nitems) {
+  const int64_t most = 1 << 24;  // (a multiple of the 8 XCDs)
+  return dim3(pl.grid > 0 ? (unsigned)pl.grid : (unsigned)(nitems < most ? nitems : most));
 }
 
 template <int D>
@@ -356,10 +356,10 @@ static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, i
     pn = pl.n_plic[prev_d];
     pitems = pl.items_plic[prev_d];
   }
-  hipLaunchKernelGGL((k_plic_b<D>), grid_of(pl, pitems, 4), dim3(256), 0, st, dboxes, psegs, pn, pitems, pl.rsize,
+  hipLaunchKernelGGL((k_plic_b<D>), grid_of(pl, pitems), dim3(64 * kPlicRegions), 0, st, dboxes, psegs, pn, pitems, pl.rsize,
                      src, cur);
   const Seg *ssegs = (const Seg *)(slab + pl.off_stream[D]);
-  const dim3 grid = grid_of(pl, pl.items_stream[D], 1);
+  const dim3 grid = grid_of(pl, pl.items_stream[D]);
   if (pl.flat)
     hipLaunchKernelGGL((k_stream_b<D, true>), grid, dim3(256), 0, st, dboxes, ssegs, pl.n_stream[D],
                        pl.items_stream[D], pl.chunk, pl.rsize, src, dst, cur ^ 1, cc);
@@ -439,8 +439,8 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   hipStream_t cs = ctx->capture_stream;
   const BoxDev *dboxes = (const BoxDev *)(slab + tab0);
   VOFMT_HIP(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  hipLaunchKernelGGL(k_scan_b, grid_of(pl, pl.items_scan, 4), dim3(256), 0, cs, dboxes, (const Seg *)(slab + pl.off_scan), pl.n_scan,
-                     pl.items_scan, pl.rsize);
+  hipLaunchKernelGGL(k_scan_b, grid_of(pl, pl.items_scan), dim3(64 * kPlicRegions), 0, cs, dboxes,
+                     (const Seg *)(slab + pl.off_scan), pl.n_scan, pl.items_scan, pl.rsize);
   int src = 0, dst = 1, cur = 0, prev_d = -1;
   for (int32_t st = 0; st < nsteps; ++st) {
     const int64_t g = step0 + st;

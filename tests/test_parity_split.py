@@ -8,7 +8,9 @@ tolerance of the other advection tests (one or two steps of fields whose
 values are O(1)). Rows that are no multiple of 64 cells take lanes across rows,
 and words of whole planes (a batch all its boxes): planes below, at and above one
 wavefront's and one workgroup's cells, lanes of several rows, in each order of
-the sweeps, alone and in a batch with a box whose rows fill their segments.
+the sweeps, alone and in a batch with a box whose rows fill their segments. The
+flux pass takes 4 list regions as one: mixed cells in one region only (the
+first, the last), in every other, and all cells of all regions.
 
 Reassignment: pairs found in LDS tiles of 64 x 8 x 8 cells (reach up to 2, up
 to 4) or from the list of boundary cells (above, or an axis no longer than the
@@ -103,6 +105,26 @@ def test_lanes_across_rows(ctx, shape, ntr, step0):
     assert torch.equal(alone, dev[0][0])
     for d, ref in zip(dev, refs):
         assert np.abs(d[0].cpu().numpy() - ref).max() <= TOL
+
+
+@pytest.mark.parametrize("where", ["first", "last", "alternate", "all"])
+def test_list_regions(ctx, where):
+    import torch
+
+    shape, ntr = (23, 30, 65), 2  # 90 000 cells: many regions, the last one short
+    c, s = _random(shape, ntr, 71)
+    flat = c.reshape(-1)
+    n = np.arange(flat.size)
+    keep = dict(first=n < 300, last=n >= flat.size - 300, alternate=n // 1024 % 2 == 1, all=n >= 0)[where]
+    flat[:] = np.where(keep, np.where(flat * (1 - flat) > 0, flat, 0.37), np.round(flat))
+    note(f"advect list regions {where}")
+    dev = [torch.from_numpy(a).to("cuda:0") for a in (c, *s)]
+    alone = dev[0].clone()
+    ctx.advect(alone, *dev[1:], step0=0, nsteps=1)
+    ctx.advect_batched([tuple(dev)], step0=0, nsteps=1)
+    torch.cuda.synchronize()
+    assert torch.equal(alone, dev[0])
+    assert np.abs(alone.cpu().numpy() - oracle.advect(c, *s, 0, 1)).max() <= TOL
 
 
 def _labelled(shape, ntr, seed, spread):
