@@ -175,7 +175,6 @@ __device__ __forceinline__ void plic_body(const double *__restrict__ cin, const 
                                           const uint32_t *__restrict__ list, const int *__restrict__ counts,
                                           int64_t nregions, int rsize, double *__restrict__ fmix, int nx, int ny,
                                           int nz, const Divisors &dv, int64_t w0) {
-  const int64_t n3 = (int64_t)nx * ny * nz;
   int end[kPlicRegions];  // entries up to a region's end
 #pragma unroll
   for (int r = 0; r < kPlicRegions; ++r)
@@ -193,13 +192,12 @@ __device__ __forceinline__ void plic_body(const double *__restrict__ cin, const 
     const int i = (int)(p32 - row * (uint32_t)nx);
     const uint32_t k32 = fast_div(row, dv.ny);
     const int j = (int)(row - k32 * (uint32_t)ny), k = (int)k32;
-    const int64_t p = p32;
-    const int64_t pu = (D == 0) ? p - i + wrap_inc(i, nx)
-                                : ((D == 1) ? ((int64_t)k * ny + wrap_inc(j, ny)) * nx + i
-                                            : ((int64_t)wrap_inc(k, nz) * ny + j) * nx + i);
-    const double s_lo = s[p], s_hi = s[pu];
-    if (!(s_lo < 0.0) && !(s_hi > 0.0)) continue;  // donates through neither face
-    const double *ct = cin + t * n3;
+    // (a box has fewer than 2^32 tracer-cells: 32-bit indices, 512^3 x 8 1.00 -> 0.95 ms)
+    const uint32_t pu = (D == 0) ? p32 - i + wrap_inc(i, nx)
+                                 : ((D == 1) ? (k32 * (uint32_t)ny + wrap_inc(j, ny)) * (uint32_t)nx + i
+                                             : ((uint32_t)wrap_inc(k, nz) * ny + j) * (uint32_t)nx + i);
+    const double s_lo = s[p32], s_hi = s[pu];
+    const uint32_t e0 = e - p32;  // the tracer's first cell
     double b[27];
     {
       const int im = wrap_dec(i, nx), ip = wrap_inc(i, nx);
@@ -212,16 +210,16 @@ __device__ __forceinline__ void plic_body(const double *__restrict__ cin, const 
       for (int az = 0; az < 3; ++az)
 #pragma unroll
         for (int ay = 0; ay < 3; ++ay) {
-          const double *rowp = ct + ((int64_t)zs[az] * ny + ys[ay]) * nx;
+          const uint32_t r0 = e0 + ((uint32_t)zs[az] * (uint32_t)ny + (uint32_t)ys[ay]) * (uint32_t)nx;
 #pragma unroll
-          for (int ax = 0; ax < 3; ++ax) b[ax + 3 * ay + 9 * az] = rowp[xs[ax]];
+          for (int ax = 0; ax < 3; ++ax) b[ax + 3 * ay + 9 * az] = cin[r0 + (uint32_t)xs[ax]];
         }
     }
+    if (!(s_lo < 0.0) && !(s_hi > 0.0)) continue;  // donates through neither face
     double f_lo, f_hi;
     plic_fluxes<D>(b, s_lo, s_hi, f_lo, f_hi);
-    double *ft = fmix + t * n3;
-    if (s_lo < 0.0) ft[p] = f_lo;
-    if (s_hi > 0.0) ft[pu] = f_hi;
+    if (s_lo < 0.0) fmix[e] = f_lo;
+    if (s_hi > 0.0) fmix[e0 + pu] = f_hi;
   }
 }
 
