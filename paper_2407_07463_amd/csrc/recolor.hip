@@ -565,7 +565,10 @@ __global__ __launch_bounds__(kBlock) void k_stencil_edges(const int32_t *__restr
 // From a list of those cells in memory (counted, scanned, written, then
 // scattered 4-byte loads, one cache line per lane) the same pairs took 1.60 ms
 // at 512^3 x 8 drops with the 40 offsets of the distance 1.5 and 0.39 ms so;
-// the 364 offsets of the stencil mode 4.9 ms, and 1.06 ms so.
+// the 364 offsets of the stencil mode 4.9 ms, and 1.06 ms so. Most boundary
+// cells have no other drop near: those whose reach, taken as whole groups of 4
+// cells along x and the whole y-range, holds one drop are not listed (0.39 ->
+// 0.33 and 1.06 -> 0.90 ms).
 // cross_T0 != null: only drops of different tracers (initial tracer per drop)
 // are related.
 constexpr int kTileX = 64, kTileY = 8, kTileZ = 8;
@@ -584,6 +587,16 @@ struct TileDims {
   static constexpr int LX = kTileX + 2 * kHaloX, LY = kTileY + 2 * R, LZ = kTileZ + R + 1;
 };
 typedef uint16_t owner2 __attribute__((ext_vector_type(2)));
+typedef int16_t sowner2 __attribute__((ext_vector_type(2)));
+// Smallest and largest drop of a group of cells, in the low and the high half:
+// minima of the unsigned values, in which cells of no or of several drops are the
+// largest, and maxima of the signed, in which they are the smallest.
+constexpr uint32_t kNoDrops = 0xFFFFFFFFu;
+__device__ __forceinline__ uint32_t low_high(uint32_t u, uint32_t v) {
+  const uint32_t lo = (u & 0xFFFFu) < (v & 0xFFFFu) ? u & 0xFFFFu : v & 0xFFFFu;
+  const int32_t hu = (int32_t)u >> 16, hv = (int32_t)v >> 16;
+  return lo | ((uint32_t)(hu > hv ? hu : hv) << 16);
+}
 
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict__ own,
@@ -601,6 +614,11 @@ __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict
   __shared__ uint16_t list[kCellsOfTile];
   __shared__ uint32_t known[kPairCache];  // pairs already in the bitmap
   __shared__ int nlist, nshared;
+  // smallest and largest drop: of 4 cells along x and all y of a plane, and of
+  // what the half balls of 4 of the tile's cells in a plane can reach
+  constexpr int kGroupsX = LX / 4, kOwnX = kTileX / 4;
+  __shared__ uint32_t of_group[kGroupsX * LZ], in_reach[kOwnX * kTileZ];
+  static_assert(kGroupsX * LZ <= kBlock && kOwnX * kTileZ <= kBlock && kMaxTileReach <= 4, "a thread each, x-reach of one group");
   // each XCD takes a contiguous run of tiles, so that a tile's halo is in its L2
   const unsigned nwg = gridDim.x, per = nwg / 8, rem = nwg % 8, k8 = blockIdx.x % 8;
   const unsigned L = k8 * per + (k8 < rem ? k8 : rem) + blockIdx.x / 8;
@@ -661,7 +679,30 @@ __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict
     for (int e = threadIdx.x; e < kRows * 8; e += kBlock) tile[(e >> 3) * LX + 64 + (e & 7)] = owner_at(e >> 3, 64 + (e & 7));
   }
   __syncthreads();
-  // boundary cells: 4 consecutive cells per lane, 4 rows per wavefront
+  if (threadIdx.x < kGroupsX * LZ) {
+    const int g = threadIdx.x % kGroupsX, lz = threadIdx.x / kGroupsX;
+    owner2 lo = (uint16_t)0xFFFF;
+    sowner2 hi = (int16_t)-1;
+    for (int ly = 0; ly < LY; ++ly) {
+      const uint2 w = *(const uint2 *)(tile + (lz * LY + ly) * LX + 4 * g);
+      lo = __builtin_elementwise_min(lo, __builtin_elementwise_min(__builtin_bit_cast(owner2, w.x), __builtin_bit_cast(owner2, w.y)));
+      hi = __builtin_elementwise_max(hi, __builtin_elementwise_max(__builtin_bit_cast(sowner2, w.x), __builtin_bit_cast(sowner2, w.y)));
+    }
+    of_group[threadIdx.x] = low_high((uint32_t)lo.x | ((uint32_t)(uint16_t)hi.x << 16), (uint32_t)lo.y | ((uint32_t)(uint16_t)hi.y << 16));
+  }
+  __syncthreads();
+  if (threadIdx.x < kOwnX * kTileZ) {
+    const int g = threadIdx.x % kOwnX + kHaloX / 4, dz = threadIdx.x / kOwnX;
+    uint32_t m = kNoDrops;
+#pragma unroll
+    for (int oz = 0; oz <= R; ++oz)
+#pragma unroll
+      for (int og = -1; og <= 1; ++og) m = low_high(m, of_group[(dz + 1 + oz) * kGroupsX + g + og]);
+    in_reach[threadIdx.x] = m;
+  }
+  __syncthreads();
+  // boundary cells: 4 consecutive cells per lane, 4 rows per wavefront; not
+  // those that reach no drop but their own
   for (int r0 = 4 * wv; r0 < kTileY * kTileZ; r0 += 4 * kWaves) {
     const int r = r0 + (lane >> 4), dy = r % kTileY, dz = r / kTileY;
     const int xl = 4 * (lane & 15), i = ((dz + 1) * LY + dy + R) * LX + kHaloX + xl;
@@ -671,6 +712,8 @@ __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict
     const uint64_t d = (c ^ ((c << 16) | (uint16_t)tile[i - 1])) | (c ^ ((c >> 16) | ((uint64_t)(uint16_t)tile[i + 4] << 48))) |
                        (c ^ four(i - LX)) | (c ^ four(i + LX)) | (c ^ four(i - LX * LY)) | (c ^ four(i + LX * LY));
     const bool in = y0 + dy < ny && z0 + dz < nz;
+    const uint32_t reached = in_reach[dz * kOwnX + (lane & 15)];
+    const bool others = (reached & 0xFFFFu) != reached >> 16;
     uint64_t mask[4];
     int total = 0, at = 0;
 #pragma unroll
@@ -678,7 +721,7 @@ __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict
       const int32_t a = (int16_t)(c >> (16 * k));
       const bool cell = in && x0 + xl + k < nx;
       if (cell && a == -2) list[kCellsOfTile - 1 - atomicAdd(&nshared, 1)] = (uint16_t)(i + k);
-      mask[k] = __ballot(cell && a >= 0 && ((d >> (16 * k)) & 0xFFFFull) != 0ull);
+      mask[k] = __ballot(others && cell && a >= 0 && ((d >> (16 * k)) & 0xFFFFull) != 0ull);
       total += (int)__popcll(mask[k]);
     }
     if (total == 0) continue;  // whole wavefront

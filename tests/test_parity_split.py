@@ -13,7 +13,7 @@ flux pass takes 4 list regions as one: mixed cells in one region only (the
 first, the last), in every other, and all cells of all regions.
 
 Reassignment: pairs found in LDS tiles of 64 x 8 x 8 cells (reach up to 2, up
-to 4) or from the list of boundary cells (above, or an axis no longer than the
+to 4; cells that reach no drop but their own left out) or from the list of boundary cells (above, or an axis no longer than the
 tile's halo), rows read in groups of 4 cells or one by one, row segments whose
 neighbours come by shifts or bit by bit (nx % 64 == 1, nx < 3). Bit-exact.
 
