@@ -375,15 +375,21 @@ __global__ __launch_bounds__(64 * IWAVES) __attribute__((amdgpu_waves_per_eu(4))
   mlp_tiles<true, true>(L, P, m, x, nullptr, acts, tgt, g_out, loss_part, IWAVES);
 }
 
-// The training forward of small batches: a workgroup per 64-sample tile, a
-// wavefront per 16 samples. Every sample goes through the operations of
-// k_mlp_fwd in their order, and the tile's loss is the same butterfly over its
-// 64 samples. With eight whole tiles per workgroup a batch of 4096 had 8
-// workgroups: 20.5 us, 6.6 us so.
-constexpr int kSmallTiles = 1024;  // batches of at most so many tiles take it
+// The forward of small batches (kTrain: training, kActs: with the activation
+// records): a workgroup per 64-sample tile, a wavefront per 16 samples. Every
+// sample goes through the operations of k_mlp_infer and k_mlp_fwd in their order,
+// and the tile's loss is the same butterfly over its 64 samples. With eight whole
+// tiles per workgroup a batch of 4096 had 8 workgroups: training forward 20.5 us,
+// 6.6 us so; plain forward, the whole call, 60000 samples 19.8 -> 11.6 us, 120000
+// 25.4 -> 13.5, 300000 34.5 -> 27.1. Each workgroup stages the weights for one
+// tile only, so the persistent kernels are ahead from about 8000 tiles on (700000
+// samples: 49.7 us there, 53.9 so).
+constexpr int kSmallTiles = 8192;  // batches of at most so many tiles take it
+template <bool kTrain, bool kActs>
 __global__ __launch_bounds__(64 * WMT) void k_mlp_fwd_small(const float *__restrict__ P, const uint4 *__restrict__ w1f_g,
                                                            const uint4 *__restrict__ w2f_g, int m,
-                                                           const float *__restrict__ x, uint8_t *__restrict__ acts,
+                                                           const float *__restrict__ x, float *__restrict__ y_out,
+                                                           uint8_t *__restrict__ acts,
                                                            const float *__restrict__ tgt, float *__restrict__ g_out,
                                                            float *__restrict__ loss_part) {
   __shared__ NetLds L;
@@ -394,11 +400,11 @@ __global__ __launch_bounds__(64 * WMT) void k_mlp_fwd_small(const float *__restr
   const int s0 = blockIdx.x * WT;
   const int rows = m - s0 < WT ? m - s0 : WT;  // rows past m read zero and are not written
   const __amdgpu_buffer_rsrc_t xr = buffer_of(x + (int64_t)s0 * 27, rows * 27 * 4);
-  const __amdgpu_buffer_rsrc_t ar = buffer_of(acts + (int64_t)s0 * ACT_BYTES, rows * ACT_BYTES);
+  const __amdgpu_buffer_rsrc_t ar = buffer_of(kActs ? acts + (int64_t)s0 * ACT_BYTES : acts, kActs ? rows * ACT_BYTES : 0);
   bf16x8 xh, xl;
   load_xfrag(xr, w, lr, lq, xh, xl);  // in flight with the weights
   const int s = s0 + 16 * w + lr;
-  const float t = s < m ? tgt[s] : 1.0f;
+  const float t = kTrain && s < m ? tgt[s] : 1.0f;
   const float b3 = P[OFF_B3];
   stage_net(L, P, w1f_g, w2f_g, tid, 64 * WMT);
   __syncthreads();
@@ -407,15 +413,20 @@ __global__ __launch_bounds__(64 * WMT) void k_mlp_fwd_small(const float *__restr
     l = xl;
   };
   auto h1out = [&](int, int kk, u32x4 bits) {
-    __builtin_amdgcn_raw_buffer_store_b128(bits, ar, (16 * w + lr) * ACT_BYTES + (32 * kk + 8 * lq) * 2, 0, 0);
+    if (kActs) __builtin_amdgcn_raw_buffer_store_b128(bits, ar, (16 * w + lr) * ACT_BYTES + (32 * kk + 8 * lq) * 2, 0, 0);
   };
   auto h2out = [&](int, int nt, f32x4 h) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h), ar,
-                                           (16 * w + lr) * ACT_BYTES + 256 + (16 * nt + 4 * lq) * 4, 0, 0);
+    if (kActs)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h), ar,
+                                             (16 * w + lr) * ACT_BYTES + 256 + (16 * nt + 4 * lq) * 4, 0, 0);
   };
   float y[1];
   net_tile<1>(L, lane, b3, xfrag, h1out, h2out, y);
-  if (lq == 0) {  // (every lane group holds the output)
+  if (!kTrain) {
+    if (lq == 0 && s < m) y_out[s] = y[0];  // (every lane group holds the output)
+    return;
+  }
+  if (lq == 0) {
     float lv = 0.0f;
     if (s < m) sample_loss(y[0], t, m, lv, g_out[s]);
     losses[16 * w + lr] = lv;
@@ -935,7 +946,14 @@ extern "C" int vofmt_mlp_forward(vofmt_ctx *ctx, const float *params, int32_t m,
   if (rc) return rc;
   const int tiles = (m + WT - 1) / WT;
   const int rec = prof_begin(ctx, "k_mlp_infer", stream);
-  if (acts)
+  auto small = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(tiles), dim3(64 * WMT), 0, stream, params, (const uint4 *)w[0],
+                       (const uint4 *)w[1], m, x, y, acts, (const float *)nullptr, (float *)nullptr, (float *)nullptr);
+  };
+  if (tiles <= kSmallTiles) {
+    if (acts) small(k_mlp_fwd_small<false, true>);
+    else small(k_mlp_fwd_small<false, false>);
+  } else if (acts)
     hipLaunchKernelGGL(k_mlp_infer<true>, dim3(persistent_grid(ctx, k_mlp_infer<true>, IWAVES, tiles)),
                        dim3(64 * IWAVES), 0, stream, params, (const uint4 *)w[0], (const uint4 *)w[1], m, x, y, acts);
   else
@@ -971,8 +989,8 @@ extern "C" int vofmt_mlp_train_step(vofmt_ctx *ctx, float *params, float *adam_m
   float *loss_part = gbuf + m;
   int rec = prof_begin(ctx, "k_mlp_fwd(train)", stream);
   if (ntiles <= kSmallTiles)
-    hipLaunchKernelGGL(k_mlp_fwd_small, dim3(ntiles), dim3(64 * WMT), 0, stream, params, (const uint4 *)w[0],
-                       (const uint4 *)w[1], m, x, acts, y_target, gbuf, loss_part);
+    hipLaunchKernelGGL((k_mlp_fwd_small<true, true>), dim3(ntiles), dim3(64 * WMT), 0, stream, params,
+                       (const uint4 *)w[0], (const uint4 *)w[1], m, x, (float *)nullptr, acts, y_target, gbuf, loss_part);
   else
     hipLaunchKernelGGL(k_mlp_fwd, dim3(persistent_grid(ctx, k_mlp_fwd, IWAVES, ntiles)), dim3(64 * IWAVES), 0, stream,
                        params, (const uint4 *)w[0], (const uint4 *)w[1], m, x, acts, y_target, gbuf, loss_part);

@@ -21,8 +21,9 @@ Interface-cell list: fields of 1 to a few blocks of 8192 cells around the edges
 of words, wavefronts and blocks, at addresses that are multiples of 8 bytes (1
 for the status) only, and above 4096 blocks, where the counts are scanned. Exact.
 
-Training forward: a workgroup per 64 samples up to 1024 tiles, whole tiles per
-wavefront above. The activation records equal the forward pass's bit for bit
+Network forward: a workgroup per 64 samples up to 8192 tiles, whole tiles per
+wavefront above: the same operations in the same order, so a batch equals its
+samples' part of a larger one bit for bit. In training the activation records equal the forward pass's bit for bit
 (the same operations in the same order), the loss the mean of its terms to the
 rounding of an FP32 sum over m (m 2^-23 relative: all terms are positive).
 
@@ -253,6 +254,36 @@ def test_drop_scan_tiles(ctx, kind, shape):
     box = np.array([nx, ny, nz], dtype=np.float64)
     d = np.abs(xyz.cpu().numpy() - rx)
     assert np.all(np.minimum(d, box - d) <= 1e-12 * box)
+
+
+@pytest.fixture(scope="module")
+def large_forward(ctx):
+    import torch
+
+    from paper_2407_07463_amd import training
+
+    m = 64 * 8192 + 17
+    x = torch.from_numpy(np.random.default_rng(5).random((m, 27), dtype=np.float32)).to("cuda:0")
+    params = torch.from_numpy(training.init_params(4)).to("cuda:0")
+    y = torch.empty(m, dtype=torch.float32, device="cuda:0")
+    acts = torch.zeros((m, 384), dtype=torch.int16, device="cuda:0")
+    ctx.mlp_forward(params, x, y, acts)
+    return params, x, y, acts
+
+
+@pytest.mark.parametrize("m,first", [(1, 0), (16, 3), (63, 64), (65, 1000), (4096, 5), (64 * 8192, 17)])
+@pytest.mark.parametrize("records", [False, True])
+def test_forward_tiles(ctx, large_forward, m, first, records):
+    import torch
+
+    params, x, y_all, acts_all = large_forward
+    note(f"forward m={m} first={first} records={records}")
+    y = torch.full((m + 1,), 7.0, dtype=torch.float32, device="cuda:0")
+    acts = torch.full((m + 1, 384), 7, dtype=torch.int16, device="cuda:0") if records else None
+    ctx.mlp_forward(params, x[first:first + m].contiguous(), y[:m], None if acts is None else acts[:m])
+    assert torch.equal(y[:m], y_all[first:first + m]) and float(y[m]) == 7.0
+    if records:
+        assert torch.equal(acts[:m], acts_all[first:first + m]) and bool((acts[m] == 7).all())
 
 
 @pytest.mark.parametrize("m", [1, 15, 17, 64, 65, 1000, 65536, 65537])
