@@ -473,6 +473,7 @@ int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes,
  * (the caller's data is untouched) with each candidate tuning -- chunk
  * {16, 32, 64} x workgroups per CU {2, 4, 8, 16} -- for nsteps steps, times
  * each graph launch with HIP events (best of two), and returns the fastest.
+ * (On the batches measured, a null tuning was faster than every candidate.)
  * best_host: HOST output. best_ms_host: nullable HOST output, its time.
  * Synchronises. Scratch: one copy of every field.
  */

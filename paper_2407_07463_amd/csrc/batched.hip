@@ -152,8 +152,8 @@ int box_xwpb(int words, int chunk) { return words <= chunk ? 0 : 4; }
 
 // Whether the boxes of a batch have the flat layout: all of them, where one gains
 // by it and all can. One kernel for both layouts has the registers of the worst
-// (121 for the x-sweep, which leaves 4 wavefronts a SIMD; flat alone 94; 21.8 -> 21.4 ms for the
-// batch below).
+// (121 for the x-sweep, which leaves 4 wavefronts a SIMD; flat alone 94, 21.8 ->
+// 21.4 ms for 32 boxes of 64 to 192 cells, three steps).
 bool batch_flat(const vofmt_box *boxes, int nboxes) {
   bool gain = false;
   for (int i = 0; i < nboxes; ++i) {
