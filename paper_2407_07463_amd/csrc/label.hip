@@ -733,7 +733,7 @@ static inline int run_shift(int nx) {
 // per-drop step turns them into the box.
 
 // Per-drop reductions go through a small hash table in LDS per workgroup. A
-// workgroup takes a tile of up to 128 x 16 x 16 cells (compact, so that few
+// workgroup takes a tile of 128 x 16 x 16 or 128 x 8 x 8 cells (compact, so that few
 // tiles meet a drop: each applies one set of global atomics per drop it met,
 // and global atomics on one address from many workgroups are serialised). A
 // wavefront takes 64 cells of a row at a time, kBatch of them in flight, and
@@ -745,13 +745,18 @@ static inline int run_shift(int nx) {
 // Before, one lane per run built and merged its record while the others waited,
 // and the tiles were 64 rows of one plane: 1483 us at 512^3 x 8 (5000 drops),
 // 770 us so, where the labels' read takes 720 at the card's copy rate.
-constexpr int kScanX = 2, kScanY = 16, kScanZ = 16;  // tile of the scan: 64-cell segments, rows, planes
+constexpr int kScanX = 2;  // tile of the scan: 64-cell segments, by SY rows, by SZ planes
+// SY x SZ: 16 x 16, and 8 x 8 where the fields have no more than so many of those:
+// a wavefront's batches are a chain, and a tile's end is its drops' global atomics
+// (198x187x206 x 3, 1014 large tiles: scan 47.6 -> 30.6 us, 35 with 8 x 4; moments
+// and shapes of 256^3 x 8, 4096 of them, 310 -> 296 us for the statistics; 512^3 x
+// 8, 32768, the scan 745 -> 769 us)
+constexpr int kFewScanTiles = 4096;
 constexpr int kTable = 64;     // LDS records per workgroup (power of two)
 constexpr int kBatch = 16;     // segments of a wavefront whose loads are issued together
 constexpr int kRuns = 128;     // runs a wavefront notes before it merges 64 of them
 constexpr int kFrames = 12;    // per drop: axis a -> min A, max A, min B, max B at 4a
 static_assert(kTable == 64, "table_slot hashes to 6 bits");
-static_assert((kScanX * kScanY * kScanZ / (kBlock / 64)) % kBatch == 0, "whole batches per wavefront");
 
 __device__ __forceinline__ int table_slot(int32_t *key, int32_t l) {
   const uint32_t h = ((uint32_t)l * 2654435761u) >> 26;  // 6 bits: kTable = 64
@@ -806,6 +811,7 @@ __device__ __forceinline__ void merge_run(int32_t *key, int32_t *rfirst, int32_t
 // First cell and the frame extents of every drop. Tile blockIdx.x (x, then y,
 // then z; tx tiles along x, ty along y) of field blockIdx.y, whose drops are
 // records toff[t] .. toff[t+1]-1.
+template <int SY, int SZ>
 __global__ __launch_bounds__(kBlock) void k_drop_scan(const int32_t *__restrict__ lab, int64_t n3, int nx, int ny,
                                                       int nz, int tx, int ty, FastDiv fnx, FastDiv fny,
                                                       const int32_t *__restrict__ toff,
@@ -836,15 +842,15 @@ __global__ __launch_bounds__(kBlock) void k_drop_scan(const int32_t *__restrict_
   uint8_t *const rn = run_len[wv];
   int n = 0;  // runs noted, wavefront-uniform
   auto merge = [&](int q) { merge_run(key, rfirst, rec, first, frames, rl[q], rc[q], rn[q], nx, ny, nz, fnx, fny); };
-  constexpr int kPer = kScanX * kScanY * kScanZ / (kBlock / 64);  // segments per wavefront
+  constexpr int kPer = kScanX * SY * SZ / (kBlock / 64);  // segments per wavefront
+  static_assert(kPer % kBatch == 0, "whole batches per wavefront");
   for (int i0 = wv * kPer; i0 < (wv + 1) * kPer; i0 += kBatch) {
     int32_t lb[kBatch];  // the labels of kBatch segments are loaded together
     int32_t cell[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u;  // segment of the tile: x, then y, then z
-      const int x = 64 * (bx * kScanX + i % kScanX), y = by * kScanY + (i / kScanX) % kScanY,
-                z = bz * kScanZ + i / (kScanX * kScanY);
+      const int x = 64 * (bx * kScanX + i % kScanX), y = by * SY + (i / kScanX) % SY, z = bz * SZ + i / (kScanX * SY);
       const bool in = y < ny && z < nz;
       cell[u] = in ? (z * ny + y) * nx + x : 0;
       lb[u] = (in && x + lane < nx) ? lab[(int64_t)cell[u] + lane] : 0;
@@ -1396,12 +1402,17 @@ static int scan_drops(vofmt_ctx *ctx, int nx, int ny, int nz, int ntracers, cons
     VOFMT_HIP(ctx, hipMemcpyAsync(ds.toff, off, sizeof(int32_t) * (size_t)(ntracers + 1), hipMemcpyHostToDevice, stream));
   const int noff = args ? ntracers + 1 : 0;
   const FastDiv fnx = make_fastdiv((uint32_t)nx), fny = make_fastdiv((uint32_t)ny);
-  const int tx = (int)ceil_div(nx, 64 * kScanX), ty = (int)ceil_div(ny, kScanY);
-  const int64_t ntile = (int64_t)tx * ty * ceil_div(nz, kScanZ);
   hipLaunchKernelGGL(k_scan_init, dim3(ceil_div(kFrames * D > noff ? kFrames * D : noff, 256)), dim3(256), 0, stream,
                      ds.first, frames, D, fo, noff, ds.toff);
-  hipLaunchKernelGGL(k_drop_scan, dim3((unsigned)ntile, ntracers), dim3(kBlock), 0, stream, labels,
-                     (int64_t)nx * ny * nz, nx, ny, nz, tx, ty, fnx, fny, ds.toff, ds.first, frames);
+  auto scan = [&](auto kernel, int sy, int sz) {
+    const int tx = (int)ceil_div(nx, 64 * kScanX), ty = (int)ceil_div(ny, sy);
+    const int64_t ntile = (int64_t)tx * ty * ceil_div(nz, sz);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ntile, ntracers), dim3(kBlock), 0, stream, labels, (int64_t)nx * ny * nz,
+                       nx, ny, nz, tx, ty, fnx, fny, ds.toff, ds.first, frames);
+  };
+  const int64_t large = (int64_t)ceil_div(nx, 64 * kScanX) * ceil_div(ny, 16) * ceil_div(nz, 16) * ntracers;
+  if (large <= kFewScanTiles) scan(k_drop_scan<8, 8>, 8, 8);
+  else scan(k_drop_scan<16, 16>, 16, 16);
   hipLaunchKernelGGL(k_drop_box, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, ds.first, frames,
                      ds.box);
   return VOFMT_OK;

@@ -31,7 +31,7 @@ Labelling: labels written 4, 2 or 1 cells a lane, as rows and the array's
 alignment go, union tiles of 512 or 2048 segments, the roots before a workgroup
 summed or (above 4096 workgroups) scanned. Exact.
 
-Drop scan: tiles of 128 x 16 x 16 cells, rows of one cell to several segments,
+Drop scan: tiles of 128 x 16 x 16 or (few tiles) 128 x 8 x 8 cells, rows of one cell to several segments,
 runs that end at a segment's end, more runs than a wavefront notes at once, more
 drops in a tile than its table holds. Volumes and centroids within the bounds of
 the other moment tests (1e-12 relative; 1e-12 of the box).
@@ -236,6 +236,16 @@ def _separate(kind, shape, rng):
                                         ("bars", (2, 3, 1000)), ("cells", (16, 16, 128)), ("cells", (5, 6, 200)),
                                         ("cells", (40, 3, 3))])
 def test_drop_scan_tiles(ctx, kind, shape):
+    _check_drop_scan(ctx, kind, shape)
+
+
+@pytest.mark.parametrize("kind,shape", [("cells", (736, 721, 5)), ("bars", (1441, 368, 5)), ("bars", (512, 1024, 5))])
+def test_drop_scan_tile_sizes(ctx, kind, shape):
+    """More than 4096 tiles of 16 rows by 16 planes, and 4096."""
+    _check_drop_scan(ctx, kind, shape)
+
+
+def _check_drop_scan(ctx, kind, shape):
     import torch
 
     nz, ny, nx = shape
