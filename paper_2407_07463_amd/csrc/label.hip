@@ -1162,7 +1162,7 @@ __global__ __launch_bounds__(kBlock) void k_shape_sums(const double *__restrict_
 // vol, xyz (nullable): the volume and centroid as well, the centroid as the
 // first cell's centre plus the box centre's offset plus the mean offset from
 // it (the moments' quantities from the shape sums).
-__global__ void k_shape_finish(int32_t K, int nx, int ny, int nz, const int32_t *__restrict__ rootpos,
+__global__ __launch_bounds__(64) void k_shape_finish(int32_t K, int nx, int ny, int nz, const int32_t *__restrict__ rootpos,
                                const int32_t *__restrict__ box, const double *__restrict__ part,
                                double *__restrict__ inertia, double *__restrict__ chi, double *__restrict__ vel,
                                double *__restrict__ vol, double *__restrict__ xyz, int32_t *__restrict__ flags) {
@@ -1173,8 +1173,18 @@ __global__ void k_shape_finish(int32_t K, int nx, int ny, int nz, const int32_t 
   if (p0 == INT32_MAX || b[0] > b[1]) return;  // reported by k_shape_sums
   double S[kShapeSums];
   for (int k = 0; k < kShapeSums; ++k) S[k] = 0.0;
+  // a drop a lane: workgroups of one wavefront spread over the compute units, and
+  // the sums' loads do not wait for each other (512^3 x 8 19.1 -> 9.3 us, 198^3 x 3: 8.7
+  // -> 7.0)
+  double in[kSumSplit][kShapeSums];
+#pragma unroll
   for (int sl = 0; sl < kSumSplit; ++sl)
-    for (int k = 0; k < kShapeSums; ++k) S[k] += part[(i * kSumSplit + sl) * kShapeSums + k];
+#pragma unroll
+    for (int k = 0; k < kShapeSums; ++k) in[sl][k] = part[(i * kSumSplit + sl) * kShapeSums + k];
+#pragma unroll
+  for (int sl = 0; sl < kSumSplit; ++sl)
+#pragma unroll
+    for (int k = 0; k < kShapeSums; ++k) S[k] += in[sl][k];
   const double V = S[0];
   const double gx = S[1] / V, gy = S[2] / V, gz = S[3] / V;
   const double self = V / 12.0;
@@ -1487,7 +1497,7 @@ static int drop_shapes_impl(vofmt_ctx *ctx, const char *fn, bool moments, int32_
   if (rc) return rc;
   hipLaunchKernelGGL(k_shape_sums, dim3((unsigned)(D * kSumSplit)), dim3(kBlock), 0, stream, c, labels, sx, sy, sz, nx,
                      ny, nz, ds.toff, ds.first, ds.box, part, ds.flags);
-  hipLaunchKernelGGL(k_shape_finish, dim3(ceil_div(D, 256)), dim3(256), 0, stream, (int32_t)D, nx, ny, nz, ds.first,
+  hipLaunchKernelGGL(k_shape_finish, dim3(ceil_div(D, 64)), dim3(64), 0, stream, (int32_t)D, nx, ny, nz, ds.first,
                      ds.box, part, inertia, chi, withu ? vel : nullptr, vol, xyz, ds.flags);
   return check_drops(ctx, fn, ds, stream);
 }
