@@ -1,6 +1,6 @@
 // Plain advection entry points: one box, one launch per pass.
 // The kernels are thin wrappers around the shared sweep bodies: every sweep
-// is a PLIC pass over the mixed cells and one streaming pass per tracer group.
+// is a PLIC pass over the mixed cells and one streaming pass over all tracers.
 #include "advect_kernels.hpp"
 
 using namespace advect;
@@ -164,8 +164,8 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
   static const char *plic_names[3] = {"k_plic<0>", "k_plic<1>", "k_plic<2>"};
   static const char *stream_names[3] = {"k_stream<0>", "k_stream<1>", "k_stream<2>"};
   int rec = prof_begin(ctx, plic_names[D], stream);
-  hipLaunchKernelGGL((k_plic<D>), dim3(ceil_div(nreg, kPlicRegions)), dim3(64 * kPlicRegions), 0, stream, cin, s, sb.list[cur],
-                     sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
+  hipLaunchKernelGGL((k_plic<D>), dim3(ceil_div(nreg, kPlicRegions)), dim3(64 * kPlicRegions), 0, stream, cin, s,
+                     sb.list[cur], sb.counts[cur], nreg, sb.stride[cur], sb.fmix, nx, ny, nz, dv);
   prof_end(ctx, rec, stream);
   const int wpb = (D == 0) ? x_wpb(words, chunk) : 4;
   const bool flat = flat_rows(nx, ny, nz);
@@ -174,11 +174,15 @@ static void launch_sweep_axis(vofmt_ctx *ctx, const double *cin, double *cout, c
   const dim3 grid(tg.gx, tg.gy, tg.gz * num_groups(ntr));
   static_assert(kMaxGroup == 4, "streaming passes are instantiated for groups of at most 4");
   rec = prof_begin(ctx, stream_names[D], stream);
+  auto launch = [&](auto GM) {
+    launch_stream<D, decltype(GM)::value>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words,
+                                          chunk, nxt, per);
+  };
   switch (largest_group(ntr)) {
-    case 4: launch_stream<D, 4>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    case 3: launch_stream<D, 3>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    case 2: launch_stream<D, 2>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
-    default: launch_stream<D, 1>(grid, flat, dv.nx, stream, cin, cout, s, sb, cc, nx, ny, nz, ntr, words, chunk, nxt, per); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 3: launch(std::integral_constant<int, 3>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    default: launch(std::integral_constant<int, 1>{}); break;
   }
   prof_end(ctx, rec, stream);
   sb.nregions[nxt] = num_groups(ntr) * per;
@@ -256,7 +260,8 @@ extern "C" int vofmt_advect(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, 
     const int64_t g = step0 + st;
     for (int r = 0; r < 3; ++r) {
       const int d = (int)((g + r) % 3);
-      int rc = launch_sweep(ctx, d, cur, nxt, s3[d], sb, cc_mode(g, r), cur_list, nx, ny, nz, ntracers, words, chunk, stream);
+      int rc = launch_sweep(ctx, d, cur, nxt, s3[d], sb, cc_mode(g, r), cur_list, nx, ny, nz, ntracers, words, chunk,
+                            stream);
       if (rc) return hip_check(ctx, (hipError_t)rc, "sweep launch");
       cur_list ^= 1;
       double *t = cur;

@@ -356,8 +356,8 @@ static void enqueue_sweep(uint8_t *slab, const Plan &pl, const BoxDev *dboxes, i
     pn = pl.n_plic[prev_d];
     pitems = pl.items_plic[prev_d];
   }
-  hipLaunchKernelGGL((k_plic_b<D>), grid_of(pl, pitems), dim3(64 * kPlicRegions), 0, st, dboxes, psegs, pn, pitems, pl.rsize,
-                     src, cur);
+  hipLaunchKernelGGL((k_plic_b<D>), grid_of(pl, pitems), dim3(64 * kPlicRegions), 0, st, dboxes, psegs, pn, pitems,
+                     pl.rsize, src, cur);
   const Seg *ssegs = (const Seg *)(slab + pl.off_stream[D]);
   const dim3 grid = grid_of(pl, pl.items_stream[D]);
   if (pl.flat)
