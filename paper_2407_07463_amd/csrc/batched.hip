@@ -109,6 +109,10 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
     else if (gm == 3) pass(std::integral_constant<int, 3>{});
     else if (gm == 2) pass(std::integral_constant<int, 2>{});
     else pass(std::integral_constant<int, 1>{});
+    // The x-sweep through LDS takes its buffers from an item's first position on: a
+    // wavefront in the next item would write the one that a slower wavefront still
+    // reads for the last position of this item (an odd number of positions).
+    if (D == 0 && !FLAT) __syncthreads();  // (the items are the workgroup's)
   }
 }
 
