@@ -44,6 +44,7 @@ void *scratch(vofmt_ctx *ctx, int slot, size_t bytes) {
   }
   ctx->buf[slot] = p;
   ctx->cap[slot] = bytes;
+  ++ctx->made[slot];
   return p;
 }
 

@@ -416,10 +416,13 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
     d.counts[0] = (int *)(slab + boff[6 * i + 4]);
     d.counts[1] = d.counts[0] + maxreg;
   }
-  // the key of this configuration: boxes, tuning, sweep order, slab
+  // the key of this configuration: boxes, tuning, sweep order, and the allocations
+  // that the graph's kernels work in (the slab holds their tables: one given back
+  // and allocated anew may have the same address, but not the tables)
   std::string key;
   key.append((const char *)boxes, sizeof(vofmt_box) * (size_t)nboxes);
-  const int64_t hdr[6] = {step0 % 3, nsteps, chunk, wg, (int64_t)(uintptr_t)slab, (int64_t)(uintptr_t)third};
+  const int64_t hdr[6] = {step0 % 3, nsteps, chunk, wg, (int64_t)ctx->made[SLOT_BATCH],
+                          third ? (int64_t)ctx->made[SLOT_THIRD] : 0};
   key.append((const char *)hdr, sizeof(hdr));
   if (ctx->graph && ctx->graph_key == key) {
     VOFMT_HIP(ctx, hipGraphLaunch(ctx->graph, stream));

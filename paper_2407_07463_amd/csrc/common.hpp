@@ -25,6 +25,7 @@ struct vofmt_ctx {
   // Scratch buffers, grown on demand (never shrunk) and reused by later calls.
   void *buf[kNumSlotsDecl] = {};
   size_t cap[kNumSlotsDecl] = {};
+  uint64_t made[kNumSlotsDecl] = {};  // how often each was allocated: its address alone may come back
   // Pinned host staging for small results read back by synchronising calls.
   void *host = nullptr;
   size_t host_cap = 0;
