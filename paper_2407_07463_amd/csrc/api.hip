@@ -39,6 +39,7 @@ void *scratch(vofmt_ctx *ctx, int slot, size_t bytes) {
   void *p = nullptr;
   hipError_t e = hipMalloc(&p, bytes);
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // the caller's error, not that of the next call's launches
     hip_check(ctx, e, "hipMalloc(scratch)");
     return nullptr;
   }
@@ -58,10 +59,7 @@ void *scratch_if_free(vofmt_ctx *ctx, int slot, size_t bytes, hipStream_t stream
   if (st != hipStreamCaptureStatusNone) return nullptr;
   const std::string err = ctx->err;
   void *p = scratch(ctx, slot, bytes);
-  if (!p) {
-    (void)hipGetLastError();
-    ctx->err = err;
-  }
+  if (!p) ctx->err = err;
   return p;
 }
 
@@ -74,6 +72,7 @@ void *host_scratch(vofmt_ctx *ctx, size_t bytes) {
   void *p = nullptr;
   hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocDefault);
   if (e != hipSuccess) {
+    (void)hipGetLastError();
     hip_check(ctx, e, "hipHostMalloc(staging)");
     return nullptr;
   }

@@ -210,8 +210,19 @@ void graph_after_failed_growth() {
   EXPECT(g_uploads == 4 && g_graph_launches == 6);
 }
 
+// A call that found no memory says so itself; the next call is none the worse.
+void call_after_no_memory() {
+  Ctx x;
+  const size_t total = g_total;
+  g_total = 1 << 20;
+  EXPECT(x.advect(128, 1, 2) == VOFMT_E_NOMEM);
+  g_total = total;
+  EXPECT(x.advect(16, 1, 2) == VOFMT_OK);
+}
+
 const std::map<std::string, std::function<void()>> kScenarios = {
     {"graph_after_failed_growth", graph_after_failed_growth},
+    {"call_after_no_memory", call_after_no_memory},
 };
 
 }  // namespace

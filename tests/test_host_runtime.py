@@ -33,3 +33,7 @@ def _holds(program, scenario):
 
 def test_graph_after_failed_growth(program):
     _holds(program, "graph_after_failed_growth")
+
+
+def test_call_after_no_memory(program):
+    _holds(program, "call_after_no_memory")
