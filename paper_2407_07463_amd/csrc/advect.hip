@@ -254,7 +254,7 @@ extern "C" int vofmt_advect(vofmt_ctx *ctx, int32_t nx, int32_t ny, int32_t nz, 
   // for the third copy the result is copied back instead (one step of
   // 134x129x141 x 7: 497 -> 445 us without that copy).
   double *third =
-      nsteps % 2 == 1 ? (double *)scratch_if_free(ctx, SLOT_THIRD, field_bytes, stream) : nullptr;
+      nsteps % 2 == 1 ? (double *)third_copy(ctx, field_bytes, stream) : nullptr;
   double *cur = c, *nxt = tmp;
   for (int32_t st = 0; st < nsteps; ++st) {
     const int64_t g = step0 + st;

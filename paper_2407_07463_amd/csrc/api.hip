@@ -49,16 +49,20 @@ void *scratch(vofmt_ctx *ctx, int slot, size_t bytes) {
   return p;
 }
 
-void *scratch_if_free(vofmt_ctx *ctx, int slot, size_t bytes, hipStream_t stream) {
-  if (ctx->cap[slot] >= bytes && ctx->buf[slot]) return ctx->buf[slot];
+void *third_copy(vofmt_ctx *ctx, size_t bytes, hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
-  if (st != hipStreamCaptureStatusNone) return nullptr;
+  const bool capturing = st != hipStreamCaptureStatusNone;
+  if (ctx->buf[SLOT_THIRD] && ctx->cap[SLOT_THIRD] >= bytes) {
+    ctx->third_captured = ctx->third_captured || capturing;
+    return ctx->buf[SLOT_THIRD];
+  }
+  if (capturing || ctx->third_captured) return nullptr;
   const std::string err = ctx->err;
-  void *p = scratch(ctx, slot, bytes);
+  void *p = scratch(ctx, SLOT_THIRD, bytes);
   if (!p) ctx->err = err;
   return p;
 }

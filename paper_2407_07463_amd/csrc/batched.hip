@@ -399,7 +399,7 @@ extern "C" int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_
   if (nsteps % 2 == 1) {
     size_t all = 0;
     for (int i = 0; i < nboxes; ++i) all += field_bytes(boxes[i]);
-    third = (uint8_t *)scratch_if_free(ctx, SLOT_THIRD, all, stream);
+    third = (uint8_t *)third_copy(ctx, all, stream);
   }
   size_t third_off = 0;
   for (int i = 0; i < nboxes; ++i) {

@@ -26,6 +26,7 @@ struct vofmt_ctx {
   void *buf[kNumSlotsDecl] = {};
   size_t cap[kNumSlotsDecl] = {};
   uint64_t made[kNumSlotsDecl] = {};  // how often each was allocated: its address alone may come back
+  bool third_captured = false;  // the third field copy is in a graph that a caller captured
   // Pinned host staging for small results read back by synchronising calls.
   void *host = nullptr;
   size_t host_cap = 0;
@@ -83,10 +84,12 @@ hipError_t noalloc_setup(int device);
 int hip_check(vofmt_ctx *ctx, hipError_t e, const char *what);
 // Device scratch of at least `bytes` in slot `slot`; nullptr on failure (error set).
 void *scratch(vofmt_ctx *ctx, int slot, size_t bytes);
-// The same for a buffer that the call can do without: nullptr and no error when
-// the memory is not there, or when it would have to be allocated while `stream`
-// is being captured.
-void *scratch_if_free(vofmt_ctx *ctx, int slot, size_t bytes, hipStream_t stream);
+// The third field copy (SLOT_THIRD), which a call can do without: nullptr and no
+// error when the memory is not there, when it would have to be allocated while
+// `stream` is being captured, or when it would have to grow and a graph that a
+// caller captured uses it (the calls that follow the capture may need a larger
+// one, but nothing else to grow).
+void *third_copy(vofmt_ctx *ctx, size_t bytes, hipStream_t stream);
 void *host_scratch(vofmt_ctx *ctx, size_t bytes);
 // Timing of one launch when profiling is on: prof_begin before the launch
 // (returns a record index, or -1), prof_end after it.

@@ -220,9 +220,31 @@ void call_after_no_memory() {
   EXPECT(x.advect(16, 1, 2) == VOFMT_OK);
 }
 
+// A captured call keeps its third field copy: a later call that would need a
+// larger one goes without it (its result is copied back), nothing is freed.
+void captured_third_copy() {
+  Ctx x;
+  EXPECT(x.advect(96, 1, 2) == VOFMT_OK);  // every other buffer is large enough from here on
+  EXPECT(x.batch(cube(64, 1), 2) == VOFMT_OK);
+  const size_t before = used();
+  EXPECT(x.advect(48, 1, 1) == VOFMT_OK && g_device_copies == 0);
+  const size_t third = used() - before;
+  EXPECT(third >= 8u * 48 * 48 * 48 && g_frees == 0);
+  g_capturing = true;
+  EXPECT(x.advect(48, 1, 1) == VOFMT_OK && g_device_copies == 0);
+  g_capturing = false;
+  EXPECT(x.advect(96, 1, 1) == VOFMT_OK);
+  EXPECT(g_device_copies == 1 && g_frees == 0 && used() == before + third);
+  EXPECT(x.batch(cube(64, 1), 1) == VOFMT_OK);
+  EXPECT(g_launches.back().kernel.find("k_copy_b") != std::string::npos);
+  EXPECT(g_frees == 0 && used() == before + third);
+  EXPECT(x.advect(40, 1, 1) == VOFMT_OK && g_device_copies == 1);  // fits: no copy back
+}
+
 const std::map<std::string, std::function<void()>> kScenarios = {
     {"graph_after_failed_growth", graph_after_failed_growth},
     {"call_after_no_memory", call_after_no_memory},
+    {"captured_third_copy", captured_third_copy},
 };
 
 }  // namespace

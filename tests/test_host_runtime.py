@@ -37,3 +37,7 @@ def test_graph_after_failed_growth(program):
 
 def test_call_after_no_memory(program):
     _holds(program, "call_after_no_memory")
+
+
+def test_captured_third_copy(program):
+    _holds(program, "captured_third_copy")
