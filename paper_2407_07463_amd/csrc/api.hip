@@ -23,6 +23,17 @@ int hip_check(vofmt_ctx *ctx, hipError_t e, const char *what) {
                  hipGetErrorString(e));
 }
 
+// Gives the third field copy back, unless there is none or a captured graph works
+// in it. (A cached batched graph that does is made anew: its key names the allocation.)
+static bool release_third(vofmt_ctx *ctx) {
+  if (!ctx->buf[SLOT_THIRD] || ctx->third_captured) return false;
+  if (hipDeviceSynchronize() != hipSuccess) return false;
+  (void)hipFree(ctx->buf[SLOT_THIRD]);
+  ctx->buf[SLOT_THIRD] = nullptr;
+  ctx->cap[SLOT_THIRD] = 0;
+  return true;
+}
+
 void *scratch(vofmt_ctx *ctx, int slot, size_t bytes) {
   if (bytes == 0) bytes = 256;
   if (ctx->cap[slot] >= bytes) return ctx->buf[slot];
@@ -38,6 +49,10 @@ void *scratch(vofmt_ctx *ctx, int slot, size_t bytes) {
   }
   void *p = nullptr;
   hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory && release_third(ctx)) {  // no call needs that one
+    (void)hipGetLastError();
+    e = hipMalloc(&p, bytes);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();  // the caller's error, not that of the next call's launches
     hip_check(ctx, e, "hipMalloc(scratch)");

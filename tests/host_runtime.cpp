@@ -174,6 +174,7 @@ int g_bad = 0;
     }                                                       \
   } while (0)
 
+constexpr size_t kRoom = 4 << 20;     // less than any call of 64^3 cells or more needs
 double *const kField = (double *)16;  // a caller's pointer (never followed)
 
 vofmt_box cube(int n, int ntr) { return vofmt_box{n, n, n, ntr, kField, kField, kField, kField}; }
@@ -241,10 +242,35 @@ void captured_third_copy() {
   EXPECT(x.advect(40, 1, 1) == VOFMT_OK && g_device_copies == 1);  // fits: no copy back
 }
 
+// The third field copy is given back to a call that finds no memory otherwise,
+// unless a captured graph works in it; a cached graph that did is made anew.
+void third_copy_given_back() {
+  {
+    Ctx x;
+    EXPECT(x.batch(cube(160, 1), 1) == VOFMT_OK && g_uploads == 1);
+    EXPECT(x.batch(cube(160, 1), 1) == VOFMT_OK && g_uploads == 1);
+    g_total = kRoom + used();
+    EXPECT(x.advect(64, 1, 2) == VOFMT_OK);  // needs more than there is
+    EXPECT(g_frees == 1);
+    EXPECT(x.batch(cube(160, 1), 1) == VOFMT_OK && g_uploads == 2);
+    EXPECT(g_launches.back().kernel.find("k_copy_b") != std::string::npos);
+  }
+  g_total = 1ull << 38;
+  g_frees = 0;
+  Ctx x;
+  EXPECT(x.advect(96, 1, 1) == VOFMT_OK);
+  g_capturing = true;
+  EXPECT(x.advect(96, 1, 1) == VOFMT_OK);
+  g_capturing = false;
+  g_total = kRoom + used();
+  EXPECT(x.batch(cube(64, 1), 2) == VOFMT_E_NOMEM && g_frees == 0);
+}
+
 const std::map<std::string, std::function<void()>> kScenarios = {
     {"graph_after_failed_growth", graph_after_failed_growth},
     {"call_after_no_memory", call_after_no_memory},
     {"captured_third_copy", captured_third_copy},
+    {"third_copy_given_back", third_copy_given_back},
 };
 
 }  // namespace

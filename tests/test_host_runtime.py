@@ -41,3 +41,7 @@ def test_call_after_no_memory(program):
 
 def test_captured_third_copy(program):
     _holds(program, "captured_third_copy")
+
+
+def test_third_copy_given_back(program):
+    _holds(program, "third_copy_given_back")
