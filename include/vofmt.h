@@ -80,10 +80,13 @@ const char *vofmt_version(void);
  * sx,sy,sz: [nz][ny][nx] FP64 face Courant numbers; the caller guarantees
  *           |s| <= 0.5 (checked only by vofmt_check_courant).
  * step0  : global index of the first step (>= 0); only g mod 3 matters.
- * Scratch: the context keeps one extra copy of c (two where nsteps is odd and
- *           the memory is there), an array of per-face
+ * Scratch: the context keeps one extra copy of c, an array of per-face
  *           fluxes of mixed donors, two lists of up to one 32-bit entry per
- *           tracer-cell and one bit per tracer-cell.
+ *           tracer-cell and one bit per tracer-cell. Where nsteps is odd, a
+ *           second copy of c is taken if a quarter of the device's memory stays
+ *           free; it is given back when another call on the context finds no
+ *           memory, unless a captured graph uses it. Without it the result is
+ *           copied back.
  * Errors : VOFMT_E_ARG for null pointers or non-positive sizes, or when
  *           ntracers * nx * ny * nz reaches 2^32.
  */
@@ -459,9 +462,9 @@ typedef struct {
  * context's own stream and launched on `stream`; a call with the same boxes,
  * tuning, nsteps and step0 mod 3 relaunches the cached graph. A call that
  * builds a new graph synchronises `stream` once (table upload). Scratch: per
- * box a second field copy (and a third where nsteps is odd and the memory is
- * there), a face-flux array, the c > 0.5 bits and the lists
- * of mixed cells, in one slab owned by the context.
+ * box a second field copy, a face-flux array, the c > 0.5 bits and the lists
+ * of mixed cells, in one slab owned by the context; third field copies where
+ * nsteps is odd, as for vofmt_advect.
  * Errors: VOFMT_E_ARG for bad sizes, null pointers, ntracers*cells >= 2^32 or
  * a bad tuning; VOFMT_E_HIP / VOFMT_E_NOMEM from the runtime.
  */

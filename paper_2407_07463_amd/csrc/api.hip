@@ -76,6 +76,14 @@ void *third_copy(vofmt_ctx *ctx, size_t bytes, hipStream_t stream) {
     return ctx->buf[SLOT_THIRD];
   }
   if (capturing || ctx->third_captured) return nullptr;
+  // It stays with the context, and saves the copy back, a tenth of a one-step call:
+  // not worth a later allocation of the caller's own that would fail.
+  size_t unused = 0, total = 0;
+  if (hipMemGetInfo(&unused, &total) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (unused + ctx->cap[SLOT_THIRD] < bytes + total / 4) return nullptr;
   const std::string err = ctx->err;
   void *p = scratch(ctx, SLOT_THIRD, bytes);
   if (!p) ctx->err = err;

@@ -85,7 +85,7 @@ int hip_check(vofmt_ctx *ctx, hipError_t e, const char *what);
 // Device scratch of at least `bytes` in slot `slot`; nullptr on failure (error set).
 void *scratch(vofmt_ctx *ctx, int slot, size_t bytes);
 // The third field copy (SLOT_THIRD), which a call can do without: nullptr and no
-// error when the memory is not there, when it would have to be allocated while
+// error when less than a quarter of the device's memory would stay free, when it would have to be allocated while
 // `stream` is being captured, or when it would have to grow and a graph that a
 // caller captured uses it (the calls that follow the capture may need a larger
 // one, but nothing else to grow).

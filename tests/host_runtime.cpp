@@ -266,11 +266,25 @@ void third_copy_given_back() {
   EXPECT(x.batch(cube(64, 1), 2) == VOFMT_E_NOMEM && g_frees == 0);
 }
 
+// The third field copy leaves a quarter of the device's memory to others.
+void third_copy_leaves_room() {
+  Ctx x;
+  EXPECT(x.advect(128, 1, 2) == VOFMT_OK);
+  const size_t field = 8u * 128 * 128 * 128, before = used();
+  g_total = 4 * (before + field) / 3 - 4096;
+  EXPECT(x.advect(128, 1, 1) == VOFMT_OK && g_device_copies == 1 && used() == before);
+  g_total = 4 * (before + field) / 3 + 4096;
+  EXPECT(x.advect(128, 1, 1) == VOFMT_OK && g_device_copies == 1 && used() == before + field);
+  g_total = before + field;  // at hand: taken, however full the device is by then
+  EXPECT(x.advect(128, 1, 3) == VOFMT_OK && g_device_copies == 1);
+}
+
 const std::map<std::string, std::function<void()>> kScenarios = {
     {"graph_after_failed_growth", graph_after_failed_growth},
     {"call_after_no_memory", call_after_no_memory},
     {"captured_third_copy", captured_third_copy},
     {"third_copy_given_back", third_copy_given_back},
+    {"third_copy_leaves_room", third_copy_leaves_room},
 };
 
 }  // namespace

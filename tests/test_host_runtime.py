@@ -45,3 +45,7 @@ def test_captured_third_copy(program):
 
 def test_third_copy_given_back(program):
     _holds(program, "third_copy_given_back")
+
+
+def test_third_copy_leaves_room(program):
+    _holds(program, "third_copy_leaves_room")
