@@ -450,14 +450,16 @@ typedef struct {
 
 typedef struct {
   int32_t chunk;             /* cells per thread along the marching axis: 8, 16, 32 or 64 */
-  int32_t workgroups_per_cu; /* persistent grid: workgroups per compute unit, 1..32 */
+  int32_t workgroups_per_cu; /* 1..8: a fixed grid of that many workgroups per compute unit; 9..32, more than one
+                                holds at once: a workgroup per work item, and the chunk halved (down to 4) while
+                                a sweep would have too few wavefronts */
 } vofmt_tuning;
 
 /*
  * boxes  : HOST array of nboxes descriptors (device pointers inside). Boxes
  *          must not share fields.
- * tuning : HOST, nullable (chunk by the number of wavefronts, no fixed grid: a
- *          workgroup per work item). Results do not depend on it.
+ * tuning : HOST, nullable (as chunk 32 and 16 workgroups per compute unit).
+ *          Results do not depend on it.
  * The launch sequence of all sweeps is captured into a HIP graph on the
  * context's own stream and launched on `stream`; a call with the same boxes,
  * tuning, nsteps and step0 mod 3 relaunches the cached graph. A call that
@@ -476,7 +478,7 @@ int vofmt_advect_batched(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes,
  * (the caller's data is untouched) with each candidate tuning -- chunk
  * {16, 32, 64} x workgroups per CU {2, 4, 8, 16} -- for nsteps steps, times
  * each graph launch with HIP events (best of two), and returns the fastest.
- * (On the batches measured, a null tuning was faster than every candidate.)
+ * Chunk 32 with 16 workgroups is what a null tuning gives.
  * best_host: HOST output. best_ms_host: nullable HOST output, its time.
  * Synchronises. Scratch: one copy of every field.
  */

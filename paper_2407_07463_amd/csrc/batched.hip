@@ -183,18 +183,18 @@ static int validate(vofmt_ctx *ctx, int32_t nboxes, const vofmt_box *boxes, cons
   return VOFMT_OK;
 }
 
-// Marching chunk without a tuning: as for one box, the longest that gives every
-// sweep kWaves wavefronts, over all boxes (8 boxes of 50 to 90 cells, one step:
+// Marching chunk of a grid per work item: as for one box, the longest (at most
+// `longest`) that gives every sweep kWaves wavefronts, over all boxes (8 boxes of 50 to 90 cells, one step:
 // 396 us at chunk 32, 342 at 16, 331 at 8), and no box's row more segments than
 // cells (its x-sweep is then by whole rows).
-static int pick_batch_chunk(const vofmt_box *boxes, int nboxes) {
+static int pick_batch_chunk(const vofmt_box *boxes, int nboxes, int longest) {
   const bool flat = batch_flat(boxes, nboxes);
   int rows = 1;
   for (int i = 0; i < nboxes && !flat; ++i) {
     const int words = (int)ceil_div(boxes[i].nx, 64);
     rows = words > rows ? words : rows;
   }
-  int chunk = kMaxChunk;
+  int chunk = longest;
   while (chunk > 4 && rows <= chunk / 2) {
     int64_t waves[3] = {0, 0, 0};
     for (int i = 0; i < nboxes; ++i) {
@@ -209,22 +209,23 @@ static int pick_batch_chunk(const vofmt_box *boxes, int nboxes) {
   return chunk;
 }
 
-// Without a tuning the grids are one workgroup per work item (wg_per_cu 0): the
+// Without a tuning, and with one of more workgroups per compute unit than it holds
+// at once, the grids are one workgroup per work item (wg_per_cu 0): the
 // workgroups of a persistent grid have equal shares of the items, whatever these
 // hold, and at 5 resident on a compute unit the last of 8 run alone (32 boxes of
 // 64 to 192 cells, three steps: 23.3 ms with 8 workgroups per compute unit, 22.1
 // with 32, 21.4 so).
+constexpr int kMostFixed = 8;  // workgroups of 4 wavefronts that a compute unit holds
 static int resolve_tuning(vofmt_ctx *ctx, const vofmt_tuning *tuning, const vofmt_box *boxes, int nboxes, int *chunk,
                           int *wg_per_cu) {
-  if (!tuning) {
-    *chunk = pick_batch_chunk(boxes, nboxes);
-    *wg_per_cu = 0;
-    return VOFMT_OK;
-  }
-  *chunk = tuning->chunk;
-  *wg_per_cu = tuning->workgroups_per_cu;
+  *chunk = tuning ? tuning->chunk : kMaxChunk;
+  *wg_per_cu = tuning ? tuning->workgroups_per_cu : 32;
   if (!(*chunk == 8 || *chunk == 16 || *chunk == 32 || *chunk == 64) || *wg_per_cu < 1 || *wg_per_cu > 32)
     return set_err(ctx, VOFMT_E_ARG, "vofmt tuning: chunk must be 8, 16, 32 or 64 and workgroups_per_cu 1..32");
+  if (*wg_per_cu > kMostFixed) {
+    *chunk = pick_batch_chunk(boxes, nboxes, *chunk);
+    *wg_per_cu = 0;
+  }
   return VOFMT_OK;
 }
 

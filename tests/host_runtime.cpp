@@ -279,12 +279,32 @@ void third_copy_leaves_room() {
   EXPECT(x.advect(128, 1, 3) == VOFMT_OK && g_device_copies == 1);
 }
 
+// The autotuner's candidates hold the launches of an untuned call, so that a caller
+// who tunes is at least as fast as one who does not; chunk 16 or 64 as well.
+void tuning_holds_untuned() {
+  Ctx x;
+  for (int n : {32, 60, 128, 200, 256}) {
+    g_launches.clear();
+    EXPECT(x.batch(cube(n, 5), 2) == VOFMT_OK);
+    const std::vector<Launch> untuned = g_launches;
+    g_launches.clear();
+    const vofmt_tuning t{32, 16};
+    EXPECT(x.batch(cube(n, 5), 2, &t) == VOFMT_OK);
+    EXPECT(g_launches.empty() || g_launches == untuned);  // (empty: the same graph)
+    g_launches.clear();
+    const vofmt_tuning fixed{32, 4};
+    EXPECT(x.batch(cube(n, 5), 2, &fixed) == VOFMT_OK);
+    for (const Launch &l : g_launches) EXPECT(l.grid.x == 4 * 256);
+  }
+}
+
 const std::map<std::string, std::function<void()>> kScenarios = {
     {"graph_after_failed_growth", graph_after_failed_growth},
     {"call_after_no_memory", call_after_no_memory},
     {"captured_third_copy", captured_third_copy},
     {"third_copy_given_back", third_copy_given_back},
     {"third_copy_leaves_room", third_copy_leaves_room},
+    {"tuning_holds_untuned", tuning_holds_untuned},
 };
 
 }  // namespace

@@ -49,3 +49,7 @@ def test_third_copy_given_back(program):
 
 def test_third_copy_leaves_room(program):
     _holds(program, "third_copy_leaves_room")
+
+
+def test_tuning_holds_untuned(program):
+    _holds(program, "tuning_holds_untuned")
