@@ -504,12 +504,7 @@ extern "C" int vofmt_autotune_batched(vofmt_ctx *ctx, int32_t nboxes, const vofm
   uint8_t *copies = (uint8_t *)scratch(ctx, SLOT_TUNE, total);
   if (!copies) return VOFMT_E_NOMEM;
   std::vector<vofmt_box> cb(boxes, boxes + nboxes);
-  for (int i = 0; i < nboxes; ++i) {
-    cb[i].c = (double *)(copies + off[i]);
-    VOFMT_HIP(ctx, hipMemcpyAsync(cb[i].c, boxes[i].c,
-                                  sizeof(double) * (size_t)boxes[i].ntracers * boxes[i].nx * boxes[i].ny * boxes[i].nz,
-                                  hipMemcpyDeviceToDevice, stream));
-  }
+  for (int i = 0; i < nboxes; ++i) cb[i].c = (double *)(copies + off[i]);
   hipEvent_t e0, e1;
   VOFMT_HIP(ctx, hipEventCreate(&e0));
   VOFMT_HIP(ctx, hipEventCreate(&e1));
@@ -519,7 +514,13 @@ extern "C" int vofmt_autotune_batched(vofmt_ctx *ctx, int32_t nboxes, const vofm
   for (int a = 0; a < 3 && rc == VOFMT_OK; ++a)
     for (int b = 0; b < 4 && rc == VOFMT_OK; ++b) {
       vofmt_tuning t{chunks[a], wgs[b]};
-      rc = vofmt_advect_batched(ctx, nboxes, cb.data(), 0, nsteps, &t, stream);  // builds the graph, warms up
+      // the same fields for every candidate: sweeps take longer as a field gets older
+      // (round-off residues, stretched drops), which favoured the first ones
+      for (int i = 0; i < nboxes && rc == VOFMT_OK; ++i)
+        rc = hip_check(ctx, hipMemcpyAsync(cb[i].c, boxes[i].c,
+                                           sizeof(double) * (size_t)boxes[i].ntracers * boxes[i].nx * boxes[i].ny * boxes[i].nz,
+                                           hipMemcpyDeviceToDevice, stream), "autotune copies");
+      if (rc == VOFMT_OK) rc = vofmt_advect_batched(ctx, nboxes, cb.data(), 0, nsteps, &t, stream);  // builds the graph, warms up
       float ms_best = -1.0f;
       for (int rep = 0; rep < 2 && rc == VOFMT_OK; ++rep) {
         if (hipEventRecord(e0, stream) != hipSuccess) rc = set_err(ctx, VOFMT_E_HIP, "hipEventRecord failed");

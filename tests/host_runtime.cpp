@@ -298,6 +298,16 @@ void tuning_holds_untuned() {
   }
 }
 
+// Every candidate is timed on the caller's fields, not on those that the candidates
+// before it have advanced.
+void tuning_on_equal_fields() {
+  Ctx x;
+  const vofmt_box b[3] = {cube(40, 2), cube(64, 1), cube(33, 3)};
+  vofmt_tuning best;
+  EXPECT(vofmt_autotune_batched(x.c, 3, b, 2, &best, nullptr, nullptr) == VOFMT_OK);
+  EXPECT(g_device_copies == 3 * 12);
+}
+
 const std::map<std::string, std::function<void()>> kScenarios = {
     {"graph_after_failed_growth", graph_after_failed_growth},
     {"call_after_no_memory", call_after_no_memory},
@@ -305,6 +315,7 @@ const std::map<std::string, std::function<void()>> kScenarios = {
     {"third_copy_given_back", third_copy_given_back},
     {"third_copy_leaves_room", third_copy_leaves_room},
     {"tuning_holds_untuned", tuning_holds_untuned},
+    {"tuning_on_equal_fields", tuning_on_equal_fields},
 };
 
 }  // namespace

@@ -53,3 +53,7 @@ def test_third_copy_leaves_room(program):
 
 def test_tuning_holds_untuned(program):
     _holds(program, "tuning_holds_untuned")
+
+
+def test_tuning_on_equal_fields(program):
+    _holds(program, "tuning_on_equal_fields")
