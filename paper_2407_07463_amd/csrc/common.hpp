@@ -111,6 +111,15 @@ __device__ __forceinline__ int wrap_any(int i, int n) {
   return r < 0 ? r + n : r;
 }
 
+// Orders LDS accesses between the lanes of a wavefront: what a lane stored before
+// it, other lanes load after it. (A wavefront's LDS accesses are in order as they
+// are; this tells the compiler.)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 static inline unsigned ceil_div(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
 
 // Division of 32-bit unsigned integers by an invariant divisor d >= 1 with a

@@ -871,13 +871,14 @@ __global__ __launch_bounds__(kBlock) void k_drop_scan(const int32_t *__restrict_
       }
       n += (int)__popcll(starts);
       if (n > kRuns - 64) {  // room for the next segment's: a full wavefront of runs is merged
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         n -= 64;
         merge(n + lane);
+        wave_sync();
       }
     }
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
   if (lane < n) merge(lane);
   __syncthreads();
   for (int i = threadIdx.x; i < kTable; i += kBlock) {

@@ -823,12 +823,6 @@ __global__ __launch_bounds__(256) void k_curv_fallback(const double *__restrict_
 // so y is bit-identical to vofmt_mlp_forward on the same stencils.
 constexpr int FWAVES = 12;  // wavefronts per workgroup (LDS: 41 KB of weights + 9 KB per wavefront)
 
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 constexpr int XSP = 36;  // row pitch (floats) of the stencil rows in LDS: 16-byte rows, conflict-free reads
 
 __global__ __launch_bounds__(64 * FWAVES) void k_curv_fused(
