@@ -576,11 +576,12 @@ constexpr int kMaxTileReach = 4;
 constexpr int kHaloX = 4;  // cells of x-halo held, whatever the reach: the tile's rows stay 8-byte aligned
 constexpr int kPairCache = 256;
 // The half ball as rows of cells along x: row k covers x + lo .. x + hi at the
-// LDS offset `base` of its (dy, dz).
+// LDS offset `base` of its (dy, dz), offsets first .. first + hi - lo of the ball's.
+constexpr int kMaxTileRows = (kMaxTileReach + 1) * (2 * kMaxTileReach + 1);
 struct TileRows {
-  int n;
-  int16_t base[(kMaxTileReach + 1) * (2 * kMaxTileReach + 1)];
-  int8_t lo[(kMaxTileReach + 1) * (2 * kMaxTileReach + 1)], hi[(kMaxTileReach + 1) * (2 * kMaxTileReach + 1)];
+  int n, all;
+  int16_t base[kMaxTileRows], first[kMaxTileRows];
+  int8_t lo[kMaxTileRows], hi[kMaxTileRows];
 };
 template <int R>
 struct TileDims {
@@ -598,12 +599,18 @@ __device__ __forceinline__ uint32_t low_high(uint32_t u, uint32_t v) {
   return lo | ((uint32_t)(hu > hv ? hu : hv) << 16);
 }
 
+// split workgroups take a tile together, each with its owners in LDS and the
+// boundary cells of every split-th group of 16 rows: up to kSplitTiles of them,
+// two a CU (two fields of 64^3, 64 tiles, a tenth of the cells shared, gap 3.5
+// and stencil 1.20 and 1.55 ms without the split, 0.49 and 0.64 so; 18 separate
+// drops 149 -> 133 and 184 -> 166 us).
+constexpr int64_t kSplitTiles = 512;
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict__ own,
                                                        const int32_t *__restrict__ lab, int nx, int ny, int nz,
-                                                       int ntr, TracerOffsets to, TileRows rows, int reach, int max_o2,
-                                                       int tx, int ty, uint32_t *__restrict__ adj, int64_t words,
-                                                       const int32_t *__restrict__ cross_T0) {
+                                                       int ntr, TracerOffsets to, TileRows rows,
+                                                       int tx, int ty, int split, uint32_t *__restrict__ adj,
+                                                       int64_t words, const int32_t *__restrict__ cross_T0) {
   constexpr int LX = TileDims<R>::LX, LY = TileDims<R>::LY, LZ = TileDims<R>::LZ;
   constexpr int kWaves = kBlock / 64, kRows = LY * LZ;
   constexpr int ND = R + 1;  // pairs of cells that cover 2 R + 1 cells from either parity
@@ -617,11 +624,16 @@ __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict
   // smallest and largest drop: of 4 cells along x and all y of a plane, and of
   // what the half balls of 4 of the tile's cells in a plane can reach
   constexpr int kGroupsX = LX / 4, kOwnX = kTileX / 4;
-  __shared__ uint32_t of_group[kGroupsX * LZ], in_reach[kOwnX * kTileZ];
+  // In their place then the half ball's offsets, for the shared cells: (ox, oy, oz)
+  // + 8 in 4 bits each, the LDS offset above (four workgroups of R = 4 a CU, not three).
+  constexpr int kBall = ((2 * R + 1) * (2 * R + 1) * (2 * R + 1) - 1) / 2, kReach = kGroupsX * LZ + kOwnX * kTileZ;
+  __shared__ uint32_t small[kBall > kReach ? kBall : kReach];
+  uint32_t *const of_group = small, *const in_reach = small + kGroupsX * LZ, *const ball = small;
   static_assert(kGroupsX * LZ <= kBlock && kOwnX * kTileZ <= kBlock && kMaxTileReach <= 4, "a thread each, x-reach of one group");
   // each XCD takes a contiguous run of tiles, so that a tile's halo is in its L2
   const unsigned nwg = gridDim.x, per = nwg / 8, rem = nwg % 8, k8 = blockIdx.x % 8;
-  const unsigned L = k8 * per + (k8 < rem ? k8 : rem) + blockIdx.x / 8;
+  const unsigned W = k8 * per + (k8 < rem ? k8 : rem) + blockIdx.x / 8, L = W / split;
+  const int part = (int)(W % split);
   const int x0 = (int)(L % tx) * kTileX, y0 = (int)((L / tx) % ty) * kTileY, z0 = (int)(L / ((unsigned)tx * ty)) * kTileZ;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // Cells before the tile's row (y0 - R + ly, z0 - 1 + lz): at_y[ly] + at_z[lz],
@@ -703,7 +715,7 @@ __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict
   __syncthreads();
   // boundary cells: 4 consecutive cells per lane, 4 rows per wavefront; not
   // those that reach no drop but their own
-  for (int r0 = 4 * wv; r0 < kTileY * kTileZ; r0 += 4 * kWaves) {
+  for (int r0 = 4 * (wv + kWaves * part); r0 < kTileY * kTileZ; r0 += 4 * kWaves * split) {
     const int r = r0 + (lane >> 4), dy = r % kTileY, dz = r / kTileY;
     const int xl = 4 * (lane & 15), i = ((dz + 1) * LY + dy + R) * LX + kHaloX + xl;
     auto four = [&](int at) { return *(const uint64_t *)(tile + at); };
@@ -776,32 +788,85 @@ __global__ __launch_bounds__(kBlock) void k_tile_edges(const owner_t *__restrict
       }
     }
   }
-  // Shared cells scan the whole ball (the cells of one drop above do not look
-  // at them), a wavefront each, a lane per offset: drops sharing the cell are
-  // neighbours (offset 0 across tracers), and each of them of every drop in
-  // the ball.
+  // Shared cells, a wavefront each: the drops sharing one are neighbours (offset 0
+  // across tracers), and those that have a boundary there (a six-neighbour without
+  // the drop; the argument above holds for each drop) look through the ball, a lane
+  // per offset of its forward half and of the opposite one. The cells of one drop
+  // above do not look at shared ones, so these look at cells of one drop on both
+  // sides, and at shared cells forwards. Every tracer's labels there are read once
+  // for all the drops of this cell.
+  // (Four fields of 192^3 whose drops overlap, the whole call with gap 1.5, gap 3.5
+  // and the stencil: every drop of the cell through the whole cube around it, shared
+  // cells both ways and their labels once per drop, 10.8, 59.5 and 65.2 ms; 3.3, 5.7
+  // and 7.4 so; from the list in memory, a thread per cell, 4.7, 15.7 and 33.8.)
+  if (nshared == 0) return;  // (uniform over the workgroup)
+  constexpr int kTurns = (kBall + 63) / 64, kLabels = 4;  // offsets a lane; tracers whose labels are in flight together
+  if (threadIdx.x < rows.n) {
+    const int base = rows.base[threadIdx.x], lo = rows.lo[threadIdx.x], first = rows.first[threadIdx.x];
+    const int row = base / LX, oz = (row + R) / LY, oy = row - oz * LY;  // (base = LX (LY oz + oy))
+    for (int dx = lo; dx <= rows.hi[threadIdx.x]; ++dx)
+      ball[first + dx - lo] = ((uint32_t)(base + dx) << 16) | (uint32_t)((oz + 8) << 8 | (oy + 8) << 4 | (dx + 8));
+  }
+  __syncthreads();
   for (int q = wv; q < nshared; q += kWaves) {
     const int i = list[kCellsOfTile - 1 - q], r = i / LX;
     const int x = x0 - kHaloX + i % LX, y = y0 - R + r % LY, z = z0 - 1 + r / LY;
-    const int64_t p = ((int64_t)z * ny + y) * nx + x;
+    auto cell_at = [&](int ox, int oy, int oz) {
+      return ((int64_t)wrap_near(z + oz, nz) * ny + wrap_near(y + oy, ny)) * nx + wrap_near(x + ox, nx);
+    };
     int32_t here = -1;  // lane t: the drop of tracer t here (at most 64 tracers)
+    bool boundary = false;
     if (lane < ntr) {
-      const int32_t l = lab[(int64_t)lane * n3 + p];
-      if (l > 0 && to.off[lane] + l <= to.off[lane + 1]) here = to.off[lane] + l - 1;
+      const int32_t *l = lab + (int64_t)lane * n3;
+      const int32_t l0 = l[cell_at(0, 0, 0)];
+      const int32_t xm = l[cell_at(-1, 0, 0)], xp = l[cell_at(1, 0, 0)], ym = l[cell_at(0, -1, 0)],
+                    yp = l[cell_at(0, 1, 0)], zm = l[cell_at(0, 0, -1)], zp = l[cell_at(0, 0, 1)];
+      if (l0 > 0 && to.off[lane] + l0 <= to.off[lane + 1]) here = to.off[lane] + l0 - 1;
+      boundary = here >= 0 && !(xm == l0 && xp == l0 && ym == l0 && yp == l0 && zm == l0 && zp == l0);
     }
-    const uint64_t drops = __ballot(here >= 0);
-    const int side = 2 * reach + 1, all = side * side * side;
-    for (int e = lane; e < ((all + 63) & ~63); e += 64) {
-      const int ox = e % side - reach, oy = (e / side) % side - reach, oz = e / (side * side) - reach;
-      const bool in = e < all && ox * ox + oy * oy + oz * oz <= max_o2;
-      const int64_t at = ((int64_t)wrap_near(z + (in ? oz : 0), nz) * ny + wrap_near(y + (in ? oy : 0), ny)) * nx +
-                         wrap_near(x + (in ? ox : 0), nx);
-      const int32_t b = in ? own[at] : -1;
-      for (uint64_t left = drops; left; left &= left - 1) {
-        const int32_t u = __builtin_amdgcn_readlane(here, (int)__builtin_ctzll(left));
-        if (b >= 0) edge(u, b);
-        else if (b == -2) for_drops_at(lab, n3, ntr, to, at, [&](int32_t v) { edge(u, v); });
-      }
+    for (uint64_t left = __ballot(here >= 0); left; left &= left - 1) {
+      const int32_t u = __builtin_amdgcn_readlane(here, (int)__builtin_ctzll(left));
+      if (here > u) edge(u, here);
+    }
+    const uint64_t drops = __ballot(boundary);
+    if (drops == 0ull || rows.all == 0) continue;  // whole wavefront
+    auto pairs_with = [&](int32_t v) {
+      for (uint64_t left = drops; left; left &= left - 1)
+        edge(__builtin_amdgcn_readlane(here, (int)__builtin_ctzll(left)), v);
+    };
+    // (every lane loads, from a valid slot when it has no offset or no shared cell there)
+    int32_t f[kTurns], g[kTurns], at[kTurns];
+    bool shared = false;
+#pragma unroll
+    for (int j = 0; j < kTurns; ++j) {
+      const bool in = lane + 64 * j < rows.all;
+      const uint32_t o = ball[in ? lane + 64 * j : 0];
+      const int ox = (int)(o & 15u) - 8, oy = (int)(o >> 4 & 15u) - 8, oz = (int)(o >> 8 & 15u) - 8;
+      f[j] = tile[i + ((int32_t)o >> 16)];
+      g[j] = own[cell_at(-ox, -oy, -oz)];
+      if (!in) f[j] = g[j] = -1;
+      at[j] = f[j] == -2 ? (int32_t)cell_at(ox, oy, oz) : (int32_t)cell_at(0, 0, 0);
+      shared = shared || f[j] == -2;
+    }
+#pragma unroll
+    for (int j = 0; j < kTurns; ++j) {
+      if (f[j] >= 0) pairs_with(f[j]);
+      if (g[j] >= 0) pairs_with(g[j]);
+    }
+    if (__ballot(shared) == 0ull) continue;  // whole wavefront
+    for (int t0 = 0; t0 < ntr; t0 += kLabels) {
+      int32_t l[kTurns][kLabels];
+#pragma unroll
+      for (int j = 0; j < kTurns; ++j)
+#pragma unroll
+        for (int k = 0; k < kLabels; ++k) l[j][k] = lab[(int64_t)(t0 + k < ntr ? t0 + k : t0) * n3 + at[j]];
+#pragma unroll
+      for (int j = 0; j < kTurns; ++j)
+#pragma unroll
+        for (int k = 0; k < kLabels; ++k) {
+          const int t = t0 + k;
+          if (t < ntr && f[j] == -2 && l[j][k] > 0 && to.off[t] + l[j][k] <= to.off[t + 1]) pairs_with(to.off[t] + l[j][k] - 1);
+        }
     }
   }
 }
@@ -1254,21 +1319,23 @@ static int recolor_impl(vofmt_ctx *ctx, const char *fn, int stencil, int32_t nx,
       const int16_t base = (int16_t)((o.z * LY + o.y) * LX);
       if (lo.n == 0 || lo.base[lo.n - 1] != base) {
         lo.base[lo.n] = base;
+        lo.first[lo.n] = (int16_t)lo.all;
         lo.lo[lo.n++] = (int8_t)o.x;
       }
+      ++lo.all;
       lo.hi[lo.n - 1] = (int8_t)o.x;
     }
     const int tx = (int)ceil_div(nx, kTileX), ty = (int)ceil_div(ny, kTileY);
     const int64_t tiles = (int64_t)tx * ty * ceil_div(nz, kTileZ);
+    int split = 1;
+    while (split < kTileY * kTileZ / (4 * (kBlock / 64)) && 2 * split * tiles <= kSplitTiles) split *= 2;
     const int32_t *cross = stencil ? (const int32_t *)T0 : nullptr;
-    int max_o2 = 0;  // the ball's offsets are those of |o|^2 <= max_o2 in the cube of reach R
-    for (const int4 &o : hoffs) max_o2 = std::max(max_o2, o.x * o.x + o.y * o.y + o.z * o.z);
     if (Rt == 2)
-      hipLaunchKernelGGL((k_tile_edges<2>), dim3((unsigned)tiles), dim3(kBlock), 0, stream, own, labels, nx, ny, nz,
-                         ntr, to, lo, R, max_o2, tx, ty, adj, words, cross);
+      hipLaunchKernelGGL((k_tile_edges<2>), dim3((unsigned)(tiles * split)), dim3(kBlock), 0, stream, own, labels, nx,
+                         ny, nz, ntr, to, lo, tx, ty, split, adj, words, cross);
     else
-      hipLaunchKernelGGL((k_tile_edges<kMaxTileReach>), dim3((unsigned)tiles), dim3(kBlock), 0, stream, own, labels,
-                         nx, ny, nz, ntr, to, lo, R, max_o2, tx, ty, adj, words, cross);
+      hipLaunchKernelGGL((k_tile_edges<kMaxTileReach>), dim3((unsigned)(tiles * split)), dim3(kBlock), 0, stream, own,
+                         labels, nx, ny, nz, ntr, to, lo, tx, ty, split, adj, words, cross);
   } else {
     // the cells that can see a pair, in order, then the pairs they see
     const int64_t lt = compact::list_tiles_if(n3);
