@@ -28,13 +28,18 @@ __device__ __forceinline__ double min_image(double d, double L) {
   return d + (d > 0.5 * L ? -L : (d <= -0.5 * L ? L : 0.0));
 }
 
+// The same up to its sign, which its square does not see: |d|, or L - |d| (of any
+// sign for points outside the box) where that is smaller, that is beyond L / 2.
+__device__ __forceinline__ double image_distance(double d, double L) { return fmin(fabs(d), L - fabs(d)); }
+
 // Candidate slices: the j range is cut into `ns` slices of `len` indices
 // (a multiple of kBlock); workgroup (ib, s) scans slice s for the kBlock
 // drops of block ib and keeps, per drop, the slice's smallest d2, the first j
 // attaining it and how many j attain it. The candidates' loop has no branch: it
-// is a chain of dependent selects that unrolled bodies overlap (with a branch
-// per axis and comparison 35 us for 125 drops and 80 for 5000, 13 and
-// 46 so).
+// is a chain of dependent selects that unrolled bodies overlap. Few drops are bound
+// by that chain, many by its instructions, whence the image's distance by a minimum
+// (the whole call for 100, 5000 and 100000 drops: a branch per axis and comparison 66, 133 and 8800 us,
+// the image by two selects 42, 91 and 10100, so 40, 79 and 6380).
 __global__ __launch_bounds__(kBlock) void k_nearest_slice(const double *__restrict__ xyz, int32_t n, Box box,
                                                           int32_t len, double *__restrict__ sbest,
                                                           int32_t *__restrict__ sbj, int32_t *__restrict__ sties) {
@@ -65,9 +70,9 @@ __global__ __launch_bounds__(kBlock) void k_nearest_slice(const double *__restri
 #pragma unroll 4
       for (int k = 0; k < m; ++k) {
         const int32_t j = j0 + k;
-        const double rx = min_image(sx[k] - xi, box.L[0]);
-        const double ry = min_image(sy[k] - yi, box.L[1]);
-        const double rz = min_image(sz[k] - zi, box.L[2]);
+        const double rx = image_distance(sx[k] - xi, box.L[0]);
+        const double ry = image_distance(sy[k] - yi, box.L[1]);
+        const double rz = image_distance(sz[k] - zi, box.L[2]);
         const double d2 = (rx * rx + ry * ry) + rz * rz;
         const bool less = (d2 < best) & (j != i), equal = (d2 == best) & (j != i);
         ties = less ? 1 : ties + (equal ? 1 : 0);
