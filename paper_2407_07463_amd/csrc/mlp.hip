@@ -382,9 +382,10 @@ __global__ __launch_bounds__(64 * IWAVES) __attribute__((amdgpu_waves_per_eu(4))
 // tiles per workgroup a batch of 4096 had 8 workgroups: training forward 20.5 us,
 // 6.6 us so; plain forward, the whole call, 60000 samples 19.8 -> 11.6 us, 120000
 // 25.4 -> 13.5, 300000 34.5 -> 27.1. Each workgroup stages the weights for one
-// tile only, so the persistent kernels are ahead from about 8000 tiles on (700000
+// tile only, so the persistent kernels are ahead from 7800 to 8200 tiles on (700000
 // samples: 49.7 us there, 53.9 so).
-constexpr int kSmallTiles = 8192;  // batches of at most so many tiles take it
+// Without records the two cross at 7800 tiles (7500: 41.1 and 39.5 us, 8192: 41.3 and 42.6).
+constexpr int kSmallTiles = 8192, kSmallPlain = 7680;  // batches of at most so many tiles take it
 template <bool kTrain, bool kActs>
 __global__ __launch_bounds__(64 * WMT) void k_mlp_fwd_small(const float *__restrict__ P, const uint4 *__restrict__ w1f_g,
                                                            const uint4 *__restrict__ w2f_g, int m,
@@ -944,7 +945,7 @@ extern "C" int vofmt_mlp_forward(vofmt_ctx *ctx, const float *params, int32_t m,
     hipLaunchKernelGGL(kernel, dim3(tiles), dim3(64 * WMT), 0, stream, params, (const uint4 *)w[0],
                        (const uint4 *)w[1], m, x, y, acts, (const float *)nullptr, (float *)nullptr, (float *)nullptr);
   };
-  if (tiles <= kSmallTiles) {
+  if (tiles <= (acts ? kSmallTiles : kSmallPlain)) {
     if (acts) small(k_mlp_fwd_small<false, true>);
     else small(k_mlp_fwd_small<false, false>);
   } else if (acts)
