@@ -672,7 +672,7 @@ __global__ __launch_bounds__(kBlock) void k_label_write(const uint64_t *__restri
   T.P += blockIdx.y * nrun;
   lab += blockIdx.y * n3;
   uint64_t m[kGroups];
-  int64_t sg[kGroups];
+  std::conditional_t<LINEAR, int64_t, int32_t> sg[kGroups];
   int b0[kGroups];
 #pragma unroll
   for (int k = 0; k < kGroups; ++k) {
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(kBlock) void k_label_write(const uint64_t *__restri
     const uint32_t pc = (uint32_t)(p < n3 ? p : 0);
     const uint32_t row = LINEAR ? 0u : fast_div(pc, fnx);
     const uint32_t x = LINEAR ? pc : pc - row * (uint32_t)nx;
-    sg[k] = (int64_t)(row * (uint32_t)words + (x >> 6));
+    sg[k] = (std::conditional_t<LINEAR, int64_t, int32_t>)(row * (uint32_t)words + (x >> 6));
     b0[k] = LINEAR ? (V * lane) & 63 : (int)(x & 63u);
     m[k] = occ[sg[k]];
   }
@@ -1265,8 +1265,12 @@ __global__ __launch_bounds__(64) void k_shape_finish(int32_t K, int nx, int ny, 
 constexpr int kTileSegs = 2048;
 // Grids with few such tiles take tiles of 512 (198x187x206 x 3, 226 tiles: 27 -> 13
 // us; 330x280x310 x 4, 1020 tiles: 60 -> 32 us; at 512^3 x 8, 8192 tiles, 0.44 ms
-// against 0.27 for passes 2a + 2b).
-constexpr int kSmallTileSegs = 512, kFewTiles = 4096;
+// against 0.27 for passes 2a + 2b). The line is at 4096 large tiles (the whole call
+// 2 to 6% faster with small ones at 2080 to 3648 tiles of 320^3 x 8, 400^3 x 6,
+// 448^3 x 5 and 384^3 x 8), but at 1024 where a row's words divide a tile's and the
+// large tile is 16 x 16 rows (512^3 x 1 and 256^3 x 8, 1024 tiles, 3 and 2% faster
+// with small ones; 512^3 x 2 and x 3 1.5 and 2.7% slower).
+constexpr int kSmallTileSegs = 512, kFewTiles = 4096, kFewSquareTiles = 1024;
 // Row tiles of the local union pass: as many whole rows as fit ts segments,
 // tz the largest power of two up to their square root (at most nz), the rest
 // along y. Rows longer than ts segments take the global unions only (ty = 0).
@@ -1318,7 +1322,8 @@ static int label_all(vofmt_ctx *ctx, int nx, int ny, int nz, int T, const double
                      nrun);
   // smaller row tiles while the larger ones would leave compute units without one
   RowTiles rt = row_tiles(ny, nz, words, kTileSegs);
-  const bool few = rt.ty > 0 && (int64_t)rt.nty * ceil_div(nz, rt.tz) * T < kFewTiles && words <= kSmallTileSegs;
+  const int line = kTileSegs % words == 0 ? kFewSquareTiles : kFewTiles;
+  const bool few = rt.ty > 0 && (int64_t)rt.nty * ceil_div(nz, rt.tz) * T <= line && words <= kSmallTileSegs;
   if (few) rt = row_tiles(ny, nz, words, kSmallTileSegs);
   if (rt.ty > 0) {
     const int ntile = (int)(rt.nty * ceil_div(nz, rt.tz));

@@ -2,10 +2,14 @@
 another turn, where other tests have only one side.
 
 Network forward without records: a workgroup per 64 samples up to 7680 tiles, whole
-tiles per wavefront above; with records up to 8192. Outputs are bit-identical."""
+tiles per wavefront above; with records up to 8192. Outputs are bit-identical.
+
+Labelling: union tiles of 2048 segments above 1024 of them where a row's words divide
+2048, on rows and planes that fill no tile. Exact."""
 import numpy as np
 import pytest
 
+import oracle
 from gpu_util import note, require_gpu
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +39,19 @@ def test_forward_without_records(ctx, m):
     ctx.mlp_forward(params, x, plain[:m])
     ctx.mlp_forward(params, x, recorded[:m], acts)
     assert torch.equal(plain, recorded) and float(plain[m]) == 7.0
+
+
+def test_large_union_tiles(ctx):
+    """361 tiles of 32 x 32 rows of 2 words a field, the last ones in y and z cut."""
+    import torch
+
+    shape, ntr = (601, 599, 70), 3
+    rng = np.random.default_rng(8)
+    c = np.where(rng.random((ntr,) + shape, dtype=np.float32) < 0.32, 0.5, 0.0)
+    note(f"large union tiles {shape} x {ntr}")
+    lab = torch.full(c.shape, -7, dtype=torch.int32, device="cuda:0")
+    nd = ctx.label_drops(torch.from_numpy(c).to("cuda:0"), lab)
+    for t in range(ntr):
+        want, k = oracle.label(c[t])
+        assert nd[t] == k
+        assert np.array_equal(lab[t].cpu().numpy(), want)
