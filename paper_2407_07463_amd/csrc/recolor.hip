@@ -125,6 +125,22 @@ __device__ __forceinline__ void edges_of(const owner_t *__restrict__ own, const 
       });
     });
   }
+  // Of a shared cell's drops only those look further that have a boundary here
+  // (bits of their tracers): see the choice of cells below, drop by drop.
+  uint64_t mine = 0;
+  if (a == -2) {
+    const int64_t plane = (int64_t)ny * nx, yr = (int64_t)y * nx, zr = z * plane;
+    const int64_t xm = zr + yr + wrap_dec(x, nx), xp = zr + yr + wrap_inc(x, nx);
+    const int64_t ym = zr + (int64_t)wrap_dec(y, ny) * nx + x, yp = zr + (int64_t)wrap_inc(y, ny) * nx + x;
+    const int64_t zm = wrap_dec(z, nz) * plane + yr + x, zp = wrap_inc(z, nz) * plane + yr + x;
+    for (int t = 0; t < ntr; ++t) {
+      const int32_t *lt = lab + (int64_t)t * n3;
+      const int32_t l = lt[p];
+      const bool inside = lt[xm] == l && lt[xp] == l && lt[ym] == l && lt[yp] == l && lt[zm] == l && lt[zp] == l;
+      if (l > 0 && to.off[t] + l <= to.off[t + 1] && !inside) mine |= 1ull << t;
+    }
+    if (mine == 0ull) return;
+  }
   // The owners of kBatch offsets are loaded together (past the last offset
   // every lane loads its own cell and ignores it); a drop just paired with
   // this cell's drop is not paired again (a boundary cell sees a neighbouring
@@ -169,7 +185,9 @@ __device__ __forceinline__ void edges_of(const owner_t *__restrict__ own, const 
         }
       };
       if (a >= 0) with_q(a);
-      else for_drops_at(lab, n3, ntr, to, p, with_q);
+      else
+        for (int t = 0; t < ntr; ++t)
+          if ((mine >> t) & 1ull) with_q(to.off[t] + lab[(int64_t)t * n3 + p] - 1);
     }
   }
 }
