@@ -68,3 +68,27 @@ def test_split_rows_of_a_fixed_grid(ctx, sizes, tuning, step0):
     """Items of the LDS x-sweep follow one another in a workgroup."""
     note(f"batched split rows {sizes} tuning={tuning} step0={step0}")
     _batch_like_plain(ctx, sizes, step0, 1, tuning, 811)
+
+
+@pytest.mark.parametrize("step0", [0, 1, 2])
+@pytest.mark.parametrize("shape,ntr", [((4, 6, 2112), 1), ((3, 5, 2112), 3), ((5, 3, 2176), 4), ((2, 4, 2112), 5),
+                                       ((4, 2, 2624), 7), ((5, 9, 2048), 3), ((9, 8, 576), 7), ((17, 33, 320), 5)])
+def test_rows_of_whole_segments(ctx, shape, ntr, step0):
+    """Above and at 2048 cells (several wavefronts a row, one), in groups of 1 to 4 tracers."""
+    import torch
+
+    c, s = _random(shape, ntr, 41 + sum(shape))
+    note(f"advect whole segments {shape} ntr={ntr} step0={step0}")
+    tc, *ts = _dev(c, *s)
+    ctx.advect(tc, *ts, step0=step0, nsteps=2)
+    torch.cuda.synchronize()
+    assert np.abs(tc.cpu().numpy() - oracle.advect(c, *s, step0, 2)).max() <= TOL
+
+
+@pytest.mark.parametrize("tuning", [None, (8, 1), (8, 16), (16, 2), (32, 4), (64, 8), (64, 32)])
+@pytest.mark.parametrize("step0,nsteps", [(0, 1), (1, 2), (5, 3)])
+def test_batch_of_whole_segments(ctx, tuning, step0, nsteps):
+    """Rows of 1 to 33 segments and groups of 1 to 4 tracers in one batch by segments."""
+    sizes = [((20, 24, 64), 3), ((9, 33, 128), 5), ((12, 10, 576), 4), ((5, 7, 320), 7), ((6, 5, 2112), 2), ((3, 4, 192), 1)]
+    note(f"batch of whole segments tuning={tuning} step0={step0} nsteps={nsteps}")
+    _batch_like_plain(ctx, sizes, step0, nsteps, tuning, 907)
