@@ -1,5 +1,5 @@
 // Device bodies of one advection sweep, shared by the plain launches
-// (vofmt_advect) and the batched persistent launches (vofmt_advect_batched):
+// (vofmt_advect) and the launches over all boxes of a batch (vofmt_advect_batched):
 // both paths run exactly this code, so their results agree bit for bit.
 //
 // Direction-split geometric PLIC advection of N tracer fields (eq. 3 of the
@@ -168,7 +168,7 @@ __device__ __forceinline__ void plic_fluxes(const double *b, double s_lo, double
 // entries is then paid once for 4 regions, and the regions' lengths even out (a
 // region to a wavefront -> this, one sweep: 64^3 x 2 10.3 -> 8.2 us,
 // 134x129x141 x 7 39.1 -> 29.1, 512^3 x 8 1060 -> 1010). The work itself is
-// bound by its FP64 instructions, 33 divisions among them.
+// bound by its FP64 instructions, 18 divisions among them.
 constexpr int kPlicRegions = 4;
 template <int D>
 __device__ __forceinline__ void plic_body(const double *__restrict__ cin, const double *__restrict__ s,
@@ -804,7 +804,11 @@ static inline int64_t stream_waves(int d, int nx, int ny, int nz, int chunk, int
 // last of a plane is full (one step, by segments -> flat: 134x129x141 x 7 444 ->
 // 372 us; 65x300x300 x 8 1136 -> 843; 250^3 x 8, 2% idle, 2138 -> 2050; 32 boxes
 // of 64 to 192 cells, three steps, 25.4 -> 23.2 ms). Rows of whole segments fill
-// them either way and keep scalar words and addresses.
+// them either way and keep scalar words and addresses. Rows that leave one lane
+// idle go either way by a few percent (120x120 rows x 4 of 63, 255, 319, 447 and 511
+// cells: 142 -> 146, 299 -> 314, 377 -> 356, 495 -> 464, 546 -> 519 us; 511^3 x 4
+// 9.87 -> 9.99 ms; a batch of 12 boxes of 128^3, one of them 127^3, 3.25 -> 3.27), so
+// the line is at whole segments.
 static inline bool flat_possible(int nx, int ny, int nz) {
   // (a plane of more than 65535 workgroups is no grid of the plain path; at
   // nx = 1 a tracer's half words could number 2^32)

@@ -1,7 +1,8 @@
 // Batched advection: many boxes of uneven sizes and tracer counts advanced
 // together. Every pass of a sweep is one launch for all boxes over a flattened
 // table of work items (box, tracer group, tile), a workgroup to an item or, with
-// a tuning, a fixed grid that walks the table, and it runs the same sweep bodies as the plain path, so each box's result is
+// a tuning of up to 8 workgroups per compute unit, a fixed grid that walks the
+// table, and it runs the same sweep bodies as the plain path, so each box's result is
 // bit-identical to advecting it alone. The whole multi-step sequence is
 // captured once into a HIP graph and replayed with a single graph launch;
 // a later call with the same configuration reuses the graph.
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(256) void k_stream_b(const BoxDev *__restrict__ box
   for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
     const Seg sg = segs[find_seg(segs, nseg, item)];
     const BoxDev &b = boxes[sg.box];
-    // (the grid is a multiple of 8 workgroups, so items 8 apart share an XCD)
+    // (workgroups go to the 8 XCDs in turn, and a fixed grid is a multiple of 8: items 8 apart share an XCD)
     const GroupTile g = group_tile(item - sg.item0, sg.gx, sg.gy, sg.gz, sg.ngrp, D == 1);
     const int64_t region0 = g.grp * sg.gstride;
     const int gm = largest_group(b.ntr);  // uniform over the workgroup
@@ -134,7 +135,7 @@ inline size_t field_bytes(const vofmt_box &b) {
 struct Plan {
   int nboxes;
   int chunk, rsize;
-  int grid;  // workgroups of the persistent launches; 0: one per work item
+  int grid;  // workgroups of the fixed grids; 0: one per work item
   bool flat;  // the boxes have the flat layout
   // table offsets in the slab (bytes) and segment counts
   size_t off_boxes;
@@ -211,7 +212,7 @@ static int pick_batch_chunk(const vofmt_box *boxes, int nboxes, int longest) {
 
 // Without a tuning, and with one of more workgroups per compute unit than it holds
 // at once, the grids are one workgroup per work item (wg_per_cu 0): the
-// workgroups of a persistent grid have equal shares of the items, whatever these
+// workgroups of a fixed grid have equal shares of the items, whatever these
 // hold, and at 5 resident on a compute unit the last of 8 run alone (32 boxes of
 // 64 to 192 cells, three steps: 23.3 ms with 8 workgroups per compute unit, 22.1
 // with 32, 21.4 so).

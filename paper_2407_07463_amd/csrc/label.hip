@@ -1301,7 +1301,6 @@ static void launch_local(vofmt_ctx *ctx, int ntile, unsigned nt, hipStream_t str
   hipLaunchKernelGGL(k_label_local<TS>, dim3((unsigned)gx, nt), dim3(kBlock), 0, stream, occ, R, nx, ny, nz, words, rt,
                      ntile, nrun);
 }
-// Label one tracer field into `lab`. Returns K via *k_dev (device int32).
 // Scratch: occupancy words (one per segment), run array (S per segment),
 // block counts (segment_blocks entries), tile offsets
 // (segment_blocks / compact::kTile + 2 entries).
@@ -1341,6 +1340,7 @@ static int label_all(vofmt_ctx *ctx, int nx, int ny, int nz, int T, const double
   hipLaunchKernelGGL(k_label_count, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, blockcount, nrun);
   // up to kDirect workgroups each sums the counts before its own: two launches
   // of about 5 us less than a scan, and a copy with the totals stored by pass 4
+  // (512^3 x 1 and 640^3 x 1, 2048 and 4000 of them: 1% faster than scanned)
   constexpr unsigned kDirect = 4096;
   if (nbg <= kDirect) {
     hipLaunchKernelGGL(k_label_rank<false>, dim3(nbg, nt), dim3(kBlock), 0, stream, occ, R, nseg, blockcount, tilesum,
