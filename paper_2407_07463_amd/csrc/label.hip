@@ -759,7 +759,10 @@ constexpr int kScanX = 2;  // tile of the scan: 64-cell segments, by SY rows, by
 // a wavefront's batches are a chain, and a tile's end is its drops' global atomics
 // (198x187x206 x 3, 1014 large tiles: scan 47.6 -> 30.6 us, 35 with 8 x 4; moments
 // and shapes of 256^3 x 8, 4096 of them, 310 -> 296 us for the statistics; 512^3 x
-// 8, 32768, the scan 745 -> 769 us)
+// 8, 32768, the scan 745 -> 769 us). Between them the call for the moments takes 165
+// us with large and 149 with small tiles at 288^3 x 5 (4860), 209 and 195 at 288^3 x
+// 8 (7776), 261 and 244 at 320^3 x 8 (9600), the same at 384^3 x 8 and 400^3 x 8 (13824
+// and 20000): the line lies below the crossing.
 constexpr int kFewScanTiles = 4096;
 constexpr int kTable = 64;     // LDS records per workgroup (power of two)
 constexpr int kBatch = 16;     // segments of a wavefront whose loads are issued together
